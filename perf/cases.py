@@ -17,6 +17,7 @@ from __future__ import annotations
 import ctypes
 import math
 
+import numpy as np
 import torch
 
 import paper_2506_11418_amd as ckv
@@ -285,6 +286,113 @@ def run(s):
             ckv.append(k, v, K, V, deg, pos=n - 1)
             ckv.decode_attn(q, K[:, :, :n], V[:, :, :n], deg=None if deg is None else deg[:, :, :n], out=o, workspace=ws)
     return s["o"], s["K"], s["V"], s["deg"], s["lens"]
+
+
+# ---- the same results in 64 bits ------------------------------------------------------------------
+def _round64(K, V, deg, chunk, r, n_sink, n_recent, scope):
+    """One round on a sequence: K, V [n, dim] in 64 bits, deg [n].  Returns the sums' quotients (64 bits) and the map."""
+    n, where = K.shape[0], torch.arange(K.shape[0], device=K.device)
+    lo, hi = (0, 0) if n <= n_sink + n_recent else (n_sink, n - n_recent)
+    whole = lo + (hi - lo) // chunk * chunk
+    src, dst, score, kept = [], [], [], []
+    for first, last, size in ((lo, whole, chunk), (whole, hi, hi - whole)):
+        if last - first < 2:
+            continue
+        x = K[first:last].view(-1, size, K.shape[1])
+        unit = x / x.norm(dim=2, keepdim=True).clamp_min(1e-300)
+        best = torch.bmm(unit[:, 0::2].contiguous(), unit[:, 1::2].transpose(1, 2).contiguous()).max(dim=2)
+        t = where[first:last].view(-1, size)
+        m = int(r * t[:, 0::2].shape[1] + 1e-9)
+        rank = best.values.argsort(dim=1, descending=True, stable=True).argsort(dim=1)
+        src.append(t[:, 0::2].reshape(-1))
+        dst.append((t[:, :1] + 2 * best.indices + 1).reshape(-1))
+        score.append(best.values.reshape(-1))
+        kept.append((rank < m).reshape(-1))
+    to = where.clone()
+    if src:
+        src, dst, score, kept = torch.cat(src), torch.cat(dst), torch.cat(score), torch.cat(kept)
+        if scope == "head":          # one ranking over the edges of all chunks
+            kept = score.argsort(descending=True, stable=True).argsort() < int(r * score.numel() + 1e-9)
+        to[src[kept]] = dst[kept]
+    left = to == where
+    d = torch.zeros_like(deg).index_add_(0, to, deg)[left]
+    K, V = (torch.zeros_like(x).index_add_(0, to, x * deg.unsqueeze(1).double())[left] / d.unsqueeze(1).double() for x in (K, V))
+    return K, V, d, (left.cumsum(0) - 1)[to]
+
+
+def _compress64(K, V, deg, dtype, chunk, rounds, n_sink, n_recent, scope):
+    """compress() of one sequence.  Between the rounds the cache is held in its own type, as the method has it."""
+    assign = torch.arange(K.shape[0], device=K.device)
+    for j, r in enumerate(rounds):
+        if j:
+            K, V = K.to(dtype), V.to(dtype)
+        K, V, deg, to = _round64(K.double(), V.double(), deg, chunk, r, n_sink, n_recent, scope)
+        assign = to[assign]
+    return K.double(), V.double(), deg.to(torch.int32), assign.to(torch.int32)
+
+
+def _exact_compress(s, rounds):
+    kw, K, V = s["kw"], s["K"], s["V"]
+    B, H, S = K.shape[:3]
+    got = []
+    for b in range(B):
+        for h in range(H):
+            deg = kw["deg"][b, h].long() if kw.get("deg") is not None else torch.ones(S, dtype=torch.long, device=DEV)
+            got.append(_compress64(K[b, h], V[b, h], deg, K.dtype, kw["chunk"], rounds, kw["n_sink"], kw["n_recent"],
+                                   kw.get("scope", "chunk")))
+    outs = []
+    for parts in zip(*got):
+        x = torch.stack(parts)
+        outs.append(x.view((B, H) + x.shape[1:]))
+    return outs
+
+
+def _to_pages(pool, table, rows):
+    """pool [n_blocks, heads, block, ...] := the sequences' first rows [batch, heads, n, ...], where the table puts them."""
+    n, bs = rows.shape[2], pool.shape[2]
+    t = torch.arange(n, device=DEV)
+    pool[table[:, t // bs].long(), :, t % bs] = rows.transpose(1, 2)
+
+
+def _rounds(kw):
+    """The merge fractions of the schedule, in 32 bits as the library carries them."""
+    rounds = kw.get("rounds")
+    if rounds is None:
+        retain = float(np.float32(kw["retain_ratio"]))
+        n = math.ceil(math.log2(1 / retain) - 1e-6)
+        rounds = [1.0] * (n - 1) + [2 * (1 - retain * 2 ** (n - 1))] if n else []
+    return [float(np.float32(r)) for r in rounds]
+
+
+def exact(case, seed):
+    s = prepare(case, seed)
+    if case["kind"] in ("prefill", "recluster"):
+        K, V, deg, assign = _exact_compress(s, _rounds(s["kw"]))
+        return K, V, deg, assign if s["kw"]["want_assign"] else None
+    if case["kind"] == "paged_prefill":            # rows behind the new length keep what the prompt wrote there
+        outs = _exact_compress(s, _rounds(s["kw"]))
+        pools = (s["pools"][0].double(), s["pools"][1].double(), s["pools"][2])
+        prompt = (s["K"].double(), s["V"].double(), torch.ones(s["K"].shape[:3], dtype=torch.int32, device=DEV))
+        for pool, before, after in zip(pools, prompt, outs):
+            _to_pages(pool, s["blocks"], before)
+            _to_pages(pool, s["blocks"], after)
+        return pools + (None, None, None)
+    o = torch.zeros_like(s["o"], dtype=torch.float64)
+    G, D, bs = case["group"], case["dim"], case["block"]
+    for i, (q, k, v, K, V, deg, _, lens) in enumerate(s["views"]):
+        for b, n in enumerate(_lens(case)):
+            if bs:                   # this sequence's blocks in order
+                blocks = s["table"][b].long()
+                Kb, Vb = (x[blocks].transpose(0, 1).reshape(case["heads"], -1, D)[:, :n].double() for x in (K, V))
+                db = None if deg is None else deg[blocks].transpose(0, 1).reshape(case["heads"], -1)[:, :n]
+            else:
+                Kb, Vb, db = K[b, :, :n].double(), V[b, :, :n].double(), None if deg is None else deg[b, :, :n]
+            Kb, Vb = torch.cat([Kb, k[b].double().unsqueeze(1)], 1), torch.cat([Vb, v[b].double().unsqueeze(1)], 1)
+            z = torch.bmm(q[b].double().view(-1, G, D), Kb.transpose(1, 2).contiguous()) / math.sqrt(D)
+            if db is not None:       # the new token's degree is 1: log 1 = 0
+                z[:, :, :n] += db.double().log().unsqueeze(1)
+            o[i, b] = torch.bmm(z.softmax(dim=2), Vb).view(-1, D)
+    return (o, None, None, None, None)               # the caches are copies
 
 
 # ---- what a pass cannot do without ----------------------------------------------------------------
