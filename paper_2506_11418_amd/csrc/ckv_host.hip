@@ -483,7 +483,7 @@ int ckv_decode_attn_workspace(const ckv_layout* kv, int32_t q_heads, size_t* byt
   if (st != CKV_OK) return st;
   if (!bytes) return CKV_EINVAL;
   if (q_heads <= 0 || q_heads % kv->heads) return CKV_ESHAPE;
-  *bytes = align_up(attn_workspace_bytes(kv->batch, kv->heads, q_heads, kv->dim, kv->seq, 0), 256);
+  *bytes = align_up(attn_workspace_bytes(kv->dtype, kv->batch, kv->heads, q_heads, kv->dim, kv->seq, 0), 256);
   return CKV_OK;
 }
 
@@ -547,7 +547,7 @@ int ckv_paged_decode_attn_workspace(const ckv_paged_layout* pl, int32_t q_heads,
   const int limit = ckv::attn_paged_span_limit(pl->block_size);
   if ((int64_t)limit * 1024 < max_len) return CKV_EUNSUPPORTED;   // more table entries per slice than the kernel holds
   if ((int64_t)pl->n_blocks * pl->heads * pl->block_size > INT32_MAX) return CKV_EUNSUPPORTED;   // pool rows are indexed in 32 bits
-  *bytes = ckv::align_up(ckv::attn_workspace_bytes(pl->batch, pl->heads, q_heads, pl->dim, max_len, limit), 256);
+  *bytes = ckv::align_up(ckv::attn_workspace_bytes(pl->dtype, pl->batch, pl->heads, q_heads, pl->dim, max_len, limit), 256);
   return CKV_OK;
 }
 

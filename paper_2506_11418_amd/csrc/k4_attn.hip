@@ -1,168 +1,258 @@
 // Decode attention over a (compressed) KV cache (Eq. 3; Algorithm 1, decode line):
 //   o_h = softmax(q_h K^T * scale + ln N) V,   one query token, G query heads per KV head.
-// Split along the sequence: every workgroup streams a contiguous slice of K and V once with
-// 16-byte loads (one row per group of row_bytes/16 lanes), serves all G query heads of its KV head
-// from registers, keeps an online softmax in the exp2 domain, and writes (max, sum, o) partials.
-// The slice that finishes last for a (batch, KV head) - found with one counter word per pair in
-// the workspace, which that workgroup puts back to zero - merges the partials of all slices with
-// the usual log-sum-exp rescaling, in slice order, so the result does not depend on which one that
-// is.  One launch per call; nothing in it is a memset.
+// Split along the sequence: every workgroup streams a contiguous slice of K and V once, serves all G
+// query heads of its KV head, keeps an online softmax in the exp2 domain, and writes (max, sum, o)
+// partials.  The slice that finishes last for a (batch, KV head) - found with one counter word per pair
+// in the workspace, which that workgroup puts back to zero - merges the partials of all slices with the
+// usual log-sum-exp rescaling, in an order fixed by the slice numbers, so the result does not depend on
+// which one that is.  One launch per call; nothing in it is a memset.
 #include <type_traits>
 
 #include "ckv_internal.h"
 #include "ckv_device.h"
+#include "k4_attn.h"
 
 namespace ckv {
 namespace {
 
-constexpr int kThreads = 256;
-constexpr float kLog2e = 1.4426950408889634f;
-
-template <typename T>
-struct Elems;
-template <>
-struct Elems<__bf16> {
-  static constexpr int E = 8;
-  typedef uint4 Raw;
-  __device__ static Raw load_raw(const __bf16* p) { return ldg16_stream(p); }
-  __device__ static void unpack(const Raw& u, float* x) {
-    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      x[2 * i] = __uint_as_float(w[i] << 16);
-      x[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-    }
-  }
-  // q.k over this lane's 8 elements: packed bf16 pairs straight into v_dot2 (products exact,
-  // fp32 accumulation), no unpacking of the key
-  typedef uint4 Q;
-  __device__ static Q load_q(const __bf16* p) { return *reinterpret_cast<const uint4*>(p); }
-  __device__ static float dot(const Q& qv, const Raw& kv) {
-    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-    const uint32_t a[4] = {qv.x, qv.y, qv.z, qv.w}, b[4] = {kv.x, kv.y, kv.z, kv.w};
-    float d = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a[i]), __builtin_bit_cast(bf16x2, b[i]), d, false);
-    return d;
-  }
-  __device__ static void load(const __bf16* p, float* x) {
-    const uint4 u = *reinterpret_cast<const uint4*>(p);
-    const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      x[2 * i] = __uint_as_float(w[i] << 16);
-      x[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-    }
-  }
-};
-template <>
-struct Elems<float> {
-  static constexpr int E = 4;
-  typedef float4 Raw;
-  __device__ static Raw load_raw(const float* p) { return *reinterpret_cast<const float4*>(p); }
-  __device__ static void unpack(const Raw& u, float* x) { x[0] = u.x; x[1] = u.y; x[2] = u.z; x[3] = u.w; }
-  typedef float4 Q;
-  __device__ static Q load_q(const float* p) { return *reinterpret_cast<const float4*>(p); }
-  __device__ static float dot(const Q& a, const Raw& b) {
-    return fmaf(a.w, b.w, fmaf(a.z, b.z, fmaf(a.y, b.y, a.x * b.x)));
-  }
-  __device__ static void load(const float* p, float* x) {
-    const float4 u = *reinterpret_cast<const float4*>(p);
-    x[0] = u.x; x[1] = u.y; x[2] = u.z; x[3] = u.w;
-  }
-};
-
-// Sum over the LANES consecutive lanes (aligned) that share a cache row; every lane gets the sum.
-// Quad steps and the mirrored half-row / row are DPP adds; 32 lanes add one cross-row exchange.
-template <int LANES>
-__device__ __forceinline__ float row_sum(float x) {
-  auto dpp = [](float v, auto ctrl) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), decltype(ctrl)::value,
-                                                                 0xF, 0xF, true));
-  };
-  x += dpp(x, std::integral_constant<int, 0xB1>{});                    // lane ^ 1
-  x += dpp(x, std::integral_constant<int, 0x4E>{});                    // lane ^ 2
-  if (LANES >= 8) x += dpp(x, std::integral_constant<int, 0x141>{});   // mirrored within 8
-  if (LANES >= 16) x += dpp(x, std::integral_constant<int, 0x140>{});  // mirrored within 16
-  if (LANES >= 32) x += __shfl_xor(x, 16);
-  return x;
-}
-
-__device__ inline uint16_t f32_to_bf16_rne(float f) {
-  const uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return (uint16_t)((u >> 16) | 0x40u);  // NaN stays NaN
-  return (uint16_t)((u + 0x7fffu + ((u >> 16) & 1u)) >> 16);
-}
+constexpr int kTableSlots = kAttnMaxTable + 64;   // block table of a slice in LDS: slices start and end on whole tiles
 
 // Partial results travel between workgroups that may sit on different XCDs (each with its own L2)
-// inside one launch.  They are written and read with device-scope relaxed atomic accesses, which go
-// through to the level all XCDs share, instead of plain accesses bracketed by device-scope fences:
-// such a fence writes back / invalidates a whole L2, and one per workgroup cost this kernel a
-// factor of three.
-__device__ __forceinline__ void store_shared_f32(float* p, float v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// inside one launch.  They are written and read with device-scope relaxed atomic accesses (8 bytes
+// each), which go through to the level all XCDs share, instead of plain accesses bracketed by
+// device-scope fences: such a fence writes back / invalidates a whole L2, and one per workgroup cost
+// this kernel a factor of three.
+struct __attribute__((aligned(8))) F2 { float x, y; };
+__device__ __forceinline__ void store_shared(float* p, float x, float y) {
+  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), __builtin_bit_cast(uint64_t, F2{x, y}), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ float load_shared_f32(const float* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ F2 load_shared(const float* p) {
+  return __builtin_bit_cast(F2, __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT));
 }
 
-// 2^x for x <= 0 as the bare hardware instruction (1 ulp; results below 2^-126 come out as zero).
-// The library routine wraps it in a range fix-up for denormal results, five more instructions per
-// call, which in the streaming loop is a fifth of all vector work and buys nothing for a softmax weight.
-__device__ __forceinline__ float exp2_raw(float x) { return __builtin_amdgcn_exp2f(x); }
+// two neighbouring outputs: sums over the tokens divided by the sum of the weights (0 for an empty cache)
+__device__ __forceinline__ void put_out(void* __restrict__ o, int o_dtype, int64_t at, float x, float y, float den) {
+  const float rx = den > 0.f ? x / den : 0.f, ry = den > 0.f ? y / den : 0.f;
+  if (o_dtype == CKV_BF16) {
+    uint16_t* op = reinterpret_cast<uint16_t*>(o) + at;
+    op[0] = f32_to_bf16_rne(rx);
+    op[1] = f32_to_bf16_rne(ry);
+  } else {
+    float* op = reinterpret_cast<float*>(o) + at;
+    op[0] = rx;
+    op[1] = ry;
+  }
+}
 
-// partial layout: o_part[((b*Hkv + kvh)*S + split)*G + g][D], ml_part[...][2] = (max, sum)
+// How a lane sees a cache row of D bf16 channels.  K rows arrive whole (16-byte pieces, consecutive lanes
+// consecutive pieces) and turn into MFMA operands through LDS.  Of a V row lane n of a 16-lane group
+// takes the EV = D/16 channels EV*n .. EV*n + EV - 1: at dim 128 a 16-byte piece straight from memory, at
+// dim 64 half a piece, for which V rows go the way of the K rows (16 pairs of 15000 .. 30000 tokens, 4
+// heads each: 25.2 us, with 8-byte loads of V 26.6).
+// A wave takes 8 KiB at a time: one tile of 16 tokens (the token side of a 16x16 MFMA) of dim 128, two of
+// dim 64.
+template <int D>
+struct RowOf {
+  static constexpr int RB = D * 2;                       // bytes of a row
+  static constexpr int PIECES = RB / 16;                 // 16-byte pieces of a row
+  static constexpr int KROWS = 64 / PIECES;              // rows per wave-wide K load
+  static constexpr int KL = 16 / KROWS;                  // K loads per tile
+  static constexpr int KSTEPS = PIECES / 4;              // a contraction step takes four pieces of every row
+  static constexpr int EV = D / 16;
+  static constexpr int TILES = 128 / D;
+  static constexpr bool VLDS = D == 64;
+  static constexpr int VL = VLDS ? KL : 4;               // V loads per tile, 16 bytes each
+  static constexpr int LDS = (VLDS ? 2 : 1) * 16 * RB;   // staging of a wave's tile
+  static constexpr int TOKENS = 16 * TILES;              // tokens per step of a wave
+  // byte offset of a 16-byte piece of a tile's row in LDS: the XOR spreads the 16 rows of one piece
+  // column over all banks
+  __device__ static int lds(int token, int piece) {
+    const int key = (PIECES == 8) ? (token >> 1) & 7 : token & 15;
+    return token * RB + ((piece ^ key) << 4);
+  }
+};
+
+__device__ __forceinline__ float bf16_at(const uint32_t* w, int e) {
+  return __uint_as_float((e & 1) ? (w[e >> 1] & 0xffff0000u) : (w[e >> 1] << 16));
+}
+
+// K piece . q piece for 16 tokens x 16 heads: one MFMA of depth 32, or two of depth 16 where a row has only
+// two steps (products exact, fp32 accumulation).  Every MFMA starts from zero and the results are added
+// up in pairs: one chain through all channels doubled the error of large logits.
+template <bool SPLIT>
+__device__ __forceinline__ f32x4 qk_step(const uint4& k, const uint4& qv) {
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  if constexpr (SPLIT) {
+    typedef __attribute__((ext_vector_type(4))) short s16x4;
+    struct Halves { s16x4 h[2]; };
+    const Halves a = __builtin_bit_cast(Halves, k), b = __builtin_bit_cast(Halves, qv);
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a.h[0], b.h[0], zero, 0, 0, 0) +
+           __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a.h[1], b.h[1], zero, 0, 0, 0);
+  } else {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k), __builtin_bit_cast(bf16x8, qv), zero, 0, 0, 0);
+  }
+}
+
+// The slices of one (batch, KV head), merged by the workgroup that arrived last: weights of the slices
+// per query head (a wave takes a head), and the slices' sums: every thread owns NC pairs of neighbouring
+// channels and adds them up over the slices; with fewer pairs than threads, groups of threads take every
+// SG-th slice and their sums are added in group order.  The first N slices of a thread (all of them for
+// up to N * SG slices) are requested before the weights are worked out, so that one memory latency covers both.
+// s_w: [G][kAttnMaxSplits] floats, s_red: two per thread.
+template <int D, int G, int W>
+__device__ __forceinline__ void merge_slices(const float* __restrict__ o_part, const float* __restrict__ ml_part,
+                                             int64_t sbase, int n_slices, float* s_w, float* s_den, float* s_red,
+                                             void* __restrict__ o, int o_dtype, int64_t o_base) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int kThreads = W * 64, PAIRS = G * D / 2;
+  constexpr int SG = (PAIRS < kThreads) ? kThreads / PAIRS : 1, NC = (PAIRS + kThreads - 1) / kThreads;
+  static_assert(PAIRS * SG == kThreads * NC, "whole pairs per thread");
+  constexpr int N = (SG * NC >= 4) ? 8 : 32 / (SG * NC);
+  const int sg = tid / (kThreads / SG);
+  float nx[NC], ny[NC];
+  const float* col[NC];
+  const float* wcol[NC];
+#pragma unroll
+  for (int k = 0; k < NC; ++k) {
+    const int c = 2 * ((tid % (kThreads / SG)) + k * kThreads);
+    nx[k] = ny[k] = 0.f;
+    col[k] = o_part + (sbase * G + c / D) * D + c % D;
+    wcol[k] = s_w + (c / D) * kAttnMaxSplits;
+  }
+  constexpr int64_t pitch = (int64_t)G * D;
+  F2 x[NC][N];
+  auto request = [&](int s0) {
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if (s0 + i * SG < n_slices) {
+#pragma unroll
+        for (int k = 0; k < NC; ++k) x[k][i] = load_shared(col[k] + (s0 + i * SG) * pitch);
+      }
+  };
+  request(sg);
+  for (int g = wave; g < G; g += W) {
+    auto pair = [&](int sp) { return load_shared(&ml_part[((sbase + sp) * G + g) * 2]); };
+    const F2 mine = (lane < n_slices) ? pair(lane) : F2{-INFINITY, 0.f};   // read once: up to 64 slices need no more
+    float mloc = mine.x;
+    for (int sp = lane + 64; sp < n_slices; sp += 64) mloc = fmaxf(mloc, pair(sp).x);
+#pragma unroll
+    for (int sh = 32; sh > 0; sh >>= 1) mloc = fmaxf(mloc, __shfl_xor(mloc, sh));
+    float dloc = 0.f;
+    for (int sp = lane; sp < n_slices; sp += 64) {
+      const F2 ml = (sp < 64) ? mine : pair(sp);
+      const float f = (ml.x == -INFINITY) ? 0.f : exp2f(ml.x - mloc);
+      s_w[g * kAttnMaxSplits + sp] = f;
+      dloc += f * ml.y;
+    }
+#pragma unroll
+    for (int sh = 32; sh > 0; sh >>= 1) dloc += __shfl_xor(dloc, sh);
+    if (lane == 0) s_den[g] = dloc;
+  }
+  __syncthreads();
+  for (int s0 = sg;;) {
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        const int sp = s0 + i * SG;
+        if (sp < n_slices) {
+          const float w = wcol[k][sp];
+          nx[k] = fmaf(x[k][i].x, w, nx[k]);
+          ny[k] = fmaf(x[k][i].y, w, ny[k]);
+        }
+      }
+    s0 += SG * N;
+    if (s0 >= n_slices) break;
+    request(s0);
+  }
+  if constexpr (SG > 1) {
+    s_red[2 * tid] = nx[0];
+    s_red[2 * tid + 1] = ny[0];
+    __syncthreads();
+    if (sg > 0) return;
+#pragma unroll
+    for (int i = 1; i < SG; ++i) {
+      nx[0] += s_red[2 * (tid + i * PAIRS)];
+      ny[0] += s_red[2 * (tid + i * PAIRS) + 1];
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < NC; ++k) {
+    const int c = 2 * ((tid % (kThreads / SG)) + k * kThreads);
+    put_out(o, o_dtype, o_base + c, nx[k], ny[k], s_den[c / D]);
+  }
+}
+
+// A wave takes tiles of 16 tokens, both contractions on the matrix cores.  The 16 columns of a tile are
+// the G query heads (repeated to fill 16), lane = 16 q + column:
+//   S[token, head]: K rows are the A operand (through a 4 KiB region of LDS per wave and back, no
+//     barrier: a wave's LDS accesses are in order), q the B operand.  MFMA row 4q + i is token 4i + q of
+//     the tile, so that a lane's four results belong to tokens q, 4 + q, 8 + q, 12 + q;
+//   O[head, channel]: those four weights, in fp32, ARE the A operand of four fp32 MFMAs of depth 4 (lane
+//     group q = contraction index q), and the V rows a lane group loads are its B operand: wave-wide
+//     load i covers the four consecutive rows 4i .. 4i + 3.
+// Weights, sums and products stay fp32 (bf16 values widen exactly).  The softmax reference of a head
+// moves only when a logit exceeds it by more than 8 (in log2): weights stay below 2^8, which costs no
+// precision, and after the first tiles the rescaling of the accumulators is rare.
 //
-// Thread mapping: LPR = row_bytes/16 lanes share one cache row ("row group"); a wave holds 64/LPR
-// row groups, so one wave-wide 16-byte load covers 64/LPR consecutive rows = 1 KiB contiguous.
-// Every row group takes kUnroll tokens per iteration: their K and V loads are all issued before
-// the first use (bytes in flight hide HBM latency), the logits of the kUnroll tokens share one
-// running-max update, so the accumulators are rescaled once per kUnroll tokens.
-constexpr int kUnroll = 4;
-constexpr int kMaxSplits = 1024;    // slices per sequence: the merge keeps one weight per slice and head in LDS
-constexpr int kMaxTableLds = 2048;   // block-table entries of one slice kept in LDS (paged caches)
-
+// What bounds it: HBM reads (a kernel that does nothing but read reaches 6.2 TB/s on 134 MB, 6.7 on 403
+// MB).  Per token row a SIMD spends 70 MFMA cycles and some 15 vector instructions where its share of that
+// rate takes 200 cycles; the dot products, row sums and weighted adds it had in vector instructions before
+// took 90 per row and four heads.  Per layer, against that form (bf16, dim 128): 403 MB of 16 sequences,
+// 4 heads per KV head, 74 us (83); the same bytes with 8 heads 71 us (133); on pages of 16 tokens 75 us (92);
+// 134 MB of one sequence 31.5 us (34.7).
+// Time line of that last one, from clock readings in the kernel: the streaming loops end between 17 and
+// 25 us, the waves of a workgroup wait for the slowest and reduce in 3.8 us, partials are acknowledged and
+// counted in 1.4 us, the merge by the last arriver takes 2.6 us.
+//
 // PAGED: K, V are a block pool [n_blocks, heads, block_size, dim] (kv.stride_s = dim, kv.stride_h =
 // block_size*dim: the tokens of one head are contiguous inside a block), token t of sequence b
 // lives in block table[b][t / block_size] at offset t % block_size, degrees in a pool
 // [n_blocks, heads, block_size].  A table entry outside the pool masks its tokens.
-template <typename T, int D, int G, bool PAGED>
-__global__ __launch_bounds__(kThreads, G <= 4 ? 3 : 2) void attn_partial_kernel(
-    const T* __restrict__ q, const T* __restrict__ K, const T* __restrict__ V, TensorView kv, int kv_heads,
+//
+// partial layout: o_part[((b*Hkv + kvh)*S + split)*G + g][D], ml_part[...][2] = (max, sum)
+template <int D, int G, int W, bool PAGED>   // W: waves per workgroup
+__global__ __launch_bounds__(W * 64, 2) void attn_mfma_kernel(
+    const __bf16* __restrict__ q, const __bf16* __restrict__ K, const __bf16* __restrict__ V, TensorView kv, int kv_heads,
     int seq, const int32_t* __restrict__ lens, const int32_t* __restrict__ deg, float scale_log2e,
-    int n_splits, int span, float* __restrict__ o_part, float* __restrict__ ml_part,
+    int n_splits, float* __restrict__ o_part, float* __restrict__ ml_part,
     int32_t* __restrict__ arrived, void* __restrict__ o, int o_dtype, PagedView paged) {
-  constexpr int E = Elems<T>::E;
-  constexpr int LPR = D / E;
-  constexpr int NRG = kThreads / LPR;
-  constexpr int U = kUnroll;
-  __shared__ float s_m[NRG][G];
-  __shared__ float s_l[NRG][G];
-  constexpr int GG = (G < 4) ? G : 4;   // query heads merged per pass of the final reduction
-  // staging rows of the workgroup's reduction; later the slice weights [G][kMaxSplits] of the merge
-  constexpr int kStageFloats = GG * NRG * D, kWeightFloats = G * kMaxSplits;
-  __shared__ float s_raw[kStageFloats > kWeightFloats ? kStageFloats : kWeightFloats];
-  float (*s_o)[NRG][D] = reinterpret_cast<float (*)[NRG][D]>(s_raw);
+  typedef RowOf<D> R;
+  constexpr int kThreads = W * 64;
+  constexpr int kStageBytes = W * R::LDS;                 // K tiles of the four waves
+  constexpr int kOutBytes = W * G * D * 4, kWeightBytes = G * kAttnMaxSplits * 4;
+  constexpr int kRawBytes = kStageBytes > kOutBytes ? (kStageBytes > kWeightBytes ? kStageBytes : kWeightBytes)
+                                                    : (kOutBytes > kWeightBytes ? kOutBytes : kWeightBytes);
+  __shared__ __attribute__((aligned(16))) unsigned char s_raw[kRawBytes];   // one after the other
+  __shared__ float s_m[W][G], s_l[W][G];
+  __shared__ float s_red[2 * kThreads];
+  __shared__ int s_is_last;
+  __shared__ int32_t s_tbl[PAGED ? kTableSlots : 1];
 
   const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
-  const int tid = threadIdx.x, rg = tid / LPR, piece = tid % LPR;
-  const int len = lens ? min(lens[b], seq) : seq;
-  const int t0 = split * span, t1 = min(t0 + span, len);
-  const int64_t base = PAGED ? piece * E : (int64_t)b * kv.stride_b + (int64_t)kvh * kv.stride_h + piece * E;
-  const T* Kp = K + base;
-  const T* Vp = V + base;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int qd = lane >> 4, n = lane & 15;
+  const int len = lens ? max(min(lens[b], seq), 0) : seq;
+  // whole tiles, split evenly over as many slices as give every wave one (a sequence far below the
+  // capacity takes fewer slices than the launch holds)
+  const int n_tiles = div_up(len, R::TOKENS);
+  const int n_slices = max(min(n_splits, div_up(n_tiles, W)), 1);
+  if (split >= n_slices) return;
+  const int tile0 = (int)((int64_t)split * n_tiles / n_slices), tile1 = (int)((int64_t)(split + 1) * n_tiles / n_slices);
+  const int t0 = tile0 * R::TOKENS, t1 = min(tile1 * R::TOKENS, len);
+  const int64_t seq_base = PAGED ? 0 : (int64_t)b * kv.stride_b + (int64_t)kvh * kv.stride_h;
   const int32_t* dseq = !deg ? nullptr : PAGED ? deg : deg + ((int64_t)b * kv_heads + kvh) * kv.deg_stride;
-  const int32_t* tbl = PAGED ? paged.table + (int64_t)b * paged.max_blocks : nullptr;
-  const int bs_mask = (1 << paged.shift) - 1;
   // the slice's blocks go to LDS first, each as the pool row ((block, head) pair times block size)
   // its first token of this head sits in, or -1 for an entry outside the pool: a row's address then
   // needs no second trip to memory and one add (the host sizes the slices so that their table
   // entries fit, and refuses pools of 2^31 rows or more)
-  __shared__ int32_t s_tbl[PAGED ? kMaxTableLds : 1];
+  const int bs_mask = (1 << paged.shift) - 1;
   const int blk0 = t0 >> paged.shift;
   if (PAGED && t0 < t1) {
-    const int n_ent = min(((t1 - 1) >> paged.shift) - blk0 + 1, kMaxTableLds);
+    const int32_t* tbl = paged.table + (int64_t)b * paged.max_blocks;
+    const int n_ent = min(((t1 - 1) >> paged.shift) - blk0 + 1, kTableSlots);
     for (int i = tid; i < n_ent; i += kThreads) {
       const int blk = tbl[blk0 + i];
       s_tbl[i] = ((unsigned)blk < (unsigned)paged.n_blocks) ? ((blk * kv_heads + kvh) << paged.shift) : -1;
@@ -170,284 +260,291 @@ __global__ __launch_bounds__(kThreads, G <= 4 ? 3 : 2) void attn_partial_kernel(
     __syncthreads();
   }
 
-  typename Elems<T>::Q qv[G];
+  const __bf16* Kp = K + seq_base + (lane % R::PIECES) * 8;
+  const __bf16* Vp = V + seq_base + (R::VLDS ? lane % R::PIECES : n) * 8;
+  unsigned char* ktile = s_raw + wave * R::LDS;
+  uint4 qv[R::KSTEPS];
+  {
+    const __bf16* qp = q + ((int64_t)b * kv_heads * G + kvh * G + n % G) * D;
 #pragma unroll
-  for (int g = 0; g < G; ++g)
-    qv[g] = Elems<T>::load_q(q + ((int64_t)b * kv_heads * G + kvh * G + g) * D + piece * E);
-  float m[G], l[G], acc[G][E];
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-    m[g] = -INFINITY;
-    l[g] = 0.f;
-#pragma unroll
-    for (int e = 0; e < E; ++e) acc[g][e] = 0.f;
+    for (int s = 0; s < R::KSTEPS; ++s) qv[s] = *reinterpret_cast<const uint4*>(qp + (4 * s + qd) * 8);
   }
 
-  // token of (iteration, slot u) for this row group: tb + u*NRG + rg.  The loads of iteration
-  // i+1 are issued before iteration i is consumed (two register sets, software pipeline).
-  struct Stage {
-    typename Elems<T>::Raw kr[U], vr[U];
-    int dg[U];
+  struct Tile {
+    uint4 k[R::KL];
+    uint4 v[R::VL];
+    int dg[4], out[4];
   };
-  auto issue = [&](Stage& st, int tb) {
+  struct Stage { Tile tile[R::TILES]; };
+  // every load of a tile, its rows clamped to the slice (always valid rows, masked at use)
+  auto issue_tile = [&](Tile& st, int t) {
+    auto row_of = [&](int tok, int& out) -> int {    // out: -1 for a token whose block is outside the pool, else 0
+      if (!PAGED) return tok;
+      const int row0 = s_tbl[min((tok >> paged.shift) - blk0, kTableSlots - 1)];
+      out = row0 >> 31;
+      return max(row0, 0) + (tok & bs_mask & ~out);  // outside the pool: row 0, masked through the degree
+    };
+    // elements from a row's first to its piece: pools are contiguous, rows of a head dim elements apart
+    auto at = [&](int row) -> int64_t { return PAGED ? (int64_t)((uint64_t)(uint32_t)row * D) : (int64_t)row * kv.stride_s; };
+    int out = 0;
+    if (dseq) {            // (the same for every workgroup of the launch)
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int tc = min(tb + u * NRG + rg, t1 - 1);   // clamp: always a valid row, masked at use
-      if (PAGED) {
-        const int row0 = s_tbl[min((tc >> paged.shift) - blk0, kMaxTableLds - 1)];
-        const bool in_pool = row0 >= 0;
-        // row 0 when outside the pool: always a valid address, masked through the degree
-        const int row = in_pool ? row0 + (tc & bs_mask) : 0;
-        st.kr[u] = Elems<T>::load_raw(Kp + (int64_t)row * kv.stride_s);
-        st.vr[u] = Elems<T>::load_raw(Vp + (int64_t)row * kv.stride_s);
-        const int d = dseq ? dseq[row] : 1;
-        st.dg[u] = in_pool ? d : 0;
+      for (int i = 0; i < 4; ++i) st.dg[i] = dseq[row_of(min(t + 4 * i + qd, t1 - 1), out)];
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) st.dg[i] = 1;
+    }
+#pragma unroll
+    for (int i = 0; i < R::KL; ++i) {
+      const int64_t x = at(row_of(min(t + R::KROWS * i + lane / R::PIECES, t1 - 1), out));
+      st.k[i] = ldg16_stream(Kp + x);
+      if (R::VLDS) st.v[i] = ldg16_stream(Vp + x);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = row_of(min(t + 4 * i + qd, t1 - 1), out);
+      if (!R::VLDS) st.v[i % R::VL] = ldg16_stream(Vp + at(row));
+      if (PAGED) st.out[i] = out;
+    }
+  };
+  auto issue = [&](Stage& st, int t) {
+#pragma unroll
+    for (int u = 0; u < R::TILES; ++u) issue_tile(st.tile[u], t + 16 * u);
+  };
+
+  f32x4 acc[R::EV];
+#pragma unroll
+  for (int j = 0; j < R::EV; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float ref = -INFINITY, ref_used = 0.f, l = 0.f;   // of this lane's head; ref_used: 0 until a token counted
+  auto consume_tile = [&](const Tile& st, int t) {
+#pragma unroll
+    for (int i = 0; i < R::KL; ++i) {
+      const int at = R::lds(R::KROWS * i + lane / R::PIECES, lane % R::PIECES);
+      *reinterpret_cast<uint4*>(ktile + at) = st.k[i];
+      if (R::VLDS) *reinterpret_cast<uint4*>(ktile + 16 * R::RB + at) = st.v[i];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // other lanes' pieces are read next: keep the order
+    const int tk = 4 * (n & 3) + (n >> 2);
+    f32x4 s[R::KSTEPS];
+#pragma unroll
+    for (int k = 0; k < R::KSTEPS; ++k)
+      s[k] = qk_step<R::KSTEPS == 2>(*reinterpret_cast<const uint4*>(ktile + R::lds(tk, 4 * k + qd)), qv[k]);
+#pragma unroll
+    for (int w = 1; w < R::KSTEPS; w *= 2)
+#pragma unroll
+      for (int k = 0; k + w < R::KSTEPS; k += 2 * w) s[k] += s[k + w];
+    struct { uint32_t w[R::EV / 2]; } v[4];        // this lane's channels of tokens 4i + qd
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if constexpr (R::VLDS) {
+        const uint2 x = *reinterpret_cast<const uint2*>(ktile + 16 * R::RB + R::lds(4 * i + qd, n >> 1) + (n & 1) * 8);
+        v[i].w[0] = x.x; v[i].w[1] = x.y;
       } else {
-        st.kr[u] = Elems<T>::load_raw(Kp + (int64_t)tc * kv.stride_s);
-        st.vr[u] = Elems<T>::load_raw(Vp + (int64_t)tc * kv.stride_s);
-        st.dg[u] = dseq ? dseq[tc] : 1;
+        const uint4 x = st.v[i];
+        v[i].w[0] = x.x; v[i].w[1] = x.y; v[i].w[2] = x.z; v[i].w[3] = x.w;
       }
     }
-  };
-  auto consume = [&](const Stage& st, int tb) {
-    float z[U][G];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    float z[4], zmax;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-#pragma unroll
-      for (int g = 0; g < G; ++g) z[u][g] = row_sum<LPR>(Elems<T>::dot(qv[g], st.kr[u]));
-      const float lb = dseq ? __log2f((float)st.dg[u]) : 0.f;
-      const bool ok = (tb + u * NRG + rg) < t1 && (!PAGED || st.dg[u] > 0);
-#pragma unroll
-      for (int g = 0; g < G; ++g) z[u][g] = ok ? fmaf(z[u][g], scale_log2e, lb) : -INFINITY;
+    for (int i = 0; i < 4; ++i) {
+      const float lb = dseq ? __log2f((float)st.dg[i]) : 0.f;
+      const bool ok = (t + 4 * i + qd) < t1 && (!PAGED || (st.out[i] == 0 && st.dg[i] > 0));
+      z[i] = ok ? fmaf(s[0][i], scale_log2e, lb) : -INFINITY;
     }
+    zmax = fmaxf(fmaxf(z[0], z[1]), fmaxf(z[2], z[3]));
+    if (__any(zmax > ref + 8.f)) {     // some head's reference moves: rescale what has been summed
+      zmax = fmaxf(zmax, __shfl_xor(zmax, 16));
+      zmax = fmaxf(zmax, __shfl_xor(zmax, 32));
+      const float moved = fmaxf(ref, zmax);
+      ref_used = (moved == -INFINITY) ? 0.f : moved;
+      const float alpha = exp2_raw(ref - ref_used);
+      ref = moved;
+      l *= alpha;
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      float mn = m[g];
+      for (int i = 0; i < 4; ++i) {    // accumulator row 4*qd + i is that column's head
+        const float a = __shfl(alpha, 4 * qd + i);
 #pragma unroll
-      for (int u = 0; u < U; ++u) mn = fmaxf(mn, z[u][g]);
-      // a row group that has seen no valid token yet keeps mn = -inf: subtract 0 instead, so that
-      // exp2(-inf) = 0 comes out rather than NaN
-      const float ref = (mn == -INFINITY) ? 0.f : mn;
-      const float alpha = exp2_raw(m[g] - ref);
-      m[g] = mn;
-      l[g] *= alpha;
-#pragma unroll
-      for (int e = 0; e < E; ++e) acc[g][e] *= alpha;
-#pragma unroll
-      for (int u = 0; u < U; ++u) z[u][g] = exp2_raw(z[u][g] - ref);   // now the weight p
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      float vx[E];
-      Elems<T>::unpack(st.vr[u], vx);
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        l[g] += z[u][g];
-#pragma unroll
-        for (int e = 0; e < E; ++e) acc[g][e] = fmaf(z[u][g], vx[e], acc[g][e]);
+        for (int j = 0; j < R::EV; ++j) acc[j][i] *= a;
       }
     }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) z[i] = exp2_raw(z[i] - ref_used);
+    l += (z[0] + z[1]) + (z[2] + z[3]);
+    // the tile's own sum from zero, then one addition into the running sums: a quarter of the roundings there
+#pragma unroll
+    for (int j0 = 0; j0 < R::EV; j0 += 4) {
+      f32x4 sum[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          sum[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(z[i], bf16_at(v[i].w, j0 + j), i == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sum[j], 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[j0 + j] += sum[j];
+    }
   };
-  constexpr int STEP = NRG * U;
-  if (t0 < t1) {
+  auto consume = [&](const Stage& st, int t) {
+#pragma unroll
+    for (int u = 0; u < R::TILES; ++u) consume_tile(st.tile[u], t + 16 * u);
+  };
+  // the loads of a wave's next step are issued before this one is consumed (two register sets)
+  constexpr int STEP = W * R::TOKENS;
+  const int tw = t0 + wave * R::TOKENS;
+  if (tw < t1) {
     Stage sa, sb;
-    issue(sa, t0);
-    for (int tb = t0; tb < t1; tb += 2 * STEP) {
-      if (tb + STEP < t1) issue(sb, tb + STEP);
-      consume(sa, tb);
-      if (tb + STEP < t1) {
-        if (tb + 2 * STEP < t1) issue(sa, tb + 2 * STEP);
-        consume(sb, tb + STEP);
-      }
+    issue(sa, tw);
+    for (int t = tw; t < t1; t += 2 * STEP) {
+      issue(sb, t + STEP);
+      consume(sa, t);
+      if (t + STEP >= t1) break;
+      issue(sa, t + 2 * STEP);
+      consume(sb, t + STEP);
     }
   }
 
-  // ---- merge the NRG row groups of this workgroup ---------------------------------------------
-  if (piece == 0) {
+  // ---- merge the waves of this workgroup -------------------------------------------------------
+  l += __shfl_xor(l, 16);
+  l += __shfl_xor(l, 32);
+  if (lane < G) { s_m[wave][lane] = ref; s_l[wave][lane] = l; }   // (lane = column = head)
+  __syncthreads();                      // also: every wave is past its K tile, s_raw changes hands
+  float (*s_o)[G][D] = reinterpret_cast<float (*)[G][D]>(s_raw);
 #pragma unroll
-    for (int g = 0; g < G; ++g) { s_m[rg][g] = m[g]; s_l[rg][g] = l[g]; }
+  for (int i = 0; i < 4; ++i) {
+    const int g = 4 * qd + i;
+    if (g < G) {
+      float M = s_m[0][g];
+#pragma unroll
+      for (int w = 1; w < W; ++w) M = fmaxf(M, s_m[w][g]);
+      const float mw = s_m[wave][g];
+      const float f = (mw == -INFINITY) ? 0.f : exp2f(mw - M);
+#pragma unroll
+      for (int j = 0; j < R::EV; ++j) s_o[wave][g][R::EV * n + j] = acc[j][i] * f;
+    }
   }
   __syncthreads();
-  const int64_t pbase = (((int64_t)b * kv_heads + kvh) * n_splits + split) * G;
-  // GG heads at a time: every row group rescales its accumulators to the workgroup's maximum and
-  // parks them in LDS, then each thread sums a few (head, channel) columns over the row groups
+  const int64_t sbase = ((int64_t)b * kv_heads + kvh) * n_splits;
+  const int64_t pbase = (sbase + split) * G, o_base = ((int64_t)b * kv_heads + kvh) * G * D;
+  auto sum_of = [&](int g) -> float {     // sum of exponentials of head g, relative to the workgroup's maximum
+    float M = s_m[0][g], L = 0.f;
 #pragma unroll
-  for (int g0 = 0; g0 < G; g0 += GG) {
-    if (g0 > 0) __syncthreads();
+    for (int w = 1; w < W; ++w) M = fmaxf(M, s_m[w][g]);
 #pragma unroll
-    for (int gg = 0; gg < GG; ++gg) {
-      const int g = g0 + gg;
-      float M = -INFINITY;
-      for (int r2 = 0; r2 < NRG; ++r2) M = fmaxf(M, s_m[r2][g]);
-      const float f = (m[g] == -INFINITY) ? 0.f : exp2f(m[g] - M);
+    for (int w = 0; w < W; ++w) {
+      const float mw = s_m[w][g];
+      L += (mw == -INFINITY) ? 0.f : s_l[w][g] * exp2f(mw - M);
+    }
+    return L;
+  };
+  for (int c = 2 * tid; c < G * D; c += 2 * kThreads) {
+    float x = 0.f, y = 0.f;
 #pragma unroll
-      for (int e = 0; e < E; ++e) s_o[gg][rg][piece * E + e] = acc[g][e] * f;
+    for (int w = 0; w < W; ++w) {
+      x += s_o[w][c / D][c % D];
+      y += s_o[w][c / D][c % D + 1];
     }
-    __syncthreads();
-    for (int idx = tid; idx < GG * D; idx += kThreads) {
-      const int gg = idx / D, d = idx % D;
-      float sum = 0.f;
-      for (int r2 = 0; r2 < NRG; ++r2) sum += s_o[gg][r2][d];
-      store_shared_f32(&o_part[(pbase + g0 + gg) * D + d], sum);
-    }
-    if (tid < GG) {
-      const int g = g0 + tid;
-      float M = -INFINITY, L = 0.f;
-      for (int r2 = 0; r2 < NRG; ++r2) M = fmaxf(M, s_m[r2][g]);
-      for (int r2 = 0; r2 < NRG; ++r2) {
-        const float mr = s_m[r2][g];
-        L += (mr == -INFINITY) ? 0.f : s_l[r2][g] * exp2f(mr - M);
-      }
-      store_shared_f32(&ml_part[(pbase + g) * 2], M);
-      store_shared_f32(&ml_part[(pbase + g) * 2 + 1], L);
-    }
+    if (n_slices == 1) put_out(o, o_dtype, o_base + c, x, y, sum_of(c / D));   // the only slice: nothing to merge
+    else store_shared(&o_part[pbase * D + c], x, y);
+  }
+  if (n_slices == 1) return;
+  if (tid < G) {
+    float M = s_m[0][tid];
+#pragma unroll
+    for (int w = 1; w < W; ++w) M = fmaxf(M, s_m[w][tid]);
+    store_shared(&ml_part[(pbase + tid) * 2], M, sum_of(tid));
   }
 
   // ---- the last slice of this (batch, KV head) to arrive merges them all ----------------------
   // Every thread waits until its own partial stores have been acknowledged, the workgroup meets,
   // and one thread counts the workgroup in; the workgroup that finds all others counted takes the
   // merge.  The counter is only ever touched with device-scope atomics.
-  __shared__ int s_is_last;
   __builtin_amdgcn_s_waitcnt(0);          // vmcnt = lgkmcnt = expcnt = 0: the stores above are complete
   __syncthreads();
   int32_t* my_count = arrived + (b * kv_heads + kvh);
-  if (tid == 0) s_is_last = (atomicAdd(my_count, 1) == n_splits - 1);
+  if (tid == 0) s_is_last = (atomicAdd(my_count, 1) == n_slices - 1);
   __syncthreads();
   if (!s_is_last) return;
-  // weights of the slices, per query head: a wave takes a head (two for G = 8)
-  float* s_w = s_raw;                     // [G][kMaxSplits] (the staging rows are no longer needed)
-  float* s_den = &s_l[0][0];              // [G]
-  const int lane = tid & 63, wave = tid >> 6;
-  const int64_t sbase = ((int64_t)b * kv_heads + kvh) * n_splits;
-  for (int g = wave; g < G; g += kThreads / 64) {
-    float mloc = -INFINITY;
-    for (int sp = lane; sp < n_splits; sp += 64) mloc = fmaxf(mloc, load_shared_f32(&ml_part[((sbase + sp) * G + g) * 2]));
-#pragma unroll
-    for (int sh = 32; sh > 0; sh >>= 1) mloc = fmaxf(mloc, __shfl_xor(mloc, sh));
-    float dloc = 0.f;
-    for (int sp = lane; sp < n_splits; sp += 64) {
-      const float ms = load_shared_f32(&ml_part[((sbase + sp) * G + g) * 2]);       // max of slice sp
-      const float ls = load_shared_f32(&ml_part[((sbase + sp) * G + g) * 2 + 1]);   // its sum of exponentials
-      const float f = (ms == -INFINITY) ? 0.f : exp2f(ms - mloc);
-      s_w[g * kMaxSplits + sp] = f;
-      dloc += f * ls;
-    }
-#pragma unroll
-    for (int sh = 32; sh > 0; sh >>= 1) dloc += __shfl_xor(dloc, sh);
-    if (lane == 0) s_den[g] = dloc;
-  }
-  __syncthreads();
-  // Every thread owns NC (head, channel) columns, consecutive threads consecutive channels (a wave's
-  // load is 256 contiguous bytes), and sums them over the slices in slice order: blocks of 32
-  // slices with all NC * 32 loads in flight, then blocks of 8, then single slices.  Which
-  // workgroup runs this never changes the order, so the bits are the same from run to run.
-  constexpr int NC = (G * D + kThreads - 1) / kThreads;
-  float num[NC];
-  const float* col[NC];
-  const float* wcol[NC];
-#pragma unroll
-  for (int k = 0; k < NC; ++k) {
-    const int c = min(tid + k * kThreads, G * D - 1);        // clamped: threads past the last column repeat it
-    num[k] = 0.f;
-    col[k] = o_part + (sbase * G + c / D) * D + c % D;
-    wcol[k] = s_w + (c / D) * kMaxSplits;
-  }
-  const int64_t pitch = (int64_t)G * D;
-  auto block = [&](int s0, auto n_c) {
-    constexpr int N = decltype(n_c)::value;
-    float x[NC][N];
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-#pragma unroll
-      for (int k = 0; k < NC; ++k) x[k][i] = load_shared_f32(col[k] + (int64_t)(s0 + i) * pitch);
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-#pragma unroll
-      for (int k = 0; k < NC; ++k) num[k] = fmaf(x[k][i], wcol[k][s0 + i], num[k]);
-  };
-  int s0 = 0;
-  for (; s0 + 32 <= n_splits; s0 += 32) block(s0, std::integral_constant<int, 32>{});
-  for (; s0 + 8 <= n_splits; s0 += 8) block(s0, std::integral_constant<int, 8>{});
-  for (; s0 < n_splits; ++s0) block(s0, std::integral_constant<int, 1>{});
-#pragma unroll
-  for (int k = 0; k < NC; ++k) {
-    const int c = tid + k * kThreads;
-    if (c < G * D) {
-      const float den = s_den[c / D];
-      const float res = den > 0.f ? num[k] / den : 0.f;
-      const int64_t oi = ((int64_t)b * kv_heads + kvh) * G * D + c;
-      if (o_dtype == CKV_BF16) reinterpret_cast<uint16_t*>(o)[oi] = f32_to_bf16_rne(res);
-      else reinterpret_cast<float*>(o)[oi] = res;
-    }
-  }
-  if (tid == 0) atomicExch(my_count, 0);  // the workspace is ready for the next call
+  if (tid == 0) atomicExch(my_count, 0);  // all have arrived: the workspace is ready for the next call
+  merge_slices<D, G, W>(o_part, ml_part, sbase, n_slices, reinterpret_cast<float*>(s_raw), &s_l[0][0], s_red, o, o_dtype,
+                        o_base);
 }
 
-template <typename T, int D, int G>
-hipError_t launch_attn_t(const void* q, const void* K, const void* V, TensorView kv, int n_b, int kv_heads,
-                         int seq, const int32_t* lens, const int32_t* deg, float scale, void* o, int o_dtype,
-                         void* workspace, int32_t* counters, PagedView paged, hipStream_t st) {
-  const int n_splits = attn_splits(n_b, kv_heads, seq, paged.table ? (kMaxTableLds << paged.shift) : 0);
-  const int span = div_up(seq, n_splits);
-  if (paged.table && span > (kMaxTableLds << paged.shift)) return hipErrorInvalidValue;
-  // workspace: arrival counters (one per (batch, KV head), zero between calls) | partial outputs | (max, sum) pairs;
-  // with counters kept elsewhere the partial outputs start the workspace
-  int32_t* arrived = counters ? counters : static_cast<int32_t*>(workspace);
-  float* o_part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) +
-                                           (counters ? 0 : attn_counter_bytes(n_b, kv_heads)));
-  float* ml_part = o_part + (size_t)n_b * kv_heads * n_splits * G * D;
-  ScopedTimer t(paged.table ? (sizeof(T) == 2 ? "attn_paged_bf16" : "attn_paged_f32")
-                            : (sizeof(T) == 2 ? "attn_bf16" : "attn_f32"), st);
-  if (paged.table)
-    hipLaunchKernelGGL((attn_partial_kernel<T, D, G, true>), dim3(n_splits, kv_heads, n_b), dim3(kThreads), 0,
-                       st, static_cast<const T*>(q), static_cast<const T*>(K), static_cast<const T*>(V), kv,
-                       kv_heads, seq, lens, deg, scale * kLog2e, n_splits, span, o_part, ml_part, arrived, o, o_dtype,
-                       paged);
-  else
-    hipLaunchKernelGGL((attn_partial_kernel<T, D, G, false>), dim3(n_splits, kv_heads, n_b), dim3(kThreads), 0,
-                       st, static_cast<const T*>(q), static_cast<const T*>(K), static_cast<const T*>(V), kv,
-                       kv_heads, seq, lens, deg, scale * kLog2e, n_splits, span, o_part, ml_part, arrived, o, o_dtype,
-                       paged);
+// Waves per workgroup (bf16).  With few (batch, KV head) pairs a long cache is cut into many slices, and the
+// merge of the slices by one workgroup counts: workgroups of eight waves halve their number (8 pairs of
+// 32769 tokens: 31.5 us with 32 slices of eight waves, 34.3 with 64 of four).  With more pairs, two
+// smaller workgroups per CU even out sequences of different lengths (128 pairs of 4112 .. 8223 tokens: 74
+// against 81 us), and a cache that gives the four waves of 512 workgroups no second tile has nothing to
+// merge that would be worth the longer reduction (8 pairs of 515 tokens: 9.6 against 11.0 us).
+int attn_waves(int n_b, int kv_heads, int seq) {
+  const int64_t bh = (int64_t)n_b * kv_heads;
+  return bh <= 16 && bh * seq > 512 * 4 * 16 ? 8 : 4;
+}
+
+template <int D, int G, int W>
+hipError_t launch_mfma_w(const AttnCall& c) {
+  const int n_splits = attn_splits(CKV_BF16, c.n_b, c.kv_heads, c.seq, c.paged.table ? (kAttnMaxTable << c.paged.shift) : 0);
+  if (c.paged.table && div_up(c.seq, n_splits) > (kAttnMaxTable << c.paged.shift)) return hipErrorInvalidValue;
+  float *o_part, *ml_part;
+  int32_t* arrived;
+  attn_carve(c, n_splits, G * D, &arrived, &o_part, &ml_part);
+  ScopedTimer t(c.paged.table ? "attn_paged_bf16" : "attn_bf16", c.st);
+#define CKV_ATTN_LAUNCH(PG)                                                                                             \
+  hipLaunchKernelGGL((attn_mfma_kernel<D, G, W, PG>), dim3(n_splits, c.kv_heads, c.n_b), dim3(W * 64), 0, c.st,         \
+                     static_cast<const __bf16*>(c.q), static_cast<const __bf16*>(c.K), static_cast<const __bf16*>(c.V), \
+                     c.kv, c.kv_heads, c.seq, c.lens, c.deg, c.scale * kLog2e, n_splits, o_part, ml_part, arrived, c.o, \
+                     c.o_dtype, c.paged)
+  if (c.paged.table) CKV_ATTN_LAUNCH(true);
+  else CKV_ATTN_LAUNCH(false);
+#undef CKV_ATTN_LAUNCH
   return hipGetLastError();
 }
 
-template <typename T, int D>
-hipError_t launch_attn_g(int G, const void* q, const void* K, const void* V, TensorView kv, int n_b,
-                         int kv_heads, int seq, const int32_t* lens, const int32_t* deg, float scale, void* o,
-                         int o_dtype, void* workspace, int32_t* counters, PagedView paged, hipStream_t st) {
+template <int D, int G>
+hipError_t launch_mfma_t(const AttnCall& c) {
+  return attn_waves(c.n_b, c.kv_heads, c.seq) == 8 ? launch_mfma_w<D, G, 8>(c) : launch_mfma_w<D, G, 4>(c);
+}
+
+template <int D>
+hipError_t launch_mfma_g(int G, const AttnCall& c) {
   switch (G) {
-    case 1: return launch_attn_t<T, D, 1>(q, K, V, kv, n_b, kv_heads, seq, lens, deg, scale, o, o_dtype, workspace, counters, paged, st);
-    case 2: return launch_attn_t<T, D, 2>(q, K, V, kv, n_b, kv_heads, seq, lens, deg, scale, o, o_dtype, workspace, counters, paged, st);
-    case 4: return launch_attn_t<T, D, 4>(q, K, V, kv, n_b, kv_heads, seq, lens, deg, scale, o, o_dtype, workspace, counters, paged, st);
-    case 8: return launch_attn_t<T, D, 8>(q, K, V, kv, n_b, kv_heads, seq, lens, deg, scale, o, o_dtype, workspace, counters, paged, st);
+    case 1: return launch_mfma_t<D, 1>(c);
+    case 2: return launch_mfma_t<D, 2>(c);
+    case 4: return launch_mfma_t<D, 4>(c);
+    case 8: return launch_mfma_t<D, 8>(c);
   }
   return hipErrorInvalidValue;
 }
 
 }  // namespace
 
-int attn_splits(int n_b, int kv_heads, int seq, int span_limit) {
-  // about two workgroups per CU (each has a fixed merge/write cost), at least 256 tokens per slice
+int attn_splits(int dtype, int n_b, int kv_heads, int seq, int span_limit) {
+  // Eight waves per CU stream fastest (two workgroups of four or one of eight).  Each workgroup has a fixed
+  // merge/write cost, so slices are at least 256 tokens; bf16 caches are cut finer, down to one tile per
+  // wave, while the launch stays within those workgroups: a short cache is bound by the latency of its
+  // longest slice.
   const int64_t bh = (int64_t)n_b * kv_heads;
-  int want = (int)((512 + bh - 1) / bh);
-  int cap = (seq + 255) / 256;
-  if (cap > kMaxSplits) cap = kMaxSplits;   // the merge keeps one weight per slice in LDS
-  if (want > cap) want = cap;
+  const int waves = dtype == CKV_BF16 ? attn_waves(n_b, kv_heads, seq) : 4;
+  const int64_t groups = 2048 / waves;
+  auto most = [&](int64_t want, int tokens) { const int cap = (seq + tokens - 1) / tokens; return want < cap ? (int)want : cap; };
+  int want = most((groups + bh - 1) / bh, 256);
+  const int fine = dtype == CKV_BF16 ? most(groups / bh, waves * 16) : 0;
+  if (fine > want) want = fine;
+  if (want > kAttnMaxSplits) want = kAttnMaxSplits;
   if (want < 1) want = 1;
   // paged caches: a slice's block-table entries must fit the kernel's LDS table
   if (span_limit > 0 && (seq + want - 1) / want > span_limit) want = (seq + span_limit - 1) / span_limit;
-  if (want > kMaxSplits) want = kMaxSplits;
+  if (want > kAttnMaxSplits) want = kAttnMaxSplits;
   return want;
 }
 
 size_t attn_counter_bytes(int n_b, int kv_heads) { return ((size_t)n_b * kv_heads * sizeof(int32_t) + 255) / 256 * 256; }
 
-int attn_paged_span_limit(int block_size) { return kMaxTableLds * block_size; }
+int attn_paged_span_limit(int block_size) { return kAttnMaxTable * block_size; }
 
-size_t attn_workspace_bytes(int n_b, int kv_heads, int q_heads, int dim, int seq, int span_limit) {
+size_t attn_workspace_bytes(int dtype, int n_b, int kv_heads, int q_heads, int dim, int seq, int span_limit) {
   // one arrival counter per (batch, KV head), then partial outputs and (max, sum) pairs per
   // (batch, query head, slice)
-  const size_t rows = (size_t)n_b * q_heads * attn_splits(n_b, kv_heads, seq, span_limit);
+  const size_t rows = (size_t)n_b * q_heads * attn_splits(dtype, n_b, kv_heads, seq, span_limit);
   return attn_counter_bytes(n_b, kv_heads) + rows * (dim + 2) * sizeof(float);
 }
 
@@ -456,17 +553,10 @@ hipError_t launch_decode_attn(const void* q, int q_heads, const void* K, const v
                               const int32_t* deg, float scale, void* o, int o_dtype, void* workspace,
                               PagedView paged, hipStream_t st, int32_t* counters) {
   const int G = q_heads / kv_heads;
-#define CKV_ATTN(T, DD) \
-  return launch_attn_g<T, DD>(G, q, K, V, kv, n_b, kv_heads, seq, lens, deg, scale, o, o_dtype, workspace, counters, paged, st)
-  if (dtype == CKV_BF16) {
-    if (dim == 128) CKV_ATTN(__bf16, 128);
-    if (dim == 64) CKV_ATTN(__bf16, 64);
-  } else {
-    if (dim == 128) CKV_ATTN(float, 128);
-    if (dim == 64) CKV_ATTN(float, 64);
-    if (dim == 32) CKV_ATTN(float, 32);
-  }
-#undef CKV_ATTN
+  const AttnCall c{q, K, V, kv, n_b, kv_heads, seq, lens, deg, scale, o, o_dtype, workspace, counters, paged, st};
+  if (dtype != CKV_BF16) return launch_attn_f32(G, dim, c);
+  if (dim == 128) return launch_mfma_g<128>(G, c);
+  if (dim == 64) return launch_mfma_g<64>(G, c);
   return hipErrorInvalidValue;
 }
 

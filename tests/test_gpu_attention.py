@@ -70,6 +70,38 @@ def test_decode_attn_shapes(B, Hkv, G, L, D, dtype):
     _check(q, K, V, None, None, o2, ATTN_TOL + 2.0 ** -8 if dtype == "bf16" else 1e-4, "vanilla")
 
 
+@pytest.mark.parametrize("B,Hkv,G,L,D,dtype", [
+    (6, 2, 4, 65, 128, "bf16"),        # around one tile (16 tokens) and one tile per wave (64)
+    (6, 2, 8, 130, 64, "bf16"),
+    (6, 2, 1, 130, 128, "f32"),
+    (6, 1, 2, 65, 32, "f32"),
+    (1, 1, 2, 32768, 128, "bf16"),     # the last length of one pair with four waves per workgroup ...
+    (1, 1, 2, 32769, 128, "bf16"),     # ... and the first with eight
+    (3, 2, 8, 8200, 64, "bf16"),       # eight waves, slices that end inside a tile
+    (2, 2, 4, 9000, 64, "f32"),
+    (17, 1, 4, 2100, 128, "bf16"),     # more pairs than eight waves are taken for
+    (520, 1, 1, 300, 64, "bf16"),      # one slice per pair: written without a merge
+])
+def test_attn_tile_and_slice_edges(B, Hkv, G, L, D, dtype):
+    """Lengths around the tiles and slices of the kernel, most of them far below the cache's capacity, with
+    and without degrees.  Logits, weights and sums are fp32: the bar is the file's own."""
+    _say(f"attn edges B={B} Hkv={Hkv} G={G} L={L} D={D} {dtype}")
+    rng = np.random.default_rng(L + D)
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    K, V = (torch.from_numpy(rng.standard_normal((B, Hkv, L, D)).astype(np.float32)).to(td).to(DEV) for _ in range(2))
+    q = torch.from_numpy(rng.standard_normal((B, Hkv * G, D)).astype(np.float32)).to(td).to(DEV)
+    deg = torch.from_numpy(rng.integers(1, 300, (B, Hkv, L)).astype(np.int32)).to(DEV)
+    edges = [L, 1, 15, 16, 17, 63, 64] if B < 17 else [L, 1, L - 1, 16, 129]
+    lens = torch.tensor([min(edges[b % len(edges)], L) for b in range(B)], dtype=torch.int32)
+    o = ckv.decode_attn(q, K, V, lens=lens.to(DEV), deg=deg, out_dtype=torch.float32)
+    plain = ckv.decode_attn(q, K, V, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    some = slice(0, min(B, 20))
+    tol = 1e-4 if dtype == "f32" else ATTN_TOL
+    _check(q[some], K[some], V[some], deg[some], lens[some], o[some], tol, "edges")
+    _check(q[some], K[some], V[some], None, None, plain[some], tol, "plain")
+
+
 def test_outlier_keys_large_logits_bf16():
     """Keys with x10 outlier channels give logits of several tens: the softmax must stay stable."""
     _say("attn outliers")
