@@ -277,6 +277,28 @@ int run_rounds(const void* K, const void* V, const int32_t* deg_in, const ckv_la
     if (assign) map = (j == 0) ? assign : reinterpret_cast<int32_t*>(ws + w.map);
     const bool keys_only = mode[j] == ROUND_KEYS_ONLY, from_origin = mode[j] == ROUND_ORIGIN;
     hipError_t err = hipSuccess;
+    EdgeCopy edges{};
+    if (mid < len) {   // sinks and recents (or a cache too short to cluster): straight copy
+      edges.K = static_cast<const unsigned char*>(curK);
+      edges.V = static_cast<const unsigned char*>(edgesV);
+      edges.deg_in = curDeg;
+      edges.in = curView;
+      edges.K_out = static_cast<unsigned char*>(oK);
+      edges.V_out = static_cast<unsigned char*>(oV);
+      edges.deg_out = oDeg;
+      edges.out = oView;
+      edges.map_out = map;
+      edges.in_len = len;
+      edges.out_len = next;
+      edges.n_head = mid > 0 ? lo : len;
+      edges.n_tail = mid > 0 ? len - hi : 0;
+      edges.pieces_per_row = in->dim * e / 16;
+      edges.elem_bytes = e;
+      edges.total = (int64_t)n_bh * (edges.n_head + edges.n_tail) * edges.pieces_per_row;
+      edges.pin = pin0;
+      edges.pok = pok0;
+      edges.pov = pov0;
+    }
     if (mid > 0) {   // cluster tokens [lo, hi): the same kernels on a view that starts at token lo
       const bool in_pool = pin.table != nullptr;
       const unsigned char* mK = static_cast<const unsigned char*>(curK) + (in_pool ? 0 : (size_t)lo * curView.stride_s * e);
@@ -295,12 +317,12 @@ int run_rounds(const void* K, const void* V, const int32_t* deg_in, const ckv_la
       int32_t* moDeg = pov.table ? oDeg : oDeg + lo;
       err = launch_merge(mK, mV, mDeg, in->dtype, in->dim, curView, n_bh, mid, p->chunk, plan.round_r[j], dst, score,
                          moK, moV, moDeg, oView, oDegStride, map ? map + lo : nullptr, curView.deg_stride, len, lo, sel,
-                         keys_only ? lists : nullptr, from_origin ? &org : nullptr, s, pin, pok, pov);
+                         keys_only ? lists : nullptr, from_origin ? &org : nullptr, s, pin, pok, pov,
+                         edges.total > 0 ? &edges : nullptr);
       if (err != hipSuccess) return hip_status(err);
+    } else {
+      err = launch_edges(edges, s);
     }
-    if (mid < len)   // sinks and recents (or a cache too short to cluster): straight copy
-      err = launch_edges(curK, edgesV, curDeg, curView, len, oK, oV, oDeg, oView, oDegStride, next, map,
-                         mid > 0 ? lo : len, mid > 0 ? len - hi : 0, n_bh, in->dim * e, e, s, pin0, pok0, pov0);
     if (err != hipSuccess) return hip_status(err);
     if (assign && j > 0) {
       err = launch_compose(assign, map, n_bh, in->seq, len, s);

@@ -79,6 +79,22 @@ struct ValueOrigin {
   PagedSide paged;        // V0 / deg0 are block pools (then V0, deg0 point at the pools, view0.heads = heads)
 };
 
+// A copy of the first n_head and the last n_tail tokens of every sequence (sinks / recents) to the head /
+// tail of the output, with their degrees and their entries of the round's map.
+struct EdgeCopy {
+  const unsigned char *K, *V;
+  const int32_t* deg_in;       // or NULL (= 1)
+  TensorView in;
+  unsigned char *K_out, *V_out;
+  int32_t* deg_out;
+  TensorView out;
+  int32_t* map_out;            // or NULL
+  int in_len, out_len, n_head, n_tail, pieces_per_row, elem_bytes;
+  int64_t total;               // 16-byte pieces in all
+  PagedSide pin, pok, pov;     // sides that live in a block pool (tok0 = 0)
+};
+hipError_t launch_edges(const EdgeCopy& edges, hipStream_t st);
+
 // Per-chunk top-r selection + degree-weighted merge + order-preserving compaction.
 // map_out[bh*map_stride + t] (t < seq) = map_offset + output index of the centroid input token t
 // joined; may be NULL.  deg_in[bh*deg_in_stride + t].  lists_out != NULL: keys-only first round of a
@@ -89,7 +105,8 @@ hipError_t launch_merge(const void* K, const void* V, const int32_t* deg_in, int
                         int32_t* deg_out, TensorView out, int64_t deg_out_stride, int32_t* map_out,
                         int64_t deg_in_stride, int64_t map_stride, int map_offset, const int32_t* sel_table,
                         int16_t* lists_out, const ValueOrigin* org, hipStream_t st, PagedSide paged_in = PagedSide{},
-                        PagedSide paged_out_k = PagedSide{}, PagedSide paged_out_v = PagedSide{});
+                        PagedSide paged_out_k = PagedSide{}, PagedSide paged_out_v = PagedSide{},
+                        const EdgeCopy* edges = nullptr);   // copied by the same launch
 
 // Selection over all chunks of a sequence: from the match scores, table[bh, chunk] = (edges of the
 // chunk among the sequence's floor(r * edges) best, first output row of the chunk), two int32 each.
@@ -102,14 +119,6 @@ hipError_t launch_global_select(const float* score, int n_bh, int seq, int chunk
 hipError_t launch_append(const void* k_new, const void* v_new, void* K, void* V, int32_t* deg, TensorView cache,
                          int batch, int capacity, int32_t* lens, int pos, int row_bytes, int elem_bytes,
                          hipStream_t st);
-
-// Copy the first n_head and the last n_tail tokens of every sequence (sinks / recents) to the
-// head / tail of the output, with their degrees and their entries of the round's map.
-hipError_t launch_edges(const void* K, const void* V, const int32_t* deg_in, TensorView in, int in_len, void* K_out,
-                        void* V_out, int32_t* deg_out, TensorView out, int64_t deg_out_stride, int out_len,
-                        int32_t* map_out, int n_head, int n_tail, int n_bh, int row_bytes, int elem_bytes,
-                        hipStream_t st, PagedSide paged_in = PagedSide{}, PagedSide paged_out_k = PagedSide{},
-                        PagedSide paged_out_v = PagedSide{});
 
 // assign[bh, t] = map[bh, assign[bh, t]] for t < seq0.
 hipError_t launch_compose(int32_t* assign, const int32_t* map, int n_bh, int seq0, int map_len,

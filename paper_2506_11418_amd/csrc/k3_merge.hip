@@ -43,6 +43,46 @@ __device__ inline int block_exclusive_scan(int v, int* s_wave_tot, int* total) {
   return base + inc - v;
 }
 
+// Tokens that bypass the clustering (Sec. 5.2: attention sinks and recent tokens are set aside
+// before partitioning; Sec. 5.3: they are concatenated back): the first n_head and the last n_tail
+// tokens of every sequence are copied to the head / tail of the output (keys, values, degree), and
+// their entries of the round's assignment map are written.  e: one 16-byte piece of one row.
+__device__ __forceinline__ void copy_edges(const EdgeCopy& ed, int64_t e) {
+  if (e >= ed.total) return;
+  const int piece = (int)(e % ed.pieces_per_row);
+  const int64_t row = e / ed.pieces_per_row;
+  const int n_edge = ed.n_head + ed.n_tail;
+  const int k = (int)(row % n_edge), bh = (int)(row / n_edge);
+  const int t_in = k < ed.n_head ? k : ed.in_len - ed.n_tail + (k - ed.n_head);
+  const int t_out = k < ed.n_head ? k : ed.out_len - ed.n_tail + (k - ed.n_head);
+  const int b = bh / ed.in.heads, h = bh % ed.in.heads;
+  // pool row of token u of this (batch, head) through a side's block table; -1 outside the pool
+  auto pool_row = [&](const PagedSide& pg, int u) -> int64_t {
+    const int blk = ((u >> pg.shift) < pg.max_blocks) ? pg.table[(int64_t)b * pg.max_blocks + (u >> pg.shift)] : -1;
+    if ((unsigned)blk >= (unsigned)pg.n_blocks) return -1;
+    return (((int64_t)blk * ed.in.heads + h) << pg.shift) + (u & ((1 << pg.shift) - 1));
+  };
+  const int64_t row_bytes = (int64_t)ed.pieces_per_row * 16;
+  int64_t ri = 0, rk = 0, rv = 0;
+  if (ed.pin.table) ri = pool_row(ed.pin, ed.pin.tok0 + t_in);
+  if (ed.pok.table) rk = pool_row(ed.pok, ed.pok.tok0 + t_out);
+  if (ed.pov.table) rv = pool_row(ed.pov, ed.pov.tok0 + t_out);
+  if (ri < 0) ri = 0;                      // a block outside the pool reads as row 0 and is not written
+  const int64_t so = ed.pin.table ? ri * row_bytes + piece * 16
+                                  : (ed.in.seq_base(bh) + (int64_t)t_in * ed.in.stride_s) * ed.elem_bytes + piece * 16;
+  const int64_t dof = (ed.out.seq_base(bh) + (int64_t)t_out * ed.out.stride_s) * ed.elem_bytes + piece * 16;
+  const int64_t dk = ed.pok.table ? rk * row_bytes + piece * 16 : dof;
+  const int64_t dv = ed.pov.table ? rv * row_bytes + piece * 16 : dof;
+  if (rk >= 0) *reinterpret_cast<uint4*>(ed.K_out + dk) = *reinterpret_cast<const uint4*>(ed.K + so);
+  if (rv >= 0) *reinterpret_cast<uint4*>(ed.V_out + dv) = *reinterpret_cast<const uint4*>(ed.V + so);
+  if (piece == 0) {
+    const int d = !ed.deg_in ? 1 : ed.pin.table ? ed.deg_in[ri] : ed.deg_in[(int64_t)bh * ed.in.deg_stride + t_in];
+    if (ed.pov.table) { if (rv >= 0) ed.deg_out[rv] = d; }
+    else ed.deg_out[(int64_t)bh * ed.out.deg_stride + t_out] = d;
+    if (ed.map_out) ed.map_out[(int64_t)bh * ed.in_len + t_in] = t_out;
+  }
+}
+
 template <typename T>
 struct Row;  // per-lane 16-byte piece arithmetic
 
@@ -105,7 +145,13 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
     int32_t* __restrict__ deg_out, TensorView out, int64_t deg_out_stride, int32_t* __restrict__ map_out,
     int64_t deg_in_stride, int64_t map_stride, int map_offset, const int2* __restrict__ sel_table,
     int16_t* __restrict__ lists_out, ValueOrigin org, int parts, PagedSide pin, PagedSide pout, int out_k_paged,
-    int out_v_paged) {
+    int out_v_paged, int edge_blocks, EdgeCopy edges) {
+  // The first workgroups copy the tokens that bypass the clustering (none of the others touches those
+  // rows): a launch of their own cost 4 to 6 us a round.
+  if ((int)blockIdx.x < edge_blocks) {
+    copy_edges(edges, (int64_t)blockIdx.x * kThreads + threadIdx.x);
+    return;
+  }
   constexpr int E = Row<T>::E;
   constexpr int LPR = D / E;                 // lanes per row
   constexpr int NRG = kThreads / LPR;        // row groups per workgroup
@@ -134,7 +180,8 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
 
   // `parts` workgroups share a chunk when the launch would otherwise leave most of the chip idle:
   // each repeats the (cheap) bookkeeping and emits every parts-th group of output rows.
-  const int part = blockIdx.x % parts, wg = blockIdx.x / parts;
+  const int id = (int)blockIdx.x - edge_blocks;
+  const int part = id % parts, wg = id / parts;
   const int g = wg % n_chunks, bh = wg / n_chunks;
   const int tid = threadIdx.x;
   const int g0 = g * chunk, L = min(chunk, seq - g0);
@@ -186,14 +233,28 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
       const int i = tid + it * kThreads;
       drop[it] = false;
       if (i < nA) {
+        // earlier indices win ties.  Which indices are earlier is known for all but the 64 of this wave, so
+        // that two instructions per score do instead of six
         const float si = s_score[i];
+        const int w0 = i & ~63, w1 = min(w0 + 64, nA_pad);
         int rank = 0;
-        for (int o4 = 0; o4 < nA_pad; o4 += 4) {
+#pragma unroll 4
+        for (int o4 = 0; o4 < w0; o4 += 4) {
+          const float4 so = *reinterpret_cast<const float4*>(&s_score[o4]);
+          rank += (so.x >= si) + (so.y >= si) + (so.z >= si) + (so.w >= si);
+        }
+#pragma unroll 2
+        for (int o4 = w0; o4 < w1; o4 += 4) {
           const float4 so = *reinterpret_cast<const float4*>(&s_score[o4]);
           rank += (so.x > si) || (so.x == si && o4 < i);
           rank += (so.y > si) || (so.y == si && o4 + 1 < i);
           rank += (so.z > si) || (so.z == si && o4 + 2 < i);
           rank += (so.w > si) || (so.w == si && o4 + 3 < i);
+        }
+#pragma unroll 4
+        for (int o4 = w1; o4 < nA_pad; o4 += 4) {
+          const float4 so = *reinterpret_cast<const float4*>(&s_score[o4]);
+          rank += (so.x > si) + (so.y > si) + (so.z > si) + (so.w > si);
         }
         drop[it] = rank >= m;
       }
@@ -733,51 +794,7 @@ __global__ void copy_rows_kernel(const unsigned char* __restrict__ src, TensorVi
   *reinterpret_cast<uint4*>(dst + dof) = *reinterpret_cast<const uint4*>(src + so);
 }
 
-// Tokens that bypass the clustering (Sec. 5.2: attention sinks and recent tokens are set aside
-// before partitioning; Sec. 5.3: they are concatenated back): the first n_head and the last n_tail
-// tokens of every sequence are copied to the head / tail of the output (keys, values, degree), and
-// their entries of the round's assignment map are written.
-__global__ void edges_kernel(const unsigned char* __restrict__ K, const unsigned char* __restrict__ V,
-                             const int32_t* __restrict__ deg_in, TensorView in, int in_len,
-                             unsigned char* __restrict__ K_out, unsigned char* __restrict__ V_out,
-                             int32_t* __restrict__ deg_out, TensorView out, int64_t deg_out_stride, int out_len,
-                             int32_t* __restrict__ map_out, int n_head, int n_tail, int pieces_per_row,
-                             int elem_bytes, int64_t total, PagedSide pin, PagedSide pok, PagedSide pov) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= total) return;
-  const int piece = (int)(e % pieces_per_row);
-  const int64_t row = e / pieces_per_row;
-  const int n_edge = n_head + n_tail;
-  const int k = (int)(row % n_edge), bh = (int)(row / n_edge);
-  const int t_in = k < n_head ? k : in_len - n_tail + (k - n_head);
-  const int t_out = k < n_head ? k : out_len - n_tail + (k - n_head);
-  const int b = bh / in.heads, h = bh % in.heads;
-  // pool row of token u of this (batch, head) through a side's block table; -1 outside the pool
-  auto pool_row = [&](const PagedSide& pg, int u) -> int64_t {
-    const int blk = ((u >> pg.shift) < pg.max_blocks) ? pg.table[(int64_t)b * pg.max_blocks + (u >> pg.shift)] : -1;
-    if ((unsigned)blk >= (unsigned)pg.n_blocks) return -1;
-    return (((int64_t)blk * in.heads + h) << pg.shift) + (u & ((1 << pg.shift) - 1));
-  };
-  const int64_t row_bytes = (int64_t)pieces_per_row * 16;
-  int64_t ri = 0, rk = 0, rv = 0;
-  if (pin.table) ri = pool_row(pin, pin.tok0 + t_in);
-  if (pok.table) rk = pool_row(pok, pok.tok0 + t_out);
-  if (pov.table) rv = pool_row(pov, pov.tok0 + t_out);
-  if (ri < 0) ri = 0;                      // a block outside the pool reads as row 0 and is not written
-  const int64_t so = pin.table ? ri * row_bytes + piece * 16
-                               : (in.seq_base(bh) + (int64_t)t_in * in.stride_s) * elem_bytes + piece * 16;
-  const int64_t dof = (out.seq_base(bh) + (int64_t)t_out * out.stride_s) * elem_bytes + piece * 16;
-  const int64_t dk = pok.table ? rk * row_bytes + piece * 16 : dof;
-  const int64_t dv = pov.table ? rv * row_bytes + piece * 16 : dof;
-  if (rk >= 0) *reinterpret_cast<uint4*>(K_out + dk) = *reinterpret_cast<const uint4*>(K + so);
-  if (rv >= 0) *reinterpret_cast<uint4*>(V_out + dv) = *reinterpret_cast<const uint4*>(V + so);
-  if (piece == 0) {
-    const int d = !deg_in ? 1 : pin.table ? deg_in[ri] : deg_in[(int64_t)bh * in.deg_stride + t_in];
-    if (pov.table) { if (rv >= 0) deg_out[rv] = d; }
-    else deg_out[(int64_t)bh * deg_out_stride + t_out] = d;
-    if (map_out) map_out[(int64_t)bh * in_len + t_in] = t_out;
-  }
-}
+__global__ void edges_kernel(EdgeCopy ed) { copy_edges(ed, (int64_t)blockIdx.x * blockDim.x + threadIdx.x); }
 
 // Cache update of a decode step (Algorithm 1, decoding part): the new token of every (batch, head)
 // goes to row lens[b] (or `pos`) with degree 1.  A sequence already at capacity is left alone.
@@ -820,10 +837,12 @@ hipError_t launch_merge_t(const void* K, const void* V, const int32_t* deg_in, T
                           void* K_out, void* V_out, int32_t* deg_out, TensorView out,
                           int64_t deg_out_stride, int32_t* map_out, int64_t deg_in_stride, int64_t map_stride,
                           int map_offset, const int32_t* sel_table, int16_t* lists_out, const ValueOrigin* org,
-                          hipStream_t st, PagedSide pin, PagedSide pok, PagedSide pov) {
+                          hipStream_t st, PagedSide pin, PagedSide pok, PagedSide pov, const EdgeCopy* edges) {
   const int n_chunks = div_up(seq, chunk);
   const int64_t total = (int64_t)n_bh * n_chunks;
-  if (total > (1 << 30)) return hipErrorInvalidValue;
+  const EdgeCopy ed = edges ? *edges : EdgeCopy{};
+  const int64_t edge_blocks = edges ? (ed.total + kThreads - 1) / kThreads : 0;
+  if (total > (1 << 30) || edge_blocks > (1 << 30)) return hipErrorInvalidValue;
   const ValueOrigin o = org ? *org : ValueOrigin{};
   // small launches: split every chunk's rows over several workgroups, aiming at 4 workgroups per CU
   int parts = 1;
@@ -835,12 +854,12 @@ hipError_t launch_merge_t(const void* K, const void* V, const int32_t* deg_in, T
     return hipErrorInvalidValue;
   const PagedSide pout = pok.table ? pok : pov;
 #define CKV_LAUNCH_MH(MODE, MH, PG)                                                                           \
-  hipLaunchKernelGGL((merge_kernel<T, D, MODE, MH, PG>), dim3((int)(total * parts)), dim3(kThreads), 0, st,  \
+  hipLaunchKernelGGL((merge_kernel<T, D, MODE, MH, PG>), dim3((unsigned)(total * parts + edge_blocks)), dim3(kThreads), 0, st, \
                      static_cast<const T*>(K), static_cast<const T*>(V), deg_in, in, seq, chunk, n_chunks, r, \
                      dst_local, score, static_cast<T*>(K_out), static_cast<T*>(V_out), deg_out, out,          \
                      deg_out_stride, map_out, deg_in_stride, map_stride, map_offset,                          \
                      reinterpret_cast<const int2*>(sel_table), lists_out, o, parts, pin, pout,                \
-                     pok.table != nullptr, pov.table != nullptr)
+                     pok.table != nullptr, pov.table != nullptr, (int)edge_blocks, ed)
   // smaller LDS arrays for chunks of up to 1024 tokens: more workgroups per CU
 #define CKV_LAUNCH(MODE)                                                    \
   do {                                                                      \
@@ -874,11 +893,11 @@ hipError_t launch_merge(const void* K, const void* V, const int32_t* deg_in, int
                         int32_t* deg_out, TensorView out, int64_t deg_out_stride, int32_t* map_out,
                         int64_t deg_in_stride, int64_t map_stride, int map_offset, const int32_t* sel_table,
                         int16_t* lists_out, const ValueOrigin* org, hipStream_t st, PagedSide paged_in,
-                        PagedSide paged_out_k, PagedSide paged_out_v) {
+                        PagedSide paged_out_k, PagedSide paged_out_v, const EdgeCopy* edges) {
 #define CKV_MERGE(T, DD)                                                                             \
   return launch_merge_t<T, DD>(K, V, deg_in, in, n_bh, seq, chunk, r, dst_local, score, K_out, V_out, \
                                deg_out, out, deg_out_stride, map_out, deg_in_stride, map_stride, map_offset, \
-                               sel_table, lists_out, org, st, paged_in, paged_out_k, paged_out_v)
+                               sel_table, lists_out, org, st, paged_in, paged_out_k, paged_out_v, edges)
   if (dtype == CKV_BF16) {
     if (dim == 128) CKV_MERGE(__bf16, 128);
     if (dim == 64) CKV_MERGE(__bf16, 64);
@@ -915,19 +934,10 @@ hipError_t launch_copy_rows(const void* src, TensorView in, void* dst, TensorVie
   return hipGetLastError();
 }
 
-hipError_t launch_edges(const void* K, const void* V, const int32_t* deg_in, TensorView in, int in_len, void* K_out,
-                        void* V_out, int32_t* deg_out, TensorView out, int64_t deg_out_stride, int out_len,
-                        int32_t* map_out, int n_head, int n_tail, int n_bh, int row_bytes, int elem_bytes,
-                        hipStream_t st, PagedSide paged_in, PagedSide paged_out_k, PagedSide paged_out_v) {
-  const int ppr = row_bytes / 16;
-  const int64_t total = (int64_t)n_bh * (n_head + n_tail) * ppr;
-  if (total == 0) return hipSuccess;
+hipError_t launch_edges(const EdgeCopy& ed, hipStream_t st) {
+  if (ed.total == 0) return hipSuccess;
   ScopedTimer t("edges_copy", st);
-  hipLaunchKernelGGL(edges_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
-                     static_cast<const unsigned char*>(K), static_cast<const unsigned char*>(V), deg_in, in, in_len,
-                     static_cast<unsigned char*>(K_out), static_cast<unsigned char*>(V_out), deg_out, out,
-                     deg_out_stride, out_len, map_out, n_head, n_tail, ppr, elem_bytes, total, paged_in, paged_out_k,
-                     paged_out_v);
+  hipLaunchKernelGGL(edges_kernel, dim3((unsigned)((ed.total + 255) / 256)), dim3(256), 0, st, ed);
   return hipGetLastError();
 }
 

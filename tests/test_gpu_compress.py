@@ -108,8 +108,7 @@ def test_match_bf16_shapes(heads, seq, dim, chunk):
     (1, 2, 191, 128, 128, "bhsd"),       # one whole chunk + a tail of 63
 ])
 def test_match_small_chunk_kernel_bf16(batch, heads, seq, dim, chunk, layout):
-    """Whole chunks go through the kernel that packs 512 tokens (8, 4 or 2 chunks) into a workgroup,
-    a ragged tail chunk through the one-chunk-per-workgroup kernel; both write one result array."""
+    """The kernel that packs 512 tokens (8, 4 or 2 chunks, the last one possibly ragged) into a workgroup."""
     _say(f"match small chunks B={batch} H={heads} S={seq} D={dim} c={chunk} {layout}")
     Ks = [kv_host(41 + b, heads, seq, dim, "bf16", alpha=0.9, n_outlier=4 if dim == 128 else 0)[0] for b in range(batch)]
     K = torch.cat(Ks, dim=0)
@@ -131,6 +130,19 @@ def test_match_small_chunk_kernel_bf16(batch, heads, seq, dim, chunk, layout):
         srcs = [t for t in range(g0, g0 + chunk // 2, 2)]
         got = i64(dst[0, heads - 1])[[t // 2 for t in srcs]]
         assert np.all(got == g0 + 1), got
+
+
+@pytest.mark.parametrize("chunk", [64, 128, 256])
+@pytest.mark.parametrize("whole", [512, 768])            # the tail opens a workgroup's block, or follows whole chunks in it
+def test_match_small_chunks_ragged_tails_bf16(whole, chunk):
+    """Tails of one token (no edge), one pair, around one tile of 32 rows and one short of a chunk."""
+    _say(f"match small chunks, tails after {whole}, c={chunk}")
+    for tail in sorted({1, 2, 3, 62, 63, min(64, chunk - 2), min(65, chunk - 1), chunk - 1}):
+        K, _, _ = kv_host(51 + tail, 2, whole + tail, 128, "bf16", alpha=0.9, n_outlier=4)
+        dst, score = ckv.match(K.to(DEV), chunk)
+        torch.cuda.synchronize()
+        for h in range(2):
+            check_match(f64(K[0, h]), chunk, i64(dst[0, h]), f64(score[0, h]), f"tail {tail} h{h}")
 
 
 # ---- the persistent kernel for whole 1024- or 2048-token chunks of 128-dim bf16 keys --------------
