@@ -2,11 +2,19 @@
 // every chunk of a sequence enter one common ranking and the best fraction r of them is merged.
 //
 // One workgroup per (batch, head) sequence finds the cut of the ranking (score descending, position
-// ascending) below its m = floor(r * edges) best edges with a 4-pass radix select over the fp32
+// ascending) below its m = floor(r * edges) best edges with a 3-pass radix select over the fp32
 // scores, then counts for every chunk how many of its edges lie above the cut and prefix-sums the
 // chunks' output offsets.  The merge kernel then keeps, in each chunk, that many of the chunk's
 // best edges under the same order, which is exactly the part of the global top-m that falls into
 // the chunk.  Everything is integer work on the stored scores: the result is deterministic.
+//
+// What bounds it: one workgroup walks its sequence's scores four times (three passes of digits and the
+// count per chunk), so the latency of its loads, not their bytes.  Every thread therefore has eight scores
+// in flight, the digits are wide (11, 11 and 10 bits: one pass less than with 8), and the wanted bin is
+// found by a scan over all threads.  With one load in flight, 8-bit digits, plain atomics and one thread
+// walking the bins it took, against now (us a launch; sequences x tokens, chunk): 8 x 1048576, 1024:
+// 1688 -> 417; 8 x 1048576, 64: 1926 -> 654; 64 x 131072, 1024: 222 -> 63; 256 x 32768, 512: 77 -> 28;
+// 8 x 16384, 256: 46 -> 20; 1 x 2000, 64: 24 -> 14.
 #include "ckv_internal.h"
 
 namespace ckv {
@@ -14,6 +22,8 @@ namespace {
 
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
+constexpr int kSelBins = 2 * kSelThreads;   // digits of 11, 11 and 10 bits; a thread scans two bins
+constexpr int kSelFlight = 8;               // scores a thread requests before it looks at the first
 
 // fp32 -> uint32 whose unsigned order is the float order (-0 and +0 compare equal, as they do
 // in the merge kernel's float comparisons)
@@ -44,13 +54,26 @@ __device__ inline int block_scan_excl(int v, int* s_wave, int* total) {
   return base + inc - v;
 }
 
+// Counts one digit per lane into the histogram.  Similarities crowd into a few values of the top digit
+// (sign, exponent, two bits of mantissa), and atomics of a wave on one LDS word go one after the other:
+// the lanes that share the first counted lane's digit add themselves up and count as one.
+__device__ inline void count_digit(int* hist, int digit, bool in, int lane) {
+  const uint64_t todo = __ballot(in);
+  if (todo == 0) return;
+  const int leader = __ffsll((unsigned long long)todo) - 1;
+  const bool same = in && digit == __shfl(digit, leader);
+  const int n = __popcll(__ballot(same));
+  if (lane == leader) atomicAdd(&hist[digit], n);
+  if (in && !same) atomicAdd(&hist[digit], 1);
+}
+
 // table[bh * n_chunks + g] = (edges of chunk g that are merged, first output row of chunk g)
 __global__ __launch_bounds__(kSelThreads) void global_select_kernel(const float* __restrict__ score, int seq,
                                                                     int chunk, int n_chunks, float r,
                                                                     int2* __restrict__ table) {
-  __shared__ int s_hist[256];
+  __shared__ int s_hist[kSelBins];
   __shared__ int s_wave[kSelWaves];
-  __shared__ uint32_t s_prefix;
+  __shared__ uint32_t s_digit;
   __shared__ int s_k;
 
   const int bh = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -66,50 +89,87 @@ __global__ __launch_bounds__(kSelThreads) void global_select_kernel(const float*
   int quota = 0;         // edges with key == cut that are merged (the lowest positions)
   const bool all = (m >= n_edges), none = (m == 0);
   if (!all && !none) {
-    if (tid == 0) { s_prefix = 0; s_k = m; }
-    for (int pass = 0; pass < 4; ++pass) {
-      const int shift = 24 - 8 * pass;
-      if (tid < 256) s_hist[tid] = 0;
+    uint32_t prefix = 0, known = 0;      // the digits found so far and the bits they cover
+    int k = m;                           // rank wanted among the edges that share the prefix
+#pragma unroll
+    for (int pass = 0; pass < 3; ++pass) {
+      const int bits = pass == 2 ? 10 : 11, shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
+      const uint32_t digit_mask = (1u << bits) - 1u;
+      for (int i = tid; i < kSelBins; i += kSelThreads) s_hist[i] = 0;
       __syncthreads();
-      const uint32_t prefix = s_prefix;
-      const uint32_t mask = pass == 0 ? 0u : (0xFFFFFFFFu << (shift + 8));
-      for (int i = tid; i < n_edges; i += kSelThreads) {
-        const uint32_t k = order_key(sc[i]);
-        if ((k & mask) == prefix) atomicAdd(&s_hist[(k >> shift) & 255], 1);
-      }
-      __syncthreads();
-      if (tid == 0) {   // walk the digits from the top until the wanted rank falls into one
-        int k = s_k, d = 255;
-        for (; d > 0; --d) {
-          const int c = s_hist[d];
-          if (c >= k) break;
-          k -= c;
+      for (int i0 = 0; i0 < n_edges; i0 += kSelThreads * kSelFlight) {
+        float x[kSelFlight];
+#pragma unroll
+        for (int e = 0; e < kSelFlight; ++e) x[e] = sc[min(i0 + e * kSelThreads + tid, n_edges - 1)];
+#pragma unroll
+        for (int e = 0; e < kSelFlight; ++e) {
+          const uint32_t key = order_key(x[e]);
+          const bool in = (i0 + e * kSelThreads + tid < n_edges) && (key & known) == prefix;
+          count_digit(s_hist, (int)((key >> shift) & digit_mask), in, lane);
         }
-        s_k = k;
-        s_prefix = prefix | ((uint32_t)d << shift);
       }
       __syncthreads();
+      // thread t holds the bins 2047 - 2t and 2046 - 2t: the scan runs from the top digit down
+      const int hi = s_hist[kSelBins - 1 - 2 * tid], lo = s_hist[kSelBins - 2 - 2 * tid];
+      int total;
+      const int above = block_scan_excl(hi + lo, s_wave, &total);
+      if (above < k && k <= above + hi + lo) {
+        const bool in_hi = k <= above + hi;
+        s_digit = (uint32_t)(kSelBins - (in_hi ? 1 : 2) - 2 * tid);
+        s_k = k - above - (in_hi ? 0 : hi);
+      }
+      __syncthreads();
+      prefix |= s_digit << shift;
+      known |= digit_mask << shift;
+      k = s_k;
     }
-    cut = s_prefix;
-    quota = s_k;
+    cut = prefix;
+    quota = k;
   }
 
   // ---- per chunk: edges above the cut and edges on it -----------------------------------------
   // table is used as scratch first: (.x = above, .y = on the cut)
-  if (half >= 32) {      // a wave per chunk
+  if (half > 64) {       // a wave per chunk, its scores 512 at a time
     for (int g = wave; g < n_chunks; g += kSelWaves) {
       const int L = min(chunk, seq - g * chunk);
       const int nA = (L >= 2) ? (L + 1) >> 1 : 0;
       int gt = 0, eq = 0;
       if (all) gt = nA;
       else if (!none)
-        for (int i0 = 0; i0 < nA; i0 += 64) {
-          const int i = i0 + lane;
-          const uint32_t k = (i < nA) ? order_key(sc[g * half + i]) : 0u;
-          gt += __popcll(__ballot(i < nA && k > cut));
-          eq += __popcll(__ballot(i < nA && k == cut));
+        for (int i0 = 0; i0 < nA; i0 += 64 * kSelFlight) {
+          float x[kSelFlight];
+#pragma unroll
+          for (int e = 0; e < kSelFlight; ++e) x[e] = sc[g * half + min(i0 + e * 64 + lane, nA - 1)];
+#pragma unroll
+          for (int e = 0; e < kSelFlight; ++e) {
+            const uint32_t k = order_key(x[e]);
+            const bool in = i0 + e * 64 + lane < nA;
+            gt += __popcll(__ballot(in && k > cut));
+            eq += __popcll(__ballot(in && k == cut));
+          }
         }
       if (lane == 0) tab[g] = make_int2(gt, eq);
+    }
+  } else if (half >= 32) {   // a wave per chunk, the scores of eight chunks at a time
+    for (int g0 = wave; g0 < n_chunks; g0 += kSelWaves * kSelFlight) {
+      float x[kSelFlight];
+      int nA[kSelFlight];
+#pragma unroll
+      for (int e = 0; e < kSelFlight; ++e) {
+        const int g = g0 + e * kSelWaves;
+        const int L = g < n_chunks ? min(chunk, seq - g * chunk) : 0;
+        nA[e] = (L >= 2) ? (L + 1) >> 1 : 0;
+        x[e] = (lane < nA[e]) ? sc[g * half + lane] : 0.f;
+      }
+#pragma unroll
+      for (int e = 0; e < kSelFlight; ++e) {
+        const int g = g0 + e * kSelWaves;
+        const uint32_t k = order_key(x[e]);
+        const bool in = lane < nA[e] && !none;
+        const int gt = all ? nA[e] : __popcll(__ballot(in && k > cut));
+        const int eq = all ? 0 : __popcll(__ballot(in && k == cut));
+        if (lane == 0 && g < n_chunks) tab[g] = make_int2(gt, eq);
+      }
     }
   } else {               // a thread per chunk
     for (int g = tid; g < n_chunks; g += kSelThreads) {

@@ -385,6 +385,36 @@ def test_whole_sequence_selection_ties_across_identical_chunks():
 
 
 # ---- layouts, degrees, degenerate inputs ------------------------------------------------------
+@pytest.mark.parametrize("edges,chunk,r,opposed", [
+    (8191, 128, 0.3, False),      # one edge less than the scores of a workgroup's step, chunks of 64 sources
+    (8192, 128, 0.5, False),
+    (8193, 64, 0.9, False),       # one more; chunks of 32 sources, eight at a time
+    (16400, 130, 0.01, False),    # chunks of 65 sources: one more than a wave
+    (9000, 1026, 0.7, False),     # 513 sources: one more than the scores of a wave's step
+    (9000, 256, 0.4, True),       # every similarity below zero
+])
+def test_whole_sequence_selection_merges_the_best_edges_exactly(edges, chunk, r, opposed):
+    """Integer work on the scores ckv_match gives: the number of edges merged in every chunk is exact."""
+    _say(f"scope=head counts edges={edges} c={chunk} r={r} opposed={opposed}")
+    seq = 2 * edges
+    K, V, _ = kv_host(47, 2, seq, 64, "bf16", alpha=0.9, n_outlier=0)
+    if opposed:
+        K = K.abs()
+        K[:, :, 1::2] *= -1
+    K, V = K.to(DEV), V.to(DEV)
+    _, score = ckv.match(K, chunk)
+    _, _, _, gas = ckv.compress(K, V, chunk, rounds=[r], scope="head")
+    torch.cuda.synchronize()
+    for h in range(2):
+        sc = score.view(2, edges)[h].cpu().numpy()
+        assert not opposed or (sc < 0).all()
+        kept = np.zeros(edges, dtype=np.int64)
+        kept[np.argsort(-sc, kind="stable")[:int(float(np.float32(r)) * edges + 1e-9)]] = 1
+        want = [kept[i:i + chunk // 2].sum() for i in range(0, edges, chunk // 2)]
+        a = i64(gas[0, h])
+        assert [len(c) - len(np.unique(c)) for c in (a[i:i + chunk] for i in range(0, seq, chunk))] == want
+
+
 def test_bshd_layout_and_padded_output():
     _say("compress strided layout")
     K, V, _ = kv_host(13, 2, 1024, 128, "bf16", n_outlier=4)
