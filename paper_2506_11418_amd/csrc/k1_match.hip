@@ -42,7 +42,7 @@ constexpr int kPanel = 128;                      // B rows per LDS panel
 // rows of the chunk's blocks are staged in LDS first.
 template <int D, int NW, bool PAGED>
 __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void match_bf16_kernel(
-    const __bf16* __restrict__ K, TensorView kv, int seq, int chunk, int n_chunks, int a_blocks,
+    const __bf16* __restrict__ K, TensorView kv, int seq, int chunk, int first_chunk, int n_chunks, int a_blocks,
     int total_work, int per_xcd, int32_t* __restrict__ dst_local, float* __restrict__ score, PagedSide paged) {
   constexpr int OCT = D / 8;                       // 16-byte pieces per key row
   constexpr int ROWB = D * 2;                      // bytes per row
@@ -59,7 +59,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void match_bf16_kernel(
   const int w = xcd_remap(blockIdx.x, per_xcd);
   if (w >= total_work) return;
   const int ab = w % a_blocks;
-  const int g = (w / a_blocks) % n_chunks;
+  const int g = first_chunk + (w / a_blocks) % n_chunks;
   const int bh = w / (a_blocks * n_chunks);
   const int g0 = g * chunk;
   const int L = min(chunk, seq - g0);
@@ -759,7 +759,8 @@ __global__ void dst_positions_kernel(const int32_t* __restrict__ dst_local, int3
 
 template <int D, int NW, bool PAGED>
 hipError_t launch_match_bf16_nw(const void* K, TensorView kv, int n_bh, int seq, int chunk,
-                                int32_t* dst_local, float* score, hipStream_t st, PagedSide paged) {
+                                int32_t* dst_local, float* score, hipStream_t st, PagedSide paged,
+                                int first_chunk = 0) {
   constexpr int ABLOCK = NW * kRowsPerWave;
   // staging area + inverse norms of two panels (+ PAGED: the pool rows of a chunk's blocks, 8 tokens or more each)
   constexpr size_t lds = (size_t)(ABLOCK > 2 * kPanel ? ABLOCK : 2 * kPanel) * D * 2 + 2 * kPanel * sizeof(float) +
@@ -767,14 +768,14 @@ hipError_t launch_match_bf16_nw(const void* K, TensorView kv, int n_bh, int seq,
   static KernelSetup setup;
   if (hipError_t e = kernel_setup(reinterpret_cast<const void*>(&match_bf16_kernel<D, NW, PAGED>), lds, setup); e != hipSuccess)
     return e;
-  const int n_chunks = div_up(seq, chunk);
-  const int a_blocks = div_up(chunk / 2, ABLOCK);
+  const int n_chunks = div_up(seq, chunk) - first_chunk;
+  const int a_blocks = div_up((min(chunk, seq - first_chunk * chunk) + 1) / 2, ABLOCK);   // the launch's longest chunk
   const int64_t total = (int64_t)n_bh * n_chunks * a_blocks;
   if (total > (1 << 30)) return hipErrorInvalidValue;
   const int per_xcd = div_up((int)total, 8);
   ScopedTimer t("match_bf16", st);
   hipLaunchKernelGGL((match_bf16_kernel<D, NW, PAGED>), dim3(per_xcd * 8), dim3(NW * 64), lds, st,
-                     static_cast<const __bf16*>(K), kv, seq, chunk, n_chunks, a_blocks, (int)total,
+                     static_cast<const __bf16*>(K), kv, seq, chunk, first_chunk, n_chunks, a_blocks, (int)total,
                      per_xcd, dst_local, score, paged);
   return hipGetLastError();
 }
@@ -830,6 +831,14 @@ hipError_t launch_match_bf16(const void* K, TensorView kv, int n_bh, int seq, in
   return launch_match_bf16_nw<D, 4, false>(K, kv, n_bh, seq, chunk, dst_local, score, st, paged);
 }
 
+// From how many chunks of 1024 tokens on sequences with a ragged tail chunk take the streaming kernel for
+// their whole chunks and a launch of the general kernel for the tails.  The second launch costs up to 9 us,
+// the streaming kernel saves about a tenth (us, one launch -> two; sequences x tokens): 8 x 8300 (64 chunks)
+// 20 -> 29; 8 x 65700 (512) 55 -> 55; 8 x 131500 (1024) 100 -> 92; 32 x 32900 (1024) 97 -> 88; 64 x 50003
+// 290 -> 259; 256 x 33700 729 -> 670.  Chunks of 2048 gain 1% at best (64 x 50003: 437 -> 446) and stay in
+// one launch.
+constexpr int kStreamRaggedChunks = 1024;
+
 }  // namespace
 
 hipError_t launch_match(const void* K, int dtype, int dim, TensorView kv, int n_bh, int seq,
@@ -837,9 +846,15 @@ hipError_t launch_match(const void* K, int dtype, int dim, TensorView kv, int n_
   if (paged.table && paged.shift < 3) return hipErrorInvalidValue;   // the kernels' LDS tables hold blocks of 8 tokens or more
   if (dtype == CKV_BF16) {
     // (the persistent streaming kernel walks memory with fixed pitches: strided tensors only)
-    if (!paged.table && dim == 128 && (chunk == 1024 || chunk == 2048) && seq % chunk == 0 && seq > 0 && kv.stride_s <= (1 << 22))
-      return chunk == 1024 ? launch_match_stream<16>(K, kv, n_bh, seq, dst_local, score, st)
-                           : launch_match_stream<32>(K, kv, n_bh, seq, dst_local, score, st);
+    const int whole = seq / chunk, tail = seq % chunk;
+    if (!paged.table && dim == 128 && (chunk == 1024 || chunk == 2048) && whole > 0 && kv.stride_s <= (1 << 22) &&
+        (tail == 0 || (chunk == 1024 && (int64_t)n_bh * whole >= kStreamRaggedChunks))) {
+      const hipError_t e = chunk == 1024 ? launch_match_stream<16>(K, kv, n_bh, seq, dst_local, score, st)
+                                         : launch_match_stream<32>(K, kv, n_bh, seq, dst_local, score, st);
+      if (e != hipSuccess || tail == 0) return e;
+      return tail > 512 ? launch_match_bf16_nw<128, 8, false>(K, kv, n_bh, seq, chunk, dst_local, score, st, paged, whole)
+                        : launch_match_bf16_nw<128, 4, false>(K, kv, n_bh, seq, chunk, dst_local, score, st, paged, whole);
+    }
     if (dim == 128) return launch_match_bf16<128>(K, kv, n_bh, seq, chunk, dst_local, score, st, paged);
     if (dim == 64) return launch_match_bf16<64>(K, kv, n_bh, seq, chunk, dst_local, score, st, paged);
     return hipErrorInvalidValue;

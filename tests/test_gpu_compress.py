@@ -174,6 +174,22 @@ def test_match_streaming_kernel_bf16(batch, heads, seq, layout, chunk):
             check_match(f64(K[b, h]), chunk, i64(dst[b, h]), f64(score[b, h]), f"b{b}h{h}")
 
 
+@pytest.mark.parametrize("tail", [1, 2, 511, 513, 1023])
+def test_match_streaming_kernel_with_ragged_tails_bf16(tail):
+    """From 1024 whole chunks on they take the streaming kernel and the tails a launch of their own: the bits
+    of the whole chunks by themselves and of the tails by themselves, on both kernels' own routes."""
+    heads, whole, chunk = 64, 16, 1024
+    _say(f"match ragged H={heads} S={whole}*{chunk}+{tail}")
+    gen = torch.Generator(device=DEV).manual_seed(tail)
+    K = torch.randn((1, heads, whole * chunk + tail, 128), generator=gen, device=DEV).to(torch.bfloat16)
+    dst, score = ckv.match(K, chunk)
+    d0, s0 = ckv.match(K[:, :, :whole * chunk], chunk)
+    d1, s1 = ckv.match(K[:, :, whole * chunk:], chunk)
+    n = whole * chunk // 2
+    assert torch.equal(dst[:, :, :n], d0) and torch.equal(score[:, :, :n], s0)
+    assert torch.equal(dst[:, :, n:], torch.where(d1 < 0, d1, d1 + whole * chunk)) and torch.equal(score[:, :, n:], s1)
+
+
 @pytest.mark.parametrize("chunk", [1024, 2048])
 def test_match_streaming_kernel_takes_the_lowest_index_among_equal_maxima(chunk):
     """Exactly equal scores in different tiles, lane halves and accumulators: lowest B index wins."""
