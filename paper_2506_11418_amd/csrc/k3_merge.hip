@@ -845,6 +845,9 @@ hipError_t launch_merge_t(const void* K, const void* V, const int32_t* deg_in, T
   if (total > (1 << 30) || edge_blocks > (1 << 30)) return hipErrorInvalidValue;
   const ValueOrigin o = org ? *org : ValueOrigin{};
   // small launches: split every chunk's rows over several workgroups, aiming at 4 workgroups per CU
+  // (compression to a quarter with 512, 1024 or 2048 workgroups as the aim, us; sequences x tokens, chunk:
+  // 8 x 32768, 1024: 135, 119, 123; 8 x 131072, 1024: 364, 337, 358; 16 x 131072, 2048: 899, 846, 864; one
+  // round of 8 x 8448, 256: 33.5, 33.1, 40.4)
   int parts = 1;
   while (parts < 8 && total * parts < 1024) parts *= 2;
   // any side in a block pool: the kernel variant that stages block tables (blocks of 8 tokens or more)
