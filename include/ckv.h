@@ -176,7 +176,9 @@ int ckv_schedule_annealed(int32_t seq, int32_t chunk, int32_t n_sink, int32_t n_
 int ckv_append(const void* k_new, const void* v_new, void* K, void* V, int32_t* deg, const ckv_layout* cache,
                int32_t* lens, int32_t pos, void* hip_stream);
 
-/* Scratch bytes ckv_decode_attn needs for this cache shape and number of query heads.
+/* Scratch bytes that serve ckv_decode_attn at this cache shape and number of query heads, and at every
+ * shape with fewer tokens or a smaller batch: a workspace sized for a cache's capacity is large enough
+ * while the cache fills.  (A call checks for what its own shape needs, which can be less.)
  * Workspace contract (ckv_decode_attn and ckv_paged_decode_attn): the first 4 * batch * heads bytes
  * are arrival counters, one int32 per (batch, KV head).  They must be ZERO when a call starts and
  * every call leaves them zero, so zero-fill a workspace once when it is allocated; after that it
@@ -210,9 +212,9 @@ int ckv_decode_attn(const void* q, int32_t q_heads, const void* K, const void* V
  * looks its address up).  The call allocates and frees nothing and launches nothing but the
  * attention kernel: the arrival counters keep the array's first 64 KiB to themselves (zero when the
  * library is loaded, left at zero by every call), the partials use the rest.
- * CKV_EWORKSPACE when batch * kv->heads exceeds 16384 or the partials (ckv_decode_attn_workspace()
- * minus its counters) exceed CKV_NOALLOC_SCRATCH_BYTES - 64 KiB (the Llama-3-8B decode shapes,
- * batch 1 to 16 at 32 query heads, need about 1.1 MB).  All calls on
+ * CKV_EWORKSPACE when batch * kv->heads exceeds 16384 or the call's own partials (four bytes times
+ * dim + 2 per query head and slice) exceed CKV_NOALLOC_SCRATCH_BYTES - 64 KiB (the Llama-3-8B decode
+ * shapes, batch 1 to 16 at 32 query heads, need about 1.1 MB).  All calls on
  * one GPU share that one array: calls that overlap in time on the same GPU (different streams or
  * threads) race; issue them on one stream, or otherwise order them. */
 #define CKV_NOALLOC_SCRATCH_BYTES (4u << 20)
@@ -236,7 +238,8 @@ typedef struct {
 
 /* ckv_decode_attn (Eq. 3) reading the paged cache in place.  lens [batch] int32 (device, required):
  * tokens of each sequence; max_len: host upper bound on them (sizes the split of the sequence;
- * lengths are clamped to it and to max_blocks*block_size).  deg_pool NULL = all ones (Eq. 1).
+ * lengths are clamped to it and to max_blocks*block_size; the workspace size for a max_len serves every
+ * smaller one and tables of any width).  deg_pool NULL = all ones (Eq. 1).
  * CKV_EUNSUPPORTED for a pool of 2^31 token rows (n_blocks*heads*block_size) or more. */
 int ckv_paged_decode_attn_workspace(const ckv_paged_layout* pl, int32_t q_heads, int32_t max_len, size_t* bytes);
 int ckv_paged_decode_attn(const void* q, int32_t q_heads, const void* K_pool, const void* V_pool,

@@ -505,22 +505,22 @@ int ckv_decode_attn_workspace(const ckv_layout* kv, int32_t q_heads, size_t* byt
   if (st != CKV_OK) return st;
   if (!bytes) return CKV_EINVAL;
   if (q_heads <= 0 || q_heads % kv->heads) return CKV_ESHAPE;
-  *bytes = align_up(attn_workspace_bytes(kv->dtype, kv->batch, kv->heads, q_heads, kv->dim, kv->seq, 0), 256);
+  *bytes = align_up(attn_reserve_bytes(kv->dtype, kv->batch, kv->heads, q_heads, kv->dim, kv->seq, 0), 256);
   return CKV_OK;
 }
 
 int ckv_decode_attn(const void* q, int32_t q_heads, const void* K, const void* V, const ckv_layout* kv,
                     const int32_t* lens, const int32_t* deg, float scale, void* o, int32_t o_dtype,
                     void* workspace, size_t workspace_bytes, void* hip_stream) {
-  size_t need = 0;
-  int st = ckv_decode_attn_workspace(kv, q_heads, &need);
+  size_t reserve = 0;
+  int st = ckv_decode_attn_workspace(kv, q_heads, &reserve);   // validates the layout and q_heads
   if (st != CKV_OK) return st;
   if (!q || !K || !V || !o || !workspace) return CKV_EINVAL;
   if (o_dtype != CKV_F32 && o_dtype != CKV_BF16) return CKV_EINVAL;
   if (((uintptr_t)q) % 16 || ((uintptr_t)K) % 16 || ((uintptr_t)V) % 16 || ((uintptr_t)o) % 4 ||
       ((uintptr_t)workspace) % 16 || ((uintptr_t)lens) % 4 || ((uintptr_t)deg) % 4)
     return CKV_EALIGN;
-  if (workspace_bytes < need) return CKV_EWORKSPACE;
+  if (workspace_bytes < attn_workspace_bytes(kv->dtype, kv->batch, kv->heads, q_heads, kv->dim, kv->seq, 0)) return CKV_EWORKSPACE;
   const int G = q_heads / kv->heads;
   if (G != 1 && G != 2 && G != 4 && G != 8) return CKV_EUNSUPPORTED;
   if (kv->dtype == CKV_BF16 ? !(kv->dim == 64 || kv->dim == 128)
@@ -569,7 +569,7 @@ int ckv_paged_decode_attn_workspace(const ckv_paged_layout* pl, int32_t q_heads,
   const int limit = ckv::attn_paged_span_limit(pl->block_size);
   if ((int64_t)limit * 1024 < max_len) return CKV_EUNSUPPORTED;   // more table entries per slice than the kernel holds
   if ((int64_t)pl->n_blocks * pl->heads * pl->block_size > INT32_MAX) return CKV_EUNSUPPORTED;   // pool rows are indexed in 32 bits
-  *bytes = ckv::align_up(ckv::attn_workspace_bytes(pl->dtype, pl->batch, pl->heads, q_heads, pl->dim, max_len, limit), 256);
+  *bytes = ckv::align_up(ckv::attn_reserve_bytes(pl->dtype, pl->batch, pl->heads, q_heads, pl->dim, max_len, limit), 256);
   return CKV_OK;
 }
 
@@ -577,8 +577,8 @@ int ckv_paged_decode_attn(const void* q, int32_t q_heads, const void* K_pool, co
                           const int32_t* deg_pool, const int32_t* block_table, const int32_t* lens,
                           const ckv_paged_layout* pl, int32_t max_len, float scale, void* o, int32_t o_dtype,
                           void* workspace, size_t workspace_bytes, void* hip_stream) {
-  size_t need = 0;
-  int st = ckv_paged_decode_attn_workspace(pl, q_heads, max_len, &need);
+  size_t reserve = 0;
+  int st = ckv_paged_decode_attn_workspace(pl, q_heads, max_len, &reserve);   // validates the layout, q_heads and max_len
   if (st != CKV_OK) return st;
   if (!q || !K_pool || !V_pool || !block_table || !lens || !o || !workspace) return CKV_EINVAL;
   if (o_dtype != CKV_F32 && o_dtype != CKV_BF16) return CKV_EINVAL;
@@ -586,7 +586,11 @@ int ckv_paged_decode_attn(const void* q, int32_t q_heads, const void* K_pool, co
       ((uintptr_t)workspace) % 16 || ((uintptr_t)lens) % 4 || ((uintptr_t)deg_pool) % 4 ||
       ((uintptr_t)block_table) % 4)
     return CKV_EALIGN;
-  if (workspace_bytes < need) return CKV_EWORKSPACE;
+  const int64_t cap = (int64_t)pl->max_blocks * pl->block_size;
+  const int seq = (int)(max_len < cap ? max_len : cap);        // what the launch is cut for, and the workspace checked for
+  if (workspace_bytes < ckv::attn_workspace_bytes(pl->dtype, pl->batch, pl->heads, q_heads, pl->dim, seq,
+                                                  ckv::attn_paged_span_limit(pl->block_size)))
+    return CKV_EWORKSPACE;
   const int G = q_heads / pl->heads;
   if (G != 1 && G != 2 && G != 4 && G != 8) return CKV_EUNSUPPORTED;
   if (pl->dtype == CKV_BF16 ? !(pl->dim == 64 || pl->dim == 128) : !(pl->dim == 32 || pl->dim == 64 || pl->dim == 128))
@@ -594,8 +598,6 @@ int ckv_paged_decode_attn(const void* q, int32_t q_heads, const void* K_pool, co
   if (!(scale > 0.f)) scale = 1.0f / sqrtf((float)pl->dim);
   int shift;
   check_paged(pl, &shift);
-  const int64_t cap = (int64_t)pl->max_blocks * pl->block_size;
-  const int seq = (int)(max_len < cap ? max_len : cap);
   return ckv::hip_status(ckv::launch_decode_attn(q, q_heads, K_pool, V_pool, pl->dtype, pl->dim, pool_view(pl), pl->batch,
                                                  pl->heads, seq, lens, deg_pool, scale, o, o_dtype, workspace,
                                                  ckv::PagedView{block_table, pl->max_blocks, shift, pl->n_blocks},

@@ -138,7 +138,9 @@ size_t attn_counter_bytes(int n_b, int kv_heads);
 // span_limit > 0 (paged caches): no slice may cover more tokens than that
 int attn_splits(int dtype, int n_b, int kv_heads, int seq, int span_limit);
 int attn_paged_span_limit(int block_size);
-size_t attn_workspace_bytes(int dtype, int n_b, int kv_heads, int q_heads, int dim, int seq, int span_limit);
+size_t attn_workspace_bytes(int dtype, int n_b, int kv_heads, int q_heads, int dim, int seq, int span_limit);   // of this very call
+// enough for every call of up to that many pairs and tokens: never falls as either grows
+size_t attn_reserve_bytes(int dtype, int n_b, int kv_heads, int q_heads, int dim, int seq, int span_limit);
 hipError_t launch_decode_attn(const void* q, int q_heads, const void* K, const void* V, int dtype,
                               int dim, TensorView kv, int n_b, int kv_heads, int seq,
                               const int32_t* lens, const int32_t* deg, float scale, void* o,

@@ -33,10 +33,11 @@ using namespace ckv;
 extern "C" int ckv_decode_attn_noalloc(const void* q, int32_t q_heads, const void* K, const void* V,
                                        const ckv_layout* kv, const int32_t* lens, const int32_t* deg, float scale,
                                        void* o, int32_t o_dtype, void* hip_stream) {
-  size_t need = 0;
-  int st = ckv_decode_attn_workspace(kv, q_heads, &need);   // validates the layout and q_heads
+  size_t reserve = 0;
+  int st = ckv_decode_attn_workspace(kv, q_heads, &reserve);   // validates the layout and q_heads
   if (st != CKV_OK) return st;
   const size_t counters = attn_counter_bytes(kv->batch, kv->heads);
+  const size_t need = (attn_workspace_bytes(kv->dtype, kv->batch, kv->heads, q_heads, kv->dim, kv->seq, 0) + 255) / 256 * 256;
   if (counters > kCounterBytes || need - counters > CKV_NOALLOC_SCRATCH_BYTES - kCounterBytes) return CKV_EWORKSPACE;
   if (!q || !K || !V || !o) return CKV_EINVAL;
   if (o_dtype != CKV_F32 && o_dtype != CKV_BF16) return CKV_EINVAL;

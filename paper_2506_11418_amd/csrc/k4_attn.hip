@@ -548,6 +548,18 @@ size_t attn_workspace_bytes(int dtype, int n_b, int kv_heads, int q_heads, int d
   return attn_counter_bytes(n_b, kv_heads) + rows * (dim + 2) * sizeof(float);
 }
 
+// The slices of attn_splits go down as well as up with the length (they halve where eight waves are taken) and
+// with the batch.  All pairs together have at most this many, whatever the lengths up to seq and the number
+// of pairs up to n_b * kv_heads: ceil(512 / pairs) each, or one per 256 tokens (bf16: per 64) of a shorter cache.
+size_t attn_reserve_bytes(int dtype, int n_b, int kv_heads, int q_heads, int dim, int seq, int span_limit) {
+  const int64_t bh = (int64_t)n_b * kv_heads;
+  int64_t slices = bh * ((seq + 255) / 256) * (dtype == CKV_BF16 ? 4 : 1);
+  if (slices > bh + 511) slices = bh + 511;
+  const int64_t spans = span_limit > 0 ? bh * ((seq + span_limit - 1) / span_limit) : 0;
+  if (slices < spans) slices = spans;
+  return attn_counter_bytes(n_b, kv_heads) + (size_t)slices * (q_heads / kv_heads) * (dim + 2) * sizeof(float);
+}
+
 hipError_t launch_decode_attn(const void* q, int q_heads, const void* K, const void* V, int dtype, int dim,
                               TensorView kv, int n_b, int kv_heads, int seq, const int32_t* lens,
                               const int32_t* deg, float scale, void* o, int o_dtype, void* workspace,

@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "ckv.h"
+#include "ckv_internal.h"
 
 static ckv_params read_params(std::istringstream& in) {
   ckv_params p;
@@ -93,6 +94,24 @@ int main() {
       size_t bytes = 0;
       const int st = ckv_decode_attn_workspace(&l, q_heads, &bytes);
       printf("attn_ws %d %zu\n", st, bytes);
+    } else if (cmd == "attn_fit") {             // what launches up to a capacity use against the workspace sized for it
+      ckv_paged_layout pl = read_paged(in);     // block_size 0: a strided cache
+      int q_heads, cap;
+      in >> q_heads >> cap;
+      size_t sized = 0;
+      int st;
+      if (pl.block_size > 0) {
+        st = ckv_paged_decode_attn_workspace(&pl, q_heads, cap, &sized);
+      } else {
+        ckv_layout l{pl.batch, pl.heads, cap, pl.dim, (int64_t)pl.heads * cap * pl.dim, (int64_t)cap * pl.dim, pl.dim, pl.dtype, 0};
+        st = ckv_decode_attn_workspace(&l, q_heads, &sized);
+      }
+      const int limit = pl.block_size > 0 ? ckv::attn_paged_span_limit(pl.block_size) : 0;
+      int over = 0;
+      for (int batch = 1; batch <= pl.batch; ++batch)
+        for (int seq = 1; seq <= cap; seq += 1 + seq / 200)
+          over += ckv::attn_workspace_bytes(pl.dtype, batch, pl.heads, q_heads, pl.dim, seq, limit) > sized;
+      printf("attn_fit %d %d\n", st, over);
     } else if (cmd == "compress_err") {         // argument errors of ckv_compress, found on the host before any launch
       ckv_layout l = read_layout(in), o = read_layout(in);
       ckv_params p = read_params(in);

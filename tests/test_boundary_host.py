@@ -157,6 +157,36 @@ def test_paged_plan_and_argument_checks():
     assert L.ckv_paged_compress(a, a, a, a, z, C.byref(pl), 4096, None, C.byref(ckv.make_params(256, 0.5)), a, 10, a, 1 << 30, z) == -2   # freed rows too short
 
 
+@pytest.mark.parametrize("dtype,dim,group", [(ckv.BF16, 128, 4), (ckv.BF16, 64, 8), (ckv.F32, 64, 1)])
+def test_attention_workspace_for_a_capacity_serves_shorter_caches_and_smaller_batches(dtype, dim, group):
+    """The number of slices falls where a workgroup gets more waves (32768 tokens over all pairs), the size
+    must not: a cache that grows keeps the workspace of its capacity, a batch that shrinks that of the largest."""
+    L, n = ckv.lib(), C.c_size_t(0)
+
+    def strided(batch, heads, seq):
+        assert L.ckv_decode_attn_workspace(C.byref(_lay(batch, heads, seq, dim, dtype)), heads * group, C.byref(n)) == 0
+        return n.value
+
+    def paged(batch, heads, max_len, block=16, max_blocks=1 << 16):
+        pl = ckv.PagedLayout(batch, heads, dim, dtype, block, max_blocks, 4096)
+        assert L.ckv_paged_decode_attn_workspace(C.byref(pl), heads * group, max_len, C.byref(n)) == 0
+        return n.value
+
+    for size in (strided, paged):
+        for pairs in list(range(1, 33)) + [64, 511, 512, 513]:
+            around = {32768 // pairs + d for d in range(-3, 4)} | set(range(1, 3000, 59)) | {2 ** k + d for k in range(17) for d in (0, 1)}
+            sizes = [size(1, pairs, seq) for seq in sorted(x for x in around if x > 0)]
+            assert sizes == sorted(sizes), f"{size.__name__}: falls with the length at {pairs} pairs"
+        for seq in (100, 515, 2048, 4096, 4097, 32768, 100000):
+            sizes = [size(batch, 8, seq) for batch in range(1, 40)]
+            assert sizes == sorted(sizes), f"{size.__name__}: falls with the batch at {seq} tokens"
+    # a max_len beyond what the table's rows hold is cut to them: the size asked for covers the cut launch
+    for pairs, max_blocks, max_len in [(8, 250, 4100), (8, 256, 4097), (1, 2048, 32769), (16, 100, 1 << 20)]:
+        assert paged(1, pairs, max_len, max_blocks=max_blocks) >= paged(1, pairs, max_blocks * 16, max_blocks=max_blocks)
+    # blocks of one token: a slice spans 2048 of them at most, however few slices the rule would take
+    assert paged(64, 8, 1 << 17, block=1) >= 512 * 64 * group * (dim + 2) * 4
+
+
 def test_plan_workspace_grows_with_rounds():
     one = ckv.plan(_lay(), ckv.make_params(1024, 0.5)).workspace_bytes
     two = ckv.plan(_lay(), ckv.make_params(1024, 0.25)).workspace_bytes

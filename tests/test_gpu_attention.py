@@ -102,6 +102,26 @@ def test_attn_tile_and_slice_edges(B, Hkv, G, L, D, dtype):
     _check(q[some], K[some], V[some], None, None, plain[some], tol, "plain")
 
 
+@pytest.mark.parametrize("H,cap,lengths", [
+    (8, 4352, (4352, 4096, 3742, 4097, 2049, 515, 4352)),        # eight waves above 32768 tokens over all heads, four up to it
+    (1, 33000, (32768, 32769, 16384, 33000, 100, 32768)),
+])
+def test_one_workspace_for_the_capacity_serves_every_length(H, cap, lengths):
+    """The bits of calls with a workspace of their own, whatever length came before."""
+    _say(f"attn one workspace H={H} capacity={cap}")
+    gen = torch.Generator(device=DEV).manual_seed(cap)
+    K, V = (torch.randn((1, H, cap, 128), generator=gen, device=DEV).to(torch.bfloat16) for _ in range(2))
+    q = torch.randn((1, 4 * H, 128), generator=gen, device=DEV).to(torch.bfloat16)
+    deg = torch.randint(1, 9, (1, H, cap), generator=gen, device=DEV, dtype=torch.int32)
+    ws = torch.zeros(ckv.decode_attn_workspace(ckv.layout_of(K, deg), 4 * H), dtype=torch.uint8, device=DEV)
+    for n in lengths:
+        call = lambda w: ckv.decode_attn(q, K[:, :, :n], V[:, :, :n], deg=deg[:, :, :n], out_dtype=torch.float32, workspace=w)
+        o, own = call(ws), call(None)
+        torch.cuda.synchronize()
+        assert torch.equal(o, own), n
+        _check(q, K[:, :, :n], V[:, :, :n], deg[:, :, :n], None, o, ATTN_TOL, f"length {n}")
+
+
 def test_outlier_keys_large_logits_bf16():
     """Keys with x10 outlier channels give logits of several tens: the softmax must stay stable."""
     _say("attn outliers")

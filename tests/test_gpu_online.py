@@ -112,6 +112,27 @@ def test_algorithm1_decode_loop(dtype, n, chunk, R, g, n_sink, n_recent, steps):
             _say(f"b{b}: a near-tie was resolved differently; per-round checks above cover it")
 
 
+def test_online_cache_steps_through_lengths_below_the_wave_switch_of_its_capacity():
+    """8 heads, capacity 4352 tokens: attention takes fewer and larger workgroups there than at the 3742
+    tokens the loop starts from, with one workspace for both."""
+    B, H, n, D = 1, 8, 16384, 128
+    K, V, _ = kv_host(83, H, n, D, "bf16", alpha=0.9, n_outlier=4)
+    oc = OnlineCache(K.to(DEV), V.to(DEV), 256, 0.25, 256, 4 * H)
+    assert oc.capacity * H > 32768 > oc.s * H
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    new = lambda heads: torch.randn((B, heads, D), generator=gen, device=DEV).to(torch.bfloat16)
+    low = 0
+    for _ in range(oc.capacity - oc.s - 1):                  # up to the step before the cache is clustered again
+        low += oc.s < 4096
+        q = new(4 * H)
+        o = oc.step(q, new(H), new(H), out_dtype=torch.float32)
+    cK, cV, cdeg = oc.view()
+    torch.cuda.synchronize()
+    assert low > 0 and oc.s == oc.capacity - 1 and oc.n_clusterings == 0
+    ref = oracle.app_attn(f64(q[0]), f64(cK[0]), f64(cV[0]), i64(cdeg[0]))
+    assert_rows_close(f64(o[0]), ref, ATTN_TOL, "last step")
+
+
 def test_append_with_device_lengths():
     """Per-sequence lengths on the device: each sequence's token lands at its own row, lens is
     incremented, a full sequence is left untouched."""

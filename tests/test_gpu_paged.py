@@ -2,6 +2,8 @@
 in-place compression with block release.  Paging is pure indexing, so the expected values are the
 oracle's (or the strided entry points') results on the same tokens laid out contiguously; the
 test packs the pool with torch indexing."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -73,6 +75,31 @@ def test_paged_decode_attention(dtype, B, H, G, S, D, bs):
     o2 = ckv.decode_attn(q.to(DEV), K.to(DEV), V.to(DEV), lens=lens.to(DEV), deg=deg.to(DEV), out_dtype=torch.float32)
     torch.cuda.synchronize()
     assert torch.equal(o, o2)
+
+
+@pytest.mark.parametrize("max_len", [4000, 4096, 4097, 4100, 1 << 17])
+def test_paged_attention_stays_inside_the_workspace_of_its_max_len(max_len):
+    """A max_len beyond the table's rows is cut to them, where the launch may take more slices than the
+    uncut length would: nothing behind the workspace is written, and the bits are those of the exact max_len."""
+    _say(f"paged attention, table of 4000 tokens, max_len {max_len}")
+    H, S, bs = 8, 4000, 16
+    gen = torch.Generator(device=DEV).manual_seed(7)
+    K_pool, V_pool = (torch.randn((S // bs, H, bs, 128), generator=gen, device=DEV).to(torch.bfloat16) for _ in range(2))
+    deg_pool = torch.randint(1, 9, (S // bs, H, bs), generator=gen, device=DEV, dtype=torch.int32)
+    table = torch.randperm(S // bs, generator=gen, device=DEV).to(torch.int32).view(1, -1)
+    q = torch.randn((1, 4 * H, 128), generator=gen, device=DEV).to(torch.bfloat16)
+    lens = torch.tensor([S], dtype=torch.int32, device=DEV)
+    n = C.c_size_t(0)
+    assert ckv.lib().ckv_paged_decode_attn_workspace(C.byref(ckv.paged_layout_of(K_pool, table)), 4 * H, max_len, C.byref(n)) == 0
+    held = torch.zeros(n.value + (4 << 20), dtype=torch.uint8, device=DEV)
+    held[n.value:] = 0xA5
+    call = lambda m, w: ckv.paged_decode_attn(q, K_pool, V_pool, deg_pool, table, lens, m, out_dtype=torch.float32, workspace=w)
+    want = call(S, None)
+    for m in (max_len, 515, max_len, min(max_len, 2048), max_len):      # and shorter ones with the same workspace
+        o = call(m, held[:n.value])
+        torch.cuda.synchronize()
+        assert bool((held[n.value:] == 0xA5).all()), m
+        assert torch.equal(o, want if m >= S else call(m, None)), m
 
 
 def test_paged_attention_masks_table_entries_outside_the_pool():

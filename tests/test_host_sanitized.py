@@ -123,6 +123,11 @@ def _cases():
         st = L.ckv_decode_attn_workspace(C.byref(ckv.Layout(*lay_w)), qh, C.byref(n))
         cases.append((["attn_ws"] + lay_w + [qh], ["attn_ws", st, n.value]))
 
+    # no attention launch on a cache of up to `cap` tokens (strided: block size 0) uses more scratch than the size for it
+    for dtype, dim, group, block, heads, cap in itertools.product([ckv.BF16, ckv.F32], [64, 128], [1, 4], [0, 1, 16],
+                                                                  [1, 3, 8], [515, 4097, 33000, 1 << 20]):
+        cases.append((["attn_fit", 20, heads, dim, dtype, block, 1 << 20, 64, group * heads, cap], ["attn_fit", 0, 0]))
+
     # argument errors of ckv_compress / ckv_match that the host finds before a launch
     good, pw = _lay_words(1, 2, 4096, 128, ckv.BF16), _par_words(256, 0.5)
     for lay_w, out_w, ws_bytes, k_addr, want in [
