@@ -135,8 +135,10 @@ hipError_t launch_fill_deg(const int32_t* deg_in, int64_t in_stride, int32_t* de
 // (launch_decode_attn with counters != NULL keeps them there instead and uses the whole workspace for
 // the partial results).
 size_t attn_counter_bytes(int n_b, int kv_heads);
+// how a call runs: waves per workgroup, slices (workgroups) per (batch, KV head)
+struct AttnCut { int waves, slices; };
 // span_limit > 0 (paged caches): no slice may cover more tokens than that
-int attn_splits(int dtype, int n_b, int kv_heads, int seq, int span_limit);
+AttnCut attn_cut(int dtype, int n_b, int kv_heads, int q_heads, int dim, int seq, int span_limit);
 int attn_paged_span_limit(int block_size);
 size_t attn_workspace_bytes(int dtype, int n_b, int kv_heads, int q_heads, int dim, int seq, int span_limit);   // of this very call
 // enough for every call of up to that many pairs and tokens: never falls as either grows

@@ -22,6 +22,7 @@ struct AttnCall {
   void* workspace;
   int32_t* counters;      // arrival counters kept outside the workspace, or NULL
   PagedView paged;
+  AttnCut cut;
   hipStream_t st;
 };
 

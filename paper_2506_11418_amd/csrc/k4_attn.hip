@@ -232,7 +232,7 @@ __global__ __launch_bounds__(W * 64, 2) void attn_mfma_kernel(
     int32_t* __restrict__ arrived, void* __restrict__ o, int o_dtype, PagedView paged) {
   typedef RowOf<D> R;
   constexpr int kThreads = W * 64;
-  constexpr int kStageBytes = W * R::LDS;                 // K tiles of the four waves
+  constexpr int kStageBytes = W * R::LDS;                 // the waves' K tiles (and V tiles at dim 64)
   constexpr int kOutBytes = W * G * D * 4, kWeightBytes = G * kAttnMaxSplits * 4;
   constexpr int kRawBytes = kStageBytes > kOutBytes ? (kStageBytes > kWeightBytes ? kStageBytes : kWeightBytes)
                                                     : (kOutBytes > kWeightBytes ? kOutBytes : kWeightBytes);
@@ -480,20 +480,9 @@ __global__ __launch_bounds__(W * 64, 2) void attn_mfma_kernel(
                         o_base);
 }
 
-// Waves per workgroup (bf16).  With few (batch, KV head) pairs a long cache is cut into many slices, and the
-// merge of the slices by one workgroup counts: workgroups of eight waves halve their number (8 pairs of
-// 32769 tokens: 31.5 us with 32 slices of eight waves, 34.3 with 64 of four).  With more pairs, two
-// smaller workgroups per CU even out sequences of different lengths (128 pairs of 4112 .. 8223 tokens: 74
-// against 81 us), and a cache that gives the four waves of 512 workgroups no second tile has nothing to
-// merge that would be worth the longer reduction (8 pairs of 515 tokens: 9.6 against 11.0 us).
-int attn_waves(int n_b, int kv_heads, int seq) {
-  const int64_t bh = (int64_t)n_b * kv_heads;
-  return bh <= 16 && bh * seq > 512 * 4 * 16 ? 8 : 4;
-}
-
 template <int D, int G, int W>
 hipError_t launch_mfma_w(const AttnCall& c) {
-  const int n_splits = attn_splits(CKV_BF16, c.n_b, c.kv_heads, c.seq, c.paged.table ? (kAttnMaxTable << c.paged.shift) : 0);
+  const int n_splits = c.cut.slices;
   if (c.paged.table && div_up(c.seq, n_splits) > (kAttnMaxTable << c.paged.shift)) return hipErrorInvalidValue;
   float *o_part, *ml_part;
   int32_t* arrived;
@@ -512,7 +501,7 @@ hipError_t launch_mfma_w(const AttnCall& c) {
 
 template <int D, int G>
 hipError_t launch_mfma_t(const AttnCall& c) {
-  return attn_waves(c.n_b, c.kv_heads, c.seq) == 8 ? launch_mfma_w<D, G, 8>(c) : launch_mfma_w<D, G, 4>(c);
+  return c.cut.waves == 8 ? launch_mfma_w<D, G, 8>(c) : launch_mfma_w<D, G, 4>(c);
 }
 
 template <int D>
@@ -528,24 +517,42 @@ hipError_t launch_mfma_g(int G, const AttnCall& c) {
 
 }  // namespace
 
-int attn_splits(int dtype, int n_b, int kv_heads, int seq, int span_limit) {
-  // Eight waves per CU stream fastest (two workgroups of four or one of eight).  Each workgroup has a fixed
-  // merge/write cost, so slices are at least 256 tokens; bf16 caches are cut finer, down to one tile per
-  // wave, while the launch stays within those workgroups: a short cache is bound by the latency of its
-  // longest slice.
+// Waves per workgroup (bf16).  With few (batch, KV head) pairs a long cache is cut into many slices, and
+// the merge of the slices by one workgroup counts: workgroups of eight waves halve their number (8 pairs of
+// 33000 tokens: 28.7 us with 32 slices of eight waves, 34.1 with 64 of four).  With more pairs, two smaller
+// workgroups per CU even out sequences of different lengths (16 pairs of 16500 and 33000 tokens, 4 heads:
+// 40.9 against 46.2 us; of 4096 and 8192 tokens 20.3 against 18.0; 128 pairs of 4112 .. 8223 tokens 74 against
+// 81), and a cache that gives the four waves of 512 workgroups no second tile has nothing to merge that would
+// be worth the longer reduction (8 pairs of 515 tokens: 9.6 against 11.0 us).
+//
+// Slices.  Eight waves per CU stream fastest (two workgroups of four or one of eight), and as many workgroups
+// as run at once are cut, not one more: a CU that gets another one ends last (24 pairs of 70000 tokens, one head:
+// 112 us with 504 workgroups, 134 with 528).  Each workgroup has a fixed merge/write cost, so slices have at least
+// 256 tokens; a short bf16 cache, bound by the latency of its longest slice, is cut finer, down to one step of
+// every wave, but into no more than 16 slices (few pairs: 32 or, at dim 64, 64), since one workgroup merges all
+// slices of a pair: one pair of 20001 tokens, 4 heads: 17.1 us in 79 slices, 27.3 in 313; 8 pairs of 4096 tokens: 14.0
+// in 16, 18.5 in 64; 8 pairs of 1030: 10.4 in 16, 12.5 in 5; 1 of 4096: 10.3 in 32, 12.8 in 16.
+AttnCut attn_cut(int dtype, int n_b, int kv_heads, int q_heads, int dim, int seq, int span_limit) {
+  const bool bf16 = dtype == CKV_BF16;
+  const int group = q_heads / kv_heads;
   const int64_t bh = (int64_t)n_b * kv_heads;
-  const int waves = dtype == CKV_BF16 ? attn_waves(n_b, kv_heads, seq) : 4;
-  const int64_t groups = 2048 / waves;
+  AttnCut cut{};
+  cut.waves = bf16 && bh * seq > 512 * 4 * 16 && (bh <= 8 || (bh <= 16 && seq <= 24576)) ? 8 : 4;
+  const int64_t groups = 2048 / cut.waves;
   auto most = [&](int64_t want, int tokens) { const int cap = (seq + tokens - 1) / tokens; return want < cap ? (int)want : cap; };
-  int want = most((groups + bh - 1) / bh, 256);
-  const int fine = dtype == CKV_BF16 ? most(groups / bh, waves * 16) : 0;
-  if (fine > want) want = fine;
+  int want = most(bf16 && 2 * bh <= groups ? groups / bh : (groups + bh - 1) / bh, 256);
+  if (bf16) {
+    const int finest = dim == 64 && group <= 2 && bh <= 2 ? 64 : bh <= (dim == 64 ? 8 : 4) ? 32 : 16;
+    const int fine = most(groups / bh < finest ? groups / bh : finest, cut.waves * (dim == 64 ? 32 : 16));
+    if (fine > want) want = fine;
+  }
   if (want > kAttnMaxSplits) want = kAttnMaxSplits;
   if (want < 1) want = 1;
   // paged caches: a slice's block-table entries must fit the kernel's LDS table
   if (span_limit > 0 && (seq + want - 1) / want > span_limit) want = (seq + span_limit - 1) / span_limit;
   if (want > kAttnMaxSplits) want = kAttnMaxSplits;
-  return want;
+  cut.slices = want;
+  return cut;
 }
 
 size_t attn_counter_bytes(int n_b, int kv_heads) { return ((size_t)n_b * kv_heads * sizeof(int32_t) + 255) / 256 * 256; }
@@ -555,13 +562,14 @@ int attn_paged_span_limit(int block_size) { return kAttnMaxTable * block_size; }
 size_t attn_workspace_bytes(int dtype, int n_b, int kv_heads, int q_heads, int dim, int seq, int span_limit) {
   // one arrival counter per (batch, KV head), then partial outputs and (max, sum) pairs per
   // (batch, query head, slice)
-  const size_t rows = (size_t)n_b * q_heads * attn_splits(dtype, n_b, kv_heads, seq, span_limit);
+  const size_t rows = (size_t)n_b * q_heads * attn_cut(dtype, n_b, kv_heads, q_heads, dim, seq, span_limit).slices;
   return attn_counter_bytes(n_b, kv_heads) + rows * (dim + 2) * sizeof(float);
 }
 
-// The slices of attn_splits go down as well as up with the length (they halve where eight waves are taken) and
+// The slices of attn_cut go down as well as up with the length (they halve where eight waves are taken) and
 // with the batch.  All pairs together have at most this many, whatever the lengths up to seq and the number
-// of pairs up to n_b * kv_heads: ceil(512 / pairs) each, or one per 256 tokens (bf16: per 64) of a shorter cache.
+// of pairs up to n_b * kv_heads: ceil(512 / pairs) each, or one per 256 tokens (bf16: per 64 or more) of a
+// shorter cache.
 size_t attn_reserve_bytes(int dtype, int n_b, int kv_heads, int q_heads, int dim, int seq, int span_limit) {
   const int64_t bh = (int64_t)n_b * kv_heads;
   int64_t slices = bh * ((seq + 255) / 256) * (dtype == CKV_BF16 ? 4 : 1);
@@ -576,7 +584,8 @@ hipError_t launch_decode_attn(const void* q, int q_heads, const void* K, const v
                               const int32_t* deg, float scale, void* o, int o_dtype, void* workspace,
                               PagedView paged, hipStream_t st, int32_t* counters) {
   const int G = q_heads / kv_heads;
-  const AttnCall c{q, K, V, kv, n_b, kv_heads, seq, lens, deg, scale, o, o_dtype, workspace, counters, paged, st};
+  const AttnCut cut = attn_cut(dtype, n_b, kv_heads, q_heads, dim, seq, paged.table ? (kAttnMaxTable << paged.shift) : 0);
+  const AttnCall c{q, K, V, kv, n_b, kv_heads, seq, lens, deg, scale, o, o_dtype, workspace, counters, paged, cut, st};
   if (dtype != CKV_BF16) return launch_attn_f32(G, dim, c);
   if (dim == 128) return launch_mfma_g<128>(G, c);
   if (dim == 64) return launch_mfma_g<64>(G, c);

@@ -314,7 +314,7 @@ __global__ __launch_bounds__(kThreads, G <= 4 ? 3 : 2) void attn_f32_kernel(
 
 template <int D, int G>
 hipError_t launch_f32_t(const AttnCall& c) {
-  const int n_splits = attn_splits(CKV_F32, c.n_b, c.kv_heads, c.seq, c.paged.table ? (kAttnMaxTable << c.paged.shift) : 0);
+  const int n_splits = c.cut.slices;
   const int span = div_up(c.seq, n_splits);
   if (c.paged.table && span > (kAttnMaxTable << c.paged.shift)) return hipErrorInvalidValue;
   float *o_part, *ml_part;

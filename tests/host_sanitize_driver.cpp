@@ -112,6 +112,17 @@ int main() {
         for (int seq = 1; seq <= cap; seq += 1 + seq / 200)
           over += ckv::attn_workspace_bytes(pl.dtype, batch, pl.heads, q_heads, pl.dim, seq, limit) > sized;
       printf("attn_fit %d %d\n", st, over);
+    } else if (cmd == "attn_cut") {             // bf16: workgroups beyond those that run at once, and short slices in large numbers
+      int group, dim, cap, beyond = 0, shorter = 0;
+      in >> group >> dim >> cap;
+      for (int pairs = 1; pairs <= 128; ++pairs)
+        for (int seq = 1; seq <= cap; seq += 1 + seq / 50) {
+          const size_t part = ckv::attn_workspace_bytes(CKV_BF16, 1, pairs, pairs * group, dim, seq, 0) - ckv::attn_counter_bytes(1, pairs);
+          const int slices = (int)(part / ((size_t)pairs * group * (dim + 2) * sizeof(float)));
+          beyond += pairs * slices > 512;
+          shorter += slices > 64 && slices > (seq + 255) / 256;
+        }
+      printf("attn_cut %d %d\n", beyond, shorter);
     } else if (cmd == "compress_err") {         // argument errors of ckv_compress, found on the host before any launch
       ckv_layout l = read_layout(in), o = read_layout(in);
       ckv_params p = read_params(in);

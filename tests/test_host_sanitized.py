@@ -128,6 +128,11 @@ def _cases():
                                                                   [1, 3, 8], [515, 4097, 33000, 1 << 20]):
         cases.append((["attn_fit", 20, heads, dim, dtype, block, 1 << 20, 64, group * heads, cap], ["attn_fit", 0, 0]))
 
+    # attention slices: as many workgroups as run at once and not one more, and no merge of more than 64 slices that
+    # are shorter than 256 tokens
+    for group, dim in itertools.product([1, 2, 4, 8], [64, 128]):
+        cases.append((["attn_cut", group, dim, 100000], ["attn_cut", 0, 0]))
+
     # argument errors of ckv_compress / ckv_match that the host finds before a launch
     good, pw = _lay_words(1, 2, 4096, 128, ckv.BF16), _par_words(256, 0.5)
     for lay_w, out_w, ws_bytes, k_addr, want in [
