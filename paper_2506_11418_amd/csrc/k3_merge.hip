@@ -121,6 +121,17 @@ struct Row<float> {
 constexpr int kRowsInFlight = 1;   // output rows of a row group per batch (two batches are in flight)
 constexpr int kRowsInFlightOrigin = 2;   // ... when every value row is itself rebuilt from several rows
 
+// What a launch without set-aside tokens does not carry: with the copy's 240 bytes among the arguments of
+// every variant the paged origin kernel parks 81 scalars in vector registers, without 65 (4 x 8 x 32768 tokens on
+// pages to a quarter, chunk 512: 572.6 -> 568.5 us).
+template <bool EDGES>
+struct EdgeBlocks {};
+template <>
+struct EdgeBlocks<true> {
+  int blocks;
+  EdgeCopy copy;
+};
+
 // MODE (two consecutive rounds whose first merges every edge, r = 1, can skip the intermediate
 // VALUE cache: a round-0 chunk then keeps exactly its B tokens, so a round-1 chunk is fed by two
 // round-0 chunks):
@@ -137,7 +148,10 @@ enum { kMergeFull = 0, kMergeKeys = 1, kMergeOrigin = 2 };
 // the original values of kMergeOrigin (org.paged), the output keys (out_k_paged) or the output values
 // and degrees (out_v_paged), each decided by its table pointer / flag at run time; the pool rows of the
 // blocks a workgroup touches are staged in LDS (blocks of 8 tokens or more).
-template <typename T, int D, int MODE, int MH, bool PAGED>   // MH: capacity of the per-chunk LDS arrays (|A| = |B| <= MH)
+//
+// EDGES: the first edge_blocks workgroups copy the tokens that bypass the clustering (none of the others
+// touches those rows).
+template <typename T, int D, int MODE, int MH, bool PAGED, bool EDGES>   // MH: capacity of the per-chunk LDS arrays (|A| = |B| <= MH)
 __global__ __launch_bounds__(kThreads) void merge_kernel(
     const T* __restrict__ K, const T* __restrict__ V, const int32_t* __restrict__ deg_in, TensorView in,
     int seq, int chunk, int n_chunks, float r, const int32_t* __restrict__ dst_local,
@@ -145,12 +159,12 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
     int32_t* __restrict__ deg_out, TensorView out, int64_t deg_out_stride, int32_t* __restrict__ map_out,
     int64_t deg_in_stride, int64_t map_stride, int map_offset, const int2* __restrict__ sel_table,
     int16_t* __restrict__ lists_out, ValueOrigin org, int parts, PagedSide pin, PagedSide pout, int out_k_paged,
-    int out_v_paged, int edge_blocks, EdgeCopy edges) {
-  // The first workgroups copy the tokens that bypass the clustering (none of the others touches those
-  // rows): a launch of their own cost 4 to 6 us a round.
-  if ((int)blockIdx.x < edge_blocks) {
-    copy_edges(edges, (int64_t)blockIdx.x * kThreads + threadIdx.x);
-    return;
+    int out_v_paged, EdgeBlocks<EDGES> edges) {
+  if constexpr (EDGES) {
+    if ((int)blockIdx.x < edges.blocks) {
+      copy_edges(edges.copy, (int64_t)blockIdx.x * kThreads + threadIdx.x);
+      return;
+    }
   }
   constexpr int E = Row<T>::E;
   constexpr int LPR = D / E;                 // lanes per row
@@ -180,7 +194,8 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
 
   // `parts` workgroups share a chunk when the launch would otherwise leave most of the chip idle:
   // each repeats the (cheap) bookkeeping and emits every parts-th group of output rows.
-  const int id = (int)blockIdx.x - edge_blocks;
+  int id = (int)blockIdx.x;
+  if constexpr (EDGES) id -= edges.blocks;
   const int part = id % parts, wg = id / parts;
   const int g = wg % n_chunks, bh = wg / n_chunks;
   const int tid = threadIdx.x;
@@ -840,9 +855,7 @@ hipError_t launch_merge_t(const void* K, const void* V, const int32_t* deg_in, T
                           hipStream_t st, PagedSide pin, PagedSide pok, PagedSide pov, const EdgeCopy* edges) {
   const int n_chunks = div_up(seq, chunk);
   const int64_t total = (int64_t)n_bh * n_chunks;
-  const EdgeCopy ed = edges ? *edges : EdgeCopy{};
-  const int64_t edge_blocks = edges ? (ed.total + kThreads - 1) / kThreads : 0;
-  if (total > (1 << 30) || edge_blocks > (1 << 30)) return hipErrorInvalidValue;
+  if (total > (1 << 30)) return hipErrorInvalidValue;
   const ValueOrigin o = org ? *org : ValueOrigin{};
   // small launches: split every chunk's rows over several workgroups, aiming at 4 workgroups per CU
   // (compression to a quarter with 512, 1024 or 2048 workgroups as the aim, us; sequences x tokens, chunk:
@@ -850,28 +863,41 @@ hipError_t launch_merge_t(const void* K, const void* V, const int32_t* deg_in, T
   // round of 8 x 8448, 256: 33.5, 33.1, 40.4)
   int parts = 1;
   while (parts < 8 && total * parts < 1024) parts *= 2;
+  // The copy of the set-aside tokens rides in the merge launch (a launch of its own costs 4 to 6 us a round),
+  // unless the two together pass the 2^32 threads of a launch.
+  const int64_t edge_blocks = edges ? (edges->total + kThreads - 1) / kThreads : 0;
+  const bool ride = edges && (total * parts + edge_blocks) * kThreads <= UINT32_MAX;
   // any side in a block pool: the kernel variant that stages block tables (blocks of 8 tokens or more)
   const bool any_paged = pin.table || pok.table || pov.table || o.paged.table;
   if (any_paged && ((pin.table && pin.shift < 3) || (pok.table && pok.shift < 3) || (pov.table && pov.shift < 3) ||
                     (o.paged.table && o.paged.shift < 3)))
     return hipErrorInvalidValue;
   const PagedSide pout = pok.table ? pok : pov;
-#define CKV_LAUNCH_MH(MODE, MH, PG)                                                                           \
-  hipLaunchKernelGGL((merge_kernel<T, D, MODE, MH, PG>), dim3((unsigned)(total * parts + edge_blocks)), dim3(kThreads), 0, st, \
+#define CKV_LAUNCH_MH(MODE, MH, PG, ED, edge_blocks, ...)                                                     \
+  hipLaunchKernelGGL((merge_kernel<T, D, MODE, MH, PG, ED>), dim3((unsigned)(total * parts + (edge_blocks))), \
+                     dim3(kThreads), 0, st,                                                                   \
                      static_cast<const T*>(K), static_cast<const T*>(V), deg_in, in, seq, chunk, n_chunks, r, \
                      dst_local, score, static_cast<T*>(K_out), static_cast<T*>(V_out), deg_out, out,          \
                      deg_out_stride, map_out, deg_in_stride, map_stride, map_offset,                          \
                      reinterpret_cast<const int2*>(sel_table), lists_out, o, parts, pin, pout,                \
-                     pok.table != nullptr, pov.table != nullptr, (int)edge_blocks, ed)
+                     pok.table != nullptr, pov.table != nullptr, EdgeBlocks<ED>{__VA_ARGS__})
+  // (fp32, the small caches: one kernel for both)
+#define CKV_LAUNCH_PG(MODE, MH, PG)                                                                          \
+  do {                                                                                                       \
+    if constexpr (sizeof(T) == 4)                                                                            \
+      CKV_LAUNCH_MH(MODE, MH, PG, true, ride ? edge_blocks : 0, ride ? (int)edge_blocks : 0, ride ? *edges : EdgeCopy{}); \
+    else if (ride) CKV_LAUNCH_MH(MODE, MH, PG, true, edge_blocks, (int)edge_blocks, *edges);                 \
+    else CKV_LAUNCH_MH(MODE, MH, PG, false, 0);                                                              \
+  } while (0)
   // smaller LDS arrays for chunks of up to 1024 tokens: more workgroups per CU
 #define CKV_LAUNCH(MODE)                                                    \
   do {                                                                      \
     if (any_paged) {                                                        \
-      if (chunk <= kMaxHalf) CKV_LAUNCH_MH(MODE, kMaxHalf / 2, true);       \
-      else CKV_LAUNCH_MH(MODE, kMaxHalf, true);                             \
+      if (chunk <= kMaxHalf) CKV_LAUNCH_PG(MODE, kMaxHalf / 2, true);       \
+      else CKV_LAUNCH_PG(MODE, kMaxHalf, true);                             \
     } else {                                                                \
-      if (chunk <= kMaxHalf) CKV_LAUNCH_MH(MODE, kMaxHalf / 2, false);      \
-      else CKV_LAUNCH_MH(MODE, kMaxHalf, false);                            \
+      if (chunk <= kMaxHalf) CKV_LAUNCH_PG(MODE, kMaxHalf / 2, false);      \
+      else CKV_LAUNCH_PG(MODE, kMaxHalf, false);                            \
     }                                                                       \
   } while (0)
   if (org) {
@@ -885,7 +911,10 @@ hipError_t launch_merge_t(const void* K, const void* V, const int32_t* deg_in, T
     CKV_LAUNCH(kMergeFull);
   }
 #undef CKV_LAUNCH
-  return hipGetLastError();
+#undef CKV_LAUNCH_PG
+#undef CKV_LAUNCH_MH
+  const hipError_t err = hipGetLastError();
+  return err == hipSuccess && edges && !ride ? launch_edges(*edges, st) : err;
 }
 
 }  // namespace

@@ -289,6 +289,23 @@ def test_compress_with_sinks_and_recents(dtype, heads, seq, dim, chunk, rounds, 
     assert int(gdeg.sum()) == heads * seq
 
 
+def test_sinks_beside_as_many_chunks_as_one_launch_takes():
+    """2^24 - 16 workgroups of 256 threads merge; with those that copy 80 sinks per sequence they would pass the
+    2^32 threads of a launch.  Same bits as the two halves of the batch."""
+    B, H, n_sink, dim = 4, 4, 80, 16
+    seq = n_sink + 2 * ((1 << 20) - 1)
+    _say(f"{B * H * ((1 << 20) - 1)} chunks of two tokens, {n_sink} sinks")
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    K, V = (torch.randn((B, H, seq, dim), generator=gen, device=DEV) for _ in range(2))
+    call = lambda k, v: ckv.compress(k, v, 2, rounds=[1.0], n_sink=n_sink, want_assign=False)[:3]
+    whole = call(K, V)
+    for part in (slice(0, 2), slice(2, 4)):
+        for got, want in zip(whole, call(K[part], V[part])):
+            assert torch.equal(got[part], want)
+    assert torch.equal(whole[0][:, :, :n_sink], K[:, :, :n_sink]) and torch.equal(whole[1][:, :, :n_sink], V[:, :, :n_sink])
+    assert bool((whole[2][:, :, :n_sink] == 1).all()) and int(whole[2].sum()) == B * H * seq
+
+
 def test_sinks_and_recents_with_strided_layout_and_retain_ratio():
     """[B,S,H,D] input, padded output, incoming degrees, retain_ratio schedule with n1=16, n2=64:
     the whole call against the oracle's compress (teacher-forcing is covered above)."""
