@@ -529,9 +529,10 @@ hipError_t launch_mfma_g(int G, const AttnCall& c) {
 // as run at once are cut, not one more: a CU that gets another one ends last (24 pairs of 70000 tokens, one head:
 // 112 us with 504 workgroups, 134 with 528).  Each workgroup has a fixed merge/write cost, so slices have at least
 // 256 tokens; a short bf16 cache, bound by the latency of its longest slice, is cut finer, down to one step of
-// every wave, but into no more than 16 slices (few pairs: 32 or, at dim 64, 64), since one workgroup merges all
-// slices of a pair: one pair of 20001 tokens, 4 heads: 17.1 us in 79 slices, 27.3 in 313; 8 pairs of 4096 tokens: 14.0
-// in 16, 18.5 in 64; 8 pairs of 1030: 10.4 in 16, 12.5 in 5; 1 of 4096: 10.3 in 32, 12.8 in 16.
+// every wave, but into no more than 16 slices (few pairs: 32 or, with one or two heads, 64), since one workgroup merges
+// all slices of a pair: one pair of 20001 tokens, 4 heads: 17.1 us in 79 slices, 27.3 in 313; 8 pairs of 4096 tokens: 14.0
+// in 16, 18.5 in 64; 8 pairs of 1030: 10.4 in 16, 12.5 in 5; 1 of 4096: 10.3 in 32, 12.8 in 16.  One head: 1 pair of 8192
+// 9.7 in 64, 11.3 in 32; 4 pairs of 4097 11.3 in 64, 9.3 in 32; dim 64, 4 pairs of 5500 9.5 in 64, 10.4 in 32.
 AttnCut attn_cut(int dtype, int n_b, int kv_heads, int q_heads, int dim, int seq, int span_limit) {
   const bool bf16 = dtype == CKV_BF16;
   const int group = q_heads / kv_heads;
@@ -542,7 +543,8 @@ AttnCut attn_cut(int dtype, int n_b, int kv_heads, int q_heads, int dim, int seq
   auto most = [&](int64_t want, int tokens) { const int cap = (seq + tokens - 1) / tokens; return want < cap ? (int)want : cap; };
   int want = most(bf16 && 2 * bh <= groups ? groups / bh : (groups + bh - 1) / bh, 256);
   if (bf16) {
-    const int finest = dim == 64 && group <= 2 && bh <= 2 ? 64 : bh <= (dim == 64 ? 8 : 4) ? 32 : 16;
+    const bool light = group == 1 ? bh <= (dim == 64 ? 4 : 2) : dim == 64 && group == 2 && bh <= 2;   // little to merge
+    const int finest = light ? 64 : bh <= (dim == 64 ? 8 : 4) ? 32 : 16;
     const int fine = most(groups / bh < finest ? groups / bh : finest, cut.waves * (dim == 64 ? 32 : 16));
     if (fine > want) want = fine;
   }

@@ -123,6 +123,10 @@ int main() {
           shorter += slices > 64 && slices > (seq + 255) / 256;
         }
       printf("attn_cut %d %d\n", beyond, shorter);
+    } else if (cmd == "attn_slices") {          // bf16: slices per pair
+      int group, dim, pairs, seq;
+      in >> group >> dim >> pairs >> seq;
+      printf("attn_slices %d\n", ckv::attn_cut(CKV_BF16, 1, pairs, pairs * group, dim, seq, 0).slices);
     } else if (cmd == "compress_err") {         // argument errors of ckv_compress, found on the host before any launch
       ckv_layout l = read_layout(in), o = read_layout(in);
       ckv_params p = read_params(in);
