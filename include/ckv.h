@@ -197,7 +197,7 @@ int ckv_decode_attn_workspace(const ckv_layout* kv, int32_t q_heads, size_t* byt
  *   (>= 1; row stride kv->deg_stride) or NULL (= 1: plain attention, Eq. 1); scale <= 0 selects 1/sqrt(dim);
  *   o [batch, q_heads, dim] contiguous in o_dtype.  Arithmetic is fp32.  One kernel launch: the
  *   sequence is split into slices, and the slice that finishes last for a (batch, KV head) merges
- *   the partial results of all of them in slice order (run-to-run identical bits).
+ *   the partial results of all of them in an order fixed by the slice numbers (run-to-run identical bits).
  * Supported: q_heads / kv->heads in {1,2,4,8}; bf16 dim 64/128; fp32 dim 32/64/128. */
 int ckv_decode_attn(const void* q, int32_t q_heads, const void* K, const void* V,
                     const ckv_layout* kv, const int32_t* lens, const int32_t* deg, float scale,
