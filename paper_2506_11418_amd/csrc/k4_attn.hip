@@ -213,10 +213,10 @@ __device__ __forceinline__ void merge_slices(const float* __restrict__ o_part, c
 // rate takes 200 cycles; the dot products, row sums and weighted adds it had in vector instructions before
 // took 90 per row and four heads.  Per layer, against that form (bf16, dim 128): 403 MB of 16 sequences,
 // 4 heads per KV head, 74 us (83); the same bytes with 8 heads 71 us (133); on pages of 16 tokens 75 us (92);
-// 134 MB of one sequence 31.5 us (34.7).
+// 134 MB of one sequence 31.4 us (34.7).
 // Time line of that last one, from clock readings in the kernel: the streaming loops end between 17 and
-// 25 us, the waves of a workgroup wait for the slowest and reduce in 3.8 us, partials are acknowledged and
-// counted in 1.4 us, the merge by the last arriver takes 2.6 us.
+// 24 us (3 us between the waves of a workgroup), the reduction after its slowest wave takes 1.8 us, partials are
+// acknowledged and counted in 1.1 us, the merge by the last arriver takes 2.4 us.
 //
 // PAGED: K, V are a block pool [n_blocks, heads, block_size, dim] (kv.stride_s = dim, kv.stride_h =
 // block_size*dim: the tokens of one head are contiguous inside a block), token t of sequence b
