@@ -523,7 +523,12 @@ hipError_t launch_mfma_g(int G, const AttnCall& c) {
 // workgroups per CU even out sequences of different lengths (16 pairs of 16500 and 33000 tokens, 4 heads:
 // 40.9 against 46.2 us; of 4096 and 8192 tokens 20.3 against 18.0; 128 pairs of 4112 .. 8223 tokens 74 against
 // 81), and a cache that gives the four waves of 512 workgroups no second tile has nothing to merge that would
-// be worth the longer reduction (8 pairs of 515 tokens: 9.6 against 11.0 us).
+// be worth the longer reduction (8 pairs of 515 tokens: 9.6 against 11.0 us).  One or two pairs of dim 128 leave most of
+// the chip idle, and the longest chain of tiles decides: from 8192 tokens on, where 64 slices hold a tile for each of eight
+// waves, up to 24576, they are cut so (four waves in 32 to 96 slices -> eight in 64; 1 pair, 2 heads: 8192 tokens 12.0 -> 10.9 us,
+// 16384 13.6 -> 12.9, 24001 15.5 -> 15.0; 4 heads: 13.4 -> 12.6, 15.9 -> 14.7, 18.6 -> 16.7; 8 heads, 24001: 24.0 -> 19.7; 2 pairs,
+// 4 heads: 13.6 -> 13.4, 16.4 -> 15.6, 18.3 -> 17.4, 8 heads: 16.3 -> 16.6, 20.4 -> 18.6, 22.3 -> 20.4).  Longer ones want more
+// slices (one head, 32768: 15.1 -> 15.4); three and four pairs gain at some lengths and lose at others.
 //
 // Slices.  Eight waves per CU stream fastest (two workgroups of four or one of eight), and as many workgroups
 // as run at once are cut, not one more: a CU that gets another one ends last (24 pairs of 70000 tokens, one head:
@@ -538,6 +543,11 @@ AttnCut attn_cut(int dtype, int n_b, int kv_heads, int q_heads, int dim, int seq
   const int group = q_heads / kv_heads;
   const int64_t bh = (int64_t)n_b * kv_heads;
   AttnCut cut{};
+  if (bf16 && dim == 128 && bh <= 2 && seq >= 64 * 8 * 16 && seq <= 24576) {
+    cut.waves = 8;
+    cut.slices = 64;      // (at most 384 tokens: a paged slice's table entries always fit)
+    return cut;
+  }
   cut.waves = bf16 && bh * seq > 512 * 4 * 16 && (bh <= 8 || (bh <= 16 && seq <= 24576)) ? 8 : 4;
   const int64_t groups = 2048 / cut.waves;
   auto most = [&](int64_t want, int tokens) { const int cap = (seq + tokens - 1) / tokens; return want < cap ? (int)want : cap; };

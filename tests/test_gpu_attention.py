@@ -75,6 +75,9 @@ def test_decode_attn_shapes(B, Hkv, G, L, D, dtype):
     (6, 2, 8, 130, 64, "bf16"),
     (6, 2, 1, 130, 128, "f32"),
     (6, 1, 2, 65, 32, "f32"),
+    (1, 2, 4, 8191, 128, "bf16"),      # two pairs: the last length in short slices of four waves ...
+    (1, 2, 4, 8192, 128, "bf16"),      # ... and the first in 64 slices of eight
+    (2, 1, 8, 24576, 128, "bf16"),     # the last in 64 slices, one sequence far below it
     (1, 1, 2, 32768, 128, "bf16"),     # the last length of one pair with four waves per workgroup ...
     (1, 1, 2, 32769, 128, "bf16"),     # ... and the first with eight
     (3, 2, 8, 8200, 64, "bf16"),       # eight waves, slices that end inside a tile

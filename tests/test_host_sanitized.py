@@ -132,8 +132,10 @@ def _cases():
     # are shorter than 256 tokens
     for group, dim in itertools.product([1, 2, 4, 8], [64, 128]):
         cases.append((["attn_cut", group, dim, 100000], ["attn_cut", 0, 0]))
-    # one head: little to merge, so that few pairs of a short cache are cut to 64 slices, at dim 128 two pairs at most
-    for group, dim, pairs, seq, want in [(1, 128, 1, 8192, 64), (1, 128, 2, 4097, 64), (1, 128, 3, 8192, 32), (2, 128, 1, 8192, 32),
+    # one head: little to merge, so that few pairs of a short cache are cut to 64 slices, at dim 128 two pairs at most;
+    # with more heads those pairs have 64 slices (of eight waves) from 8192 to 24576 tokens
+    for group, dim, pairs, seq, want in [(1, 128, 1, 8192, 64), (1, 128, 2, 4097, 64), (1, 128, 3, 8192, 32), (2, 128, 1, 8191, 32),
+                                         (2, 128, 1, 8192, 64), (8, 128, 2, 24576, 64), (8, 128, 2, 24577, 97), (4, 128, 3, 8192, 32),
                                          (1, 64, 4, 8192, 64), (1, 64, 5, 8192, 32), (2, 64, 2, 8192, 64), (1, 128, 1, 515, 9)]:
         cases.append((["attn_slices", group, dim, pairs, seq], ["attn_slices", want]))
 
