@@ -881,7 +881,8 @@ hipError_t launch_merge_t(const void* K, const void* V, const int32_t* deg_in, T
                      deg_out_stride, map_out, deg_in_stride, map_stride, map_offset,                          \
                      reinterpret_cast<const int2*>(sel_table), lists_out, o, parts, pin, pout,                \
                      pok.table != nullptr, pov.table != nullptr, EdgeBlocks<ED>{__VA_ARGS__})
-  // (fp32, the small caches: one kernel for both)
+  // (fp32, the small caches: one kernel for both; with two, 1024 tokens of dim 64, chunk 64, take as long: 7.27 against
+  // 7.30 us a launch, for 48 kernels more)
 #define CKV_LAUNCH_PG(MODE, MH, PG)                                                                          \
   do {                                                                                                       \
     if constexpr (sizeof(T) == 4)                                                                            \
