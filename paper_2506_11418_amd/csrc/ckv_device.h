@@ -15,6 +15,7 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 
 typedef __attribute__((ext_vector_type(2))) float f32x2;
+typedef __attribute__((ext_vector_type(2))) uint16_t u16x2;
 
 union Piece {   // 16 bytes = 8 bf16
   uint4 u;
@@ -102,7 +103,7 @@ __device__ __forceinline__ void tile_argmax(const f32x16& acc, const f32x4 (&ib)
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
     sc[r] = acc[r] * ib[r >> 2][r & 3];
-    if (RAGGED && (8 * (r >> 2) + 4 * half + (r & 3)) >= valid) sc[r] = -INFINITY;
+    if (RAGGED && (8 * (r >> 2) + (r & 3)) >= valid - 4 * half) sc[r] = -INFINITY;
   }
   float mt = __builtin_fmaxf(sc[0], sc[1]);
 #pragma unroll
@@ -206,22 +207,24 @@ __device__ __forceinline__ uint32_t round_bf16_near_midpoint(float S, float fn, 
   return ((H >> 16) + up) & 0xffffu;
 }
 
-__device__ __forceinline__ uint4 round_div_pack_bf16(const float* acc, int n) {
-  const float fn = (float)n;
+__device__ __forceinline__ uint4 round_div_pack_bf16(const float* acc, float fn) {
   // 1/n: hardware reciprocal (1 ulp) + one Newton step.  Exact for powers of two; otherwise within
   // an ulp of 1/n, which keeps q within the 3 ulp the window below allows for (checked on the CPU
   // against exact rational arithmetic with the reciprocal forced one ulp off either way).
   float rcp = __builtin_amdgcn_rcpf(fn);
   rcp = fmaf(fmaf(-fn, rcp, 1.0f), rcp, rcp);
-  const bool pow2 = (n & (n - 1)) == 0;          // then acc*rcp IS the quotient: no second rounding
+  const bool pow2 = (__float_as_uint(fn) & 0x007fffffu) == 0;   // then acc*rcp IS the quotient: no second rounding
   float qv[8];
-  uint32_t nearest = 0xffffffffu;                // min over the elements of (low 16 bits - 0x7ffd) mod 2^16
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    qv[i] = acc[i] * rcp;
-    nearest = min(nearest, (uint32_t)(uint16_t)(__float_as_uint(qv[i]) - 0x7ffdu));
+  for (int i = 0; i < 8; ++i) qv[i] = acc[i] * rcp;
+  // min over the elements of (low 16 bits - 0x7ffd) mod 2^16, two elements per packed instruction
+  u16x2 near2 = {0xffff, 0xffff};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t low = __builtin_amdgcn_perm(__float_as_uint(qv[2 * i + 1]), __float_as_uint(qv[2 * i]), 0x05040100u);
+    near2 = __builtin_elementwise_min(near2, __builtin_bit_cast(u16x2, low) - u16x2{0x7ffd, 0x7ffd});
   }
-  const bool window = (nearest <= 6u) & !pow2;
+  const bool window = (min((uint32_t)near2.x, (uint32_t)near2.y) <= 6u) & !pow2;
   uint32_t w[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -249,6 +252,7 @@ __device__ __forceinline__ uint4 round_div_pack_bf16(const float* acc, int n) {
   }
   return make_uint4(w[0], w[1], w[2], w[3]);
 }
+__device__ __forceinline__ uint4 round_div_pack_bf16(const float* acc, int n) { return round_div_pack_bf16(acc, (float)n); }
 
 // Streaming 16-byte accesses: rows that are read or written once and not reused by this kernel
 // are marked non-temporal so they do not displace reusable lines from the caches.
@@ -306,5 +310,56 @@ __device__ __forceinline__ void fma_bf16x8(float* acc, const uint4& u, int w) {
   if (__any(w > 256)) fma_bf16x8_t<true>(acc, u, w);
   else fma_bf16x8_t<false>(acc, u, w);
 }
+
+// Tokens that bypass the clustering (Sec. 5.2: attention sinks and recent tokens are set aside
+// before partitioning; Sec. 5.3: they are concatenated back): the first n_head and the last n_tail
+// tokens of every sequence are copied to the head / tail of the output (keys, values, degree), and
+// their entries of the round's assignment map are written.  e: one 16-byte piece of one row.
+__device__ __forceinline__ void copy_edges(const EdgeCopy& ed, int64_t e) {
+  if (e >= ed.total) return;
+  const int piece = (int)(e % ed.pieces_per_row);
+  const int64_t row = e / ed.pieces_per_row;
+  const int n_edge = ed.n_head + ed.n_tail;
+  const int k = (int)(row % n_edge), bh = (int)(row / n_edge);
+  const int t_in = k < ed.n_head ? k : ed.in_len - ed.n_tail + (k - ed.n_head);
+  const int t_out = k < ed.n_head ? k : ed.out_len - ed.n_tail + (k - ed.n_head);
+  const int b = bh / ed.in.heads, h = bh % ed.in.heads;
+  // pool row of token u of this (batch, head) through a side's block table; -1 outside the pool
+  auto pool_row = [&](const PagedSide& pg, int u) -> int64_t {
+    const int blk = ((u >> pg.shift) < pg.max_blocks) ? pg.table[(int64_t)b * pg.max_blocks + (u >> pg.shift)] : -1;
+    if ((unsigned)blk >= (unsigned)pg.n_blocks) return -1;
+    return (((int64_t)blk * ed.in.heads + h) << pg.shift) + (u & ((1 << pg.shift) - 1));
+  };
+  const int64_t row_bytes = (int64_t)ed.pieces_per_row * 16;
+  int64_t ri = 0, rk = 0, rv = 0;
+  if (ed.pin.table) ri = pool_row(ed.pin, ed.pin.tok0 + t_in);
+  if (ed.pok.table) rk = pool_row(ed.pok, ed.pok.tok0 + t_out);
+  if (ed.pov.table) rv = pool_row(ed.pov, ed.pov.tok0 + t_out);
+  if (ri < 0) ri = 0;                      // a block outside the pool reads as row 0 and is not written
+  const int64_t so = ed.pin.table ? ri * row_bytes + piece * 16
+                                  : (ed.in.seq_base(bh) + (int64_t)t_in * ed.in.stride_s) * ed.elem_bytes + piece * 16;
+  const int64_t dof = (ed.out.seq_base(bh) + (int64_t)t_out * ed.out.stride_s) * ed.elem_bytes + piece * 16;
+  const int64_t dk = ed.pok.table ? rk * row_bytes + piece * 16 : dof;
+  const int64_t dv = ed.pov.table ? rv * row_bytes + piece * 16 : dof;
+  if (rk >= 0) *reinterpret_cast<uint4*>(ed.K_out + dk) = *reinterpret_cast<const uint4*>(ed.K + so);
+  if (rv >= 0) *reinterpret_cast<uint4*>(ed.V_out + dv) = *reinterpret_cast<const uint4*>(ed.V + so);
+  if (piece == 0) {
+    const int d = !ed.deg_in ? 1 : ed.pin.table ? ed.deg_in[ri] : ed.deg_in[(int64_t)bh * ed.in.deg_stride + t_in];
+    if (ed.pov.table) { if (rv >= 0) ed.deg_out[rv] = d; }
+    else ed.deg_out[(int64_t)bh * ed.out.deg_stride + t_out] = d;
+    if (ed.map_out) ed.map_out[(int64_t)bh * ed.in_len + t_in] = t_out;
+  }
+}
+
+// What a launch without set-aside tokens does not carry: with the copy's 240 bytes among the arguments of
+// every variant the paged origin kernel parks 81 scalars in vector registers, without 65 (4 x 8 x 32768 tokens on
+// pages to a quarter, chunk 512: 572.6 -> 568.5 us).
+template <bool EDGES>
+struct EdgeBlocks {};
+template <>
+struct EdgeBlocks<true> {
+  int blocks;
+  EdgeCopy copy;
+};
 
 }  // namespace ckv

@@ -82,7 +82,9 @@ int seq_after_round(int len, int chunk, float r, int n_sink, int n_recent, int s
 // writes.  It pays once the second round has enough workgroups (one per chunk, each rebuilding the
 // values of 2*chunk original tokens) to fill the chip: from about 4 per CU on MI355X (measured
 // crossover at 1024 chunks); smaller jobs run every round in full unless the caller's flags say
-// otherwise.
+// otherwise.  Nor do chunks whose round is one launch (round_is_small): that launch reads and writes values at
+// the rate of a copy, while a pair's second round gathers them (two rounds at r = 1, dim 128, pair / full, us:
+// 64 x 32768 tokens, chunk 256 553 / 431, chunk 64 688 / 420; 256 x 65536, chunk 256 4146 / 3465).
 enum RoundMode { ROUND_FULL = 0, ROUND_KEYS_ONLY = 1, ROUND_ORIGIN = 2 };
 constexpr int64_t kDeferMinChunks = 1024;
 
@@ -97,7 +99,8 @@ void plan_routes(const ckv_layout* in, const ckv_params* p, const ckv_plan_t* pl
     clusterable(plan->round_len[j + 1], p->n_sink, p->n_recent, &lo2, &hi2);
     const bool pair = allow && (j == 0 || j + 2 == plan->n_rounds) && plan->round_r[j] == 1.0f &&
                       p->scope == CKV_SCOPE_CHUNK && hi > lo && hi2 > lo2 &&
-                      (force || n_bh * div_up(plan->round_len[j + 1], p->chunk) >= kDeferMinChunks);
+                      (force || (!round_is_small(in->dtype, in->dim, p->chunk) &&
+                                 n_bh * div_up(plan->round_len[j + 1], p->chunk) >= kDeferMinChunks));
     if (pair) {
       mode[j] = ROUND_KEYS_ONLY;
       mode[j + 1] = ROUND_ORIGIN;
@@ -304,21 +307,26 @@ int run_rounds(const void* K, const void* V, const int32_t* deg_in, const ckv_la
       const unsigned char* mK = static_cast<const unsigned char*>(curK) + (in_pool ? 0 : (size_t)lo * curView.stride_s * e);
       const unsigned char* mV = static_cast<const unsigned char*>(curV) + (in_pool ? 0 : (size_t)lo * curView.stride_s * e);
       const int32_t* mDeg = !curDeg ? nullptr : in_pool ? curDeg : curDeg + lo;
-      err = launch_match(mK, in->dtype, in->dim, curView, n_bh, mid, p->chunk, dst, score, s, pin);
-      if (err != hipSuccess) return hip_status(err);
-      int32_t* sel = nullptr;
-      if (p->scope == CKV_SCOPE_HEAD) {
-        sel = reinterpret_cast<int32_t*>(ws + w.sel);
-        err = launch_global_select(score, n_bh, mid, p->chunk, plan.round_r[j], sel, s);
-        if (err != hipSuccess) return hip_status(err);
-      }
       unsigned char* moK = static_cast<unsigned char*>(oK) + (pok.table ? 0 : (size_t)lo * oView.stride_s * e);
       unsigned char* moV = static_cast<unsigned char*>(oV) + (pov.table ? 0 : (size_t)lo * oView.stride_s * e);
       int32_t* moDeg = pov.table ? oDeg : oDeg + lo;
-      err = launch_merge(mK, mV, mDeg, in->dtype, in->dim, curView, n_bh, mid, p->chunk, plan.round_r[j], dst, score,
-                         moK, moV, moDeg, oView, oDegStride, map ? map + lo : nullptr, curView.deg_stride, len, lo, sel,
-                         keys_only ? lists : nullptr, from_origin ? &org : nullptr, s, pin, pok, pov,
-                         edges.total > 0 ? &edges : nullptr);
+      const EdgeCopy* ride = edges.total > 0 ? &edges : nullptr;
+      if (mode[j] == ROUND_FULL && p->scope == CKV_SCOPE_CHUNK && round_fits(in->dtype, in->dim, n_bh, mid, p->chunk, ride)) {
+        err = launch_round(RoundCall{mK, mV, mDeg, curView, n_bh, mid, p->chunk, plan.round_r[j], moK, moV, moDeg, oView,
+                                     oDegStride, map ? map + lo : nullptr, len, lo, pin, pok, pov, ride}, in->dim, s);
+      } else {
+        err = launch_match(mK, in->dtype, in->dim, curView, n_bh, mid, p->chunk, dst, score, s, pin);
+        if (err != hipSuccess) return hip_status(err);
+        int32_t* sel = nullptr;
+        if (p->scope == CKV_SCOPE_HEAD) {
+          sel = reinterpret_cast<int32_t*>(ws + w.sel);
+          err = launch_global_select(score, n_bh, mid, p->chunk, plan.round_r[j], sel, s);
+          if (err != hipSuccess) return hip_status(err);
+        }
+        err = launch_merge(mK, mV, mDeg, in->dtype, in->dim, curView, n_bh, mid, p->chunk, plan.round_r[j], dst, score,
+                           moK, moV, moDeg, oView, oDegStride, map ? map + lo : nullptr, curView.deg_stride, len, lo, sel,
+                           keys_only ? lists : nullptr, from_origin ? &org : nullptr, s, pin, pok, pov, ride);
+      }
       if (err != hipSuccess) return hip_status(err);
     } else {
       err = launch_edges(edges, s);

@@ -108,6 +108,30 @@ hipError_t launch_merge(const void* K, const void* V, const int32_t* deg_in, int
                         PagedSide paged_out_k = PagedSide{}, PagedSide paged_out_v = PagedSide{},
                         const EdgeCopy* edges = nullptr);   // copied by the same launch
 
+// A whole round of small chunks in one launch: match + merge (per-chunk selection, keys and values), same
+// bits.  round_is_small: chunks that can run that way; round_fits: and the launch is not too large for it.
+struct RoundCall {
+  const void *K, *V;
+  const int32_t* deg_in;       // or NULL (= 1); rows in.deg_stride apart
+  TensorView in;
+  int n_bh, seq, chunk;
+  float r;
+  void *K_out, *V_out;
+  int32_t* deg_out;
+  TensorView out;
+  int64_t deg_out_stride;
+  int32_t* map_out;            // or NULL
+  int64_t map_stride;
+  int map_offset;
+  PagedSide pin, out_k, out_v;
+  const EdgeCopy* edges;       // copied by the same launch, or NULL
+};
+inline bool round_is_small(int dtype, int dim, int chunk) {
+  return dtype == CKV_BF16 && (dim == 64 || dim == 128) && (chunk == 64 || chunk == 128 || chunk == 256);
+}
+bool round_fits(int dtype, int dim, int n_bh, int seq, int chunk, const EdgeCopy* edges);
+hipError_t launch_round(const RoundCall& c, int dim, hipStream_t st);
+
 // Selection over all chunks of a sequence: from the match scores, table[bh, chunk] = (edges of the
 // chunk among the sequence's floor(r * edges) best, first output row of the chunk), two int32 each.
 // launch_merge with sel_table = table then merges exactly those.

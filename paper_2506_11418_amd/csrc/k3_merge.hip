@@ -43,46 +43,6 @@ __device__ inline int block_exclusive_scan(int v, int* s_wave_tot, int* total) {
   return base + inc - v;
 }
 
-// Tokens that bypass the clustering (Sec. 5.2: attention sinks and recent tokens are set aside
-// before partitioning; Sec. 5.3: they are concatenated back): the first n_head and the last n_tail
-// tokens of every sequence are copied to the head / tail of the output (keys, values, degree), and
-// their entries of the round's assignment map are written.  e: one 16-byte piece of one row.
-__device__ __forceinline__ void copy_edges(const EdgeCopy& ed, int64_t e) {
-  if (e >= ed.total) return;
-  const int piece = (int)(e % ed.pieces_per_row);
-  const int64_t row = e / ed.pieces_per_row;
-  const int n_edge = ed.n_head + ed.n_tail;
-  const int k = (int)(row % n_edge), bh = (int)(row / n_edge);
-  const int t_in = k < ed.n_head ? k : ed.in_len - ed.n_tail + (k - ed.n_head);
-  const int t_out = k < ed.n_head ? k : ed.out_len - ed.n_tail + (k - ed.n_head);
-  const int b = bh / ed.in.heads, h = bh % ed.in.heads;
-  // pool row of token u of this (batch, head) through a side's block table; -1 outside the pool
-  auto pool_row = [&](const PagedSide& pg, int u) -> int64_t {
-    const int blk = ((u >> pg.shift) < pg.max_blocks) ? pg.table[(int64_t)b * pg.max_blocks + (u >> pg.shift)] : -1;
-    if ((unsigned)blk >= (unsigned)pg.n_blocks) return -1;
-    return (((int64_t)blk * ed.in.heads + h) << pg.shift) + (u & ((1 << pg.shift) - 1));
-  };
-  const int64_t row_bytes = (int64_t)ed.pieces_per_row * 16;
-  int64_t ri = 0, rk = 0, rv = 0;
-  if (ed.pin.table) ri = pool_row(ed.pin, ed.pin.tok0 + t_in);
-  if (ed.pok.table) rk = pool_row(ed.pok, ed.pok.tok0 + t_out);
-  if (ed.pov.table) rv = pool_row(ed.pov, ed.pov.tok0 + t_out);
-  if (ri < 0) ri = 0;                      // a block outside the pool reads as row 0 and is not written
-  const int64_t so = ed.pin.table ? ri * row_bytes + piece * 16
-                                  : (ed.in.seq_base(bh) + (int64_t)t_in * ed.in.stride_s) * ed.elem_bytes + piece * 16;
-  const int64_t dof = (ed.out.seq_base(bh) + (int64_t)t_out * ed.out.stride_s) * ed.elem_bytes + piece * 16;
-  const int64_t dk = ed.pok.table ? rk * row_bytes + piece * 16 : dof;
-  const int64_t dv = ed.pov.table ? rv * row_bytes + piece * 16 : dof;
-  if (rk >= 0) *reinterpret_cast<uint4*>(ed.K_out + dk) = *reinterpret_cast<const uint4*>(ed.K + so);
-  if (rv >= 0) *reinterpret_cast<uint4*>(ed.V_out + dv) = *reinterpret_cast<const uint4*>(ed.V + so);
-  if (piece == 0) {
-    const int d = !ed.deg_in ? 1 : ed.pin.table ? ed.deg_in[ri] : ed.deg_in[(int64_t)bh * ed.in.deg_stride + t_in];
-    if (ed.pov.table) { if (rv >= 0) ed.deg_out[rv] = d; }
-    else ed.deg_out[(int64_t)bh * ed.out.deg_stride + t_out] = d;
-    if (ed.map_out) ed.map_out[(int64_t)bh * ed.in_len + t_in] = t_out;
-  }
-}
-
 template <typename T>
 struct Row;  // per-lane 16-byte piece arithmetic
 
@@ -120,17 +80,6 @@ struct Row<float> {
 
 constexpr int kRowsInFlight = 1;   // output rows of a row group per batch (two batches are in flight)
 constexpr int kRowsInFlightOrigin = 2;   // ... when every value row is itself rebuilt from several rows
-
-// What a launch without set-aside tokens does not carry: with the copy's 240 bytes among the arguments of
-// every variant the paged origin kernel parks 81 scalars in vector registers, without 65 (4 x 8 x 32768 tokens on
-// pages to a quarter, chunk 512: 572.6 -> 568.5 us).
-template <bool EDGES>
-struct EdgeBlocks {};
-template <>
-struct EdgeBlocks<true> {
-  int blocks;
-  EdgeCopy copy;
-};
 
 // MODE (two consecutive rounds whose first merges every edge, r = 1, can skip the intermediate
 // VALUE cache: a round-0 chunk then keeps exactly its B tokens, so a round-1 chunk is fed by two

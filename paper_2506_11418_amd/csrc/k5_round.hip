@@ -1,0 +1,415 @@
+// One clustering round of small chunks (64, 128 or 256 tokens, bf16) in one launch: similarity, matching,
+// top-r, merge and compaction (Sec. 5.2 - 5.3) of 256 consecutive tokens per workgroup.
+//
+// The block's keys and values are read once, in order, and written once, in order: the key rows are parked
+// in LDS, where the similarity tiles, the merge and the compaction read them; the value rows are requested
+// together with them, wait in registers while the matching runs, and take the keys' place in LDS once these
+// have been emitted.  A launch pair of match_small_bf16_kernel and merge_kernel reads the keys twice, gathers
+// the rows of both tensors from memory behind LDS lookups and passes the matching through memory.
+// Same operand order, norms, fold, member order and rounding as those two: same bits.
+//
+// What bounds it: large launches the HBM stream (64 sequences of 50003 tokens, chunk 256, eight rounds: 9.1 GB
+// in 1603 us = 5.7 TB/s, nine tenths of the chip's copy rate; two launches a round took 2283), small ones the
+// chain of one workgroup: request 1.0 us, keys 1.8, similarity 2.2, ranking and lists 2.8, keys out 2.9, values
+// in and out 2.8 (8 x 8448 tokens, 21.6 us a call; two launches 35.4).  Two workgroups per CU: 64 KiB of rows
+// each, and 128 registers, 32 of them the waiting values.
+#include <type_traits>
+
+#include "ckv_internal.h"
+#include "ckv_device.h"
+
+namespace ckv {
+namespace {
+
+constexpr int kTok = 256, kHalfTok = kTok / 2;   // tokens, and A (= B) rows, of a workgroup
+
+template <int D, bool PAGED, bool EDGES>
+__global__ __launch_bounds__(4 * D, 4) void round_small_kernel(
+    const __bf16* __restrict__ K, const __bf16* __restrict__ V, const int32_t* __restrict__ deg_in, TensorView in,
+    int seq, int chunk, int blocks_per_seq, int m_full, int m_tail, __bf16* __restrict__ K_out,
+    __bf16* __restrict__ V_out, int32_t* __restrict__ deg_out, TensorView out, int64_t deg_out_stride,
+    int32_t* __restrict__ map_out, int64_t deg_in_stride, int64_t map_stride, int map_offset, PagedSide pin,
+    PagedSide pout, int out_k_paged, int out_v_paged, EdgeBlocks<EDGES> edges) {
+  constexpr int THREADS = 4 * D, NW = THREADS / 64;
+  constexpr int OCT = D / 8, ROWB = D * 2, KEYSHIFT = (ROWB == 256) ? 0 : 1, KSTEPS = D / 16;
+  constexpr int NRG = THREADS / OCT;               // rows per pass = row groups: 32
+  constexpr int PASSES = kTok / NRG;               // 8
+  constexpr int LPA = THREADS / kHalfTok;          // lanes that share the bookkeeping of one source
+  static_assert(NRG == 32 && PASSES == 8, "32 rows per pass");
+  if constexpr (EDGES) {
+    if ((int)blockIdx.x < edges.blocks) {
+      copy_edges(edges.copy, (int64_t)blockIdx.x * THREADS + threadIdx.x);
+      return;
+    }
+  }
+  // rows 0 .. 127: the A tokens, 128 .. 255: the B tokens
+  extern __shared__ __attribute__((aligned(16))) unsigned char s_rows[];
+  __shared__ __attribute__((aligned(16))) float s_score[kHalfTok];
+  __shared__ __attribute__((aligned(16))) float s_ib[kHalfTok];
+  __shared__ __attribute__((aligned(16))) int16_t s_dstk[kHalfTok];   // B row a kept source merges into, or -1
+  __shared__ __attribute__((aligned(16))) int16_t s_slot[kTok];       // output row of a retained token
+  __shared__ int16_t s_dst[kHalfTok], s_start[kHalfTok], s_place[kHalfTok];
+  __shared__ int32_t s_cnt[kHalfTok];
+  __shared__ int32_t s_deg[kTok];                  // by LDS row
+  // A row as the emit loops see it: where its first piece sits in LDS (a lane XORs its own piece number in) and,
+  // in the upper half, its degree as bf16 (exact up to 256)
+  __shared__ uint32_t s_word[kTok];
+  __shared__ uint32_t s_members[kHalfTok];         // the words of the merged sources, list after list
+  __shared__ uint2 s_desc[kTok];                   // what to emit: word | output row, members << 8, first of them << 16
+  __shared__ float s_best2[NW == 8 ? kHalfTok : 1];
+  __shared__ int16_t s_dst2[NW == 8 ? kHalfTok : 1];
+  __shared__ int s_wide, s_n_merged, s_n_copied;
+  __shared__ int32_t s_rb_in[PAGED ? kTok / 8 + 2 : 1], s_rb_out[PAGED ? kTok / 8 + 2 : 1];
+
+  int w = (int)blockIdx.x;
+  if constexpr (EDGES) w -= edges.blocks;
+  const int sb = w % blocks_per_seq, bh = w / blocks_per_seq;
+  const int t0 = sb * kTok;
+  const int n_tok = min(kTok, seq - t0);
+  const int nA = (n_tok + 1) >> 1, nB = n_tok >> 1;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int piece = tid % OCT, rg = tid / OCT;
+  const int n_whole = n_tok / chunk, tail = n_tok - n_whole * chunk;   // (a short chunk ends the sequence)
+  const int n_out = n_tok - n_whole * m_full - (tail ? m_tail : 0);
+  const int out_base = (t0 / chunk) * (chunk - m_full);
+
+  RowBases rb_in{}, rb_out{};
+  const bool in_paged = PAGED && pin.table != nullptr;
+  const bool ok_paged = PAGED && out_k_paged, ov_paged = PAGED && out_v_paged;
+  if (PAGED) {
+    const int b = bh / in.heads, h = bh % in.heads;
+    if (in_paged) rb_in = stage_row_bases(s_rb_in, pin, b, h, in.heads, pin.tok0 + t0, pin.tok0 + t0 + n_tok - 1, tid, THREADS);
+    if (ok_paged || ov_paged)
+      rb_out = stage_row_bases(s_rb_out, pout, b, h, in.heads, pout.tok0 + out_base, pout.tok0 + out_base + n_out - 1, tid, THREADS);
+    if (in_paged) __syncthreads();
+  }
+
+  // ---- every load of the block, before the first use ------------------------------------------
+  const int64_t seq_at = in_paged ? 0 : in.seq_base(bh) + (int64_t)t0 * in.stride_s;
+  const __bf16* Kp = K + seq_at + piece * 8;
+  const __bf16* Vp = V + seq_at + piece * 8;
+  auto row_at = [&](int u) -> int64_t {            // rows past the block's end re-read its last one
+    const int t = min(u, n_tok - 1);
+    return in_paged ? (int64_t)rb_in.row(pin.tok0 + t0 + t) * D : (int64_t)t * in.stride_s;
+  };
+  Piece kx[PASSES];
+  uint4 vx[PASSES];
+#pragma unroll
+  for (int it = 0; it < PASSES; ++it) kx[it].u = ldg16_stream(Kp + row_at(it * NRG + rg));
+  int dg = 1;
+  if (deg_in && tid < n_tok) dg = in_paged ? deg_in[rb_in.row(pin.tok0 + t0 + tid)] : deg_in[(int64_t)bh * deg_in_stride + t0 + tid];
+#pragma unroll
+  for (int it = 0; it < PASSES; ++it) vx[it] = ldg16_stream(Vp + row_at(it * NRG + rg));
+
+  auto swz = [](int row, int pc) -> int { return row * ROWB + (((pc ^ (row >> KEYSHIFT)) & (OCT - 1)) << 4); };
+  const int row0 = (rg & 1) * kHalfTok + (rg >> 1);      // LDS row of token rg; 32 tokens on: 16 rows on, same XOR
+  const int lds0 = swz(row0, piece);
+  if (tid < kHalfTok) { s_cnt[tid] = 0; s_score[tid] = -INFINITY; }
+  if (tid < kTok) {
+    const int row = (tid & 1) * kHalfTok + (tid >> 1);
+    s_deg[row] = dg;
+    s_word[row] = (uint32_t)swz(row, 0) | (__float_as_uint((float)dg) & 0xffff0000u);
+    s_desc[tid] = make_uint2(0, 0);
+  }
+  if (tid == 0) { s_wide = 0; s_n_merged = 0; s_n_copied = 0; }
+#pragma unroll
+  for (int it = 0; it < PASSES; ++it) {
+    if (it * NRG + rg >= n_tok) kx[it].u = make_uint4(0, 0, 0, 0);
+    const float ss = row_sum<OCT>(sumsq8(kx[it]));
+    *reinterpret_cast<uint4*>(s_rows + lds0 + it * (NRG / 2) * ROWB) = kx[it].u;
+    if (piece == 0 && (rg & 1)) s_ib[it * (NRG / 2) + (rg >> 1)] = inv_norm(ss);
+  }
+  __syncthreads();
+  if (tid < kTok && dg > 256) s_wide = 1;
+
+  // ---- similarity and matching: a 32-row tile of sources against the tiles of its own chunk -------
+  const int half = lane >> 5, col = lane & 31;
+  {
+    const int wv = __builtin_amdgcn_readfirstlane(wave);
+    const int at = (NW == 8) ? wv >> 1 : wv, hb = (NW == 8) ? wv & 1 : 0;
+    const int tpc = chunk >> 6, first = at & -tpc;                         // tiles per chunk (1, 2 or 4); its first tile
+    const int lo = (NW == 8) ? (hb * tpc + 1) / 2 : 0, hi = (NW == 8 && hb == 0) ? (tpc + 1) / 2 : tpc;
+    float best = -INFINITY, inva = 0.f;
+    int bestj = 0;
+    if (at * 32 < nA && lo < hi) {                 // (the same for the whole wave)
+      // two tiles at a time where there are two: their MFMA chains run side by side.  The source operands pass
+      // through (the values wait in 32 registers): the sum of their squares is taken as they do, in the order of
+      // inv_norm_of_operand_row
+      float ss = 0.f;
+      auto tiles = [&](auto count_c, int tt) {
+        constexpr int C = decltype(count_c)::value;
+        f32x16 acc[C];
+        ss = 0.f;
+#pragma unroll
+        for (int c = 0; c < C; ++c) acc[c] = f32x16{0};
+#pragma unroll
+        for (int s = 0; s < KSTEPS; ++s) {
+          const int off = swz(col, 2 * s + half);
+          Piece afrag;
+          afrag.u = *reinterpret_cast<const uint4*>(s_rows + at * 32 * ROWB + off);
+#pragma unroll
+          for (int c = 0; c < C; ++c)
+            acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                *reinterpret_cast<const bf16x8*>(s_rows + (kHalfTok + (first + tt + c) * 32) * ROWB + off), afrag.v, acc[c],
+                0, 0, 0);
+          ss += sumsq8(afrag);
+          // (operands requested further ahead, or kept for the sum, push the values into scratch)
+          if (s % 2 == 1) asm volatile("" : "+v"(ss) : : "memory");
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+          const int bt = first + tt + c;
+          f32x4 ib[4];
+#pragma unroll
+          for (int qd = 0; qd < 4; ++qd) ib[qd] = *reinterpret_cast<const f32x4*>(s_ib + bt * 32 + 4 * half + 8 * qd);
+          const int valid = nB - bt * 32;          // rows of this tile that exist (>= 32: all)
+          if (valid >= 32) tile_argmax<false>(acc[c], ib, bt * 32, half, 32, best, bestj);
+          else if (valid > 0) tile_argmax<true>(acc[c], ib, bt * 32, half, valid, best, bestj);
+          __builtin_amdgcn_sched_barrier(0);       // (one fold after the other)
+        }
+      };
+      if (hi - lo == 1) tiles(std::integral_constant<int, 1>{}, lo);
+      else tiles(std::integral_constant<int, 2>{}, lo);
+      if (NW == 4 && hi - lo == 4) tiles(std::integral_constant<int, 2>{}, lo + 2);
+      inva = inv_norm(ss + __shfl_xor(ss, 32));
+      const float ob = __shfl_xor(best, 32);
+      const int oj = __shfl_xor(bestj, 32);
+      if (ob > best || (ob == best && oj < bestj)) { best = ob; bestj = oj; }
+    }
+    const int a = at * 32 + col;
+    if (NW == 8) {
+      if (hb == 1 && half == 0) { s_best2[a] = best; s_dst2[a] = (int16_t)bestj; }
+      __syncthreads();
+      if (hb == 0 && s_best2[a] > best) { best = s_best2[a]; bestj = s_dst2[a]; }   // (the other wave's rows come later)
+    }
+    if (hb == 0 && half == 0 && a < nA) {
+      s_dst[a] = (nB <= first * 32) ? (int16_t)-1 : (int16_t)bestj;   // a one-token tail chunk: nothing to match
+      s_score[a] = best * inva;
+    }
+  }
+  __syncthreads();
+
+  // ---- top-r of every chunk: rank by counting (score descending, index ascending) ---------------
+  const int a = tid / LPA, sub = tid % LPA;
+  const int a_lo = a & ~((chunk >> 1) - 1), nAc = min(chunk >> 1, nA - a_lo);
+  const int m = (nAc == (chunk >> 1) && 2 * a_lo + chunk <= n_tok) ? m_full : m_tail;
+  int d = -1;
+  if (a < nA && m > 0) {
+    d = s_dst[a];
+    if (m < nAc) {
+      // an equal score of an earlier source ranks above: those are counted from the score itself on, the later
+      // ones from the next larger number on (sources that do not exist hold -inf and come later)
+      const float si = s_score[a] + 0.f;           // (-0 as +0)
+      const float above = __uint_as_float(__float_as_uint(si) + (si < 0.f ? 0xffffffffu : 1u));
+      int rank = 0;
+      for (int o = a_lo + 4 * sub; o < a_lo + nAc; o += 4 * LPA) {
+        const float4 so = *reinterpret_cast<const float4*>(&s_score[o]);
+        rank += (so.x >= (o < a ? si : above)) + (so.y >= (o + 1 < a ? si : above)) +
+                (so.z >= (o + 2 < a ? si : above)) + (so.w >= (o + 3 < a ? si : above));
+      }
+#pragma unroll
+      for (int x = 1; x < LPA; x <<= 1) rank += __shfl_xor(rank, x);
+      if (rank >= m) d = -1;
+    }
+  }
+  if (sub == 0) {
+    s_dstk[a] = (int16_t)d;
+    if (d >= 0) atomicAdd(&s_cnt[d], 1);
+  }
+  __syncthreads();
+
+  // ---- member lists (ascending inside a list) and the retained tokens' output rows ---------------
+  if (wave == 0) {                                 // where every B row's list starts, and its place among the merged rows
+    // one scan of three sums, ten bits each: members, lists of two or more, lists of one
+    const int c0 = s_cnt[2 * lane], c1 = s_cnt[2 * lane + 1];
+    auto sums = [](int c) -> uint32_t { return (uint32_t)c | (uint32_t)(c > 1) << 10 | (uint32_t)(c == 1) << 20; };
+    const uint32_t f0 = sums(c0), f1 = sums(c1);
+    uint32_t inc = f0 + f1;
+#pragma unroll
+    for (int x = 1; x < 64; x <<= 1) {
+      const uint32_t o = __shfl_up(inc, x);
+      if (lane >= x) inc += o;
+    }
+    const uint32_t all = __shfl(inc, 63);
+    const int n_long = (int)(all >> 10 & 1023u);
+    auto place = [&](uint32_t before, int c) { return (int16_t)(c > 1 ? before >> 10 & 1023u : n_long + (before >> 20)); };
+    const uint32_t b0 = inc - f0 - f1, b1 = inc - f1;
+    s_start[2 * lane] = (int16_t)(b0 & 1023u);
+    s_start[2 * lane + 1] = (int16_t)(b1 & 1023u);
+    s_place[2 * lane] = place(b0, c0);
+    s_place[2 * lane + 1] = place(b1, c1);
+    if (lane == 0) s_n_merged = n_long + (int)(all >> 20);
+  } else if (wave == 1) {                          // four tokens per lane
+    const int u = 4 * lane;
+    const int k0 = u < n_tok && s_dstk[2 * lane] < 0, k1 = u + 1 < n_tok;
+    const int k2 = u + 2 < n_tok && s_dstk[2 * lane + 1] < 0, k3 = u + 3 < n_tok;
+    int inc = k0 + k1 + k2 + k3;
+#pragma unroll
+    for (int x = 1; x < 64; x <<= 1) {
+      const int o = __shfl_up(inc, x);
+      if (lane >= x) inc += o;
+    }
+    const int base = inc - (k0 + k1 + k2 + k3);
+    const int p1 = base + k0, p2 = p1 + k1, p3 = p2 + k2;
+    *reinterpret_cast<uint2*>(&s_slot[u]) = make_uint2((uint32_t)base | ((uint32_t)p1 << 16), (uint32_t)p2 | ((uint32_t)p3 << 16));
+  }
+  int pos = 0;                                     // earlier sources of the same list
+  if (d >= 0 && s_cnt[d] > 1) {
+    for (int o = a_lo + 8 * sub; o < a; o += 8 * LPA) {
+      struct { int16_t v[8]; } x = *reinterpret_cast<const decltype(x)*>(&s_dstk[o]);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) pos += (x.v[i] == d) && (o + i < a);
+    }
+#pragma unroll
+    for (int x = 1; x < LPA; x <<= 1) pos += __shfl_xor(pos, x);
+  }
+  __syncthreads();
+  // Rows with two or more members come first, then those with one, then the copies: the row groups of a wave
+  // then do the same work side by side (in output order nine waves in ten carried some row to merge).
+  if (sub == 0 && d >= 0) s_members[s_start[d] + pos] = s_word[a];
+  if (wave < kTok / 64) {
+    const int u = tid, j = u >> 1, row = (u & 1) * kHalfTok + j;
+    const int into = (u & 1) || u >= n_tok ? -1 : (int)s_dstk[j];
+    const int n = (u & 1) ? s_cnt[j] : 0;
+    const bool copied = u < n_tok && into < 0 && n == 0;
+    const uint64_t mask = __ballot(copied);
+    int at = 0;
+    if (lane == 0) at = atomicAdd(&s_n_copied, __popcll(mask));
+    at = s_n_merged + __shfl(at, 0) + __popcll(mask & ((1ull << lane) - 1));
+    const uint32_t o = (uint32_t)s_slot[u];
+    if (copied) s_desc[at] = make_uint2(s_word[row], o);
+    else if (u < n_tok && into < 0) s_desc[s_place[j]] = make_uint2(s_word[row], o | (uint32_t)n << 8 | (uint32_t)s_start[j] << 16);
+    if (map_out && u < n_tok) map_out[(int64_t)bh * map_stride + t0 + u] = map_offset + out_base + (into < 0 ? s_slot[u] : s_slot[2 * into + 1]);
+  }
+  __syncthreads();
+
+  // ---- emit the rows of one tensor: keys first, then the values in their place ---------------------
+  const int64_t out_at = out.seq_base(bh) + (int64_t)out_base * out.stride_s;
+  const int u_out0 = pout.tok0 + out_base;
+  const int n_merged = s_n_merged;
+  const uint32_t lane_piece = (uint32_t)piece << 4;
+  auto row_of = [&](uint32_t word) -> uint4 {
+    return *reinterpret_cast<const uint4*>(s_rows + ((word & 0xffffu) ^ lane_piece));
+  };
+  auto degree_of = [&](uint32_t word) -> int { return s_deg[(word & 0xffffu) / ROWB]; };
+  auto weighed = [&](float* acc, const uint4& x, uint32_t word) {      // + degree * row, degrees up to 256
+    const bf16x2 lo = __builtin_bit_cast(bf16x2, word >> 16), hi = __builtin_bit_cast(bf16x2, word & 0xffff0000u);
+    const uint32_t v[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      acc[2 * i] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, v[i]), lo, acc[2 * i], false);
+      acc[2 * i + 1] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, v[i]), hi, acc[2 * i + 1], false);
+    }
+  };
+  auto emit = [&](auto wide_c, auto keys_c) {
+    constexpr bool WIDE = decltype(wide_c)::value, KEYS = decltype(keys_c)::value;
+    const bool o_paged = KEYS ? ok_paged : ov_paged;
+    __bf16* O = (KEYS ? K_out : V_out) + piece * 8 + (o_paged ? 0 : out_at);
+    auto put = [&](int o, const uint4& x, int nd) {
+      if (PAGED && (ok_paged || ov_paged) && rb_out.base_of(u_out0 + o) < 0) return;   // a block outside the pool
+      stg16_stream(O + (o_paged ? (int64_t)rb_out.row(u_out0 + o) * D : (int64_t)o * out.stride_s), x);
+      if (KEYS && piece == 0) {
+        if (ov_paged) deg_out[rb_out.row(u_out0 + o)] = nd;
+        else deg_out[(int64_t)bh * deg_out_stride + out_base + o] = nd;
+      }
+    };
+    for (int i = rg; i < n_merged; i += NRG) {
+      const uint2 w = s_desc[i];
+      const int o = (int)(w.y & 0xffu), n = (int)(w.y >> 8 & 0xffu);
+      const uint32_t* list = s_members + (w.y >> 16);
+      const uint4 x = row_of(w.x);
+      float acc[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+      if constexpr (WIDE) {
+        int nd = degree_of(w.x);
+        fma_bf16x8_t<true>(acc, x, nd);
+#pragma unroll 1
+        for (int q = 0; q < n; ++q) {
+          const int dm = degree_of(list[q]);
+          fma_bf16x8_t<true>(acc, row_of(list[q]), dm);
+          nd += dm;
+        }
+        put(o, round_div_pack_bf16(acc, nd), nd);
+      } else {
+        float nd = __uint_as_float(w.x & 0xffff0000u);
+        uint32_t wm = list[0];
+        weighed(acc, x, w.x);
+        weighed(acc, row_of(wm), wm);
+        nd += __uint_as_float(wm & 0xffff0000u);
+#pragma unroll 1
+        for (int q = 1; q < n; ++q) {
+          wm = list[q];
+          weighed(acc, row_of(wm), wm);
+          nd += __uint_as_float(wm & 0xffff0000u);
+        }
+        put(o, round_div_pack_bf16(acc, nd), (int)nd);
+      }
+    }
+    // untouched tokens, bit by bit (the row groups that had one merged row less start)
+    for (int i = n_merged + (rg + NRG - n_merged % NRG) % NRG; i < n_out; i += NRG) {
+      const uint2 w = s_desc[i];
+      put((int)(w.y & 0xffu), row_of(w.x), degree_of(w.x));
+    }
+  };
+  const bool wide = s_wide != 0;
+#pragma unroll
+  for (int it = 0; it < PASSES; ++it)              // the values are here by now: waited for before any store is counted
+    asm volatile("" : "+v"(vx[it].x), "+v"(vx[it].y), "+v"(vx[it].z), "+v"(vx[it].w));
+  if (wide) emit(std::true_type{}, std::true_type{});
+  else emit(std::false_type{}, std::true_type{});
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < PASSES; ++it) *reinterpret_cast<uint4*>(s_rows + lds0 + it * (NRG / 2) * ROWB) = vx[it];
+  __syncthreads();
+  if (wide) emit(std::true_type{}, std::false_type{});
+  else emit(std::false_type{}, std::false_type{});
+}
+
+template <int D>
+hipError_t launch_round_t(const RoundCall& c, hipStream_t st) {
+  constexpr int THREADS = 4 * D;
+  constexpr size_t lds = (size_t)kTok * D * 2;
+  const int blocks = div_up(c.seq, kTok);
+  const int64_t total = (int64_t)c.n_bh * blocks;
+  const int64_t edge_blocks = c.edges ? (c.edges->total + THREADS - 1) / THREADS : 0;
+  const int nA_tail = (c.seq % c.chunk + 1) / 2;
+  const int m_full = merge_count(c.r, c.chunk / 2), m_tail = c.seq % c.chunk >= 2 ? merge_count(c.r, nA_tail) : 0;
+  const PagedSide pout = c.out_k.table ? c.out_k : c.out_v;
+  ScopedTimer t("round_bf16", st);
+#define CKV_ROUND(PG, ED, ...)                                                                                  \
+  do {                                                                                                          \
+    static KernelSetup setup;                                                                                   \
+    if (hipError_t e = kernel_setup(reinterpret_cast<const void*>(&round_small_kernel<D, PG, ED>), lds, setup); \
+        e != hipSuccess)                                                                                        \
+      return e;                                                                                                 \
+    hipLaunchKernelGGL((round_small_kernel<D, PG, ED>), dim3((unsigned)(total + edge_blocks)), dim3(THREADS), lds, st, \
+                       static_cast<const __bf16*>(c.K), static_cast<const __bf16*>(c.V), c.deg_in, c.in, c.seq, c.chunk, \
+                       blocks, m_full, m_tail, static_cast<__bf16*>(c.K_out), static_cast<__bf16*>(c.V_out), c.deg_out,  \
+                       c.out, c.deg_out_stride, c.map_out, c.in.deg_stride, c.map_stride, c.map_offset, c.pin, pout,     \
+                       c.out_k.table != nullptr, c.out_v.table != nullptr, EdgeBlocks<ED>{__VA_ARGS__});                 \
+  } while (0)
+  if (c.pin.table || pout.table) {
+    if (c.edges) CKV_ROUND(true, true, (int)edge_blocks, *c.edges);
+    else CKV_ROUND(true, false);
+  } else {
+    if (c.edges) CKV_ROUND(false, true, (int)edge_blocks, *c.edges);
+    else CKV_ROUND(false, false);
+  }
+#undef CKV_ROUND
+  return hipGetLastError();
+}
+
+}  // namespace
+
+bool round_fits(int dtype, int dim, int n_bh, int seq, int chunk, const EdgeCopy* edges) {
+  if (!round_is_small(dtype, dim, chunk)) return false;
+  const int64_t threads = 4 * dim;
+  return ((int64_t)n_bh * div_up(seq, kTok) + (edges ? edges->total / threads + 1 : 0)) * threads <= UINT32_MAX;
+}
+
+hipError_t launch_round(const RoundCall& c, int dim, hipStream_t st) {
+  return dim == 128 ? launch_round_t<128>(c, st) : launch_round_t<64>(c, st);
+}
+
+}  // namespace ckv

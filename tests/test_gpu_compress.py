@@ -252,6 +252,46 @@ def test_compress_config2_llama_layer_bf16():
     assert int(gdeg.sum()) == 8 * 32768
 
 
+# ---- rounds of small chunks: one launch of 256 tokens per workgroup -----------------------------
+@pytest.mark.parametrize("chunk", [64, 128, 256])
+@pytest.mark.parametrize("seq,dim,r,big_degrees,n_sink,n_recent", [
+    (256, 128, 0.8, False, 0, 0),
+    (257, 128, 1.0, False, 0, 0),            # a one-token chunk in a block of its own
+    (512 + 65, 64, 0.5, False, 0, 0),        # chunk 64: a one-token chunk behind a whole one
+    (768 + 255, 128, 0.3, True, 0, 0),       # the longest tail; weights beyond the packed route's 256
+    (2 * 256 + 130, 64, 1.0, True, 16, 64),
+    (80 + 3, 128, 1.0, False, 16, 64),       # three tokens to cluster
+    (300, 64, 0.0, False, 0, 9),             # nothing merged
+])
+def test_rounds_of_small_chunks_in_one_launch(seq, dim, r, big_degrees, n_sink, n_recent, chunk):
+    """Against the oracle, and at r = 1 (where ranking per chunk and over the whole sequence merge the same
+    edges) bit for bit against the separate match, selection and merge kernels."""
+    _say(f"round in one launch S={seq} D={dim} c={chunk} r={r} n1={n_sink} n2={n_recent}")
+    K, V, _ = kv_host(41, 4, seq, dim, "bf16", alpha=0.9, n_outlier=4 if dim == 128 else 0)
+    K, V = K.reshape(2, 2, seq, dim).to(DEV), V.reshape(2, 2, seq, dim).to(DEV)
+    deg = np.random.default_rng(seq).integers(1, 9, (2, 2, seq))
+    if big_degrees:
+        deg[1, 0, seq // 2:] *= 999
+    deg = torch.from_numpy(deg.astype(np.int32)).to(DEV)
+    kw = dict(rounds=[r], deg=deg, n_sink=n_sink, n_recent=n_recent)
+    ckv.timing_reset()
+    ckv.timing_enable(True)
+    got = ckv.compress(K, V, chunk, **kw)
+    torch.cuda.synchronize()
+    ckv.timing_enable(False)
+    assert list(ckv.timing_read()) == ["round_bf16"]
+    for b in range(2):
+        for h in range(2):
+            check_round_with_edges(f64(K[b, h]), f64(V[b, h]), i64(deg[b, h]), chunk, r, "bf16", n_sink, n_recent,
+                                   f64(got[0][b, h]), f64(got[1][b, h]), i64(got[2][b, h]), i64(got[3][b, h]),
+                                   what=f"b{b} h{h}")
+    if r == 1.0:
+        ref = ckv.compress(K, V, chunk, scope="head", **kw)
+        torch.cuda.synchronize()
+        for n, a, e in zip(["K'", "V'", "deg'", "assign"], got, ref):
+            assert torch.equal(a, e), f"{n} differs from the separate kernels"
+
+
 # ---- attention sinks and recent tokens (Sec. 5.2 / 5.3) ----------------------------------------
 @pytest.mark.parametrize("dtype,heads,seq,dim,chunk,rounds,n_sink,n_recent", [
     ("bf16", 2, 4096 + 80, 128, 1024, [1.0, 1.0], 16, 64),
