@@ -99,7 +99,7 @@ void plan_routes(const ckv_layout* in, const ckv_params* p, const ckv_plan_t* pl
     clusterable(plan->round_len[j + 1], p->n_sink, p->n_recent, &lo2, &hi2);
     const bool pair = allow && (j == 0 || j + 2 == plan->n_rounds) && plan->round_r[j] == 1.0f &&
                       p->scope == CKV_SCOPE_CHUNK && hi > lo && hi2 > lo2 &&
-                      (force || (!round_is_small(in->dtype, in->dim, p->chunk) &&
+                      (force || (!(in->dtype == CKV_BF16 && round_is_small(in->dtype, in->dim, p->chunk)) &&
                                  n_bh * div_up(plan->round_len[j + 1], p->chunk) >= kDeferMinChunks));
     if (pair) {
       mode[j] = ROUND_KEYS_ONLY;
@@ -311,9 +311,9 @@ int run_rounds(const void* K, const void* V, const int32_t* deg_in, const ckv_la
       unsigned char* moV = static_cast<unsigned char*>(oV) + (pov.table ? 0 : (size_t)lo * oView.stride_s * e);
       int32_t* moDeg = pov.table ? oDeg : oDeg + lo;
       const EdgeCopy* ride = edges.total > 0 ? &edges : nullptr;
-      if (mode[j] == ROUND_FULL && p->scope == CKV_SCOPE_CHUNK && round_fits(in->dtype, in->dim, n_bh, mid, p->chunk, ride)) {
+      if (mode[j] == ROUND_FULL && p->scope == CKV_SCOPE_CHUNK && round_fits(in->dtype, in->dim, n_bh, mid, p->chunk, ride, pc != nullptr)) {
         err = launch_round(RoundCall{mK, mV, mDeg, curView, n_bh, mid, p->chunk, plan.round_r[j], moK, moV, moDeg, oView,
-                                     oDegStride, map ? map + lo : nullptr, len, lo, pin, pok, pov, ride}, in->dim, s);
+                                     oDegStride, map ? map + lo : nullptr, len, lo, pin, pok, pov, ride}, in->dtype, in->dim, s);
       } else {
         err = launch_match(mK, in->dtype, in->dim, curView, n_bh, mid, p->chunk, dst, score, s, pin);
         if (err != hipSuccess) return hip_status(err);

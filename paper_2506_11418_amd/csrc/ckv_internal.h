@@ -109,7 +109,8 @@ hipError_t launch_merge(const void* K, const void* V, const int32_t* deg_in, int
                         const EdgeCopy* edges = nullptr);   // copied by the same launch
 
 // A whole round of small chunks in one launch: match + merge (per-chunk selection, keys and values), same
-// bits.  round_is_small: chunks that can run that way; round_fits: and the launch is not too large for it.
+// bits.  round_is_small: chunks that can run that way; round_fits: and the launch is not too large for it
+// (fp32: strided caches only).
 struct RoundCall {
   const void *K, *V;
   const int32_t* deg_in;       // or NULL (= 1); rows in.deg_stride apart
@@ -127,10 +128,11 @@ struct RoundCall {
   const EdgeCopy* edges;       // copied by the same launch, or NULL
 };
 inline bool round_is_small(int dtype, int dim, int chunk) {
-  return dtype == CKV_BF16 && (dim == 64 || dim == 128) && (chunk == 64 || chunk == 128 || chunk == 256);
+  return (dim == 64 || dim == 128 || (dtype == CKV_F32 && (dim == 16 || dim == 32))) &&
+         (chunk == 64 || chunk == 128 || chunk == 256);
 }
-bool round_fits(int dtype, int dim, int n_bh, int seq, int chunk, const EdgeCopy* edges);
-hipError_t launch_round(const RoundCall& c, int dim, hipStream_t st);
+bool round_fits(int dtype, int dim, int n_bh, int seq, int chunk, const EdgeCopy* edges, bool paged);
+hipError_t launch_round(const RoundCall& c, int dtype, int dim, hipStream_t st);
 
 // Selection over all chunks of a sequence: from the match scores, table[bh, chunk] = (edges of the
 // chunk among the sequence's floor(r * edges) best, first output row of the chunk), two int32 each.

@@ -23,6 +23,147 @@ namespace {
 
 constexpr int kTok = 256, kHalfTok = kTok / 2;   // tokens, and A (= B) rows, of a workgroup
 
+// The bookkeeping of a block of up to HALF sources and HALF destinations (rows of LDS 0 .. HALF-1 and HALF .. 2 HALF-1;
+// token u is row (u & 1) * HALF + u / 2): which edges are kept, who merges into whom, where everything goes.
+template <int HALF>
+struct RoundLds {
+  __attribute__((aligned(16))) float score[HALF];
+  __attribute__((aligned(16))) int16_t kept[HALF];     // destination a kept source merges into, or -1
+  __attribute__((aligned(16))) int16_t slot[2 * HALF]; // output row of a retained token
+  int16_t dst[HALF], start[HALF], place[HALF];
+  int32_t cnt[HALF];
+  int32_t deg[2 * HALF];       // by row
+  uint32_t word[2 * HALF];     // a row as the emit loops see it (the kernel's own encoding)
+  uint32_t members[HALF];      // the words of the merged sources, list after list, ascending inside a list
+  uint2 desc[2 * HALF];        // what to emit: word | output row, members << 8, first of them << 16
+  int n_merged, n_copied;
+};
+
+// In: score, dst (-1: nothing to merge into), deg and word of every row; cnt, desc, n_merged, n_copied zero, scores of
+// sources that do not exist -inf.  Chunks of `chunk` tokens, the last one of the block possibly short: m_full / m_tail
+// edges of a whole / short one are merged.  Begins and ends with a barrier.
+template <int HALF, int THREADS>
+__device__ __forceinline__ void round_lists(RoundLds<HALF>& s, int n_tok, int chunk, int m_full, int m_tail,
+                                            int32_t* __restrict__ map, int map_base) {
+  constexpr int LPA = THREADS / HALF;              // lanes that share the bookkeeping of one source
+  static_assert(LPA >= 1 && LPA <= 8, "lanes per source");
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int nA = (n_tok + 1) >> 1;
+  __syncthreads();
+
+  // ---- top-r of every chunk: rank by counting (score descending, index ascending) ---------------
+  const int a = tid / LPA, sub = tid % LPA;
+  const int a_lo = a & ~((chunk >> 1) - 1), nAc = min(chunk >> 1, nA - a_lo);
+  const int m = (nAc == (chunk >> 1) && 2 * a_lo + chunk <= n_tok) ? m_full : m_tail;
+  int d = -1;
+  if (a < nA && m > 0) {
+    d = s.dst[a];
+    if (m < nAc) {
+      // an equal score of an earlier source ranks above: those are counted from the score itself on, the later
+      // ones from the next larger number on (sources that do not exist hold -inf and come later)
+      const float si = s.score[a] + 0.f;           // (-0 as +0)
+      const float above = __uint_as_float(__float_as_uint(si) + (si < 0.f ? 0xffffffffu : 1u));
+      int rank = 0;
+      for (int o = a_lo + 4 * sub; o < a_lo + nAc; o += 4 * LPA) {
+        const float4 so = *reinterpret_cast<const float4*>(&s.score[o]);
+        rank += (so.x >= (o < a ? si : above)) + (so.y >= (o + 1 < a ? si : above)) +
+                (so.z >= (o + 2 < a ? si : above)) + (so.w >= (o + 3 < a ? si : above));
+      }
+#pragma unroll
+      for (int x = 1; x < LPA; x <<= 1) rank += __shfl_xor(rank, x);
+      if (rank >= m) d = -1;
+    }
+  }
+  if (sub == 0) {
+    s.kept[a] = (int16_t)d;
+    if (d >= 0) atomicAdd(&s.cnt[d], 1);
+  }
+  __syncthreads();
+
+  // ---- member lists (ascending inside a list) and the retained tokens' output rows ---------------
+  if (wave == 0) {                                 // where every destination's list starts, and its place among the merged rows
+    // one scan of three sums, ten bits each: members, lists of two or more, lists of one
+    constexpr int PER = HALF >= 64 ? HALF / 64 : 1;
+    auto sums = [](int c) -> uint32_t { return (uint32_t)c | (uint32_t)(c > 1) << 10 | (uint32_t)(c == 1) << 20; };
+    int c[PER];
+    uint32_t mine = 0;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      c[e] = lane * PER + e < HALF ? s.cnt[lane * PER + e] : 0;
+      mine += sums(c[e]);
+    }
+    uint32_t inc = mine;
+#pragma unroll
+    for (int x = 1; x < 64; x <<= 1) {
+      const uint32_t o = __shfl_up(inc, x);
+      if (lane >= x) inc += o;
+    }
+    const uint32_t all = __shfl(inc, 63);
+    const int n_long = (int)(all >> 10 & 1023u);
+    uint32_t before = inc - mine;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      const int j = lane * PER + e;
+      if (j < HALF) {
+        s.start[j] = (int16_t)(before & 1023u);
+        s.place[j] = (int16_t)(c[e] > 1 ? before >> 10 & 1023u : n_long + (before >> 20));
+      }
+      before += sums(c[e]);
+    }
+    if (lane == 0) s.n_merged = n_long + (int)(all >> 20);
+  } else if (wave == 1) {
+    constexpr int PER = 2 * HALF / 64;             // neighbouring tokens per lane
+    int keep[PER], mine = 0;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      const int u = lane * PER + e;
+      keep[e] = u < n_tok && ((u & 1) || s.kept[u >> 1] < 0);
+      mine += keep[e];
+    }
+    int inc = mine;
+#pragma unroll
+    for (int x = 1; x < 64; x <<= 1) {
+      const int o = __shfl_up(inc, x);
+      if (lane >= x) inc += o;
+    }
+    int at = inc - mine;
+#pragma unroll
+    for (int e = 0; e < PER; ++e) {
+      s.slot[lane * PER + e] = (int16_t)at;
+      at += keep[e];
+    }
+  }
+  int pos = 0;                                     // earlier sources of the same list
+  if (d >= 0 && s.cnt[d] > 1) {
+    for (int o = a_lo + 8 * sub; o < a; o += 8 * LPA) {
+      struct { int16_t v[8]; } x = *reinterpret_cast<const decltype(x)*>(&s.kept[o]);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) pos += (x.v[i] == d) && (o + i < a);
+    }
+#pragma unroll
+    for (int x = 1; x < LPA; x <<= 1) pos += __shfl_xor(pos, x);
+  }
+  __syncthreads();
+  // Rows with two or more members come first, then those with one, then the copies: the row groups of a wave
+  // then do the same work side by side (in output order nine waves in ten carried some row to merge).
+  if (sub == 0 && d >= 0) s.members[s.start[d] + pos] = s.word[a];
+  if (tid < 2 * HALF) {                            // (whole waves)
+    const int u = tid, j = u >> 1, row = (u & 1) * HALF + j;
+    const int into = (u & 1) || u >= n_tok ? -1 : (int)s.kept[j];
+    const int n = (u & 1) ? s.cnt[j] : 0;
+    const bool copied = u < n_tok && into < 0 && n == 0;
+    const uint64_t mask = __ballot(copied);
+    int at = 0;
+    if (lane == 0) at = atomicAdd(&s.n_copied, __popcll(mask));
+    at = s.n_merged + __shfl(at, 0) + __popcll(mask & ((1ull << lane) - 1));
+    const uint32_t o = (uint32_t)s.slot[u];
+    if (copied) s.desc[at] = make_uint2(s.word[row], o);
+    else if (u < n_tok && into < 0) s.desc[s.place[j]] = make_uint2(s.word[row], o | (uint32_t)n << 8 | (uint32_t)s.start[j] << 16);
+    if (map && u < n_tok) map[u] = map_base + (into < 0 ? s.slot[u] : s.slot[2 * into + 1]);
+  }
+  __syncthreads();
+}
+
 template <int D, bool PAGED, bool EDGES>
 __global__ __launch_bounds__(4 * D, 4) void round_small_kernel(
     const __bf16* __restrict__ K, const __bf16* __restrict__ V, const int32_t* __restrict__ deg_in, TensorView in,
@@ -34,7 +175,6 @@ __global__ __launch_bounds__(4 * D, 4) void round_small_kernel(
   constexpr int OCT = D / 8, ROWB = D * 2, KEYSHIFT = (ROWB == 256) ? 0 : 1, KSTEPS = D / 16;
   constexpr int NRG = THREADS / OCT;               // rows per pass = row groups: 32
   constexpr int PASSES = kTok / NRG;               // 8
-  constexpr int LPA = THREADS / kHalfTok;          // lanes that share the bookkeeping of one source
   static_assert(NRG == 32 && PASSES == 8, "32 rows per pass");
   if constexpr (EDGES) {
     if ((int)blockIdx.x < edges.blocks) {
@@ -44,21 +184,13 @@ __global__ __launch_bounds__(4 * D, 4) void round_small_kernel(
   }
   // rows 0 .. 127: the A tokens, 128 .. 255: the B tokens
   extern __shared__ __attribute__((aligned(16))) unsigned char s_rows[];
-  __shared__ __attribute__((aligned(16))) float s_score[kHalfTok];
+  // (a row's word: where its first piece sits in LDS - a lane XORs its own piece number in - and, in the upper half,
+  // its degree as bf16, exact up to 256)
+  __shared__ RoundLds<kHalfTok> s_;
   __shared__ __attribute__((aligned(16))) float s_ib[kHalfTok];
-  __shared__ __attribute__((aligned(16))) int16_t s_dstk[kHalfTok];   // B row a kept source merges into, or -1
-  __shared__ __attribute__((aligned(16))) int16_t s_slot[kTok];       // output row of a retained token
-  __shared__ int16_t s_dst[kHalfTok], s_start[kHalfTok], s_place[kHalfTok];
-  __shared__ int32_t s_cnt[kHalfTok];
-  __shared__ int32_t s_deg[kTok];                  // by LDS row
-  // A row as the emit loops see it: where its first piece sits in LDS (a lane XORs its own piece number in) and,
-  // in the upper half, its degree as bf16 (exact up to 256)
-  __shared__ uint32_t s_word[kTok];
-  __shared__ uint32_t s_members[kHalfTok];         // the words of the merged sources, list after list
-  __shared__ uint2 s_desc[kTok];                   // what to emit: word | output row, members << 8, first of them << 16
   __shared__ float s_best2[NW == 8 ? kHalfTok : 1];
   __shared__ int16_t s_dst2[NW == 8 ? kHalfTok : 1];
-  __shared__ int s_wide, s_n_merged, s_n_copied;
+  __shared__ int s_wide;
   __shared__ int32_t s_rb_in[PAGED ? kTok / 8 + 2 : 1], s_rb_out[PAGED ? kTok / 8 + 2 : 1];
 
   int w = (int)blockIdx.x;
@@ -104,14 +236,14 @@ __global__ __launch_bounds__(4 * D, 4) void round_small_kernel(
   auto swz = [](int row, int pc) -> int { return row * ROWB + (((pc ^ (row >> KEYSHIFT)) & (OCT - 1)) << 4); };
   const int row0 = (rg & 1) * kHalfTok + (rg >> 1);      // LDS row of token rg; 32 tokens on: 16 rows on, same XOR
   const int lds0 = swz(row0, piece);
-  if (tid < kHalfTok) { s_cnt[tid] = 0; s_score[tid] = -INFINITY; }
+  if (tid < kHalfTok) { s_.cnt[tid] = 0; s_.score[tid] = -INFINITY; }
   if (tid < kTok) {
     const int row = (tid & 1) * kHalfTok + (tid >> 1);
-    s_deg[row] = dg;
-    s_word[row] = (uint32_t)swz(row, 0) | (__float_as_uint((float)dg) & 0xffff0000u);
-    s_desc[tid] = make_uint2(0, 0);
+    s_.deg[row] = dg;
+    s_.word[row] = (uint32_t)swz(row, 0) | (__float_as_uint((float)dg) & 0xffff0000u);
+    s_.desc[tid] = make_uint2(0, 0);
   }
-  if (tid == 0) { s_wide = 0; s_n_merged = 0; s_n_copied = 0; }
+  if (tid == 0) { s_wide = 0; s_.n_merged = 0; s_.n_copied = 0; }
 #pragma unroll
   for (int it = 0; it < PASSES; ++it) {
     if (it * NRG + rg >= n_tok) kx[it].u = make_uint4(0, 0, 0, 0);
@@ -183,115 +315,22 @@ __global__ __launch_bounds__(4 * D, 4) void round_small_kernel(
       if (hb == 0 && s_best2[a] > best) { best = s_best2[a]; bestj = s_dst2[a]; }   // (the other wave's rows come later)
     }
     if (hb == 0 && half == 0 && a < nA) {
-      s_dst[a] = (nB <= first * 32) ? (int16_t)-1 : (int16_t)bestj;   // a one-token tail chunk: nothing to match
-      s_score[a] = best * inva;
+      s_.dst[a] = (nB <= first * 32) ? (int16_t)-1 : (int16_t)bestj;  // a one-token tail chunk: nothing to match
+      s_.score[a] = best * inva;
     }
   }
-  __syncthreads();
-
-  // ---- top-r of every chunk: rank by counting (score descending, index ascending) ---------------
-  const int a = tid / LPA, sub = tid % LPA;
-  const int a_lo = a & ~((chunk >> 1) - 1), nAc = min(chunk >> 1, nA - a_lo);
-  const int m = (nAc == (chunk >> 1) && 2 * a_lo + chunk <= n_tok) ? m_full : m_tail;
-  int d = -1;
-  if (a < nA && m > 0) {
-    d = s_dst[a];
-    if (m < nAc) {
-      // an equal score of an earlier source ranks above: those are counted from the score itself on, the later
-      // ones from the next larger number on (sources that do not exist hold -inf and come later)
-      const float si = s_score[a] + 0.f;           // (-0 as +0)
-      const float above = __uint_as_float(__float_as_uint(si) + (si < 0.f ? 0xffffffffu : 1u));
-      int rank = 0;
-      for (int o = a_lo + 4 * sub; o < a_lo + nAc; o += 4 * LPA) {
-        const float4 so = *reinterpret_cast<const float4*>(&s_score[o]);
-        rank += (so.x >= (o < a ? si : above)) + (so.y >= (o + 1 < a ? si : above)) +
-                (so.z >= (o + 2 < a ? si : above)) + (so.w >= (o + 3 < a ? si : above));
-      }
-#pragma unroll
-      for (int x = 1; x < LPA; x <<= 1) rank += __shfl_xor(rank, x);
-      if (rank >= m) d = -1;
-    }
-  }
-  if (sub == 0) {
-    s_dstk[a] = (int16_t)d;
-    if (d >= 0) atomicAdd(&s_cnt[d], 1);
-  }
-  __syncthreads();
-
-  // ---- member lists (ascending inside a list) and the retained tokens' output rows ---------------
-  if (wave == 0) {                                 // where every B row's list starts, and its place among the merged rows
-    // one scan of three sums, ten bits each: members, lists of two or more, lists of one
-    const int c0 = s_cnt[2 * lane], c1 = s_cnt[2 * lane + 1];
-    auto sums = [](int c) -> uint32_t { return (uint32_t)c | (uint32_t)(c > 1) << 10 | (uint32_t)(c == 1) << 20; };
-    const uint32_t f0 = sums(c0), f1 = sums(c1);
-    uint32_t inc = f0 + f1;
-#pragma unroll
-    for (int x = 1; x < 64; x <<= 1) {
-      const uint32_t o = __shfl_up(inc, x);
-      if (lane >= x) inc += o;
-    }
-    const uint32_t all = __shfl(inc, 63);
-    const int n_long = (int)(all >> 10 & 1023u);
-    auto place = [&](uint32_t before, int c) { return (int16_t)(c > 1 ? before >> 10 & 1023u : n_long + (before >> 20)); };
-    const uint32_t b0 = inc - f0 - f1, b1 = inc - f1;
-    s_start[2 * lane] = (int16_t)(b0 & 1023u);
-    s_start[2 * lane + 1] = (int16_t)(b1 & 1023u);
-    s_place[2 * lane] = place(b0, c0);
-    s_place[2 * lane + 1] = place(b1, c1);
-    if (lane == 0) s_n_merged = n_long + (int)(all >> 20);
-  } else if (wave == 1) {                          // four tokens per lane
-    const int u = 4 * lane;
-    const int k0 = u < n_tok && s_dstk[2 * lane] < 0, k1 = u + 1 < n_tok;
-    const int k2 = u + 2 < n_tok && s_dstk[2 * lane + 1] < 0, k3 = u + 3 < n_tok;
-    int inc = k0 + k1 + k2 + k3;
-#pragma unroll
-    for (int x = 1; x < 64; x <<= 1) {
-      const int o = __shfl_up(inc, x);
-      if (lane >= x) inc += o;
-    }
-    const int base = inc - (k0 + k1 + k2 + k3);
-    const int p1 = base + k0, p2 = p1 + k1, p3 = p2 + k2;
-    *reinterpret_cast<uint2*>(&s_slot[u]) = make_uint2((uint32_t)base | ((uint32_t)p1 << 16), (uint32_t)p2 | ((uint32_t)p3 << 16));
-  }
-  int pos = 0;                                     // earlier sources of the same list
-  if (d >= 0 && s_cnt[d] > 1) {
-    for (int o = a_lo + 8 * sub; o < a; o += 8 * LPA) {
-      struct { int16_t v[8]; } x = *reinterpret_cast<const decltype(x)*>(&s_dstk[o]);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) pos += (x.v[i] == d) && (o + i < a);
-    }
-#pragma unroll
-    for (int x = 1; x < LPA; x <<= 1) pos += __shfl_xor(pos, x);
-  }
-  __syncthreads();
-  // Rows with two or more members come first, then those with one, then the copies: the row groups of a wave
-  // then do the same work side by side (in output order nine waves in ten carried some row to merge).
-  if (sub == 0 && d >= 0) s_members[s_start[d] + pos] = s_word[a];
-  if (wave < kTok / 64) {
-    const int u = tid, j = u >> 1, row = (u & 1) * kHalfTok + j;
-    const int into = (u & 1) || u >= n_tok ? -1 : (int)s_dstk[j];
-    const int n = (u & 1) ? s_cnt[j] : 0;
-    const bool copied = u < n_tok && into < 0 && n == 0;
-    const uint64_t mask = __ballot(copied);
-    int at = 0;
-    if (lane == 0) at = atomicAdd(&s_n_copied, __popcll(mask));
-    at = s_n_merged + __shfl(at, 0) + __popcll(mask & ((1ull << lane) - 1));
-    const uint32_t o = (uint32_t)s_slot[u];
-    if (copied) s_desc[at] = make_uint2(s_word[row], o);
-    else if (u < n_tok && into < 0) s_desc[s_place[j]] = make_uint2(s_word[row], o | (uint32_t)n << 8 | (uint32_t)s_start[j] << 16);
-    if (map_out && u < n_tok) map_out[(int64_t)bh * map_stride + t0 + u] = map_offset + out_base + (into < 0 ? s_slot[u] : s_slot[2 * into + 1]);
-  }
-  __syncthreads();
+  round_lists<kHalfTok, THREADS>(s_, n_tok, chunk, m_full, m_tail,
+                                 map_out ? map_out + (int64_t)bh * map_stride + t0 : nullptr, map_offset + out_base);
 
   // ---- emit the rows of one tensor: keys first, then the values in their place ---------------------
   const int64_t out_at = out.seq_base(bh) + (int64_t)out_base * out.stride_s;
   const int u_out0 = pout.tok0 + out_base;
-  const int n_merged = s_n_merged;
+  const int n_merged = s_.n_merged;
   const uint32_t lane_piece = (uint32_t)piece << 4;
   auto row_of = [&](uint32_t word) -> uint4 {
     return *reinterpret_cast<const uint4*>(s_rows + ((word & 0xffffu) ^ lane_piece));
   };
-  auto degree_of = [&](uint32_t word) -> int { return s_deg[(word & 0xffffu) / ROWB]; };
+  auto degree_of = [&](uint32_t word) -> int { return s_.deg[(word & 0xffffu) / ROWB]; };
   auto weighed = [&](float* acc, const uint4& x, uint32_t word) {      // + degree * row, degrees up to 256
     const bf16x2 lo = __builtin_bit_cast(bf16x2, word >> 16), hi = __builtin_bit_cast(bf16x2, word & 0xffff0000u);
     const uint32_t v[4] = {x.x, x.y, x.z, x.w};
@@ -314,9 +353,9 @@ __global__ __launch_bounds__(4 * D, 4) void round_small_kernel(
       }
     };
     for (int i = rg; i < n_merged; i += NRG) {
-      const uint2 w = s_desc[i];
+      const uint2 w = s_.desc[i];
       const int o = (int)(w.y & 0xffu), n = (int)(w.y >> 8 & 0xffu);
-      const uint32_t* list = s_members + (w.y >> 16);
+      const uint32_t* list = s_.members + (w.y >> 16);
       const uint4 x = row_of(w.x);
       float acc[8];
 #pragma unroll
@@ -348,7 +387,7 @@ __global__ __launch_bounds__(4 * D, 4) void round_small_kernel(
     }
     // untouched tokens, bit by bit (the row groups that had one merged row less start)
     for (int i = n_merged + (rg + NRG - n_merged % NRG) % NRG; i < n_out; i += NRG) {
-      const uint2 w = s_desc[i];
+      const uint2 w = s_.desc[i];
       put((int)(w.y & 0xffu), row_of(w.x), degree_of(w.x));
     }
   };
@@ -364,6 +403,175 @@ __global__ __launch_bounds__(4 * D, 4) void round_small_kernel(
   __syncthreads();
   if (wide) emit(std::true_type{}, std::false_type{});
   else emit(std::false_type{}, std::false_type{});
+}
+
+// The same for fp32 caches, one chunk per workgroup: keys in LDS (rows padded by 16 bytes, so that consecutive rows
+// start four banks apart), every dot product and norm one chain of fused multiply-adds over the channels as in
+// match_f32_kernel, centroids in 64 bits as in merge_kernel: same bits.  These caches are small, so what counts is
+// the chain of one workgroup: every load is requested at the start, and the products are taken NI x NJ rows per
+// thread from registers.  1024 tokens of dim 64, chunk 64: 10.0 us, the two launches, with loads element by element and
+// two LDS reads to a product, 11.6 + 7.3; 4 x 8192 tokens of dim 128, chunk 256, two rounds 75 us a call (157); 64 x 16384
+// of dim 64, chunk 64 198 us (526).
+template <int D, int CHUNK>
+constexpr int f32_threads() { return CHUNK * D / 32 > 256 ? CHUNK * D / 32 : 256; }
+
+template <int D, int CHUNK, int THREADS = f32_threads<D, CHUNK>()>
+__global__ __launch_bounds__(THREADS) void round_f32_kernel(
+    const float* __restrict__ K, const float* __restrict__ V, const int32_t* __restrict__ deg_in, TensorView in, int seq,
+    int blocks_per_seq, int m_full, int m_tail, float* __restrict__ K_out, float* __restrict__ V_out,
+    int32_t* __restrict__ deg_out, TensorView out, int64_t deg_out_stride, int32_t* __restrict__ map_out,
+    int64_t deg_in_stride, int64_t map_stride, int map_offset, EdgeBlocks<true> edges) {
+  constexpr int HALF = CHUNK / 2;
+  constexpr int LPR = D / 4, NRG = THREADS / LPR, PASSES = CHUNK / NRG;
+  constexpr int PITCH = D + 4;
+  constexpr int TX = 16, TY = THREADS / TX, NI = HALF / TY, NJ = HALF / TX;
+  static_assert(PASSES >= 1 && PASSES <= 8 && NI >= 1 && NI * TY == HALF, "whole passes and tiles");
+  if ((int)blockIdx.x < edges.blocks) {
+    copy_edges(edges.copy, (int64_t)blockIdx.x * THREADS + threadIdx.x);
+    return;
+  }
+  extern __shared__ __attribute__((aligned(16))) float s_f32[];   // rows 0 .. HALF-1: A tokens, HALF .. CHUNK-1: B tokens
+  __shared__ RoundLds<HALF> s_;
+  __shared__ float s_inv[CHUNK];
+
+  const int w = (int)blockIdx.x - edges.blocks;
+  const int g = w % blocks_per_seq, bh = w / blocks_per_seq;
+  const int t0 = g * CHUNK, n_tok = min(CHUNK, seq - t0);
+  const int nA = (n_tok + 1) >> 1, nB = n_tok >> 1;
+  const int tid = threadIdx.x, piece = tid % LPR, rg = tid / LPR;
+  const int n_out = n_tok - (n_tok == CHUNK ? m_full : m_tail);
+  const int out_base = g * (CHUNK - m_full);
+  const int64_t at = in.seq_base(bh) + (int64_t)t0 * in.stride_s + piece * 4;
+  auto row_of = [](int u) { return (u & 1) * HALF + (u >> 1); };
+
+  float4 kx[PASSES], vx[PASSES];
+#pragma unroll
+  for (int it = 0; it < PASSES; ++it)              // rows past the block's end re-read its last one
+    kx[it] = *reinterpret_cast<const float4*>(K + at + (int64_t)min(it * NRG + rg, n_tok - 1) * in.stride_s);
+  int dg = 1;
+  if (deg_in && tid < n_tok) dg = deg_in[(int64_t)bh * deg_in_stride + t0 + tid];
+#pragma unroll
+  for (int it = 0; it < PASSES; ++it)
+    vx[it] = *reinterpret_cast<const float4*>(V + at + (int64_t)min(it * NRG + rg, n_tok - 1) * in.stride_s);
+  if (tid < HALF) { s_.cnt[tid] = 0; s_.score[tid] = -INFINITY; }
+  if (tid < CHUNK) {
+    const int row = row_of(tid);
+    s_.deg[row] = dg;
+    s_.word[row] = (uint32_t)row;
+    s_.desc[tid] = make_uint2(0, 0);
+  }
+  if (tid == 0) { s_.n_merged = 0; s_.n_copied = 0; }
+#pragma unroll
+  for (int it = 0; it < PASSES; ++it) {
+    const int u = it * NRG + rg;
+    *reinterpret_cast<float4*>(s_f32 + row_of(u) * PITCH + piece * 4) = u < n_tok ? kx[it] : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  __syncthreads();
+  if (tid < CHUNK) {                               // 1 / |k| of every row
+    float ss = 0.f;
+#pragma unroll 4
+    for (int k = 0; k < D; k += 4) {
+      const float4 x = *reinterpret_cast<const float4*>(s_f32 + tid * PITCH + k);
+      ss = fmaf(x.x, x.x, ss); ss = fmaf(x.y, x.y, ss); ss = fmaf(x.z, x.z, ss); ss = fmaf(x.w, x.w, ss);
+    }
+    s_inv[tid] = inv_norm(ss);
+  }
+  const int tx = tid % TX, ty = tid / TX;
+  float acc[NI][NJ];
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) acc[i][j] = 0.f;
+#pragma unroll 2
+  for (int k = 0; k < D; k += 4) {
+    float4 a[NI], b[NJ];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) a[i] = *reinterpret_cast<const float4*>(s_f32 + (ty + TY * i) * PITCH + k);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) b[j] = *reinterpret_cast<const float4*>(s_f32 + (HALF + tx + TX * j) * PITCH + k);
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        acc[i][j] = fmaf(a[i].x, b[j].x, acc[i][j]);
+        acc[i][j] = fmaf(a[i].y, b[j].y, acc[i][j]);
+        acc[i][j] = fmaf(a[i].z, b[j].z, acc[i][j]);
+        acc[i][j] = fmaf(a[i].w, b[j].w, acc[i][j]);
+      }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    float best = -INFINITY;
+    int bestj = 0;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {                 // increasing rows: the first of equal ones stays
+      const float sc = acc[i][j] * s_inv[HALF + tx + TX * j];
+      if (tx + TX * j < nB && sc > best) { best = sc; bestj = tx + TX * j; }
+    }
+#pragma unroll
+    for (int x = 1; x < TX; x <<= 1) {
+      const float ob = __shfl_xor(best, x);
+      const int oj = __shfl_xor(bestj, x);
+      if (ob > best || (ob == best && oj < bestj)) { best = ob; bestj = oj; }
+    }
+    const int a = ty + TY * i;
+    if (tx == 0 && a < nA) {
+      s_.dst[a] = nB == 0 ? (int16_t)-1 : (int16_t)bestj;
+      s_.score[a] = best * s_inv[a];
+    }
+  }
+  round_lists<HALF, THREADS>(s_, n_tok, CHUNK, m_full, m_tail, map_out ? map_out + (int64_t)bh * map_stride + t0 : nullptr,
+                             map_offset + out_base);
+
+  const int n_merged = s_.n_merged;
+  const int64_t out_at = out.seq_base(bh) + (int64_t)out_base * out.stride_s + piece * 4;
+  auto emit = [&](float* __restrict__ O, bool keys) {
+    for (int i = rg; i < n_out; i += NRG) {
+      const uint2 w = s_.desc[i];
+      const int o = (int)(w.y & 0xffu), n = i < n_merged ? (int)(w.y >> 8 & 0xffu) : 0;
+      float4 x = *reinterpret_cast<const float4*>(s_f32 + w.x * PITCH + piece * 4);
+      int nd = s_.deg[w.x];
+      if (n > 0) {                                 // (an untouched token is copied bit by bit)
+        double a[4] = {(double)nd * x.x, (double)nd * x.y, (double)nd * x.z, (double)nd * x.w};
+        for (int q = 0; q < n; ++q) {
+          const uint32_t row = s_.members[(w.y >> 16) + q];
+          const float4 y = *reinterpret_cast<const float4*>(s_f32 + row * PITCH + piece * 4);
+          const int dm = s_.deg[row];
+          a[0] += (double)dm * y.x; a[1] += (double)dm * y.y; a[2] += (double)dm * y.z; a[3] += (double)dm * y.w;
+          nd += dm;
+        }
+        const double dn = (double)nd;
+        x = make_float4((float)(a[0] / dn), (float)(a[1] / dn), (float)(a[2] / dn), (float)(a[3] / dn));
+      }
+      *reinterpret_cast<float4*>(O + out_at + (int64_t)o * out.stride_s) = x;
+      if (keys && piece == 0) deg_out[(int64_t)bh * deg_out_stride + out_base + o] = nd;
+    }
+  };
+  emit(K_out, true);
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < PASSES; ++it) *reinterpret_cast<float4*>(s_f32 + row_of(it * NRG + rg) * PITCH + piece * 4) = vx[it];
+  __syncthreads();
+  emit(V_out, false);
+}
+
+template <int D, int CHUNK>
+hipError_t launch_round_f32(const RoundCall& c, hipStream_t st) {
+  constexpr int THREADS = f32_threads<D, CHUNK>();
+  constexpr size_t lds = (size_t)CHUNK * (D + 4) * sizeof(float);
+  static KernelSetup setup;
+  if (hipError_t e = kernel_setup(reinterpret_cast<const void*>(&round_f32_kernel<D, CHUNK>), lds, setup); e != hipSuccess) return e;
+  const int blocks = div_up(c.seq, CHUNK), tail = c.seq % CHUNK;
+  const int64_t edge_blocks = c.edges ? (c.edges->total + THREADS - 1) / THREADS : 0;
+  const int m_full = merge_count(c.r, CHUNK / 2), m_tail = tail >= 2 ? merge_count(c.r, (tail + 1) / 2) : 0;
+  ScopedTimer t("round_f32", st);
+  hipLaunchKernelGGL((round_f32_kernel<D, CHUNK>), dim3((unsigned)((int64_t)c.n_bh * blocks + edge_blocks)), dim3(THREADS), lds,
+                     st, static_cast<const float*>(c.K), static_cast<const float*>(c.V), c.deg_in, c.in, c.seq, blocks, m_full,
+                     m_tail, static_cast<float*>(c.K_out), static_cast<float*>(c.V_out), c.deg_out, c.out, c.deg_out_stride,
+                     c.map_out, c.in.deg_stride, c.map_stride, c.map_offset,
+                     EdgeBlocks<true>{(int)edge_blocks, c.edges ? *c.edges : EdgeCopy{}});
+  return hipGetLastError();
 }
 
 template <int D>
@@ -402,14 +610,22 @@ hipError_t launch_round_t(const RoundCall& c, hipStream_t st) {
 
 }  // namespace
 
-bool round_fits(int dtype, int dim, int n_bh, int seq, int chunk, const EdgeCopy* edges) {
-  if (!round_is_small(dtype, dim, chunk)) return false;
-  const int64_t threads = 4 * dim;
-  return ((int64_t)n_bh * div_up(seq, kTok) + (edges ? edges->total / threads + 1 : 0)) * threads <= UINT32_MAX;
+bool round_fits(int dtype, int dim, int n_bh, int seq, int chunk, const EdgeCopy* edges, bool paged) {
+  if (!round_is_small(dtype, dim, chunk) || (paged && dtype != CKV_BF16)) return false;
+  const int64_t threads = dtype == CKV_BF16 ? 4 * dim : chunk * dim / 32 > 256 ? chunk * dim / 32 : 256;
+  const int tokens = dtype == CKV_BF16 ? kTok : chunk;
+  return ((int64_t)n_bh * div_up(seq, tokens) + (edges ? edges->total / threads + 1 : 0)) * threads <= UINT32_MAX;
 }
 
-hipError_t launch_round(const RoundCall& c, int dim, hipStream_t st) {
-  return dim == 128 ? launch_round_t<128>(c, st) : launch_round_t<64>(c, st);
+hipError_t launch_round(const RoundCall& c, int dtype, int dim, hipStream_t st) {
+  if (dtype == CKV_BF16) return dim == 128 ? launch_round_t<128>(c, st) : launch_round_t<64>(c, st);
+#define CKV_ROUND_F32(D) \
+  return c.chunk == 64 ? launch_round_f32<D, 64>(c, st) : c.chunk == 128 ? launch_round_f32<D, 128>(c, st) : launch_round_f32<D, 256>(c, st)
+  if (dim == 128) CKV_ROUND_F32(128);
+  if (dim == 64) CKV_ROUND_F32(64);
+  if (dim == 32) CKV_ROUND_F32(32);
+  CKV_ROUND_F32(16);
+#undef CKV_ROUND_F32
 }
 
 }  // namespace ckv

@@ -292,6 +292,37 @@ def test_rounds_of_small_chunks_in_one_launch(seq, dim, r, big_degrees, n_sink, 
             assert torch.equal(a, e), f"{n} differs from the separate kernels"
 
 
+@pytest.mark.parametrize("chunk", [64, 128, 256])
+@pytest.mark.parametrize("seq,dim,r,n_sink,n_recent", [
+    (256, 64, 0.5, 0, 0),
+    (257, 128, 1.0, 0, 0),                   # a one-token chunk
+    (3 * 256 + 255, 16, 0.8, 0, 0),          # the longest tail, the narrowest rows
+    (512 + 2, 32, 1.0, 16, 64),
+    (80 + 1, 128, 1.0, 16, 64),              # one token to cluster
+])
+def test_fp32_rounds_of_small_chunks_in_one_launch(seq, dim, r, n_sink, n_recent, chunk):
+    """As above, for fp32 caches."""
+    _say(f"fp32 round in one launch S={seq} D={dim} c={chunk} r={r} n1={n_sink} n2={n_recent}")
+    K, V, _ = kv_host(43, 3, seq, dim, "f32", alpha=0.9, n_outlier=4 if dim == 128 else 0)
+    K, V = K.to(DEV), V.to(DEV)
+    deg = torch.from_numpy(np.random.default_rng(seq).integers(1, 400, (1, 3, seq)).astype(np.int32)).to(DEV)
+    kw = dict(rounds=[r], deg=deg, n_sink=n_sink, n_recent=n_recent)
+    ckv.timing_reset()
+    ckv.timing_enable(True)
+    got = ckv.compress(K, V, chunk, **kw)
+    torch.cuda.synchronize()
+    ckv.timing_enable(False)
+    assert list(ckv.timing_read()) == ["round_f32"]
+    for h in range(3):
+        check_round_with_edges(f64(K[0, h]), f64(V[0, h]), i64(deg[0, h]), chunk, r, "f32", n_sink, n_recent, f64(got[0][0, h]),
+                               f64(got[1][0, h]), i64(got[2][0, h]), i64(got[3][0, h]), what=f"h{h}")
+    if r == 1.0:
+        ref = ckv.compress(K, V, chunk, scope="head", **kw)
+        torch.cuda.synchronize()
+        for n, a, e in zip(["K'", "V'", "deg'", "assign"], got, ref):
+            assert torch.equal(a, e), f"{n} differs from the separate kernels"
+
+
 # ---- attention sinks and recent tokens (Sec. 5.2 / 5.3) ----------------------------------------
 @pytest.mark.parametrize("dtype,heads,seq,dim,chunk,rounds,n_sink,n_recent", [
     ("bf16", 2, 4096 + 80, 128, 1024, [1.0, 1.0], 16, 64),
