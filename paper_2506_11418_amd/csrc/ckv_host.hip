@@ -83,14 +83,19 @@ int seq_after_round(int len, int chunk, float r, int n_sink, int n_recent, int s
 // values of 2*chunk original tokens) to fill the chip: from about 4 per CU on MI355X (measured
 // crossover at 1024 chunks); smaller jobs run every round in full unless the caller's flags say
 // otherwise.  Nor do chunks whose round is one launch (round_is_small): that launch reads and writes values at
-// the rate of a copy, while a pair's second round gathers them (two rounds at r = 1, dim 128, pair / full, us:
-// 64 x 32768 tokens, chunk 256 553 / 431, chunk 64 688 / 420; 256 x 65536, chunk 256 4146 / 3465).
+// the rate of a copy, while a pair's second round gathers them (two rounds at r = 1, pair / full, us: dim 128, 64 x 32768
+// tokens, chunk 256 553 / 431, chunk 64 688 / 420; 256 x 65536, chunk 256 4146 / 3465; dim 64, 64 x 32768, chunk 512 339 /
+// 273) - unless one workgroup's rows fill a CU's LDS, where the pair wins from about 1536 chunks on (dim 128, chunk 512,
+// 32768 tokens: 40 sequences 403 / 377, 48 445 / 451, 64 554 / 586; dim 64, chunk 1024: 32 x 65536 417 / 407, 128 x 65536
+// 1512 / 1542).
 enum RoundMode { ROUND_FULL = 0, ROUND_KEYS_ONLY = 1, ROUND_ORIGIN = 2 };
-constexpr int64_t kDeferMinChunks = 1024;
+constexpr int64_t kDeferMinChunks = 1024, kDeferMinChunksFullLds = 1536;
 
 void plan_routes(const ckv_layout* in, const ckv_params* p, const ckv_plan_t* plan, RoundMode (&mode)[CKV_MAX_ROUNDS]) {
   const int64_t n_bh = (int64_t)in->batch * in->heads;
   const bool allow = !(p->flags & CKV_ROUTE_FULL_ROUNDS), force = (p->flags & CKV_ROUTE_DEFER_ALWAYS) != 0;
+  const bool one_launch = in->dtype == CKV_BF16 && round_is_small(in->dtype, in->dim, p->chunk);
+  const int64_t worth = !one_launch ? kDeferMinChunks : p->chunk * in->dim == 65536 ? kDeferMinChunksFullLds : INT64_MAX;
   for (int j = 0; j < CKV_MAX_ROUNDS; ++j) mode[j] = ROUND_FULL;
   for (int j = 0; j + 1 < plan->n_rounds; ++j) {
     int lo, hi;
@@ -99,8 +104,7 @@ void plan_routes(const ckv_layout* in, const ckv_params* p, const ckv_plan_t* pl
     clusterable(plan->round_len[j + 1], p->n_sink, p->n_recent, &lo2, &hi2);
     const bool pair = allow && (j == 0 || j + 2 == plan->n_rounds) && plan->round_r[j] == 1.0f &&
                       p->scope == CKV_SCOPE_CHUNK && hi > lo && hi2 > lo2 &&
-                      (force || (!(in->dtype == CKV_BF16 && round_is_small(in->dtype, in->dim, p->chunk)) &&
-                                 n_bh * div_up(plan->round_len[j + 1], p->chunk) >= kDeferMinChunks));
+                      (force || n_bh * div_up(plan->round_len[j + 1], p->chunk) >= worth);
     if (pair) {
       mode[j] = ROUND_KEYS_ONLY;
       mode[j + 1] = ROUND_ORIGIN;

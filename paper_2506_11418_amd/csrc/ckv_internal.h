@@ -128,6 +128,8 @@ struct RoundCall {
   const EdgeCopy* edges;       // copied by the same launch, or NULL
 };
 inline bool round_is_small(int dtype, int dim, int chunk) {
+  // one chunk's rows in a workgroup's LDS
+  if (dtype == CKV_BF16 && ((chunk == 512 && (dim == 64 || dim == 128)) || (chunk == 1024 && dim == 64))) return true;
   return (dim == 64 || dim == 128 || (dtype == CKV_F32 && (dim == 16 || dim == 32))) &&
          (chunk == 64 || chunk == 128 || chunk == 256);
 }

@@ -1,10 +1,11 @@
-// One clustering round of small chunks (64, 128 or 256 tokens, bf16) in one launch: similarity, matching,
-// top-r, merge and compaction (Sec. 5.2 - 5.3) of 256 consecutive tokens per workgroup.
+// One clustering round in one launch, for chunks whose rows fit the LDS: similarity, matching, top-r, merge and
+// compaction (Sec. 5.2 - 5.3).  bf16: 256 consecutive tokens per workgroup for chunks of 64, 128 or 256, one chunk of 512
+// tokens or, at dim 64, of 1024.
 //
 // The block's keys and values are read once, in order, and written once, in order: the key rows are parked
 // in LDS, where the similarity tiles, the merge and the compaction read them; the value rows are requested
 // together with them, wait in registers while the matching runs, and take the keys' place in LDS once these
-// have been emitted.  A launch pair of match_small_bf16_kernel and merge_kernel reads the keys twice, gathers
+// have been emitted.  A launch pair of a match kernel and merge_kernel reads the keys twice, gathers
 // the rows of both tensors from memory behind LDS lookups and passes the matching through memory.
 // Same operand order, norms, fold, member order and rounding as those two: same bits.
 //
@@ -12,7 +13,11 @@
 // in 1603 us = 5.7 TB/s, nine tenths of the chip's copy rate; two launches a round took 2283), small ones the
 // chain of one workgroup: request 1.0 us, keys 1.8, similarity 2.2, ranking and lists 2.8, keys out 2.9, values
 // in and out 2.8 (8 x 8448 tokens, 21.6 us a call; two launches 35.4).  Two workgroups per CU: 64 KiB of rows
-// each, and 128 registers, 32 of them the waiting values.
+// each, and 128 registers, 32 of them the waiting values.  Whole chunks (us a call, two launches a round / one): dim 128,
+// chunk 512: 8 x 8448 tokens, r = 0.8 40.0 / 25.2, 64 x 50003, annealed 2176 / 2011 (one workgroup per CU: 128 KiB of
+// rows); dim 64: chunk 512, 64 x 32768, two rounds 355 / 269, chunk 1024, 8 x 40000 88.4 / 64.9.  Chunks of 1024 at dim
+// 128 do not fit; holding the B rows in registers instead and each tensor's halves in turn was slower than two launches
+// (256 x 131072, two rounds 10.2 ms against 9.7): one workgroup per CU ends up in a chain of 54 us a chunk.
 #include <type_traits>
 
 #include "ckv_internal.h"
@@ -21,7 +26,8 @@
 namespace ckv {
 namespace {
 
-constexpr int kTok = 256, kHalfTok = kTok / 2;   // tokens, and A (= B) rows, of a workgroup
+constexpr int kTok = 256;        // tokens of a workgroup that takes chunks of up to as many
+constexpr uint32_t kPlace = 0x1ffffu;
 
 // The bookkeeping of a block of up to HALF sources and HALF destinations (rows of LDS 0 .. HALF-1 and HALF .. 2 HALF-1;
 // token u is row (u & 1) * HALF + u / 2): which edges are kept, who merges into whom, where everything goes.
@@ -35,9 +41,15 @@ struct RoundLds {
   int32_t deg[2 * HALF];       // by row
   uint32_t word[2 * HALF];     // a row as the emit loops see it (the kernel's own encoding)
   uint32_t members[HALF];      // the words of the merged sources, list after list, ascending inside a list
-  uint2 desc[2 * HALF];        // what to emit: word | output row, members << 8, first of them << 16
-  int n_merged, n_copied;
+  uint2 desc[2 * HALF];        // what to emit: word | output row, members << 10, first of them << 20
+  int n_merged, n_copied, sel[2];
 };
+
+// an order-preserving integer image of a score: greater is greater, -0 as +0
+__device__ __forceinline__ uint32_t ordered(float x) {
+  const uint32_t u = __float_as_uint(x + 0.f);
+  return u ^ ((u >> 31) ? 0xffffffffu : 0x80000000u);
+}
 
 // In: score, dst (-1: nothing to merge into), deg and word of every row; cnt, desc, n_merged, n_copied zero, scores of
 // sources that do not exist -inf.  Chunks of `chunk` tokens, the last one of the block possibly short: m_full / m_tail
@@ -58,7 +70,7 @@ __device__ __forceinline__ void round_lists(RoundLds<HALF>& s, int n_tok, int ch
   int d = -1;
   if (a < nA && m > 0) {
     d = s.dst[a];
-    if (m < nAc) {
+    if (HALF <= 128 && m < nAc) {
       // an equal score of an earlier source ranks above: those are counted from the score itself on, the later
       // ones from the next larger number on (sources that do not exist hold -inf and come later)
       const float si = s.score[a] + 0.f;           // (-0 as +0)
@@ -72,6 +84,51 @@ __device__ __forceinline__ void round_lists(RoundLds<HALF>& s, int n_tok, int ch
 #pragma unroll
       for (int x = 1; x < LPA; x <<= 1) rank += __shfl_xor(rank, x);
       if (rank >= m) d = -1;
+    }
+  }
+  if constexpr (HALF > 128) {
+    // one chunk: the key of its m-th best edge by a radix select, equal ones by position (ranks by counting grow with
+    // the square: 512 sources take 4 us of the vector units)
+    if (m > 0 && m < nAc) {
+      uint32_t* histogram = s.members;             // (not in use yet)
+      const uint32_t key = a < nA ? ordered(s.score[a]) : 0u;
+      uint32_t cut = 0;
+      int left = m, equal = 0;
+#pragma unroll 1
+      for (int shift = 24; shift >= 0; shift -= 8) {
+        if (tid < 256) histogram[tid] = 0;
+        __syncthreads();
+        if (sub == 0 && d >= 0 && (shift == 24 || (key ^ cut) >> (shift + 8) == 0)) atomicAdd(&histogram[key >> shift & 255u], 1u);
+        __syncthreads();
+        if (wave == 0) {                           // lane l: bins 255 - 4l downwards
+          int c[4], sum = 0;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) sum += c[e] = (int)histogram[255 - 4 * lane - e];
+          int inc = sum;
+#pragma unroll
+          for (int x = 1; x < 64; x <<= 1) {
+            const int o = __shfl_up(inc, x);
+            if (lane >= x) inc += o;
+          }
+          int above = inc - sum;
+          if (above < left && inc >= left) {       // the bin of the left-th largest is one of this lane's
+            int e = 0;
+            while (e < 3 && above + c[e] < left) above += c[e++];
+            s.sel[0] = (255 - 4 * lane - e) | c[e] << 8;
+            s.sel[1] = left - above;
+          }
+        }
+        __syncthreads();
+        cut |= (uint32_t)(s.sel[0] & 255) << shift;
+        equal = s.sel[0] >> 8;
+        left = s.sel[1];
+      }
+      if (d >= 0 && key <= cut) {
+        int earlier = 0;
+        if (key == cut && left < equal)
+          for (int o = 0; o < a; ++o) earlier += ordered(s.score[o]) == cut;
+        if (key < cut || earlier >= left) d = -1;
+      }
     }
   }
   if (sub == 0) {
@@ -134,7 +191,14 @@ __device__ __forceinline__ void round_lists(RoundLds<HALF>& s, int n_tok, int ch
     }
   }
   int pos = 0;                                     // earlier sources of the same list
-  if (d >= 0 && s.cnt[d] > 1) {
+  if (HALF > 128) {
+    // slots handed out by atomics (in the descriptors' place, still zero) and every short list sorted below, so that no
+    // atomic decides an order; lists beyond eight (degenerate inputs) are placed by counting
+    if (sub == 0 && d >= 0 && s.cnt[d] > 1) {
+      if (s.cnt[d] <= 8) pos = (int)atomicAdd(&s.desc[d].x, 1u);
+      else for (int o = 0; o < a; ++o) pos += s.kept[o] == d;
+    }
+  } else if (d >= 0 && s.cnt[d] > 1) {
     for (int o = a_lo + 8 * sub; o < a; o += 8 * LPA) {
       struct { int16_t v[8]; } x = *reinterpret_cast<const decltype(x)*>(&s.kept[o]);
 #pragma unroll
@@ -158,46 +222,67 @@ __device__ __forceinline__ void round_lists(RoundLds<HALF>& s, int n_tok, int ch
     at = s.n_merged + __shfl(at, 0) + __popcll(mask & ((1ull << lane) - 1));
     const uint32_t o = (uint32_t)s.slot[u];
     if (copied) s.desc[at] = make_uint2(s.word[row], o);
-    else if (u < n_tok && into < 0) s.desc[s.place[j]] = make_uint2(s.word[row], o | (uint32_t)n << 8 | (uint32_t)s.start[j] << 16);
+    else if (u < n_tok && into < 0) s.desc[s.place[j]] = make_uint2(s.word[row], o | (uint32_t)n << 10 | (uint32_t)s.start[j] << 20);
     if (map && u < n_tok) map[u] = map_base + (into < 0 ? s.slot[u] : s.slot[2 * into + 1]);
   }
   __syncthreads();
+  if constexpr (HALF > 128) {
+    const int n = tid < HALF ? s.cnt[tid] : 0;
+    if (n > 1 && n <= 8) {
+      uint32_t* list = &s.members[s.start[tid]];   // (a word's place in LDS, its low 17 bits, grows with the row)
+      for (int x = 1; x < n; ++x) {
+        const uint32_t v = list[x];
+        int y = x - 1;
+        while (y >= 0 && (list[y] & kPlace) > (v & kPlace)) { list[y + 1] = list[y]; --y; }
+        list[y + 1] = v;
+      }
+    }
+    __syncthreads();
+  }
 }
 
-template <int D, bool PAGED, bool EDGES>
-__global__ __launch_bounds__(4 * D, 4) void round_small_kernel(
+// A lane's value as if it were new: what is worked out from it is then not kept in registers around a loop.
+__device__ __forceinline__ int lane_anew(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// TOK: tokens of a workgroup; above kTok its one chunk.
+template <int D, int TOK, bool PAGED, bool EDGES>
+__global__ __launch_bounds__(TOK * D / 64, 4) void round_small_kernel(
     const __bf16* __restrict__ K, const __bf16* __restrict__ V, const int32_t* __restrict__ deg_in, TensorView in,
     int seq, int chunk, int blocks_per_seq, int m_full, int m_tail, __bf16* __restrict__ K_out,
     __bf16* __restrict__ V_out, int32_t* __restrict__ deg_out, TensorView out, int64_t deg_out_stride,
     int32_t* __restrict__ map_out, int64_t deg_in_stride, int64_t map_stride, int map_offset, PagedSide pin,
     PagedSide pout, int out_k_paged, int out_v_paged, EdgeBlocks<EDGES> edges) {
-  constexpr int THREADS = 4 * D, NW = THREADS / 64;
+  constexpr int THREADS = TOK * D / 64, HALF = TOK / 2;
+  constexpr int WPT = THREADS / 64 / (HALF / 32);  // waves per 32-row tile of sources: 2 or 1
   constexpr int OCT = D / 8, ROWB = D * 2, KEYSHIFT = (ROWB == 256) ? 0 : 1, KSTEPS = D / 16;
-  constexpr int NRG = THREADS / OCT;               // rows per pass = row groups: 32
-  constexpr int PASSES = kTok / NRG;               // 8
-  static_assert(NRG == 32 && PASSES == 8, "32 rows per pass");
+  constexpr int NRG = THREADS / OCT;               // rows per pass = row groups
+  constexpr int PASSES = TOK / NRG;
+  static_assert(PASSES == 8 && NRG % 32 == 0 && TOK * ROWB <= 1 << 17, "whole swizzle periods, places of 17 bits");
   if constexpr (EDGES) {
     if ((int)blockIdx.x < edges.blocks) {
       copy_edges(edges.copy, (int64_t)blockIdx.x * THREADS + threadIdx.x);
       return;
     }
   }
-  // rows 0 .. 127: the A tokens, 128 .. 255: the B tokens
+  // rows 0 .. HALF-1: the A tokens, the others: the B tokens
   extern __shared__ __attribute__((aligned(16))) unsigned char s_rows[];
-  // (a row's word: where its first piece sits in LDS - a lane XORs its own piece number in - and, in the upper half,
-  // its degree as bf16, exact up to 256)
-  __shared__ RoundLds<kHalfTok> s_;
-  __shared__ __attribute__((aligned(16))) float s_ib[kHalfTok];
-  __shared__ float s_best2[NW == 8 ? kHalfTok : 1];
-  __shared__ int16_t s_dst2[NW == 8 ? kHalfTok : 1];
+  // (a row's word: where its first piece sits in LDS - a lane XORs its own piece number in - and above those 17 bits
+  // its degree as bf16, exact up to 256; a positive number has 15)
+  __shared__ RoundLds<HALF> s_;
+  __shared__ __attribute__((aligned(16))) float s_ib[HALF];
+  __shared__ float s_best2[WPT == 2 ? HALF : 1];
+  __shared__ int16_t s_dst2[WPT == 2 ? HALF : 1];
   __shared__ int s_wide;
-  __shared__ int32_t s_rb_in[PAGED ? kTok / 8 + 2 : 1], s_rb_out[PAGED ? kTok / 8 + 2 : 1];
+  __shared__ int32_t s_rb_in[PAGED ? TOK / 8 + 2 : 1], s_rb_out[PAGED ? TOK / 8 + 2 : 1];
 
   int w = (int)blockIdx.x;
   if constexpr (EDGES) w -= edges.blocks;
   const int sb = w % blocks_per_seq, bh = w / blocks_per_seq;
-  const int t0 = sb * kTok;
-  const int n_tok = min(kTok, seq - t0);
+  const int t0 = sb * TOK;
+  const int n_tok = min(TOK, seq - t0);
   const int nA = (n_tok + 1) >> 1, nB = n_tok >> 1;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int piece = tid % OCT, rg = tid / OCT;
@@ -234,13 +319,13 @@ __global__ __launch_bounds__(4 * D, 4) void round_small_kernel(
   for (int it = 0; it < PASSES; ++it) vx[it] = ldg16_stream(Vp + row_at(it * NRG + rg));
 
   auto swz = [](int row, int pc) -> int { return row * ROWB + (((pc ^ (row >> KEYSHIFT)) & (OCT - 1)) << 4); };
-  const int row0 = (rg & 1) * kHalfTok + (rg >> 1);      // LDS row of token rg; 32 tokens on: 16 rows on, same XOR
+  const int row0 = (rg & 1) * HALF + (rg >> 1);      // LDS row of token rg; 32 tokens on: 16 rows on, same XOR
   const int lds0 = swz(row0, piece);
-  if (tid < kHalfTok) { s_.cnt[tid] = 0; s_.score[tid] = -INFINITY; }
-  if (tid < kTok) {
-    const int row = (tid & 1) * kHalfTok + (tid >> 1);
+  if (tid < HALF) { s_.cnt[tid] = 0; s_.score[tid] = -INFINITY; }
+  if (tid < TOK) {
+    const int row = (tid & 1) * HALF + (tid >> 1);
     s_.deg[row] = dg;
-    s_.word[row] = (uint32_t)swz(row, 0) | (__float_as_uint((float)dg) & 0xffff0000u);
+    s_.word[row] = (uint32_t)swz(row, 0) | (__float_as_uint((float)dg) & 0x7fff0000u) << 1;
     s_.desc[tid] = make_uint2(0, 0);
   }
   if (tid == 0) { s_wide = 0; s_.n_merged = 0; s_.n_copied = 0; }
@@ -252,15 +337,15 @@ __global__ __launch_bounds__(4 * D, 4) void round_small_kernel(
     if (piece == 0 && (rg & 1)) s_ib[it * (NRG / 2) + (rg >> 1)] = inv_norm(ss);
   }
   __syncthreads();
-  if (tid < kTok && dg > 256) s_wide = 1;
+  if (tid < TOK && dg > 256) s_wide = 1;
 
   // ---- similarity and matching: a 32-row tile of sources against the tiles of its own chunk -------
   const int half = lane >> 5, col = lane & 31;
   {
     const int wv = __builtin_amdgcn_readfirstlane(wave);
-    const int at = (NW == 8) ? wv >> 1 : wv, hb = (NW == 8) ? wv & 1 : 0;
-    const int tpc = chunk >> 6, first = at & -tpc;                         // tiles per chunk (1, 2 or 4); its first tile
-    const int lo = (NW == 8) ? (hb * tpc + 1) / 2 : 0, hi = (NW == 8 && hb == 0) ? (tpc + 1) / 2 : tpc;
+    const int at = wv / WPT, hb = wv % WPT;
+    const int tpc = chunk >> 6, first = at & -tpc;                         // tiles per chunk (a power of two); its first tile
+    const int lo = WPT == 2 ? (hb * tpc + 1) / 2 : 0, hi = WPT == 2 && hb == 0 ? (tpc + 1) / 2 : tpc;
     float best = -INFINITY, inva = 0.f;
     int bestj = 0;
     if (at * 32 < nA && lo < hi) {                 // (the same for the whole wave)
@@ -276,13 +361,13 @@ __global__ __launch_bounds__(4 * D, 4) void round_small_kernel(
         for (int c = 0; c < C; ++c) acc[c] = f32x16{0};
 #pragma unroll
         for (int s = 0; s < KSTEPS; ++s) {
-          const int off = swz(col, 2 * s + half);
+          const int off = swz(TOK == 256 ? col : lane_anew(col), 2 * s + half);
           Piece afrag;
           afrag.u = *reinterpret_cast<const uint4*>(s_rows + at * 32 * ROWB + off);
 #pragma unroll
           for (int c = 0; c < C; ++c)
             acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-                *reinterpret_cast<const bf16x8*>(s_rows + (kHalfTok + (first + tt + c) * 32) * ROWB + off), afrag.v, acc[c],
+                *reinterpret_cast<const bf16x8*>(s_rows + (HALF + (first + tt + c) * 32) * ROWB + off), afrag.v, acc[c],
                 0, 0, 0);
           ss += sumsq8(afrag);
           // (operands requested further ahead, or kept for the sum, push the values into scratch)
@@ -302,14 +387,19 @@ __global__ __launch_bounds__(4 * D, 4) void round_small_kernel(
       };
       if (hi - lo == 1) tiles(std::integral_constant<int, 1>{}, lo);
       else tiles(std::integral_constant<int, 2>{}, lo);
-      if (NW == 4 && hi - lo == 4) tiles(std::integral_constant<int, 2>{}, lo + 2);
+      if constexpr (TOK == 256) {                  // (at most four; a loop would keep sixteen offsets for both)
+        if (WPT == 1 && hi - lo == 4) tiles(std::integral_constant<int, 2>{}, lo + 2);
+      } else {
+#pragma unroll 1
+        for (int tt = lo + 2; tt < hi; tt += 2) tiles(std::integral_constant<int, 2>{}, tt);
+      }
       inva = inv_norm(ss + __shfl_xor(ss, 32));
       const float ob = __shfl_xor(best, 32);
       const int oj = __shfl_xor(bestj, 32);
       if (ob > best || (ob == best && oj < bestj)) { best = ob; bestj = oj; }
     }
     const int a = at * 32 + col;
-    if (NW == 8) {
+    if (WPT == 2) {
       if (hb == 1 && half == 0) { s_best2[a] = best; s_dst2[a] = (int16_t)bestj; }
       __syncthreads();
       if (hb == 0 && s_best2[a] > best) { best = s_best2[a]; bestj = s_dst2[a]; }   // (the other wave's rows come later)
@@ -319,7 +409,7 @@ __global__ __launch_bounds__(4 * D, 4) void round_small_kernel(
       s_.score[a] = best * inva;
     }
   }
-  round_lists<kHalfTok, THREADS>(s_, n_tok, chunk, m_full, m_tail,
+  round_lists<HALF, THREADS>(s_, n_tok, chunk, m_full, m_tail,
                                  map_out ? map_out + (int64_t)bh * map_stride + t0 : nullptr, map_offset + out_base);
 
   // ---- emit the rows of one tensor: keys first, then the values in their place ---------------------
@@ -328,11 +418,12 @@ __global__ __launch_bounds__(4 * D, 4) void round_small_kernel(
   const int n_merged = s_.n_merged;
   const uint32_t lane_piece = (uint32_t)piece << 4;
   auto row_of = [&](uint32_t word) -> uint4 {
-    return *reinterpret_cast<const uint4*>(s_rows + ((word & 0xffffu) ^ lane_piece));
+    return *reinterpret_cast<const uint4*>(s_rows + ((word & kPlace) ^ lane_piece));
   };
-  auto degree_of = [&](uint32_t word) -> int { return s_.deg[(word & 0xffffu) / ROWB]; };
+  auto degree_of = [&](uint32_t word) -> int { return s_.deg[(word & kPlace) / ROWB]; };
   auto weighed = [&](float* acc, const uint4& x, uint32_t word) {      // + degree * row, degrees up to 256
-    const bf16x2 lo = __builtin_bit_cast(bf16x2, word >> 16), hi = __builtin_bit_cast(bf16x2, word & 0xffff0000u);
+    const uint32_t w = word >> 17;
+    const bf16x2 lo = __builtin_bit_cast(bf16x2, w), hi = __builtin_bit_cast(bf16x2, w << 16);
     const uint32_t v[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -354,8 +445,8 @@ __global__ __launch_bounds__(4 * D, 4) void round_small_kernel(
     };
     for (int i = rg; i < n_merged; i += NRG) {
       const uint2 w = s_.desc[i];
-      const int o = (int)(w.y & 0xffu), n = (int)(w.y >> 8 & 0xffu);
-      const uint32_t* list = s_.members + (w.y >> 16);
+      const int o = (int)(w.y & 1023u), n = (int)(w.y >> 10 & 1023u);
+      const uint32_t* list = s_.members + (w.y >> 20);
       const uint4 x = row_of(w.x);
       float acc[8];
 #pragma unroll
@@ -371,16 +462,16 @@ __global__ __launch_bounds__(4 * D, 4) void round_small_kernel(
         }
         put(o, round_div_pack_bf16(acc, nd), nd);
       } else {
-        float nd = __uint_as_float(w.x & 0xffff0000u);
+        float nd = __uint_as_float(w.x >> 17 << 16);
         uint32_t wm = list[0];
         weighed(acc, x, w.x);
         weighed(acc, row_of(wm), wm);
-        nd += __uint_as_float(wm & 0xffff0000u);
+        nd += __uint_as_float(wm >> 17 << 16);
 #pragma unroll 1
         for (int q = 1; q < n; ++q) {
           wm = list[q];
           weighed(acc, row_of(wm), wm);
-          nd += __uint_as_float(wm & 0xffff0000u);
+          nd += __uint_as_float(wm >> 17 << 16);
         }
         put(o, round_div_pack_bf16(acc, nd), (int)nd);
       }
@@ -388,7 +479,7 @@ __global__ __launch_bounds__(4 * D, 4) void round_small_kernel(
     // untouched tokens, bit by bit (the row groups that had one merged row less start)
     for (int i = n_merged + (rg + NRG - n_merged % NRG) % NRG; i < n_out; i += NRG) {
       const uint2 w = s_.desc[i];
-      put((int)(w.y & 0xffu), row_of(w.x), degree_of(w.x));
+      put((int)(w.y & 1023u), row_of(w.x), degree_of(w.x));
     }
   };
   const bool wide = s_wide != 0;
@@ -529,13 +620,13 @@ __global__ __launch_bounds__(THREADS) void round_f32_kernel(
   auto emit = [&](float* __restrict__ O, bool keys) {
     for (int i = rg; i < n_out; i += NRG) {
       const uint2 w = s_.desc[i];
-      const int o = (int)(w.y & 0xffu), n = i < n_merged ? (int)(w.y >> 8 & 0xffu) : 0;
+      const int o = (int)(w.y & 1023u), n = i < n_merged ? (int)(w.y >> 10 & 1023u) : 0;
       float4 x = *reinterpret_cast<const float4*>(s_f32 + w.x * PITCH + piece * 4);
       int nd = s_.deg[w.x];
       if (n > 0) {                                 // (an untouched token is copied bit by bit)
         double a[4] = {(double)nd * x.x, (double)nd * x.y, (double)nd * x.z, (double)nd * x.w};
         for (int q = 0; q < n; ++q) {
-          const uint32_t row = s_.members[(w.y >> 16) + q];
+          const uint32_t row = s_.members[(w.y >> 20) + q];
           const float4 y = *reinterpret_cast<const float4*>(s_f32 + row * PITCH + piece * 4);
           const int dm = s_.deg[row];
           a[0] += (double)dm * y.x; a[1] += (double)dm * y.y; a[2] += (double)dm * y.z; a[3] += (double)dm * y.w;
@@ -574,11 +665,11 @@ hipError_t launch_round_f32(const RoundCall& c, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <int D>
+template <int D, int TOK>
 hipError_t launch_round_t(const RoundCall& c, hipStream_t st) {
-  constexpr int THREADS = 4 * D;
-  constexpr size_t lds = (size_t)kTok * D * 2;
-  const int blocks = div_up(c.seq, kTok);
+  constexpr int THREADS = TOK * D / 64;
+  constexpr size_t lds = (size_t)TOK * D * 2;
+  const int blocks = div_up(c.seq, TOK);
   const int64_t total = (int64_t)c.n_bh * blocks;
   const int64_t edge_blocks = c.edges ? (c.edges->total + THREADS - 1) / THREADS : 0;
   const int nA_tail = (c.seq % c.chunk + 1) / 2;
@@ -588,10 +679,10 @@ hipError_t launch_round_t(const RoundCall& c, hipStream_t st) {
 #define CKV_ROUND(PG, ED, ...)                                                                                  \
   do {                                                                                                          \
     static KernelSetup setup;                                                                                   \
-    if (hipError_t e = kernel_setup(reinterpret_cast<const void*>(&round_small_kernel<D, PG, ED>), lds, setup); \
+    if (hipError_t e = kernel_setup(reinterpret_cast<const void*>(&round_small_kernel<D, TOK, PG, ED>), lds, setup); \
         e != hipSuccess)                                                                                        \
       return e;                                                                                                 \
-    hipLaunchKernelGGL((round_small_kernel<D, PG, ED>), dim3((unsigned)(total + edge_blocks)), dim3(THREADS), lds, st, \
+    hipLaunchKernelGGL((round_small_kernel<D, TOK, PG, ED>), dim3((unsigned)(total + edge_blocks)), dim3(THREADS), lds, st, \
                        static_cast<const __bf16*>(c.K), static_cast<const __bf16*>(c.V), c.deg_in, c.in, c.seq, c.chunk, \
                        blocks, m_full, m_tail, static_cast<__bf16*>(c.K_out), static_cast<__bf16*>(c.V_out), c.deg_out,  \
                        c.out, c.deg_out_stride, c.map_out, c.in.deg_stride, c.map_stride, c.map_offset, c.pin, pout,     \
@@ -612,13 +703,17 @@ hipError_t launch_round_t(const RoundCall& c, hipStream_t st) {
 
 bool round_fits(int dtype, int dim, int n_bh, int seq, int chunk, const EdgeCopy* edges, bool paged) {
   if (!round_is_small(dtype, dim, chunk) || (paged && dtype != CKV_BF16)) return false;
-  const int64_t threads = dtype == CKV_BF16 ? 4 * dim : chunk * dim / 32 > 256 ? chunk * dim / 32 : 256;
-  const int tokens = dtype == CKV_BF16 ? kTok : chunk;
+  const int tokens = dtype == CKV_BF16 && chunk < kTok ? kTok : chunk;
+  const int64_t threads = dtype == CKV_BF16 ? tokens * dim / 64 : chunk * dim / 32 > 256 ? chunk * dim / 32 : 256;
   return ((int64_t)n_bh * div_up(seq, tokens) + (edges ? edges->total / threads + 1 : 0)) * threads <= UINT32_MAX;
 }
 
 hipError_t launch_round(const RoundCall& c, int dtype, int dim, hipStream_t st) {
-  if (dtype == CKV_BF16) return dim == 128 ? launch_round_t<128>(c, st) : launch_round_t<64>(c, st);
+  if (dtype == CKV_BF16) {
+    if (dim == 128) return c.chunk == 512 ? launch_round_t<128, 512>(c, st) : launch_round_t<128, 256>(c, st);
+    return c.chunk == 1024 ? launch_round_t<64, 1024>(c, st) : c.chunk == 512 ? launch_round_t<64, 512>(c, st)
+                                                                              : launch_round_t<64, 256>(c, st);
+  }
 #define CKV_ROUND_F32(D) \
   return c.chunk == 64 ? launch_round_f32<D, 64>(c, st) : c.chunk == 128 ? launch_round_f32<D, 128>(c, st) : launch_round_f32<D, 256>(c, st)
   if (dim == 128) CKV_ROUND_F32(128);

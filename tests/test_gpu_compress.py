@@ -292,6 +292,43 @@ def test_rounds_of_small_chunks_in_one_launch(seq, dim, r, big_degrees, n_sink, 
             assert torch.equal(a, e), f"{n} differs from the separate kernels"
 
 
+@pytest.mark.parametrize("chunk,dim", [(512, 128), (512, 64), (1024, 64)])
+@pytest.mark.parametrize("whole,tail,r,directions", [
+    (1, 0, 0.8, 0),
+    (2, 1, 1.0, 0),              # a one-token chunk
+    (1, 509, 0.3, 0),            # the first rows of the last tile masked
+    (0, 33, 1.0, 0),             # a short chunk alone
+    (1, 300, 0.6, 5),            # keys of five directions: lists far beyond eight members, scores equal at the cut
+    (2, 0, 1.0, 12),
+])
+def test_rounds_of_one_chunk_per_workgroup(whole, tail, r, directions, chunk, dim):
+    """Chunks of 512 and 1024 tokens in one launch, against the oracle, and at r = 1 bit for bit against the separate
+    kernels."""
+    from synth.kv import prototype_kv_host
+    seq = whole * chunk + tail
+    _say(f"round in one launch S={seq} D={dim} c={chunk} r={r} directions={directions}")
+    if directions:
+        K, V = prototype_kv_host(47, 2, seq, dim, "bf16", directions)
+    else:
+        K, V, _ = kv_host(47, 2, seq, dim, "bf16", alpha=0.9, n_outlier=4 if dim == 128 else 0)
+    K, V = K.to(DEV), V.to(DEV)
+    deg = torch.from_numpy(np.random.default_rng(seq).integers(1, 9, (1, 2, seq)).astype(np.int32)).to(DEV)
+    ckv.timing_reset()
+    ckv.timing_enable(True)
+    got = ckv.compress(K, V, chunk, rounds=[r], deg=deg)
+    torch.cuda.synchronize()
+    ckv.timing_enable(False)
+    assert list(ckv.timing_read()) == ["round_bf16"]
+    for h in range(2):
+        check_round(f64(K[0, h]), f64(V[0, h]), i64(deg[0, h]), chunk, r, "bf16", f64(got[0][0, h]), f64(got[1][0, h]),
+                    i64(got[2][0, h]), i64(got[3][0, h]), what=f"h{h}")
+    if r == 1.0:
+        ref = ckv.compress(K, V, chunk, rounds=[r], deg=deg, scope="head")
+        torch.cuda.synchronize()
+        for n, a, e in zip(["K'", "V'", "deg'", "assign"], got, ref):
+            assert torch.equal(a, e), f"{n} differs from the separate kernels"
+
+
 @pytest.mark.parametrize("chunk", [64, 128, 256])
 @pytest.mark.parametrize("seq,dim,r,n_sink,n_recent", [
     (256, 64, 0.5, 0, 0),
