@@ -87,6 +87,12 @@ __device__ inline RowBases stage_row_bases(int32_t* s_rb, const PagedSide& pg, i
   return RowBases{s_rb, blk0, pg.shift, (1 << pg.shift) - 1};
 }
 
+// fp32 -> uint32 whose unsigned order is the float order (-0 and +0 compare equal)
+__device__ __forceinline__ uint32_t order_key(float x) {
+  const uint32_t u = __float_as_uint(x + 0.0f);
+  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+
 // Map dispatch order to logical work so that the 8 XCDs (which receive consecutive workgroup ids
 // round-robin) each walk a contiguous range: neighbours in the range (the A blocks of one chunk,
 // adjacent chunks) then share an L2.

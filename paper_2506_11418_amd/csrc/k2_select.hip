@@ -16,6 +16,7 @@
 // 1688 -> 417; 8 x 1048576, 64: 1926 -> 654; 64 x 131072, 1024: 222 -> 63; 256 x 32768, 512: 77 -> 28;
 // 8 x 16384, 256: 46 -> 20; 1 x 2000, 64: 24 -> 14.
 #include "ckv_internal.h"
+#include "ckv_device.h"
 
 namespace ckv {
 namespace {
@@ -24,13 +25,6 @@ constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / 64;
 constexpr int kSelBins = 2 * kSelThreads;   // digits of 11, 11 and 10 bits; a thread scans two bins
 constexpr int kSelFlight = 8;               // scores a thread requests before it looks at the first
-
-// fp32 -> uint32 whose unsigned order is the float order (-0 and +0 compare equal, as they do
-// in the merge kernel's float comparisons)
-__device__ inline uint32_t order_key(float x) {
-  const uint32_t u = __float_as_uint(x + 0.0f);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
 
 __device__ inline int block_scan_excl(int v, int* s_wave, int* total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;

@@ -3,7 +3,7 @@
 // centroid equation; values merged with the same weights).
 //
 // One workgroup per (sequence, chunk).  Integer bookkeeping lives in LDS:
-//   keep[i]      source i is among the m = floor(r*|A|) best edges (score desc, index asc);
+//   keep[i]      source i is among the m = floor(r*|A|) best edges (score desc, index asc; radix select);
 //   members[]    kept sources grouped by destination, ascending inside a group (rank by counting:
 //                no atomics decide an order, so results are run-to-run identical);
 //   local_out[]  prefix sum over retained tokens (all B tokens, unkept A tokens).
@@ -126,7 +126,7 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
   __shared__ __attribute__((aligned(16))) int16_t s_dstk[MH];
   __shared__ __attribute__((aligned(16))) float s_score[MH];
   __shared__ int32_t s_cnt[MH];
-  __shared__ int32_t s_fill[MH];
+  __shared__ __attribute__((aligned(16))) int32_t s_fill[MH];
   __shared__ int16_t s_start[MH];
   __shared__ int16_t s_members[MH];
   __shared__ int16_t s_local_out[2 * MH];
@@ -180,54 +180,101 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
   }
   const int n_src = n_sources(seq, chunk);
   const int64_t src_base = (int64_t)bh * n_src + (int64_t)g * (chunk >> 1);
-  const int nA_pad = (nA + 7) & ~7;
-
-  for (int i = tid; i < nA_pad; i += kThreads) {
-    s_dstk[i] = (i < nA && m > 0) ? (int16_t)dst_local[src_base + i] : (int16_t)-1;
-    if (m > 0 && m < nA) s_score[i] = (i < nA) ? score[src_base + i] : -INFINITY;
+  // ---- top-r: the key of the m-th best edge by a radix select, equal ones by position -------------
+  // (a rank by counting compares every score with every other one: 8 x 8448 tokens, chunk 1024, r = 0.8 43 us a launch,
+  // one digit at a time 29)
+  constexpr int PER = MH / kThreads;               // sources per thread
+  int d_of[PER];
+#pragma unroll
+  for (int it = 0; it < PER; ++it) {
+    const int i = tid + it * kThreads;
+    d_of[it] = (i < nA && m > 0) ? dst_local[src_base + i] : -1;
+  }
+  const bool ranked = m > 0 && m < nA;
+  uint32_t key[PER];
+  static_assert(MH >= 512 && kThreads == 256, "two histograms of a digit in either array");
+  uint32_t* hist_of[4] = {reinterpret_cast<uint32_t*>(s_fill), reinterpret_cast<uint32_t*>(s_fill) + 256,
+                          reinterpret_cast<uint32_t*>(s_score), reinterpret_cast<uint32_t*>(s_score) + 256};
+  if (ranked) {
+#pragma unroll
+    for (int p = 0; p < 4; ++p) hist_of[p][tid] = 0;
+#pragma unroll
+    for (int it = 0; it < PER; ++it) {
+      const int i = tid + it * kThreads;
+      key[it] = i < nA ? order_key(score[src_base + i]) : 0u;
+    }
   }
   for (int j = tid; j < nB; j += kThreads) s_cnt[j] = 0;
-  __syncthreads();
-
-  // ---- top-r: rank by counting (score descending, index ascending) ----------------------------
-  if (m > 0 && m < nA) {
-    bool drop[MH / kThreads];
+  if (PAGED) __syncthreads();                      // (the rows of the blocks)
+  // Two versions of the emit loop: weights up to 256 ride in a packed bf16 operand (one v_dot2 per
+  // element); a chunk that holds a larger degree takes the general route.  Same bits either way.
+  // (asked here, so that the degrees' latency is the one of the matches)
+  int big = 0;
+  if (deg_in) {
+    const int32_t* dc = in_paged ? deg_in : deg_in + (int64_t)bh * deg_in_stride + g0;
+    for (int u = tid; u < L; u += kThreads) big |= dc[in_paged ? rb_in.row(pin.tok0 + g0 + u) : u] > 256;
+  }
+  if (MODE == kMergeOrigin && org.deg0) {
+    const int32_t* dc = org_paged ? org.deg0 : org.deg0 + (int64_t)bh * org.view0.deg_stride;
+    const int t_lo = 2 * g * chunk, t_hi = min(org.seq0, t_lo + 2 * chunk);
+    for (int t = t_lo + tid; t < t_hi; t += kThreads) big |= dc[org_paged ? rb_org.row(org.paged.tok0 + t) : t] > 256;
+  }
+  const bool wide = __syncthreads_or(big) != 0;
+  if (ranked) {
+    const int lane = tid & 63;
+    uint32_t cut = 0;
+    int left = m, equal = 0;                       // of the keys that agree with the cut so far, the left best are kept
 #pragma unroll
-    for (int it = 0; it < MH / kThreads; ++it) {
-      const int i = tid + it * kThreads;
-      drop[it] = false;
-      if (i < nA) {
-        // earlier indices win ties.  Which indices are earlier is known for all but the 64 of this wave, so
-        // that two instructions per score do instead of six
-        const float si = s_score[i];
-        const int w0 = i & ~63, w1 = min(w0 + 64, nA_pad);
-        int rank = 0;
-#pragma unroll 4
-        for (int o4 = 0; o4 < w0; o4 += 4) {
-          const float4 so = *reinterpret_cast<const float4*>(&s_score[o4]);
-          rank += (so.x >= si) + (so.y >= si) + (so.z >= si) + (so.w >= si);
+    for (int p = 0; p < 4; ++p) {
+      const int shift = 24 - 8 * p;
+#pragma unroll
+      for (int it = 0; it < PER; ++it)
+        if (tid + it * kThreads < nA && (p == 0 || ((key[it] ^ cut) >> (shift + 8)) == 0))
+          atomicAdd(&hist_of[p][key[it] >> shift & 255u], 1u);
+      __syncthreads();
+      // every wave finds the bin for itself; lane l: bins 255 - 4l downwards
+      int c[4], sum = 0;
+      const uint4 h = *reinterpret_cast<const uint4*>(&hist_of[p][252 - 4 * lane]);
+      c[0] = (int)h.w; c[1] = (int)h.z; c[2] = (int)h.y; c[3] = (int)h.x;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sum += c[e];
+      int inc = sum;
+#pragma unroll
+      for (int x = 1; x < 64; x <<= 1) {
+        const int o = __shfl_up(inc, x);
+        if (lane >= x) inc += o;
+      }
+      const int owner = __ffsll((unsigned long long)__ballot(inc >= left)) - 1;   // (the last lane's sum reaches it)
+      int above = inc - sum, e = 0;
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        if (e == k && above + c[k] < left) { above += c[k]; ++e; }
+      const int n = e == 0 ? c[0] : e == 1 ? c[1] : e == 2 ? c[2] : c[3];
+      cut |= (uint32_t)__shfl(255 - 4 * lane - e, owner) << shift;
+      left -= __shfl(above, owner);
+      equal = __shfl(n, owner);
+    }
+    if (left < equal) {                            // (the same for every thread) only the earliest of the equal ones
+      int16_t* at_cut = s_local_out;               // (not in use yet)
+#pragma unroll
+      for (int it = 0; it < PER; ++it) {
+        const int i = tid + it * kThreads;
+        if (i < nA) at_cut[i] = key[it] == cut;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int it = 0; it < PER; ++it) {
+        const int i = tid + it * kThreads;
+        if (i < nA && key[it] == cut) {
+          int earlier = 0;
+          for (int o = 0; o < i; ++o) earlier += at_cut[o];
+          if (earlier >= left) d_of[it] = -1;
         }
-#pragma unroll 2
-        for (int o4 = w0; o4 < w1; o4 += 4) {
-          const float4 so = *reinterpret_cast<const float4*>(&s_score[o4]);
-          rank += (so.x > si) || (so.x == si && o4 < i);
-          rank += (so.y > si) || (so.y == si && o4 + 1 < i);
-          rank += (so.z > si) || (so.z == si && o4 + 2 < i);
-          rank += (so.w > si) || (so.w == si && o4 + 3 < i);
-        }
-#pragma unroll 4
-        for (int o4 = w1; o4 < nA_pad; o4 += 4) {
-          const float4 so = *reinterpret_cast<const float4*>(&s_score[o4]);
-          rank += (so.x > si) + (so.y > si) + (so.z > si) + (so.w > si);
-        }
-        drop[it] = rank >= m;
       }
     }
-    __syncthreads();
 #pragma unroll
-    for (int it = 0; it < MH / kThreads; ++it)
-      if (drop[it]) s_dstk[tid + it * kThreads] = -1;
-    __syncthreads();
+    for (int it = 0; it < PER; ++it)
+      if (key[it] < cut) d_of[it] = -1;
   }
 
   // ---- kept sources grouped by destination, ascending within a group --------------------------
@@ -237,10 +284,10 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
   // are placed by rank counting instead.
   constexpr int kSortMax = 8;
 #pragma unroll
-  for (int it = 0; it < MH / kThreads; ++it) {
+  for (int it = 0; it < PER; ++it) {
     const int i = tid + it * kThreads;
-    const int d = (i < nA) ? (int)s_dstk[i] : -1;
-    if (d >= 0) atomicAdd(&s_cnt[d], 1);
+    if (i < nA) s_dstk[i] = (int16_t)d_of[it];
+    if (d_of[it] >= 0) atomicAdd(&s_cnt[d_of[it]], 1);
   }
   __syncthreads();
   int longest = 0;
@@ -264,9 +311,9 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
   }
   const bool any_long = __syncthreads_or(longest > kSortMax);
 #pragma unroll
-  for (int it = 0; it < MH / kThreads; ++it) {
+  for (int it = 0; it < PER; ++it) {
     const int i = tid + it * kThreads;
-    const int d = (i < nA) ? (int)s_dstk[i] : -1;
+    const int d = d_of[it];
     if (d >= 0) {
       int pos;
       if (any_long && s_cnt[d] > kSortMax) {        // rank among earlier sources of the same list
@@ -706,20 +753,6 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
       finish(wide_c, b2);
     }
   };
-  // Two versions of the emit loop: weights up to 256 ride in a packed bf16 operand (one v_dot2 per
-  // element); a chunk that holds a larger degree takes the general route.  Same bits either way.
-  bool wide;
-  {
-    int big = 0;
-    if (deg_in) {
-      for (int u = tid; u < L; u += kThreads) big |= in_deg(u) > 256;
-    }
-    if (MODE == kMergeOrigin && d0p) {
-      const int t_lo = 2 * g * chunk, t_hi = min(org.seq0, t_lo + 2 * chunk);
-      for (int t = t_lo + tid; t < t_hi; t += kThreads) big |= d0_at(t) > 256;
-    }
-    wide = __syncthreads_or(big) != 0;
-  }
   if (wide) emit(std::true_type{});
   else emit(std::false_type{});
 }

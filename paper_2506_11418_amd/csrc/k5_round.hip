@@ -45,12 +45,6 @@ struct RoundLds {
   int n_merged, n_copied, sel[2];
 };
 
-// an order-preserving integer image of a score: greater is greater, -0 as +0
-__device__ __forceinline__ uint32_t ordered(float x) {
-  const uint32_t u = __float_as_uint(x + 0.f);
-  return u ^ ((u >> 31) ? 0xffffffffu : 0x80000000u);
-}
-
 // In: score, dst (-1: nothing to merge into), deg and word of every row; cnt, desc, n_merged, n_copied zero, scores of
 // sources that do not exist -inf.  Chunks of `chunk` tokens, the last one of the block possibly short: m_full / m_tail
 // edges of a whole / short one are merged.  Begins and ends with a barrier.
@@ -91,7 +85,7 @@ __device__ __forceinline__ void round_lists(RoundLds<HALF>& s, int n_tok, int ch
     // the square: 512 sources take 4 us of the vector units)
     if (m > 0 && m < nAc) {
       uint32_t* histogram = s.members;             // (not in use yet)
-      const uint32_t key = a < nA ? ordered(s.score[a]) : 0u;
+      const uint32_t key = a < nA ? order_key(s.score[a]) : 0u;
       uint32_t cut = 0;
       int left = m, equal = 0;
 #pragma unroll 1
@@ -126,7 +120,7 @@ __device__ __forceinline__ void round_lists(RoundLds<HALF>& s, int n_tok, int ch
       if (d >= 0 && key <= cut) {
         int earlier = 0;
         if (key == cut && left < equal)
-          for (int o = 0; o < a; ++o) earlier += ordered(s.score[o]) == cut;
+          for (int o = 0; o < a; ++o) earlier += order_key(s.score[o]) == cut;
         if (key < cut || earlier >= left) d = -1;
       }
     }

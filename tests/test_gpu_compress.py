@@ -329,6 +329,46 @@ def test_rounds_of_one_chunk_per_workgroup(whole, tail, r, directions, chunk, di
             assert torch.equal(a, e), f"{n} differs from the separate kernels"
 
 
+@pytest.mark.parametrize("dtype,dim,chunk", [("bf16", 128, 384), ("bf16", 128, 1024), ("bf16", 64, 2048), ("f32", 64, 1024),
+                                             ("bf16", 128, 2)])
+@pytest.mark.parametrize("whole,tail,r,directions", [
+    (2, 0, 0.8, 0),
+    (1, 333, 0.5, 0),
+    (1, 0, 0.999, 0),            # all edges of a long chunk but one
+    (2, 5, 0.002, 0),            # one or two, none in the tail
+    (1, 77, 0.6, 3),             # keys of three directions: most scores equal, whichever cut is taken
+])
+def test_the_best_edges_of_a_chunk_are_merged_and_the_earliest_of_equal_ones(whole, tail, r, directions, dtype, dim, chunk):
+    """The separate merge kernel's selection against the scores of the match kernel, exactly, and the round against the
+    oracle."""
+    from synth.kv import prototype_kv_host
+    seq = whole * chunk + tail
+    _say(f"selection {dtype} S={seq} D={dim} c={chunk} r={r} directions={directions}")
+    if directions:
+        K, V = prototype_kv_host(53, 2, seq, dim, dtype, directions)
+    else:
+        K, V, _ = kv_host(53, 2, seq, dim, dtype, alpha=0.9, n_outlier=4 if dim == 128 else 0)
+    K, V = K.to(DEV), V.to(DEV)
+    deg = torch.from_numpy(np.random.default_rng(seq).integers(1, 9, (1, 2, seq)).astype(np.int32)).to(DEV)
+    dst, score = ckv.match(K, chunk)
+    got = ckv.compress(K, V, chunk, rounds=[r], deg=deg)
+    torch.cuda.synchronize()
+    for h in range(2):
+        to, first = i64(got[3][0, h]), 0
+        for lo in range(0, seq, chunk):
+            n = min(chunk, seq - lo)
+            n_src, n_edges = (n + 1) // 2, (n + 1) // 2 if n > 1 else 0
+            at, sc = i64(dst[0, h])[first:first + n_src], score[0, h][first:first + n_src].cpu().numpy()
+            first += n_src
+            m = int(np.floor(float(np.float32(r)) * n_edges + 1e-9))
+            want = np.zeros(n_src, dtype=bool)
+            want[np.argsort(-sc, kind="stable")[:m]] = True
+            merged = np.array([j >= 0 and to[lo + 2 * i] == to[j] for i, j in enumerate(at)])
+            assert np.array_equal(merged, want), f"h{h} chunk at {lo}: {np.flatnonzero(merged != want)[:8]}"
+        check_round(f64(K[0, h]), f64(V[0, h]), i64(deg[0, h]), chunk, r, dtype, f64(got[0][0, h]), f64(got[1][0, h]),
+                    i64(got[2][0, h]), i64(got[3][0, h]), what=f"h{h}")
+
+
 @pytest.mark.parametrize("chunk", [64, 128, 256])
 @pytest.mark.parametrize("seq,dim,r,n_sink,n_recent", [
     (256, 64, 0.5, 0, 0),
