@@ -4,13 +4,12 @@
 // For every A token i:  j*(i) = argmax_j  k_i.k_j / (|k_i||k_j|)  (lowest j on ties) and that
 // maximum.  The |A| x |B| similarity matrix lives only in MFMA accumulators.
 //
-// Three bf16 kernels.  Common to all: 64 A rows per wave held as MFMA operands in registers; the
+// Three bf16 kernels.  Common to all: 64 A rows (or 32) per wave held as MFMA operands in registers; the
 // MFMA computes S^T (B index on the M side) so that a lane's 16 accumulators of a 32x32 tile all
 // belong to ONE A row (no cross-lane step until the very end); inverse norms come from the same
 // bytes (v_dot2 on the packed pairs): the B rows' while they are staged into LDS, the A rows'
 // from the operand registers.
-//   match_bf16_kernel: one workgroup = (sequence, chunk, block of A rows); 8 waves (512 A rows) for
-// chunks above 512 tokens, 4 waves otherwise.  The A rows are staged once through LDS; the chunk's
+//   match_bf16_kernel: one workgroup = (sequence, chunk, block of 128, 256 or 512 A rows).  The A rows are staged once through LDS; the chunk's
 // B rows stream through two LDS panels of 128 rows (global -> registers -> LDS, one barrier per
 // panel).  Blocks made of full tiles fold tile q into the running maxima while the MFMAs of tile
 // q+1 run; ragged blocks take the maximum first and resolve the index only for tiles that raise
@@ -35,12 +34,12 @@ constexpr int kThreads = 256;
 constexpr int kRowsPerWave = 64;                 // two 32-row MFMA tiles
 constexpr int kPanel = 128;                      // B rows per LDS panel
 
-// NW waves x 64 A rows per workgroup: 4 waves (two workgroups per CU) for chunks of up to 512 tokens,
-// 8 waves (one workgroup per CU) for larger chunks, so that the B rows of a 1024-token chunk are
-// fetched, normed and written to LDS once instead of once per 256 A rows.
+// NW waves x RT tiles of 32 A rows per workgroup; launch_match_general has the rule and what the forms measured.
+// 8 x 2 (one workgroup per CU): the B rows of a 1024-token chunk are fetched, normed and written to LDS once,
+// and every B operand feeds two MFMAs.
 // PAGED: K is a block pool and the rows are reached through a block table (see PagedSide); the pool
 // rows of the chunk's blocks are staged in LDS first.
-template <int D, int NW, bool PAGED>
+template <int D, int NW, int RT, bool PAGED>   // RT: 32-row tiles of A rows per wave
 __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void match_bf16_kernel(
     const __bf16* __restrict__ K, TensorView kv, int seq, int chunk, int first_chunk, int n_chunks, int a_blocks,
     int total_work, int per_xcd, int32_t* __restrict__ dst_local, float* __restrict__ score, PagedSide paged) {
@@ -49,7 +48,8 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void match_bf16_kernel(
   constexpr int KEYSHIFT = (ROWB == 256) ? 0 : 1;  // rows per 256 B of LDS = 1 << KEYSHIFT
   constexpr int KSTEPS = D / 16;
   constexpr int THREADS = NW * 64;
-  constexpr int ABLOCK = NW * kRowsPerWave;        // A rows per workgroup
+  constexpr int ROWS = RT * 32;                    // A rows per wave
+  constexpr int ABLOCK = NW * ROWS;                // A rows per workgroup
   constexpr int PANELS_B = (ABLOCK > 2 * kPanel ? ABLOCK : 2 * kPanel) * ROWB;   // staging area: A block or 2 panels
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   unsigned char* panel0 = smem;                                // 2 panels of kPanel rows; the A
@@ -141,7 +141,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void match_bf16_kernel(
   // most similar to their neighbours, so the running maxima settle in the first panel)
   const int n_panels = div_up(nB, kPanel);
   // a block of full tiles takes the software-pipelined loop below, panels in increasing order
-  const bool pipelined = (NW == 8) && (a0 + ABLOCK <= nA) && (nB % kPanel == 0);
+  const bool pipelined = (NW == 8 && RT == 2) && (a0 + ABLOCK <= nA) && (nB % kPanel == 0);
   const int p_first = pipelined ? 0 : min(a0 / kPanel, n_panels - 1);
   {
     constexpr int APIECES = ABLOCK * OCT / THREADS;
@@ -165,20 +165,20 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void match_bf16_kernel(
   bf16x8 afrag[2][KSTEPS];
   const int half = lane >> 5, col = lane & 31;
 #pragma unroll
-  for (int rt = 0; rt < 2; ++rt) {
-    const int row = wave * kRowsPerWave + rt * 32 + col;
+  for (int rt = 0; rt < RT; ++rt) {
+    const int row = wave * ROWS + rt * 32 + col;
 #pragma unroll
     for (int s = 0; s < KSTEPS; ++s)
       afrag[rt][s] = *reinterpret_cast<const bf16x8*>(panel0 + swz(row, 2 * s + half));
   }
   // 1/|k_i| of this lane's two A rows, from the operand registers
-  const float my_inva[2] = {inv_norm_of_operand_row<KSTEPS>(afrag[0]), inv_norm_of_operand_row<KSTEPS>(afrag[1])};
+  const float my_inva[2] = {inv_norm_of_operand_row<KSTEPS>(afrag[0]), inv_norm_of_operand_row<KSTEPS>(afrag[RT - 1])};
   __syncthreads();
 
   // ---- stream B panels -----------------------------------------------------------------------
   float best[2] = {-INFINITY, -INFINITY};
   int bestj[2] = {0, 0};
-  const bool wave_active = (a0 + wave * kRowsPerWave) < nA;
+  const bool wave_active = (a0 + wave * ROWS) < nA;
   // LDS byte offsets of this lane's B fragments inside a 32-row tile: the swizzle key of row
   // ct*32 + col only depends on col, so tile and buffer offsets are compile-time immediates
   int boff[KSTEPS];
@@ -198,7 +198,7 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void match_bf16_kernel(
       for (int s = 0; s < KSTEPS; ++s) {
         const bf16x8 bfrag = *reinterpret_cast<const bf16x8*>(pb + ct * 32 * ROWB + boff[s]);
         acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfrag, afrag[0][s], acc0, 0, 0, 0);
-        acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfrag, afrag[1][s], acc1, 0, 0, 0);
+        if (RT == 2) acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfrag, afrag[RT - 1][s], acc1, 0, 0, 0);
       }
       // accumulator r of this lane: B row 8*(r/4) + 4*half + r%4 of the tile, A row = col
       f32x4 ib[4];
@@ -209,10 +209,10 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void match_bf16_kernel(
       const int valid = rows_here - ct * 32;      // rows of this tile that exist (>= 32: all)
       if (FULL || valid >= 32) {
         tile_argmax<false>(acc0, ib, jbase, half, valid, best[0], bestj[0]);
-        tile_argmax<false>(acc1, ib, jbase, half, valid, best[1], bestj[1]);
+        if (RT == 2) tile_argmax<false>(acc1, ib, jbase, half, valid, best[1], bestj[1]);
       } else {
         tile_argmax<true>(acc0, ib, jbase, half, valid, best[0], bestj[0]);
-        tile_argmax<true>(acc1, ib, jbase, half, valid, best[1], bestj[1]);
+        if (RT == 2) tile_argmax<true>(acc1, ib, jbase, half, valid, best[1], bestj[1]);
       }
     }
   };
@@ -304,13 +304,13 @@ __global__ __launch_bounds__(NW * 64, NW == 4 ? 2 : 1) void match_bf16_kernel(
   // ---- merge the two lane halves of every A row and write ------------------------------------
   if (wave_active) {
 #pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
+    for (int rt = 0; rt < RT; ++rt) {
       const float ob = __shfl_xor(best[rt], 32);
       const int oj = __shfl_xor(bestj[rt], 32);
       float b = best[rt];
       int j = bestj[rt];
       if (ob > b || (ob == b && oj < j)) { b = ob; j = oj; }
-      const int a = a0 + wave * kRowsPerWave + rt * 32 + col;
+      const int a = a0 + wave * ROWS + rt * 32 + col;
       if (half == 0 && a < nA) {
         dst_local[out_base + a] = j;
         score[out_base + a] = b * my_inva[rt];
@@ -757,16 +757,16 @@ __global__ void dst_positions_kernel(const int32_t* __restrict__ dst_local, int3
   dst_pos[e] = (j < 0) ? -1 : g * chunk + 2 * j + 1;
 }
 
-template <int D, int NW, bool PAGED>
+template <int D, int NW, int RT, bool PAGED>
 hipError_t launch_match_bf16_nw(const void* K, TensorView kv, int n_bh, int seq, int chunk,
                                 int32_t* dst_local, float* score, hipStream_t st, PagedSide paged,
                                 int first_chunk = 0) {
-  constexpr int ABLOCK = NW * kRowsPerWave;
+  constexpr int ABLOCK = NW * RT * 32;
   // staging area + inverse norms of two panels (+ PAGED: the pool rows of a chunk's blocks, 8 tokens or more each)
   constexpr size_t lds = (size_t)(ABLOCK > 2 * kPanel ? ABLOCK : 2 * kPanel) * D * 2 + 2 * kPanel * sizeof(float) +
                          (PAGED ? (2048 / 8 + 2) * sizeof(int32_t) : 0);
   static KernelSetup setup;
-  if (hipError_t e = kernel_setup(reinterpret_cast<const void*>(&match_bf16_kernel<D, NW, PAGED>), lds, setup); e != hipSuccess)
+  if (hipError_t e = kernel_setup(reinterpret_cast<const void*>(&match_bf16_kernel<D, NW, RT, PAGED>), lds, setup); e != hipSuccess)
     return e;
   const int n_chunks = div_up(seq, chunk) - first_chunk;
   const int a_blocks = div_up((min(chunk, seq - first_chunk * chunk) + 1) / 2, ABLOCK);   // the launch's longest chunk
@@ -774,7 +774,7 @@ hipError_t launch_match_bf16_nw(const void* K, TensorView kv, int n_bh, int seq,
   if (total > (1 << 30)) return hipErrorInvalidValue;
   const int per_xcd = div_up((int)total, 8);
   ScopedTimer t("match_bf16", st);
-  hipLaunchKernelGGL((match_bf16_kernel<D, NW, PAGED>), dim3(per_xcd * 8), dim3(NW * 64), lds, st,
+  hipLaunchKernelGGL((match_bf16_kernel<D, NW, RT, PAGED>), dim3(per_xcd * 8), dim3(NW * 64), lds, st,
                      static_cast<const __bf16*>(K), kv, seq, chunk, first_chunk, n_chunks, a_blocks, (int)total,
                      per_xcd, dst_local, score, paged);
   return hipGetLastError();
@@ -818,17 +818,44 @@ hipError_t launch_match_stream(const void* K, TensorView kv, int n_bh, int seq, 
   return hipGetLastError();
 }
 
+// Workgroups of 256 A rows a launch would have; up to kFillChip of them leave CUs idle (one workgroup each).
+constexpr int64_t kFillChip = 256;
+
+int64_t row_blocks(int n_bh, int n_chunks, int longest) { return (int64_t)n_bh * n_chunks * div_up((longest + 1) / 2, 256); }
+
+// The general kernel for chunks first_chunk and after.  A wave takes two tiles of A rows (every B operand
+// read from LDS feeds two MFMAs) only where whole blocks keep the pipelined loop busy:
+//   chunks of 512 rows or multiples (1024, 2048 tokens): 8 waves x 64, but 8 x 32 for launches that leave CUs idle,
+// which are bound by the chain of one workgroup (us; 8 sequences of dim 128, 64 -> 32 rows: 5000 tokens, chunk 1024 18.1
+// -> 13.2, chunk 2048 28.0 -> 22.9; 16384 tokens, 1024 18.8 -> 13.9, 2048 30.9 -> 23.8; 20001 tokens 18.8 against 21.5);
+//   other chunks above 512 tokens: 8 x 32 always (chunk 700, 64 x 20001, dim 128 130 -> 113, dim 64 91 -> 72.5);
+//   up to 512 tokens: 8 x 32 in place of 4 x 64 (chunk 384, 8 x 5000 10.2 -> 7.7, 64 x 32768 135 -> 122), except dim 64 with
+// more than two workgroups per CU (384, 64 x 32768: 4 x 64 72, 8 x 32 74);
+//   up to 256 tokens: 4 x 32 (chunk 200, 64 x 20001 103 -> 79).
+template <int D, bool PAGED>
+hipError_t launch_match_general(const void* K, TensorView kv, int n_bh, int seq, int chunk, int32_t* dst_local, float* score,
+                                hipStream_t st, PagedSide paged, int first_chunk = 0) {
+  const int longest = min(chunk, seq - first_chunk * chunk);
+  const int64_t blocks = row_blocks(n_bh, div_up(seq, chunk) - first_chunk, longest);
+#define CKV_MATCH(NW, RT) \
+  return launch_match_bf16_nw<D, NW, RT, PAGED>(K, kv, n_bh, seq, chunk, dst_local, score, st, paged, first_chunk)
+  if (longest <= 256) CKV_MATCH(4, 1);
+  if (longest <= 512) {
+    if (D == 64 && blocks > 2 * kFillChip) CKV_MATCH(4, 2);
+    CKV_MATCH(8, 1);
+  }
+  if (longest % 1024 == 0 && blocks > kFillChip) CKV_MATCH(8, 2);
+  CKV_MATCH(8, 1);
+#undef CKV_MATCH
+}
+
 template <int D>
 hipError_t launch_match_bf16(const void* K, TensorView kv, int n_bh, int seq, int chunk,
                              int32_t* dst_local, float* score, hipStream_t st, PagedSide paged) {
-  if (paged.table) {
-    if (chunk > 512) return launch_match_bf16_nw<D, 8, true>(K, kv, n_bh, seq, chunk, dst_local, score, st, paged);
-    return launch_match_bf16_nw<D, 4, true>(K, kv, n_bh, seq, chunk, dst_local, score, st, paged);
-  }
-  if (chunk > 512) return launch_match_bf16_nw<D, 8, false>(K, kv, n_bh, seq, chunk, dst_local, score, st, paged);
+  if (paged.table) return launch_match_general<D, true>(K, kv, n_bh, seq, chunk, dst_local, score, st, paged);
   if ((chunk == 64 || chunk == 128 || chunk == 256) && seq >= chunk)
     return launch_match_small<D>(K, kv, n_bh, seq, chunk, dst_local, score, st);
-  return launch_match_bf16_nw<D, 4, false>(K, kv, n_bh, seq, chunk, dst_local, score, st, paged);
+  return launch_match_general<D, false>(K, kv, n_bh, seq, chunk, dst_local, score, st, paged);
 }
 
 // From how many chunks of 1024 tokens on sequences with a ragged tail chunk take the streaming kernel for
@@ -848,12 +875,11 @@ hipError_t launch_match(const void* K, int dtype, int dim, TensorView kv, int n_
     // (the persistent streaming kernel walks memory with fixed pitches: strided tensors only)
     const int whole = seq / chunk, tail = seq % chunk;
     if (!paged.table && dim == 128 && (chunk == 1024 || chunk == 2048) && whole > 0 && kv.stride_s <= (1 << 22) &&
-        (tail == 0 || (chunk == 1024 && (int64_t)n_bh * whole >= kStreamRaggedChunks))) {
+        row_blocks(n_bh, whole, chunk) > kFillChip && (tail == 0 || (chunk == 1024 && (int64_t)n_bh * whole >= kStreamRaggedChunks))) {
       const hipError_t e = chunk == 1024 ? launch_match_stream<16>(K, kv, n_bh, seq, dst_local, score, st)
                                          : launch_match_stream<32>(K, kv, n_bh, seq, dst_local, score, st);
       if (e != hipSuccess || tail == 0) return e;
-      return tail > 512 ? launch_match_bf16_nw<128, 8, false>(K, kv, n_bh, seq, chunk, dst_local, score, st, paged, whole)
-                        : launch_match_bf16_nw<128, 4, false>(K, kv, n_bh, seq, chunk, dst_local, score, st, paged, whole);
+      return launch_match_general<128, false>(K, kv, n_bh, seq, chunk, dst_local, score, st, paged, whole);
     }
     if (dim == 128) return launch_match_bf16<128>(K, kv, n_bh, seq, chunk, dst_local, score, st, paged);
     if (dim == 64) return launch_match_bf16<64>(K, kv, n_bh, seq, chunk, dst_local, score, st, paged);

@@ -97,6 +97,26 @@ def test_match_bf16_shapes(heads, seq, dim, chunk):
         check_match(f64(K[0, h]), chunk, i64(dst[0, h]), f64(score[0, h]), f"h{h}")
 
 
+@pytest.mark.parametrize("heads,seq,dim,chunk", [
+    (300, 201, 128, 200), (300, 200, 64, 200),      # 4 waves x 32 rows, a block per chunk
+    (300, 641, 64, 384), (90, 1153, 128, 384),      # dim 64: 8 x 32 for a few chunks, 4 x 64 for many
+    (130, 1537, 128, 1024), (130, 1024, 64, 1024),  # 8 x 32 for a few, 8 x 64 (or the streaming kernel) for many
+    (70, 2048 + 515, 128, 2048), (70, 1400, 64, 1400),
+])
+def test_match_kernels_for_few_and_for_many_rows_agree(heads, seq, dim, chunk):
+    """A chunk's matches do not depend on how many others share its launch: same bits, and the oracle's matching."""
+    _say(f"match forms H={heads} S={seq} D={dim} c={chunk}")
+    K, _, _ = kv_host(61, 2, seq, dim, "bf16", alpha=0.9, n_outlier=4 if dim == 128 else 0)
+    K = K.to(DEV)
+    few = [x.clone() for x in ckv.match(K, chunk)]
+    many = ckv.match(K.repeat(1, heads // 2, 1, 1), chunk)
+    torch.cuda.synchronize()
+    for a, b in zip(few, many):
+        assert torch.equal(a.repeat(1, heads // 2, 1), b)
+    for h in range(2):
+        check_match(f64(K[0, h]), chunk, i64(few[0][0, h]), f64(few[1][0, h]), f"h{h}")
+
+
 # ---- chunks of 64, 128 and 256 tokens (the paper's chunk ablation): several chunks per workgroup ----
 @pytest.mark.parametrize("batch,heads,seq,dim,chunk,layout", [
     (1, 2, 2048, 128, 64, "bhsd"),       # four full blocks of 512 tokens per sequence
