@@ -87,6 +87,22 @@ __device__ inline RowBases stage_row_bases(int32_t* s_rb, const PagedSide& pg, i
   return RowBases{s_rb, blk0, pg.shift, (1 << pg.shift) - 1};
 }
 
+// RoundMap with fold > 0: the entries of the original tokens of input tokens [u0, u0 + n), n a whole number of chunks,
+// THREADS threads of which this is number `tid`; place(u): output index of input token u0 + u.  Four loads in flight.
+template <class F>
+__device__ __forceinline__ void fold_map(const RoundMap& map, int64_t bh, int u0, int n, int threads, int tid, F&& place) {
+  int32_t* a = map.p + bh * map.stride;
+  const int hi = (int)min((int64_t)map.len, ((int64_t)u0 + n) << map.fold);
+  for (int t = (u0 << map.fold) + tid; t < hi; t += 4 * threads) {
+    int u[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) u[i] = a[min((int64_t)t + (int64_t)i * threads, (int64_t)hi - 1)];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if ((int64_t)t + (int64_t)i * threads < hi) a[t + i * threads] = place(u[i] - u0);
+  }
+}
+
 // fp32 -> uint32 whose unsigned order is the float order (-0 and +0 compare equal)
 __device__ __forceinline__ uint32_t order_key(float x) {
   const uint32_t u = __float_as_uint(x + 0.0f);

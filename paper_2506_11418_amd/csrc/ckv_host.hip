@@ -282,6 +282,8 @@ int run_rounds(const void* K, const void* V, const int32_t* deg_in, const ckv_la
     const int64_t oDegStride = oView.deg_stride;
     int32_t* map = nullptr;
     if (assign) map = (j == 0) ? assign : reinterpret_cast<int32_t*>(ws + w.map);
+    bool fold = assign && j > 0 && p->scope == CKV_SCOPE_CHUNK && p->n_sink == 0 && p->n_recent == 0;   // see RoundMap
+    for (int i = 0; i < j; ++i) fold = fold && plan.round_r[i] == 1.0f;
     const bool keys_only = mode[j] == ROUND_KEYS_ONLY, from_origin = mode[j] == ROUND_ORIGIN;
     hipError_t err = hipSuccess;
     EdgeCopy edges{};
@@ -315,9 +317,10 @@ int run_rounds(const void* K, const void* V, const int32_t* deg_in, const ckv_la
       unsigned char* moV = static_cast<unsigned char*>(oV) + (pov.table ? 0 : (size_t)lo * oView.stride_s * e);
       int32_t* moDeg = pov.table ? oDeg : oDeg + lo;
       const EdgeCopy* ride = edges.total > 0 ? &edges : nullptr;
+      const RoundMap rmap = fold ? RoundMap{assign, in->seq, 0, j, in->seq} : RoundMap{map ? map + lo : nullptr, len, lo, 0, 0};
       if (mode[j] == ROUND_FULL && p->scope == CKV_SCOPE_CHUNK && round_fits(in->dtype, in->dim, n_bh, mid, p->chunk, ride, pc != nullptr)) {
         err = launch_round(RoundCall{mK, mV, mDeg, curView, n_bh, mid, p->chunk, plan.round_r[j], moK, moV, moDeg, oView,
-                                     oDegStride, map ? map + lo : nullptr, len, lo, pin, pok, pov, ride}, in->dtype, in->dim, s);
+                                     oDegStride, rmap, pin, pok, pov, ride}, in->dtype, in->dim, s);
       } else {
         err = launch_match(mK, in->dtype, in->dim, curView, n_bh, mid, p->chunk, dst, score, s, pin);
         if (err != hipSuccess) return hip_status(err);
@@ -328,7 +331,7 @@ int run_rounds(const void* K, const void* V, const int32_t* deg_in, const ckv_la
           if (err != hipSuccess) return hip_status(err);
         }
         err = launch_merge(mK, mV, mDeg, in->dtype, in->dim, curView, n_bh, mid, p->chunk, plan.round_r[j], dst, score,
-                           moK, moV, moDeg, oView, oDegStride, map ? map + lo : nullptr, curView.deg_stride, len, lo, sel,
+                           moK, moV, moDeg, oView, oDegStride, rmap, curView.deg_stride, sel,
                            keys_only ? lists : nullptr, from_origin ? &org : nullptr, s, pin, pok, pov, ride);
       }
       if (err != hipSuccess) return hip_status(err);
@@ -336,7 +339,7 @@ int run_rounds(const void* K, const void* V, const int32_t* deg_in, const ckv_la
       err = launch_edges(edges, s);
     }
     if (err != hipSuccess) return hip_status(err);
-    if (assign && j > 0) {
+    if (assign && j > 0 && !fold) {
       err = launch_compose(assign, map, n_bh, in->seq, len, s);
       if (err != hipSuccess) return hip_status(err);
     }

@@ -105,8 +105,8 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
     const T* __restrict__ K, const T* __restrict__ V, const int32_t* __restrict__ deg_in, TensorView in,
     int seq, int chunk, int n_chunks, float r, const int32_t* __restrict__ dst_local,
     const float* __restrict__ score, T* __restrict__ K_out, T* __restrict__ V_out,
-    int32_t* __restrict__ deg_out, TensorView out, int64_t deg_out_stride, int32_t* __restrict__ map_out,
-    int64_t deg_in_stride, int64_t map_stride, int map_offset, const int2* __restrict__ sel_table,
+    int32_t* __restrict__ deg_out, TensorView out, int64_t deg_out_stride, RoundMap map,
+    int64_t deg_in_stride, const int2* __restrict__ sel_table,
     int16_t* __restrict__ lists_out, ValueOrigin org, int parts, PagedSide pin, PagedSide pout, int out_k_paged,
     int out_v_paged, EdgeBlocks<EDGES> edges) {
   if constexpr (EDGES) {
@@ -375,12 +375,16 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
   }
 
   // ---- assignment map of this round ----------------------------------------------------------
-  if (map_out != nullptr && part == 0) {
-    int32_t* mp = map_out + (int64_t)bh * map_stride + g0;
-    for (int u = tid; u < L; u += kThreads) {
+  if (map.p != nullptr) {
+    auto place = [&](int u) -> int {
       const int d = (u & 1) ? -1 : (int)s_dstk[u >> 1];
-      const int slot = (d < 0) ? s_local_out[u] : s_local_out[2 * d + 1];
-      mp[u] = map_offset + out_base + slot;
+      return map.offset + out_base + ((d < 0) ? s_local_out[u] : s_local_out[2 * d + 1]);
+    };
+    if (map.fold > 0) {
+      fold_map(map, bh, g0, chunk, parts * kThreads, part * kThreads + tid, place);
+    } else if (part == 0) {
+      int32_t* mp = map.p + (int64_t)bh * map.stride + g0;
+      for (int u = tid; u < L; u += kThreads) mp[u] = place(u);
     }
   }
 
@@ -832,8 +836,7 @@ template <typename T, int D>
 hipError_t launch_merge_t(const void* K, const void* V, const int32_t* deg_in, TensorView in, int n_bh,
                           int seq, int chunk, float r, const int32_t* dst_local, const float* score,
                           void* K_out, void* V_out, int32_t* deg_out, TensorView out,
-                          int64_t deg_out_stride, int32_t* map_out, int64_t deg_in_stride, int64_t map_stride,
-                          int map_offset, const int32_t* sel_table, int16_t* lists_out, const ValueOrigin* org,
+                          int64_t deg_out_stride, RoundMap map, int64_t deg_in_stride, const int32_t* sel_table, int16_t* lists_out, const ValueOrigin* org,
                           hipStream_t st, PagedSide pin, PagedSide pok, PagedSide pov, const EdgeCopy* edges) {
   const int n_chunks = div_up(seq, chunk);
   const int64_t total = (int64_t)n_bh * n_chunks;
@@ -864,7 +867,7 @@ hipError_t launch_merge_t(const void* K, const void* V, const int32_t* deg_in, T
                      dim3(kThreads), 0, st,                                                                   \
                      static_cast<const T*>(K), static_cast<const T*>(V), deg_in, in, seq, chunk, n_chunks, r, \
                      dst_local, score, static_cast<T*>(K_out), static_cast<T*>(V_out), deg_out, out,          \
-                     deg_out_stride, map_out, deg_in_stride, map_stride, map_offset,                          \
+                     deg_out_stride, map, deg_in_stride,                                                      \
                      reinterpret_cast<const int2*>(sel_table), lists_out, o, parts, pin, pout,                \
                      pok.table != nullptr, pov.table != nullptr, EdgeBlocks<ED>{__VA_ARGS__})
   // (fp32, the small caches: one kernel for both; with two, 1024 tokens of dim 64, chunk 64, take as long: 7.27 against
@@ -909,13 +912,13 @@ hipError_t launch_merge_t(const void* K, const void* V, const int32_t* deg_in, T
 hipError_t launch_merge(const void* K, const void* V, const int32_t* deg_in, int dtype, int dim,
                         TensorView in, int n_bh, int seq, int chunk, float r,
                         const int32_t* dst_local, const float* score, void* K_out, void* V_out,
-                        int32_t* deg_out, TensorView out, int64_t deg_out_stride, int32_t* map_out,
-                        int64_t deg_in_stride, int64_t map_stride, int map_offset, const int32_t* sel_table,
+                        int32_t* deg_out, TensorView out, int64_t deg_out_stride, RoundMap map,
+                        int64_t deg_in_stride, const int32_t* sel_table,
                         int16_t* lists_out, const ValueOrigin* org, hipStream_t st, PagedSide paged_in,
                         PagedSide paged_out_k, PagedSide paged_out_v, const EdgeCopy* edges) {
 #define CKV_MERGE(T, DD)                                                                             \
   return launch_merge_t<T, DD>(K, V, deg_in, in, n_bh, seq, chunk, r, dst_local, score, K_out, V_out, \
-                               deg_out, out, deg_out_stride, map_out, deg_in_stride, map_stride, map_offset, \
+                               deg_out, out, deg_out_stride, map, deg_in_stride, \
                                sel_table, lists_out, org, st, paged_in, paged_out_k, paged_out_v, edges)
   if (dtype == CKV_BF16) {
     if (dim == 128) CKV_MERGE(__bf16, 128);

@@ -50,11 +50,23 @@ struct RoundLds {
 // edges of a whole / short one are merged.  Begins and ends with a barrier.
 template <int HALF, int THREADS>
 __device__ __forceinline__ void round_lists(RoundLds<HALF>& s, int n_tok, int chunk, int m_full, int m_tail,
-                                            int32_t* __restrict__ map, int map_base) {
+                                            const RoundMap& map, int64_t bh, int u0, int out_base) {
   constexpr int LPA = THREADS / HALF;              // lanes that share the bookkeeping of one source
   static_assert(LPA >= 1 && LPA <= 8, "lanes per source");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int nA = (n_tok + 1) >> 1;
+  // the map's entries of a block's two original tokens to each of its own are requested here: waited for after the
+  // lists, 64 x 32768 tokens, chunk 256, took 445 us for 437
+  constexpr int EARLY = 4 * HALF > THREADS ? 4 * HALF / THREADS : 1;
+  int part_of[EARLY];
+  int32_t* originals = nullptr;
+  int n_orig = 0;
+  if (map.p && map.fold == 1) {
+    originals = map.p + bh * map.stride + 2 * (int64_t)u0;
+    n_orig = min(4 * HALF, map.len - 2 * u0);
+#pragma unroll
+    for (int i = 0; i < EARLY; ++i) part_of[i] = originals[min(tid + i * THREADS, n_orig - 1)];
+  }
   __syncthreads();
 
   // ---- top-r of every chunk: rank by counting (score descending, index ascending) ---------------
@@ -217,7 +229,21 @@ __device__ __forceinline__ void round_lists(RoundLds<HALF>& s, int n_tok, int ch
     const uint32_t o = (uint32_t)s.slot[u];
     if (copied) s.desc[at] = make_uint2(s.word[row], o);
     else if (u < n_tok && into < 0) s.desc[s.place[j]] = make_uint2(s.word[row], o | (uint32_t)n << 10 | (uint32_t)s.start[j] << 20);
-    if (map && u < n_tok) map[u] = map_base + (into < 0 ? s.slot[u] : s.slot[2 * into + 1]);
+    if (map.p && map.fold == 0 && u < n_tok)
+      map.p[bh * map.stride + u0 + u] = map.offset + out_base + (into < 0 ? s.slot[u] : s.slot[2 * into + 1]);
+  }
+  if (map.p && map.fold > 0) {
+    auto place = [&](int u) -> int {
+      const int into = (u & 1) ? -1 : (int)s.kept[u >> 1];
+      return map.offset + out_base + s.slot[into < 0 ? u : 2 * into + 1];
+    };
+    if (map.fold == 1) {
+#pragma unroll
+      for (int i = 0; i < EARLY; ++i)
+        if (tid + i * THREADS < n_orig) originals[tid + i * THREADS] = place(part_of[i] - u0);
+    } else {
+      fold_map(map, bh, u0, 2 * HALF, THREADS, tid, place);
+    }
   }
   __syncthreads();
   if constexpr (HALF > 128) {
@@ -247,7 +273,7 @@ __global__ __launch_bounds__(TOK * D / 64, 4) void round_small_kernel(
     const __bf16* __restrict__ K, const __bf16* __restrict__ V, const int32_t* __restrict__ deg_in, TensorView in,
     int seq, int chunk, int blocks_per_seq, int m_full, int m_tail, __bf16* __restrict__ K_out,
     __bf16* __restrict__ V_out, int32_t* __restrict__ deg_out, TensorView out, int64_t deg_out_stride,
-    int32_t* __restrict__ map_out, int64_t deg_in_stride, int64_t map_stride, int map_offset, PagedSide pin,
+    RoundMap map, int64_t deg_in_stride, PagedSide pin,
     PagedSide pout, int out_k_paged, int out_v_paged, EdgeBlocks<EDGES> edges) {
   constexpr int THREADS = TOK * D / 64, HALF = TOK / 2;
   constexpr int WPT = THREADS / 64 / (HALF / 32);  // waves per 32-row tile of sources: 2 or 1
@@ -403,8 +429,7 @@ __global__ __launch_bounds__(TOK * D / 64, 4) void round_small_kernel(
       s_.score[a] = best * inva;
     }
   }
-  round_lists<HALF, THREADS>(s_, n_tok, chunk, m_full, m_tail,
-                                 map_out ? map_out + (int64_t)bh * map_stride + t0 : nullptr, map_offset + out_base);
+  round_lists<HALF, THREADS>(s_, n_tok, chunk, m_full, m_tail, map, bh, t0, out_base);
 
   // ---- emit the rows of one tensor: keys first, then the values in their place ---------------------
   const int64_t out_at = out.seq_base(bh) + (int64_t)out_base * out.stride_s;
@@ -504,8 +529,8 @@ template <int D, int CHUNK, int THREADS = f32_threads<D, CHUNK>()>
 __global__ __launch_bounds__(THREADS) void round_f32_kernel(
     const float* __restrict__ K, const float* __restrict__ V, const int32_t* __restrict__ deg_in, TensorView in, int seq,
     int blocks_per_seq, int m_full, int m_tail, float* __restrict__ K_out, float* __restrict__ V_out,
-    int32_t* __restrict__ deg_out, TensorView out, int64_t deg_out_stride, int32_t* __restrict__ map_out,
-    int64_t deg_in_stride, int64_t map_stride, int map_offset, EdgeBlocks<true> edges) {
+    int32_t* __restrict__ deg_out, TensorView out, int64_t deg_out_stride, RoundMap map,
+    int64_t deg_in_stride, EdgeBlocks<true> edges) {
   constexpr int HALF = CHUNK / 2;
   constexpr int LPR = D / 4, NRG = THREADS / LPR, PASSES = CHUNK / NRG;
   constexpr int PITCH = D + 4;
@@ -606,8 +631,7 @@ __global__ __launch_bounds__(THREADS) void round_f32_kernel(
       s_.score[a] = best * s_inv[a];
     }
   }
-  round_lists<HALF, THREADS>(s_, n_tok, CHUNK, m_full, m_tail, map_out ? map_out + (int64_t)bh * map_stride + t0 : nullptr,
-                             map_offset + out_base);
+  round_lists<HALF, THREADS>(s_, n_tok, CHUNK, m_full, m_tail, map, bh, t0, out_base);
 
   const int n_merged = s_.n_merged;
   const int64_t out_at = out.seq_base(bh) + (int64_t)out_base * out.stride_s + piece * 4;
@@ -654,7 +678,7 @@ hipError_t launch_round_f32(const RoundCall& c, hipStream_t st) {
   hipLaunchKernelGGL((round_f32_kernel<D, CHUNK>), dim3((unsigned)((int64_t)c.n_bh * blocks + edge_blocks)), dim3(THREADS), lds,
                      st, static_cast<const float*>(c.K), static_cast<const float*>(c.V), c.deg_in, c.in, c.seq, blocks, m_full,
                      m_tail, static_cast<float*>(c.K_out), static_cast<float*>(c.V_out), c.deg_out, c.out, c.deg_out_stride,
-                     c.map_out, c.in.deg_stride, c.map_stride, c.map_offset,
+                     c.map, c.in.deg_stride,
                      EdgeBlocks<true>{(int)edge_blocks, c.edges ? *c.edges : EdgeCopy{}});
   return hipGetLastError();
 }
@@ -679,7 +703,7 @@ hipError_t launch_round_t(const RoundCall& c, hipStream_t st) {
     hipLaunchKernelGGL((round_small_kernel<D, TOK, PG, ED>), dim3((unsigned)(total + edge_blocks)), dim3(THREADS), lds, st, \
                        static_cast<const __bf16*>(c.K), static_cast<const __bf16*>(c.V), c.deg_in, c.in, c.seq, c.chunk, \
                        blocks, m_full, m_tail, static_cast<__bf16*>(c.K_out), static_cast<__bf16*>(c.V_out), c.deg_out,  \
-                       c.out, c.deg_out_stride, c.map_out, c.in.deg_stride, c.map_stride, c.map_offset, c.pin, pout,     \
+                       c.out, c.deg_out_stride, c.map, c.in.deg_stride, c.pin, pout,                                     \
                        c.out_k.table != nullptr, c.out_v.table != nullptr, EdgeBlocks<ED>{__VA_ARGS__});                 \
   } while (0)
   if (c.pin.table || pout.table) {

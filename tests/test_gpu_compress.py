@@ -349,6 +349,32 @@ def test_rounds_of_one_chunk_per_workgroup(whole, tail, r, directions, chunk, di
             assert torch.equal(a, e), f"{n} differs from the separate kernels"
 
 
+@pytest.mark.parametrize("route", [None, "full_rounds", "defer_always"])
+@pytest.mark.parametrize("dtype,seq,dim,chunk,rounds", [
+    ("bf16", 1, 128, 64, [1.0, 1.0]),                    # a token alone in every round
+    ("bf16", 4099, 128, 2, [1.0, 1.0, 0.5]),             # the smallest chunk, a one-token tail
+    ("bf16", 3001, 64, 64, [1.0, 1.0, 1.0, 0.6]),        # eight original tokens to an input token of the last round
+    ("bf16", 2500, 128, 384, [1.0, 0.7]),
+    ("bf16", 2561, 128, 512, [1.0, 1.0]),                # tails of one token and of a half chunk
+    ("bf16", 5121, 128, 1024, [1.0, 0.8, 1.0]),          # after a round below 1 the chunks no longer nest
+    ("bf16", 9000, 128, 2048, [1.0, 1.0, 0.3]),
+    ("f32", 777, 64, 128, [1.0, 1.0, 0.5]),
+    ("f32", 1200, 32, 300, [0.9, 1.0]),
+])
+def test_assignments_of_several_rounds_are_the_rounds_maps_chained(dtype, seq, dim, chunk, rounds, route):
+    _say(f"chained maps {dtype} S={seq} D={dim} c={chunk} rounds={rounds} route={route}")
+    K, V, _ = kv_host(67, 2, seq, dim, dtype, alpha=0.9)
+    K, V = K.to(DEV), V.to(DEV)
+    got = _compress(route, K, V, chunk, rounds=rounds)
+    k, v, deg, to = K, V, None, None
+    for r in rounds:
+        k, v, deg, m = ckv.compress(k, v, chunk, rounds=[r], deg=deg)
+        to = m if to is None else torch.gather(m, 2, to.long())
+    torch.cuda.synchronize()
+    for n, a, e in zip(["K'", "V'", "deg'", "assign"], got, (k, v, deg, to)):
+        assert torch.equal(a, e), f"{n} differs from the chained rounds"
+
+
 @pytest.mark.parametrize("dtype,dim,chunk", [("bf16", 128, 384), ("bf16", 128, 1024), ("bf16", 64, 2048), ("f32", 64, 1024),
                                              ("bf16", 128, 2)])
 @pytest.mark.parametrize("whole,tail,r,directions", [
