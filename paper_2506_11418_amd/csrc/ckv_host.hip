@@ -88,6 +88,14 @@ int seq_after_round(int len, int chunk, float r, int n_sink, int n_recent, int s
 // 273) - unless one workgroup's rows fill a CU's LDS, where the pair wins from about 1536 chunks on (dim 128, chunk 512,
 // 32768 tokens: 40 sequences 403 / 377, 48 445 / 451, 64 554 / 586; dim 64, chunk 1024: 32 x 65536 417 / 407, 128 x 65536
 // 1512 / 1542).
+// Whether round j ranks the edges of all chunks of a sequence together.  At r = 1 every edge is merged whichever way
+// they are ranked, so that round runs like one with per-chunk selection: no ranking, one launch for small chunks, deferred
+// values (to a quarter, dim 128, us, ranked / not: 8 x 8000 tokens, chunk 256 60.1 / 27.6; 8 x 20001, chunk 384 84.6 / 74.4;
+// 64 x 32768, chunk 64 680 / 426, chunk 1024 669 / 606).
+bool ranks_whole_sequence(const ckv_params* p, const ckv_plan_t* plan, int j) {
+  return p->scope == CKV_SCOPE_HEAD && plan->round_r[j] != 1.0f;
+}
+
 enum RoundMode { ROUND_FULL = 0, ROUND_KEYS_ONLY = 1, ROUND_ORIGIN = 2 };
 constexpr int64_t kDeferMinChunks = 1024, kDeferMinChunksFullLds = 1536;
 
@@ -103,7 +111,7 @@ void plan_routes(const ckv_layout* in, const ckv_params* p, const ckv_plan_t* pl
     int lo2, hi2;   // both rounds must have tokens to cluster (a cache of sinks and recents only is copied)
     clusterable(plan->round_len[j + 1], p->n_sink, p->n_recent, &lo2, &hi2);
     const bool pair = allow && (j == 0 || j + 2 == plan->n_rounds) && plan->round_r[j] == 1.0f &&
-                      p->scope == CKV_SCOPE_CHUNK && hi > lo && hi2 > lo2 &&
+                      !ranks_whole_sequence(p, plan, j + 1) && hi > lo && hi2 > lo2 &&
                       (force || n_bh * div_up(plan->round_len[j + 1], p->chunk) >= worth);
     if (pair) {
       mode[j] = ROUND_KEYS_ONLY;
@@ -282,8 +290,9 @@ int run_rounds(const void* K, const void* V, const int32_t* deg_in, const ckv_la
     const int64_t oDegStride = oView.deg_stride;
     int32_t* map = nullptr;
     if (assign) map = (j == 0) ? assign : reinterpret_cast<int32_t*>(ws + w.map);
-    bool fold = assign && j > 0 && p->scope == CKV_SCOPE_CHUNK && p->n_sink == 0 && p->n_recent == 0;   // see RoundMap
+    bool fold = assign && j > 0 && p->n_sink == 0 && p->n_recent == 0;   // see RoundMap
     for (int i = 0; i < j; ++i) fold = fold && plan.round_r[i] == 1.0f;
+    const bool whole = ranks_whole_sequence(p, &plan, j);
     const bool keys_only = mode[j] == ROUND_KEYS_ONLY, from_origin = mode[j] == ROUND_ORIGIN;
     hipError_t err = hipSuccess;
     EdgeCopy edges{};
@@ -318,14 +327,14 @@ int run_rounds(const void* K, const void* V, const int32_t* deg_in, const ckv_la
       int32_t* moDeg = pov.table ? oDeg : oDeg + lo;
       const EdgeCopy* ride = edges.total > 0 ? &edges : nullptr;
       const RoundMap rmap = fold ? RoundMap{assign, in->seq, 0, j, in->seq} : RoundMap{map ? map + lo : nullptr, len, lo, 0, 0};
-      if (mode[j] == ROUND_FULL && p->scope == CKV_SCOPE_CHUNK && round_fits(in->dtype, in->dim, n_bh, mid, p->chunk, ride, pc != nullptr)) {
+      if (mode[j] == ROUND_FULL && !whole && round_fits(in->dtype, in->dim, n_bh, mid, p->chunk, ride, pc != nullptr)) {
         err = launch_round(RoundCall{mK, mV, mDeg, curView, n_bh, mid, p->chunk, plan.round_r[j], moK, moV, moDeg, oView,
                                      oDegStride, rmap, pin, pok, pov, ride}, in->dtype, in->dim, s);
       } else {
         err = launch_match(mK, in->dtype, in->dim, curView, n_bh, mid, p->chunk, dst, score, s, pin);
         if (err != hipSuccess) return hip_status(err);
         int32_t* sel = nullptr;
-        if (p->scope == CKV_SCOPE_HEAD) {
+        if (whole) {
           sel = reinterpret_cast<int32_t*>(ws + w.sel);
           err = launch_global_select(score, n_bh, mid, p->chunk, plan.round_r[j], sel, s);
           if (err != hipSuccess) return hip_status(err);

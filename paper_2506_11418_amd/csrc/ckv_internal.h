@@ -101,15 +101,16 @@ hipError_t launch_edges(const EdgeCopy& edges, hipStream_t st);
 // of, and is replaced by that token's output index.  After j rounds that merged every edge of every chunk of `chunk`
 // tokens and set none aside, the tokens [u, u + chunk) of this round's input, u a multiple of chunk, are made of the
 // original tokens [u << j, (u + chunk) << j) and of no others, so that a workgroup replaces the entries of its own
-// chunks (of its own launch, us -> in the round: 8 x 2048 tokens, chunk 256, two rounds 27.8 -> 25.7; 8 x 20001, chunk 384 76.4 ->
-// 73.8; 64 x 20001, chunk 1024 438.9 -> 434.5).
+// chunks (two rounds with a launch for it behind the second / without, us: 8 x 2048 tokens, chunk 256 27.8 / 25.7; 8 x
+// 20001, chunk 384 76.4 / 73.8; 64 x 20001, chunk 1024 438.9 / 434.5).
 struct RoundMap {
   int32_t* p;                  // or NULL
   int64_t stride;
   int offset, fold, len;
 };
 
-// Per-chunk top-r selection + degree-weighted merge + order-preserving compaction.  deg_in[bh*deg_in_stride + t].  lists_out != NULL: keys-only first round of a
+// Per-chunk top-r selection + degree-weighted merge + order-preserving compaction.
+// deg_in[bh*deg_in_stride + t].  lists_out != NULL: keys-only first round of a
 // deferred-value pair (V, V_out unused); org != NULL: its second round (V unused).
 hipError_t launch_merge(const void* K, const void* V, const int32_t* deg_in, int dtype, int dim,
                         TensorView in, int n_bh, int seq, int chunk, float r,

@@ -356,6 +356,9 @@ def test_rounds_of_one_chunk_per_workgroup(whole, tail, r, directions, chunk, di
     ("bf16", 3001, 64, 64, [1.0, 1.0, 1.0, 0.6]),        # eight original tokens to an input token of the last round
     ("bf16", 2500, 128, 384, [1.0, 0.7]),
     ("bf16", 2561, 128, 512, [1.0, 1.0]),                # tails of one token and of a half chunk
+    ("bf16", 1700, 128, 128, [1.0, 1.0]),
+    ("bf16", 3333, 64, 256, [1.0, 1.0, 0.4]),
+    ("bf16", 3100, 64, 1024, [1.0, 1.0]),
     ("bf16", 5121, 128, 1024, [1.0, 0.8, 1.0]),          # after a round below 1 the chunks no longer nest
     ("bf16", 9000, 128, 2048, [1.0, 1.0, 0.3]),
     ("f32", 777, 64, 128, [1.0, 1.0, 0.5]),
@@ -369,6 +372,29 @@ def test_assignments_of_several_rounds_are_the_rounds_maps_chained(dtype, seq, d
     k, v, deg, to = K, V, None, None
     for r in rounds:
         k, v, deg, m = ckv.compress(k, v, chunk, rounds=[r], deg=deg)
+        to = m if to is None else torch.gather(m, 2, to.long())
+    torch.cuda.synchronize()
+    for n, a, e in zip(["K'", "V'", "deg'", "assign"], got, (k, v, deg, to)):
+        assert torch.equal(a, e), f"{n} differs from the chained rounds"
+
+
+@pytest.mark.parametrize("dtype,seq,dim,chunk,rounds,n_sink,n_recent", [
+    ("bf16", 2049, 128, 256, [1.0, 1.0], 0, 0),
+    ("bf16", 5000, 128, 384, [1.0, 1.0], 4, 9),
+    ("bf16", 3500, 64, 512, [1.0, 0.7, 1.0], 0, 0),      # the second round ranks the whole sequence
+    ("bf16", 70001, 128, 1024, [1.0, 0.4], 0, 0),
+    ("f32", 1000, 64, 64, [1.0], 0, 0),
+])
+def test_ranking_over_the_whole_sequence_where_every_edge_is_merged(dtype, seq, dim, chunk, rounds, n_sink, n_recent):
+    """A round at r = 1 gives the same bits with either selection, alone and among others."""
+    _say(f"whole-sequence ranking at r = 1 {dtype} S={seq} D={dim} c={chunk} rounds={rounds}")
+    K, V, _ = kv_host(71, 2, seq, dim, dtype, alpha=0.9)
+    K, V = K.to(DEV), V.to(DEV)
+    got = ckv.compress(K, V, chunk, rounds=rounds, n_sink=n_sink, n_recent=n_recent, scope="head")
+    k, v, deg, to = K, V, None, None
+    for r in rounds:
+        k, v, deg, m = ckv.compress(k, v, chunk, rounds=[r], deg=deg, n_sink=n_sink, n_recent=n_recent,
+                                    scope="chunk" if r == 1.0 else "head")
         to = m if to is None else torch.gather(m, 2, to.long())
     torch.cuda.synchronize()
     for n, a, e in zip(["K'", "V'", "deg'", "assign"], got, (k, v, deg, to)):
