@@ -125,6 +125,25 @@ def test_one_workspace_for_the_capacity_serves_every_length(H, cap, lengths):
         _check(q, K[:, :, :n], V[:, :, :n], deg[:, :, :n], None, o, ATTN_TOL, f"length {n}")
 
 
+@pytest.mark.parametrize("B,Hkv,G,L,D", [
+    (1, 8, 4, 128, 128), (1, 8, 4, 129, 128), (3, 2, 1, 256, 64), (3, 2, 8, 257, 64),     # two steps of four waves, and a row more
+    (24, 8, 2, 1536, 128), (24, 8, 1, 1537, 64), (32, 8, 1, 700, 128), (33, 8, 1, 300, 64),   # a workgroup of eight waves per pair
+])
+def test_caches_of_one_slice(B, Hkv, G, L, D):
+    """Sequences of lengths down to zero on both sides of the sizes up to which a cache is not cut."""
+    _say(f"one slice B={B} Hkv={Hkv} G={G} L={L} D={D}")
+    K, V, _ = kv_host(83, Hkv, L, D, "bf16", n_outlier=0)
+    K, V = K.expand(B, Hkv, L, D).contiguous().to(DEV), V.expand(B, Hkv, L, D).contiguous().to(DEV)
+    q = query_host(84, B, Hkv * G, D, "bf16").to(DEV)
+    deg = torch.from_numpy(np.random.default_rng(L).integers(1, 6, (B, Hkv, L)).astype(np.int32)).to(DEV)
+    lens = torch.tensor([L - b * L // max(B - 1, 1) for b in range(B)], dtype=torch.int32, device=DEV)
+    o = ckv.decode_attn(q, K, V, lens=lens, deg=deg, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    some = [b for b in range(B) if int(lens[b]) > 0 and (B <= 8 or b % 5 == 0)]
+    assert B == 1 or not o[B - 1].any()              # an empty cache
+    _check(q[some], K[some], V[some], deg[some], lens[some], o[some], what="one slice")
+
+
 def test_outlier_keys_large_logits_bf16():
     """Keys with x10 outlier channels give logits of several tens: the softmax must stay stable."""
     _say("attn outliers")
