@@ -74,8 +74,29 @@ struct RowOf {
   }
 };
 
-__device__ __forceinline__ float bf16_at(const uint32_t* w, int e) {
-  return __uint_as_float((e & 1) ? (w[e >> 1] & 0xffff0000u) : (w[e >> 1] << 16));
+typedef __attribute__((ext_vector_type(4))) short s16x4;
+
+// Four fp32 weights as sums of three bf16 numbers each, largest parts first, exactly.
+__device__ __forceinline__ void split_weights(const float (&z)[4], s16x4 (&part)[3]) {
+  uint32_t u[3][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    u[0][i] = __float_as_uint(z[i]);
+    const float r = z[i] - __uint_as_float(u[0][i] & 0xffff0000u);
+    u[1][i] = __float_as_uint(r);
+    u[2][i] = __float_as_uint(r - __uint_as_float(u[1][i] & 0xffff0000u));
+  }
+#pragma unroll
+  for (int p = 0; p < 3; ++p)      // the upper halves of two words side by side
+    part[p] = __builtin_bit_cast(s16x4, make_uint2(__builtin_amdgcn_perm(u[p][1], u[p][0], 0x07060302u),
+                                                   __builtin_amdgcn_perm(u[p][3], u[p][2], 0x07060302u)));
+}
+
+// The lower (0) or upper (1) bf16 of four words.
+template <int HI>
+__device__ __forceinline__ s16x4 column(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+  constexpr uint32_t sel = HI ? 0x07060302u : 0x05040100u;
+  return __builtin_bit_cast(s16x4, make_uint2(__builtin_amdgcn_perm(b, a, sel), __builtin_amdgcn_perm(d, c, sel)));
 }
 
 // K piece . q piece for 16 tokens x 16 heads: one MFMA of depth 32, or two of depth 16 where a row has only
@@ -85,7 +106,6 @@ template <bool SPLIT>
 __device__ __forceinline__ f32x4 qk_step(const uint4& k, const uint4& qv) {
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
   if constexpr (SPLIT) {
-    typedef __attribute__((ext_vector_type(4))) short s16x4;
     struct Halves { s16x4 h[2]; };
     const Halves a = __builtin_bit_cast(Halves, k), b = __builtin_bit_cast(Halves, qv);
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a.h[0], b.h[0], zero, 0, 0, 0) +
@@ -201,20 +221,22 @@ __device__ __forceinline__ void merge_slices(const float* __restrict__ o_part, c
 //   S[token, head]: K rows are the A operand (through a 4 KiB region of LDS per wave and back, no
 //     barrier: a wave's LDS accesses are in order), q the B operand.  MFMA row 4q + i is token 4i + q of
 //     the tile, so that a lane's four results belong to tokens q, 4 + q, 8 + q, 12 + q;
-//   O[head, channel]: those four weights, in fp32, ARE the A operand of four fp32 MFMAs of depth 4 (lane
-//     group q = contraction index q), and the V rows a lane group loads are its B operand: wave-wide
-//     load i covers the four consecutive rows 4i .. 4i + 3.
-// Weights, sums and products stay fp32 (bf16 values widen exactly).  The softmax reference of a head
+//   O[head, channel]: those four weights, each an exact sum of three bf16 numbers, ARE the A operand of three bf16
+//     MFMAs of depth 16 (contraction index 4q + i = token 4i + q), and the V rows a lane group loads are their B
+//     operand: wave-wide load i covers the four consecutive rows 4i .. 4i + 3.
+// Weights, sums and products stay fp32 (the parts add up to the fp32 weight, products are exact, sums accumulate in
+// fp32).  The matrix unit rounds its sums downwards: over a long cache of values around zero that bias added up
+// (32768 tokens: 4.4e-7 of the result, fp32 MFMAs of depth 4 2.35e-7), so every other tile, and every other wave's, sums
+// up the negated weights and is subtracted: 2.24e-7.  The softmax reference of a head
 // moves only when a logit exceeds it by more than 8 (in log2): weights stay below 2^8, which costs no
 // precision, and after the first tiles the rescaling of the accumulators is rare.
 //
 // What bounds it: HBM reads (a kernel that does nothing but read reaches 6.2 TB/s on 134 MB, 6.7 on 403
-// MB).  Per token row a SIMD spends 70 MFMA cycles and some 15 vector instructions where its share of that
-// rate takes 200 cycles; the dot products, row sums and weighted adds it had in vector instructions before
-// took 90 per row and four heads.  Per layer, against that form (bf16, dim 128): 403 MB of 16 sequences,
-// 4 heads per KV head, 74 us (83); the same bytes with 8 heads 71 us (133); on pages of 16 tokens 75 us (92);
-// 134 MB of one sequence 31.4 us (34.7).
-// Time line of that last one, from clock readings in the kernel: the streaming loops end between 17 and
+// MB), and for short caches the chain of a tile.  Four fp32 MFMAs of depth 4 per channel took 1024 MFMA cycles a tile, three
+// bf16 ones of depth 16 a third to half of that and fewer instructions to widen V.  Per layer, fp32 / bf16 parts (us, 4 heads
+// per KV head, dim 128): one sequence of 515 tokens 8.65 / 8.18, of 32768 (134 MB) 29.6 / 27.5; 16 sequences of 1000 17.8 /
+// 15.9, of 8000 92 / 88; 32 of 1000 28.5 / 24.0; 4 of 32768, 8 heads 96.3 / 92.9; dim 64, 8 of 5000, 2 heads 22.8 / 19.8.
+// Time line of the 134 MB launch with fp32 MFMAs, from clock readings in the kernel: the streaming loops end between 17 and
 // 24 us (3 us between the waves of a workgroup), the reduction after its slowest wave takes 1.8 us, partials are
 // acknowledged and counted in 1.1 us, the merge by the last arriver takes 2.4 us.
 //
@@ -327,7 +349,7 @@ __global__ __launch_bounds__(W * 64, 2) void attn_mfma_kernel(
 #pragma unroll
   for (int j = 0; j < R::EV; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
   float ref = -INFINITY, ref_used = 0.f, l = 0.f;   // of this lane's head; ref_used: 0 until a token counted
-  auto consume_tile = [&](const Tile& st, int t) {
+  auto consume_tile = [&](const Tile& st, int t, float sign) {
 #pragma unroll
     for (int i = 0; i < R::KL; ++i) {
       const int at = R::lds(R::KROWS * i + lane / R::PIECES, lane % R::PIECES);
@@ -382,35 +404,47 @@ __global__ __launch_bounds__(W * 64, 2) void attn_mfma_kernel(
 #pragma unroll
     for (int i = 0; i < 4; ++i) z[i] = exp2_raw(z[i] - ref_used);
     l += (z[0] + z[1]) + (z[2] + z[3]);
-    // the tile's own sum from zero, then one addition into the running sums: a quarter of the roundings there
+    // the tile's own sum from zero, then one addition into the running sums: a quarter of the roundings there.
+    // The weights as three bf16 parts (8 + 8 + 8 bits: exactly the 24 of an fp32), the smallest first, all of a tile
+    // with one sign
+    s16x4 part[3];
 #pragma unroll
-    for (int j0 = 0; j0 < R::EV; j0 += 4) {
-      f32x4 sum[4];
+    for (int i = 0; i < 4; ++i) z[i] *= sign;
+    split_weights(z, part);
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+    for (int j = 0; j < R::EV; j += 2) {
+      const s16x4 v0 = column<0>(v[0].w[j / 2], v[1].w[j / 2], v[2].w[j / 2], v[3].w[j / 2]);
+      const s16x4 v1 = column<1>(v[0].w[j / 2], v[1].w[j / 2], v[2].w[j / 2], v[3].w[j / 2]);
+      f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-          sum[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(z[i], bf16_at(v[i].w, j0 + j), i == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : sum[j], 0, 0, 0);
+      for (int p = 2; p >= 0; --p) {
+        s0 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(part[p], v0, s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(part[p], v1, s1, 0, 0, 0);
+      }
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[j0 + j] += sum[j];
+      for (int i = 0; i < 4; ++i) {
+        acc[j][i] = fmaf(s0[i], sign, acc[j][i]);
+        acc[j + 1][i] = fmaf(s1[i], sign, acc[j + 1][i]);
+      }
     }
   };
-  auto consume = [&](const Stage& st, int t) {
+  auto consume = [&](const Stage& st, int t, float sign) {
 #pragma unroll
-    for (int u = 0; u < R::TILES; ++u) consume_tile(st.tile[u], t + 16 * u);
+    for (int u = 0; u < R::TILES; ++u) consume_tile(st.tile[u], t + 16 * u, u % 2 ? -sign : sign);
   };
   // the loads of a wave's next step are issued before this one is consumed (two register sets)
   constexpr int STEP = W * R::TOKENS;
   const int tw = t0 + wave * R::TOKENS;
   if (tw < t1) {
     Stage sa, sb;
+    const float sign = (wave & 1) ? -1.f : 1.f;
     issue(sa, tw);
     for (int t = tw; t < t1; t += 2 * STEP) {
       issue(sb, t + STEP);
-      consume(sa, t);
+      consume(sa, t, sign);
       if (t + STEP >= t1) break;
       issue(sa, t + 2 * STEP);
-      consume(sb, t + STEP);
+      consume(sb, t + STEP, -sign);
     }
   }
 
