@@ -7,7 +7,9 @@ shared library has not been built, or a call fails, an exception is raised.
 The calls of a decode step and compress() are marshalled by csrc/binding.cpp when outputs and workspace are
 passed in and everything is well-formed (one layer's step over a 515-token cache, append and attention, two
 launches: 12.1 us, 27.6 with ctypes; compress() of 1024 tokens 3.9 us on the caller's side, 15).  What it does not
-take (None), or the library refuses, goes on to the ctypes route below, which makes the call or reports it.
+take (None) goes on to the ctypes route below, which makes the call or reports it.  A status means that the call has
+been made: it is raised and the call not made again, for a status of the runtime can come from behind a launch (an
+append made twice would advance the lengths twice).
 """
 from __future__ import annotations
 
@@ -226,10 +228,14 @@ def compress(K: torch.Tensor, V: torch.Tensor, chunk: int, retain_ratio: float =
     `out` may pass preallocated (K_out, V_out, deg_out, assign) and `workspace` a uint8 tensor, so
     that a timed loop allocates nothing."""
     if workspace is not None and type(out) is tuple and len(out) == 4 and K.is_cuda:
-        if (_native or _binding()).compress(
-                K, V, deg, chunk, retain_ratio, rounds if rounds is None or type(rounds) is list else list(rounds), n_sink,
-                n_recent, SCOPES.get(scope), ROUTES.get(route), *out, workspace, _raw_stream()) == 0:
+        st = (_native or _binding()).compress(
+            K, V, deg, chunk, retain_ratio, rounds if rounds is None or type(rounds) is list else list(rounds), n_sink,
+            n_recent, SCOPES.get(scope), ROUTES.get(route), *out, workspace, _raw_stream())
+        if st == 0:
             return out
+        if st is not None:
+            plan(layout_of(K, deg), make_params(chunk, retain_ratio, rounds, n_sink, n_recent, scope, route))   # (raises what it refuses)
+            raise CkvError(st, "ckv_compress")
     lay = layout_of(K, deg)
     if layout_of(V).dtype != lay.dtype or V.shape != K.shape:
         raise ValueError("K and V must have the same shape and dtype")
@@ -268,8 +274,11 @@ def decode_attn(q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, lens: Optiona
     """ckv_decode_attn: q [B,Hq,D], K/V [B,Hkv,L,D], lens [B] int32, deg [B,Hkv,L] int32 -> o [B,Hq,D].
     A `workspace` passed in must have been zero-filled when it was allocated (torch.zeros)."""
     if out is not None and workspace is not None and q.is_cuda:
-        if (_native or _binding()).decode_attn(q, K, V, lens, deg, scale, out, workspace, _raw_stream()) == 0:
+        st = (_native or _binding()).decode_attn(q, K, V, lens, deg, scale, out, workspace, _raw_stream())
+        if st == 0:
             return out
+        if st is not None:
+            raise CkvError(st, "ckv_decode_attn")
     lay = layout_of(K, deg)
     if not q.is_contiguous() or q.dim() != 3 or q.dtype != K.dtype:
         raise ValueError("q must be a contiguous [batch, q_heads, dim] tensor of the cache dtype")
@@ -327,8 +336,11 @@ def append(k_new: torch.Tensor, v_new: torch.Tensor, K: torch.Tensor, V: torch.T
     [batch, heads, capacity, dim] (deg [batch, heads, capacity] := 1 there) at row lens[b]
     (device int32, incremented by the call) or at row `pos`."""
     if K.is_cuda:
-        if (_native or _binding()).append(k_new, v_new, K, V, deg, lens, pos, _raw_stream()) == 0:
+        st = (_native or _binding()).append(k_new, v_new, K, V, deg, lens, pos, _raw_stream())
+        if st == 0:
             return
+        if st is not None:
+            raise CkvError(st, "ckv_append")
     lay = layout_of(K, deg)
     B, H, _, D = K.shape
     for t in (k_new, v_new):
@@ -357,9 +369,12 @@ def paged_decode_attn(q, K_pool, V_pool, deg_pool, block_table, lens, max_len: i
                       out_dtype=None, out=None, workspace=None):
     """ckv_paged_decode_attn: Eq. 3 over a block-paged cache read in place."""
     if out is not None and workspace is not None and q.is_cuda:
-        if (_native or _binding()).paged_decode_attn(q, K_pool, V_pool, deg_pool, block_table, lens, max_len, scale, out,
-                                                     workspace, _raw_stream()) == 0:
+        st = (_native or _binding()).paged_decode_attn(q, K_pool, V_pool, deg_pool, block_table, lens, max_len, scale, out,
+                                                       workspace, _raw_stream())
+        if st == 0:
             return out
+        if st is not None:
+            raise CkvError(st, "ckv_paged_decode_attn")
     pl = paged_layout_of(K_pool, block_table)
     q_heads = q.shape[1]
     if not q.is_contiguous() or q.dim() != 3 or q.dtype != K_pool.dtype:
@@ -383,8 +398,11 @@ def paged_decode_attn(q, K_pool, V_pool, deg_pool, block_table, lens, max_len: i
 def paged_append(k_new, v_new, K_pool, V_pool, deg_pool, block_table, lens) -> None:
     """ckv_paged_append: one new token per sequence at position lens[b] (then lens[b] += 1)."""
     if K_pool.is_cuda:
-        if (_native or _binding()).paged_append(k_new, v_new, K_pool, V_pool, deg_pool, block_table, lens, _raw_stream()) == 0:
+        st = (_native or _binding()).paged_append(k_new, v_new, K_pool, V_pool, deg_pool, block_table, lens, _raw_stream())
+        if st == 0:
             return
+        if st is not None:
+            raise CkvError(st, "ckv_paged_append")
     pl = paged_layout_of(K_pool, block_table)
     for t in (k_new, v_new):
         if tuple(t.shape) != (pl.batch, pl.heads, pl.dim) or not t.is_contiguous() or t.dtype != K_pool.dtype:
