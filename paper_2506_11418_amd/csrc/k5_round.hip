@@ -33,7 +33,7 @@ constexpr uint32_t kPlace = 0x1ffffu;
 // token u is row (u & 1) * HALF + u / 2): which edges are kept, who merges into whom, where everything goes.
 template <int HALF>
 struct RoundLds {
-  __attribute__((aligned(16))) float score[HALF];
+  __attribute__((aligned(16))) uint32_t key[HALF];     // a source's score (rank_key)
   __attribute__((aligned(16))) int16_t kept[HALF];     // destination a kept source merges into, or -1
   __attribute__((aligned(16))) int16_t slot[2 * HALF]; // output row of a retained token
   int16_t dst[HALF], start[HALF], place[HALF];
@@ -45,8 +45,12 @@ struct RoundLds {
   int n_merged, n_copied, sel[2];
 };
 
-// In: score, dst (-1: nothing to merge into), deg and word of every row; cnt, desc, n_merged, n_copied zero, scores of
-// sources that do not exist -inf.  Chunks of `chunk` tokens, the last one of the block possibly short: m_full / m_tail
+// A source's score as a number that orders like it, a NaN beyond the infinity of its sign: whatever the bits, exactly m
+// edges are kept.  Below the largest number, so that there is a next larger one.
+__device__ __forceinline__ uint32_t rank_key(float score) { return min(order_key(score), 0xfffffffeu); }
+
+// In: key, dst (-1: nothing to merge into), deg and word of every row; cnt, desc, n_merged, n_copied zero, keys of
+// sources that do not exist zero.  Chunks of `chunk` tokens, the last one of the block possibly short: m_full / m_tail
 // edges of a whole / short one are merged.  Begins and ends with a barrier.
 template <int HALF, int THREADS>
 __device__ __forceinline__ void round_lists(RoundLds<HALF>& s, int n_tok, int chunk, int m_full, int m_tail,
@@ -77,15 +81,14 @@ __device__ __forceinline__ void round_lists(RoundLds<HALF>& s, int n_tok, int ch
   if (a < nA && m > 0) {
     d = s.dst[a];
     if (HALF <= 128 && m < nAc) {
-      // an equal score of an earlier source ranks above: those are counted from the score itself on, the later
-      // ones from the next larger number on (sources that do not exist hold -inf and come later)
-      const float si = s.score[a] + 0.f;           // (-0 as +0)
-      const float above = __uint_as_float(__float_as_uint(si) + (si < 0.f ? 0xffffffffu : 1u));
+      // an equal score of an earlier source ranks above: those are counted from the key itself on, the later
+      // ones from the next larger number on (sources that do not exist hold 0 and come later)
+      const uint32_t key = s.key[a], above = key + 1;
       int rank = 0;
       for (int o = a_lo + 4 * sub; o < a_lo + nAc; o += 4 * LPA) {
-        const float4 so = *reinterpret_cast<const float4*>(&s.score[o]);
-        rank += (so.x >= (o < a ? si : above)) + (so.y >= (o + 1 < a ? si : above)) +
-                (so.z >= (o + 2 < a ? si : above)) + (so.w >= (o + 3 < a ? si : above));
+        const uint4 so = *reinterpret_cast<const uint4*>(&s.key[o]);
+        rank += (so.x >= (o < a ? key : above)) + (so.y >= (o + 1 < a ? key : above)) +
+                (so.z >= (o + 2 < a ? key : above)) + (so.w >= (o + 3 < a ? key : above));
       }
 #pragma unroll
       for (int x = 1; x < LPA; x <<= 1) rank += __shfl_xor(rank, x);
@@ -97,7 +100,7 @@ __device__ __forceinline__ void round_lists(RoundLds<HALF>& s, int n_tok, int ch
     // the square: 512 sources take 4 us of the vector units)
     if (m > 0 && m < nAc) {
       uint32_t* histogram = s.members;             // (not in use yet)
-      const uint32_t key = a < nA ? order_key(s.score[a]) : 0u;
+      const uint32_t key = s.key[a];
       uint32_t cut = 0;
       int left = m, equal = 0;
 #pragma unroll 1
@@ -132,7 +135,7 @@ __device__ __forceinline__ void round_lists(RoundLds<HALF>& s, int n_tok, int ch
       if (d >= 0 && key <= cut) {
         int earlier = 0;
         if (key == cut && left < equal)
-          for (int o = 0; o < a; ++o) earlier += order_key(s.score[o]) == cut;
+          for (int o = 0; o < a; ++o) earlier += s.key[o] == cut;
         if (key < cut || earlier >= left) d = -1;
       }
     }
@@ -341,7 +344,7 @@ __global__ __launch_bounds__(TOK * D / 64, 4) void round_small_kernel(
   auto swz = [](int row, int pc) -> int { return row * ROWB + (((pc ^ (row >> KEYSHIFT)) & (OCT - 1)) << 4); };
   const int row0 = (rg & 1) * HALF + (rg >> 1);      // LDS row of token rg; 32 tokens on: 16 rows on, same XOR
   const int lds0 = swz(row0, piece);
-  if (tid < HALF) { s_.cnt[tid] = 0; s_.score[tid] = -INFINITY; }
+  if (tid < HALF) { s_.cnt[tid] = 0; s_.key[tid] = 0; }
   if (tid < TOK) {
     const int row = (tid & 1) * HALF + (tid >> 1);
     s_.deg[row] = dg;
@@ -367,7 +370,7 @@ __global__ __launch_bounds__(TOK * D / 64, 4) void round_small_kernel(
     const int tpc = chunk >> 6, first = at & -tpc;                         // tiles per chunk (a power of two); its first tile
     const int lo = WPT == 2 ? (hb * tpc + 1) / 2 : 0, hi = WPT == 2 && hb == 0 ? (tpc + 1) / 2 : tpc;
     float best = -INFINITY, inva = 0.f;
-    int bestj = 0;
+    int bestj = first * 32;                        // (where no score compares: the first row of its own chunk)
     if (at * 32 < nA && lo < hi) {                 // (the same for the whole wave)
       // two tiles at a time where there are two: their MFMA chains run side by side.  The source operands pass
       // through (the values wait in 32 registers): the sum of their squares is taken as they do, in the order of
@@ -426,7 +429,7 @@ __global__ __launch_bounds__(TOK * D / 64, 4) void round_small_kernel(
     }
     if (hb == 0 && half == 0 && a < nA) {
       s_.dst[a] = (nB <= first * 32) ? (int16_t)-1 : (int16_t)bestj;  // a one-token tail chunk: nothing to match
-      s_.score[a] = best * inva;
+      s_.key[a] = rank_key(best * inva);
     }
   }
   round_lists<HALF, THREADS>(s_, n_tok, chunk, m_full, m_tail, map, bh, t0, out_base);
@@ -563,7 +566,7 @@ __global__ __launch_bounds__(THREADS) void round_f32_kernel(
 #pragma unroll
   for (int it = 0; it < PASSES; ++it)
     vx[it] = *reinterpret_cast<const float4*>(V + at + (int64_t)min(it * NRG + rg, n_tok - 1) * in.stride_s);
-  if (tid < HALF) { s_.cnt[tid] = 0; s_.score[tid] = -INFINITY; }
+  if (tid < HALF) { s_.cnt[tid] = 0; s_.key[tid] = 0; }
   if (tid < CHUNK) {
     const int row = row_of(tid);
     s_.deg[row] = dg;
@@ -628,7 +631,7 @@ __global__ __launch_bounds__(THREADS) void round_f32_kernel(
     const int a = ty + TY * i;
     if (tx == 0 && a < nA) {
       s_.dst[a] = nB == 0 ? (int16_t)-1 : (int16_t)bestj;
-      s_.score[a] = best * s_inv[a];
+      s_.key[a] = rank_key(best * s_inv[a]);
     }
   }
   round_lists<HALF, THREADS>(s_, n_tok, CHUNK, m_full, m_tail, map, bh, t0, out_base);

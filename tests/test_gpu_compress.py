@@ -472,6 +472,43 @@ def test_fp32_rounds_of_small_chunks_in_one_launch(seq, dim, r, n_sink, n_recent
             assert torch.equal(a, e), f"{n} differs from the separate kernels"
 
 
+@pytest.mark.parametrize("dtype,dim,chunk,r", [
+    ("bf16", 128, 64, 1.0), ("bf16", 64, 64, 0.5), ("bf16", 128, 128, 0.7), ("bf16", 64, 256, 0.5), ("bf16", 64, 512, 0.6),
+    ("bf16", 128, 1024, 0.5), ("f32", 64, 64, 0.5), ("f32", 128, 128, 1.0), ("f32", 32, 256, 0.3), ("f32", 64, 512, 0.5),
+])
+@pytest.mark.parametrize("rows", ["a source", "a destination", "every source", "every row"])
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), 3e30])
+def test_keys_without_a_cosine_stay_inside_their_chunk(dtype, dim, chunk, r, rows, value):
+    """A key that is not finite, or whose norm is not: every other chunk as without it, and in its own chunk as many edges
+    merged and every token accounted for."""
+    _say(f"keys without a cosine {dtype} D={dim} c={chunk} r={r}: {rows} {value}")
+    seq = 3 * chunk + chunk // 2 + 1
+    K, V, _ = kv_host(91, 2, seq, dim, dtype, alpha=0.9)
+    K, V = K.to(DEV), V.to(DEV)
+    bad = {"a source": slice(chunk + 6, chunk + 7), "a destination": slice(chunk + 5, chunk + 6),
+           "every source": slice(chunk, 2 * chunk, 2), "every row": slice(chunk, 2 * chunk)}[rows]
+    P = K.clone()
+    P[0, 0, bad, 3] = value
+    want, got = (ckv.compress(k, V, chunk, rounds=[r]) for k in (K, P))
+    torch.cuda.synchronize()
+    kept = chunk - int(np.floor(float(np.float32(r)) * (chunk // 2) + 1e-9))       # rows a whole chunk leaves
+    outside = [slice(0, kept), slice(2 * kept, None)]
+    for n, a, e in zip(["K'", "V'", "deg'"], got, want):
+        assert torch.equal(a[0, 1], e[0, 1]), n
+        for x in outside:
+            assert torch.equal(a[0, 0, x], e[0, 0, x]), n
+    to = i64(got[3][0, 0])
+    assert torch.equal(got[3][0, 1], want[3][0, 1])
+    assert np.array_equal(to[:chunk], i64(want[3][0, 0])[:chunk]) and np.array_equal(to[2 * chunk:], i64(want[3][0, 0])[2 * chunk:])
+    mine = to[chunk:2 * chunk]
+    assert mine.min() >= kept and mine.max() < 2 * kept
+    assert np.array_equal(np.bincount(mine - kept, minlength=kept), i64(got[2][0, 0])[kept:2 * kept])
+    ref = np.zeros((kept, dim))
+    np.add.at(ref, mine - kept, f64(V[0, 0])[chunk:2 * chunk])
+    assert_rows_close(f64(got[1][0, 0])[kept:2 * kept], ref / np.bincount(mine - kept)[:, None], TOL[dtype] if dtype == "f32" else 2.0 ** -8,
+                      "V' of the chunk")
+
+
 # ---- attention sinks and recent tokens (Sec. 5.2 / 5.3) ----------------------------------------
 @pytest.mark.parametrize("dtype,heads,seq,dim,chunk,rounds,n_sink,n_recent", [
     ("bf16", 2, 4096 + 80, 128, 1024, [1.0, 1.0], 16, 64),
