@@ -76,8 +76,10 @@ struct RowOf {
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 
-// Four fp32 weights as sums of three bf16 numbers each, largest parts first, exactly.
-__device__ __forceinline__ void split_weights(const float (&z)[4], s16x4 (&part)[3]) {
+// Four fp32 weights (zero or above) as sums of three bf16 numbers each, largest parts first, exactly but for 2^-125, and
+// their signs flipped where `flip` has the sign bits.  No part of a weight above zero is zero: a zero part would make
+// a NaN of an infinite value.
+__device__ __forceinline__ void split_weights(const float (&z)[4], uint32_t flip, s16x4 (&part)[3]) {
   uint32_t u[3][4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -86,10 +88,19 @@ __device__ __forceinline__ void split_weights(const float (&z)[4], s16x4 (&part)
     u[1][i] = __float_as_uint(r);
     u[2][i] = __float_as_uint(r - __uint_as_float(u[1][i] & 0xffff0000u));
   }
+  struct Words { uint32_t w[2]; } out[3];
 #pragma unroll
-  for (int p = 0; p < 3; ++p)      // the upper halves of two words side by side
-    part[p] = __builtin_bit_cast(s16x4, make_uint2(__builtin_amdgcn_perm(u[p][1], u[p][0], 0x07060302u),
-                                                   __builtin_amdgcn_perm(u[p][3], u[p][2], 0x07060302u)));
+  for (int i = 0; i < 2; ++i) {    // the upper halves of two words side by side
+    u16x2 v[3];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) v[p] = __builtin_bit_cast(u16x2, __builtin_amdgcn_perm(u[p][2 * i + 1], u[p][2 * i], 0x07060302u));
+    const u16x2 least = __builtin_elementwise_min(v[0], u16x2{0x0080, 0x0080});   // 2^-126, zero for a weight of zero
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+      out[p].w[i] = __builtin_bit_cast(uint32_t, p == 0 ? v[0] : __builtin_elementwise_max(v[p], least)) ^ flip;
+  }
+#pragma unroll
+  for (int p = 0; p < 3; ++p) part[p] = __builtin_bit_cast(s16x4, out[p]);
 }
 
 // The lower (0) or upper (1) bf16 of four words.
@@ -408,9 +419,7 @@ __global__ __launch_bounds__(W * 64, 2) void attn_mfma_kernel(
     // The weights as three bf16 parts (8 + 8 + 8 bits: exactly the 24 of an fp32), the smallest first, all of a tile
     // with one sign
     s16x4 part[3];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) z[i] *= sign;
-    split_weights(z, part);
+    split_weights(z, sign < 0.f ? 0x80008000u : 0u, part);
 #pragma unroll
     for (int j = 0; j < R::EV; j += 2) {
       const s16x4 v0 = column<0>(v[0].w[j / 2], v[1].w[j / 2], v[2].w[j / 2], v[3].w[j / 2]);

@@ -144,6 +144,28 @@ def test_caches_of_one_slice(B, Hkv, G, L, D):
     _check(q[some], K[some], V[some], deg[some], lens[some], o[some], what="one slice")
 
 
+@pytest.mark.parametrize("B,Hkv,G,L,D", [(1, 2, 4, 40, 128), (2, 1, 8, 515, 64), (1, 1, 2, 5000, 128), (1, 4, 1, 9001, 64)])
+@pytest.mark.parametrize("scale", [0.0, 1e-6])          # ordinary weights, and all of them within a bit of 1
+def test_infinite_values_reach_their_own_channels_only(B, Hkv, G, L, D, scale):
+    """A value of infinity under a weight above zero: infinity in that channel, every other channel as the oracle has it."""
+    _say(f"attn infinite values B={B} Hkv={Hkv} G={G} L={L} D={D} scale={scale}")
+    K, V, _ = kv_host(93, Hkv, L, D, "bf16", n_outlier=0)
+    K, V = K.expand(B, Hkv, L, D).contiguous().to(DEV), V.expand(B, Hkv, L, D).contiguous().to(DEV)
+    q = query_host(94, B, Hkv * G, D, "bf16").to(DEV)
+    deg = torch.from_numpy(np.random.default_rng(L).integers(1, 6, (B, Hkv, L)).astype(np.int32)).to(DEV)
+    hit = {0: (0, np.inf), 3: (L // 2, -np.inf), D - 1: (L - 2, np.inf), 5: (17, np.inf)}    # channel: token, value
+    P = V.clone()
+    for c, (t, x) in hit.items():
+        P[:, :, t, c] = x
+    o = ckv.decode_attn(q, K, P, deg=deg, scale=scale, out_dtype=torch.float32)
+    plain = ckv.decode_attn(q, K, V, deg=deg, scale=scale, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    for c, (_, x) in hit.items():
+        assert bool((o[:, :, c] == x).all()), (c, o[0, :, c])
+    rest = [c for c in range(D) if c not in hit]
+    assert torch.equal(o[:, :, rest], plain[:, :, rest])
+
+
 def test_outlier_keys_large_logits_bf16():
     """Keys with x10 outlier channels give logits of several tens: the softmax must stay stable."""
     _say("attn outliers")
