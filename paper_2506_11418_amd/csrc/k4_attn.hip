@@ -583,9 +583,11 @@ hipError_t launch_mfma_g(int G, const AttnCall& c) {
 // 9.7 in 64, 11.3 in 32; 4 pairs of 4097 11.3 in 64, 9.3 in 32; dim 64, 4 pairs of 5500 9.5 in 64, 10.4 in 32.
 //
 // One slice.  Partials and their merge cost as much as two to three steps of a wave: a cache of up to two steps of four
-// waves is not cut (4 heads, us, two slices / one: 8 pairs of 128 tokens 7.9 / 6.7, of 130 7.7 / 7.8, 256 pairs of 128
-// 9.5 / 7.4; dim 64, 8 pairs of 256 8.1 / 7.2, of 260 8.0 / 8.7).  Nor are up to 1536 tokens of 192 to 256 pairs, a workgroup of
-// eight waves per pair and CU (half to all of n tokens, two slices of four waves / one of eight: 256 pairs, n = 200 11.3 / 9.9,
+// waves is not cut (4 heads, us, two slices / one: 8 pairs of 128 tokens 7.9 / 6.7, of 130 7.7 / 7.8; dim 64, 8 pairs of 256
+// 8.1 / 7.2, of 260 8.0 / 8.7).  Nor are up to 1536 tokens of 192 to 256 pairs, a workgroup per pair and CU: four waves up to
+// 128 tokens (4 heads, eight waves / four: 256 pairs of 64 tokens 5.74 / 5.47, of 128 7.71 / 6.68, 192 pairs of 128 7.19 /
+// 6.37; 8 heads, 256 pairs of 64 5.80 / 5.84, of 128 7.73 / 6.90; dim 64, 4 heads, 256 pairs of 128 5.81 / 5.60, of 160 6.87 / 7.20), then
+// eight (half to all of n tokens, two slices of four waves / one of eight: 256 pairs, n = 200 11.3 / 9.9,
 // 700 19.5 / 18.2, 2000 40.4 / 40.6, 4000 76.0 / 75.2; 192 pairs 11.1 / 9.8, 18.5 / 17.3, 37.7 / 37.6, 66.5 / 68.3; 160 pairs,
 // 700 15.4 / 17.1).
 AttnCut attn_cut(int dtype, int n_b, int kv_heads, int q_heads, int dim, int seq, int span_limit) {
@@ -599,7 +601,7 @@ AttnCut attn_cut(int dtype, int n_b, int kv_heads, int q_heads, int dim, int seq
     return cut;
   }
   if (bf16 && (seq <= 2 * 4 * (dim == 64 ? 32 : 16) || (bh >= 192 && bh <= 256 && seq <= 1536))) {
-    cut.waves = bh >= 192 && bh <= 256 ? 8 : 4;
+    cut.waves = bh >= 192 && bh <= 256 && seq > 128 ? 8 : 4;
     cut.slices = 1;       // (at most 1536 tokens: a paged slice's table entries always fit)
     return cut;
   }

@@ -128,6 +128,7 @@ def test_one_workspace_for_the_capacity_serves_every_length(H, cap, lengths):
 @pytest.mark.parametrize("B,Hkv,G,L,D", [
     (1, 8, 4, 128, 128), (1, 8, 4, 129, 128), (3, 2, 1, 256, 64), (3, 2, 8, 257, 64),     # two steps of four waves, and a row more
     (24, 8, 2, 1536, 128), (24, 8, 1, 1537, 64), (32, 8, 1, 700, 128), (33, 8, 1, 300, 64),   # a workgroup of eight waves per pair
+    (24, 8, 1, 128, 128), (24, 8, 4, 129, 128), (32, 8, 8, 128, 64), (32, 8, 1, 129, 64),     # four waves up to 128 tokens of that many
 ])
 def test_caches_of_one_slice(B, Hkv, G, L, D):
     """Sequences of lengths down to zero on both sides of the sizes up to which a cache is not cut."""
