@@ -76,10 +76,10 @@ struct RowOf {
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 
-// Four fp32 weights (zero or above) as sums of three bf16 numbers each, largest parts first, exactly but for 2^-125, and
-// their signs flipped where `flip` has the sign bits.  No part of a weight above zero is zero: a zero part would make
-// a NaN of an infinite value.
-__device__ __forceinline__ void split_weights(const float (&z)[4], uint32_t flip, s16x4 (&part)[3]) {
+// Four fp32 weights, all of the sign that `smallest` has, as sums of three bf16 numbers each, largest parts first, exactly but
+// for 2^-125.  smallest: two bf16 of +-2^-126.  No part of a weight that is not zero is smaller: a zero part would make a
+// NaN of an infinite value.  (Of equal signs, the larger bits are the larger magnitude.)
+__device__ __forceinline__ void split_weights(const float (&z)[4], uint32_t smallest, s16x4 (&part)[3]) {
   uint32_t u[3][4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -94,10 +94,10 @@ __device__ __forceinline__ void split_weights(const float (&z)[4], uint32_t flip
     u16x2 v[3];
 #pragma unroll
     for (int p = 0; p < 3; ++p) v[p] = __builtin_bit_cast(u16x2, __builtin_amdgcn_perm(u[p][2 * i + 1], u[p][2 * i], 0x07060302u));
-    const u16x2 least = __builtin_elementwise_min(v[0], u16x2{0x0080, 0x0080});   // 2^-126, zero for a weight of zero
+    const u16x2 least = __builtin_elementwise_min(v[0], __builtin_bit_cast(u16x2, smallest));   // (zero for a weight of zero)
+    out[0].w[i] = __builtin_bit_cast(uint32_t, v[0]);
 #pragma unroll
-    for (int p = 0; p < 3; ++p)
-      out[p].w[i] = __builtin_bit_cast(uint32_t, p == 0 ? v[0] : __builtin_elementwise_max(v[p], least)) ^ flip;
+    for (int p = 1; p < 3; ++p) out[p].w[i] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(v[p], least));
   }
 #pragma unroll
   for (int p = 0; p < 3; ++p) part[p] = __builtin_bit_cast(s16x4, out[p]);
@@ -419,7 +419,9 @@ __global__ __launch_bounds__(W * 64, 2) void attn_mfma_kernel(
     // The weights as three bf16 parts (8 + 8 + 8 bits: exactly the 24 of an fp32), the smallest first, all of a tile
     // with one sign
     s16x4 part[3];
-    split_weights(z, sign < 0.f ? 0x80008000u : 0u, part);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) z[i] *= sign;
+    split_weights(z, sign < 0.f ? 0x80808080u : 0x00800080u, part);
 #pragma unroll
     for (int j = 0; j < R::EV; j += 2) {
       const s16x4 v0 = column<0>(v[0].w[j / 2], v[1].w[j / 2], v[2].w[j / 2], v[3].w[j / 2]);
