@@ -147,7 +147,9 @@ int ckv_match(const void* K, const ckv_layout* in, int32_t chunk, int32_t* dst, 
  * or closes the schedule together with its successor leaves the values to that successor, which
  * rebuilds them from the round's input, once the job is large enough for that to pay;
  * CKV_ROUTE_FULL_ROUNDS makes every round write its value cache, CKV_ROUTE_DEFER_ALWAYS defers
- * whatever the size.  ckv_plan sizes the workspace for the route the same flags select. */
+ * whatever the size.  ckv_plan sizes the workspace for the route the same flags select.  Where small
+ * chunks are faster with every round writing its value cache, a workspace of the size that leaving
+ * them takes (the plan of a large job with CKV_ROUTE_DEFER_ALWAYS) is accepted too. */
 int ckv_compress(const void* K, const void* V, const int32_t* deg_in, const ckv_layout* in,
                  const ckv_params* p, void* K_out, void* V_out, int32_t* deg_out,
                  const ckv_layout* out, int32_t* assign, void* workspace, size_t workspace_bytes,

@@ -72,6 +72,20 @@ int seq_after_round(int len, int chunk, float r, int n_sink, int n_recent, int s
   return (len - mid) + full * chunk_out(chunk, r) + chunk_out(tail, r);
 }
 
+// Whether round j ranks the edges of all chunks of a sequence together.  At r = 1 every edge is merged whichever way
+// they are ranked, so that round runs like one with per-chunk selection: no ranking, one launch for small chunks, deferred
+// values (to a quarter, dim 128, us, ranked / not: 8 x 8000 tokens, chunk 256 60.1 / 27.6; 8 x 20001, chunk 384 84.6 / 74.4;
+// 64 x 32768, chunk 64 680 / 426, chunk 1024 669 / 606).
+bool ranks_whole_sequence(const ckv_params* p, const ckv_plan_t* plan, int j) {
+  return p->scope == CKV_SCOPE_HEAD && plan->round_r[j] != 1.0f;
+}
+
+// FASTEST is what ckv_plan sizes the workspace for.  LEAST takes no account of what a round in one launch saves: values
+// are left to the next round by the size of the job alone, and only where chunks are ranked by themselves, so that large
+// jobs of small chunks need about half the scratch (256 sequences of 131072 tokens, dim 128, chunk 256: 4.34 GiB for
+// 8.25).  A call whose workspace holds no more than that runs so: callers that keep a size, and those that cannot spare more.
+enum class Scratch { FASTEST, LEAST };
+
 // How each round of a schedule runs.  FULL: match + merge writing keys, values and degrees.
 // A deferred pair: when round j merges every edge (r = 1) and another round follows, round j may
 // write keys and degrees only (KEYS_ONLY) and round j+1 rebuild the value rows it needs from round
@@ -88,21 +102,15 @@ int seq_after_round(int len, int chunk, float r, int n_sink, int n_recent, int s
 // 273) - unless one workgroup's rows fill a CU's LDS, where the pair wins from about 1536 chunks on (dim 128, chunk 512,
 // 32768 tokens: 40 sequences 403 / 377, 48 445 / 451, 64 554 / 586; dim 64, chunk 1024: 32 x 65536 417 / 407, 128 x 65536
 // 1512 / 1542).
-// Whether round j ranks the edges of all chunks of a sequence together.  At r = 1 every edge is merged whichever way
-// they are ranked, so that round runs like one with per-chunk selection: no ranking, one launch for small chunks, deferred
-// values (to a quarter, dim 128, us, ranked / not: 8 x 8000 tokens, chunk 256 60.1 / 27.6; 8 x 20001, chunk 384 84.6 / 74.4;
-// 64 x 32768, chunk 64 680 / 426, chunk 1024 669 / 606).
-bool ranks_whole_sequence(const ckv_params* p, const ckv_plan_t* plan, int j) {
-  return p->scope == CKV_SCOPE_HEAD && plan->round_r[j] != 1.0f;
-}
-
 enum RoundMode { ROUND_FULL = 0, ROUND_KEYS_ONLY = 1, ROUND_ORIGIN = 2 };
 constexpr int64_t kDeferMinChunks = 1024, kDeferMinChunksFullLds = 1536;
 
-void plan_routes(const ckv_layout* in, const ckv_params* p, const ckv_plan_t* plan, RoundMode (&mode)[CKV_MAX_ROUNDS]) {
+void plan_routes(const ckv_layout* in, const ckv_params* p, const ckv_plan_t* plan, Scratch scratch,
+                 RoundMode (&mode)[CKV_MAX_ROUNDS]) {
   const int64_t n_bh = (int64_t)in->batch * in->heads;
   const bool allow = !(p->flags & CKV_ROUTE_FULL_ROUNDS), force = (p->flags & CKV_ROUTE_DEFER_ALWAYS) != 0;
-  const bool one_launch = in->dtype == CKV_BF16 && round_is_small(in->dtype, in->dim, p->chunk);
+  const bool least = scratch == Scratch::LEAST;
+  const bool one_launch = in->dtype == CKV_BF16 && round_is_small(in->dtype, in->dim, p->chunk) && !least;
   const int64_t worth = !one_launch ? kDeferMinChunks : p->chunk * in->dim == 65536 ? kDeferMinChunksFullLds : INT64_MAX;
   for (int j = 0; j < CKV_MAX_ROUNDS; ++j) mode[j] = ROUND_FULL;
   for (int j = 0; j + 1 < plan->n_rounds; ++j) {
@@ -111,7 +119,7 @@ void plan_routes(const ckv_layout* in, const ckv_params* p, const ckv_plan_t* pl
     int lo2, hi2;   // both rounds must have tokens to cluster (a cache of sinks and recents only is copied)
     clusterable(plan->round_len[j + 1], p->n_sink, p->n_recent, &lo2, &hi2);
     const bool pair = allow && (j == 0 || j + 2 == plan->n_rounds) && plan->round_r[j] == 1.0f &&
-                      !ranks_whole_sequence(p, plan, j + 1) && hi > lo && hi2 > lo2 &&
+                      !(least ? p->scope == CKV_SCOPE_HEAD : ranks_whole_sequence(p, plan, j + 1)) && hi > lo && hi2 > lo2 &&
                       (force || n_bh * div_up(plan->round_len[j + 1], p->chunk) >= worth);
     if (pair) {
       mode[j] = ROUND_KEYS_ONLY;
@@ -125,13 +133,13 @@ struct Workspace {
   size_t dst, score, sel, lists, map, K[2], V[2], deg[2], total;
 };
 
-Workspace carve(const ckv_layout* in, const ckv_params* p, const ckv_plan_t* plan) {
+Workspace carve(const ckv_layout* in, const ckv_params* p, const ckv_plan_t* plan, Scratch scratch) {
   Workspace w{};
   const int chunk = p->chunk;
   const size_t n_bh = (size_t)in->batch * in->heads;
   const size_t e = elem_bytes(in->dtype);
   RoundMode mode[CKV_MAX_ROUNDS];
-  plan_routes(in, p, plan, mode);
+  plan_routes(in, p, plan, scratch, mode);
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
   const size_t n_src0 = n_sources(in->seq, chunk);
@@ -194,7 +202,7 @@ int make_plan(const ckv_layout* in, const ckv_params* p, ckv_plan_t* plan) {
     plan->round_len[j + 1] = seq_after_round(plan->round_len[j], p->chunk, plan->round_r[j], p->n_sink, p->n_recent,
                                              p->scope);
   plan->out_seq = plan->round_len[plan->n_rounds];
-  plan->workspace_bytes = carve(in, p, plan).total;
+  plan->workspace_bytes = carve(in, p, plan, Scratch::FASTEST).total;
   return CKV_OK;
 }
 
@@ -248,13 +256,13 @@ struct PagedCall {
 // The rounds of one compression (Algorithm 1, the loop after prefill), launches only.
 int run_rounds(const void* K, const void* V, const int32_t* deg_in, const ckv_layout* in, const ckv_params* p,
                const ckv_plan_t* planp, void* K_out, void* V_out, int32_t* deg_out, const ckv_layout* out,
-               int32_t* assign, void* workspace, PagedCall* pc, hipStream_t s) {
+               int32_t* assign, void* workspace, Scratch scratch, PagedCall* pc, hipStream_t s) {
   const ckv_plan_t& plan = *planp;
   const int n_bh = in->batch * in->heads;
   const int e = in->dtype == CKV_BF16 ? 2 : 4;
-  const Workspace w = carve(in, p, &plan);
+  const Workspace w = carve(in, p, &plan, scratch);
   RoundMode mode[CKV_MAX_ROUNDS];
-  plan_routes(in, p, &plan, mode);
+  plan_routes(in, p, &plan, scratch, mode);
   unsigned char* ws = static_cast<unsigned char*>(workspace);
   int32_t* dst = reinterpret_cast<int32_t*>(ws + w.dst);
   float* score = reinterpret_cast<float*>(ws + w.score);
@@ -439,9 +447,14 @@ int ckv_compress(const void* K, const void* V, const int32_t* deg_in, const ckv_
       ((uintptr_t)deg_out) % 4 || ((uintptr_t)deg_in) % 4 || ((uintptr_t)assign) % 4)
     return CKV_EALIGN;
   if (!dims_supported(in->dtype, in->dim)) return CKV_EUNSUPPORTED;
+  Scratch scratch = Scratch::FASTEST;
   if (plan.workspace_bytes > 0) {
     if (!workspace) return CKV_EINVAL;
     if (((uintptr_t)workspace) % 256) return CKV_EALIGN;
+    if (workspace_bytes < plan.workspace_bytes) {
+      scratch = Scratch::LEAST;
+      plan.workspace_bytes = carve(in, p, &plan, scratch).total;
+    }
     if (workspace_bytes < plan.workspace_bytes) return CKV_EWORKSPACE;
   }
   {
@@ -471,7 +484,7 @@ int ckv_compress(const void* K, const void* V, const int32_t* deg_in, const ckv_
     return hip_status(err);
   }
 
-  return run_rounds(K, V, deg_in, in, p, &plan, K_out, V_out, deg_out, out, assign, workspace, nullptr, s);
+  return run_rounds(K, V, deg_in, in, p, &plan, K_out, V_out, deg_out, out, assign, workspace, scratch, nullptr, s);
 }
 
 int32_t ckv_n_sources(int32_t seq, int32_t chunk) {
@@ -712,14 +725,15 @@ ckv_paged_layout run_layout(const ckv_paged_layout* pl, const PagedRun& r) {
   return x;
 }
 
-int paged_run_plan(const ckv_paged_layout* pl, const PagedRun& run, const ckv_params* p, ckv_plan_t* plan, PagedWs* w) {
+int paged_run_plan(const ckv_paged_layout* pl, const PagedRun& run, const ckv_params* p, Scratch scratch, ckv_plan_t* plan,
+                   PagedWs* w) {
   if (run.seq <= 0 || (int64_t)run.seq > (int64_t)pl->max_blocks * pl->block_size) return CKV_ESHAPE;
   const ckv_paged_layout rl = run_layout(pl, run);
   const ckv_layout in = staging_layout(&rl, run.seq);
   int st = ckv_plan(&in, p, plan);
   if (st != CKV_OK) return st;
   RoundMode mode[CKV_MAX_ROUNDS];
-  plan_routes(&in, p, plan, mode);
+  plan_routes(&in, p, plan, scratch, mode);
   const bool stage_k = plan->n_rounds == 1;
   const bool stage_v = plan->n_rounds == 1 || (plan->n_rounds == 2 && mode[0] == ROUND_KEYS_ONLY);
   const size_t e = ckv::elem_bytes(pl->dtype), n_bh = (size_t)run.n * pl->heads;
@@ -728,7 +742,7 @@ int paged_run_plan(const ckv_paged_layout* pl, const PagedRun& run, const ckv_pa
   w->sK = take(stage_k ? n_bh * plan->out_seq * pl->dim * e : 0);
   w->sV = take(stage_v ? n_bh * plan->out_seq * pl->dim * e : 0);
   w->sdeg = take(stage_v ? n_bh * plan->out_seq * 4 : 0);
-  w->inner = take(plan->workspace_bytes);
+  w->inner = take(carve(&in, p, plan, scratch).total);
   w->total = off;
   return CKV_OK;
 }
@@ -743,10 +757,9 @@ int check_paged_compress(const ckv_paged_layout* pl, int32_t seq, const int32_t*
   if (!seq_lens && (seq <= 0 || (int64_t)seq > (int64_t)pl->max_blocks * pl->block_size)) return CKV_ESHAPE;
   return CKV_OK;
 }
-}  // namespace
 
-int ckv_paged_compress_plan(const ckv_paged_layout* pl, int32_t seq, const int32_t* seq_lens, const ckv_params* p,
-                            int32_t* out_seq, int32_t* n_freed, size_t* workspace_bytes) {
+int paged_plan(const ckv_paged_layout* pl, int32_t seq, const int32_t* seq_lens, const ckv_params* p, Scratch scratch,
+               int32_t* out_seq, int32_t* n_freed, size_t* workspace_bytes) {
   int st = check_paged_compress(pl, seq, seq_lens);
   if (st != CKV_OK) return st;
   std::vector<PagedRun> runs(pl->batch);
@@ -756,7 +769,7 @@ int ckv_paged_compress_plan(const ckv_paged_layout* pl, int32_t seq, const int32
   for (int i = 0; i < n_runs; ++i) {
     ckv_plan_t plan;
     PagedWs w;
-    st = paged_run_plan(pl, runs[i], p, &plan, &w);
+    st = paged_run_plan(pl, runs[i], p, scratch, &plan, &w);
     if (st != CKV_OK) return st;
     need = w.total > need ? w.total : need;
     const int nf = ckv::div_up(runs[i].seq, pl->block_size) - ckv::div_up(plan.out_seq, pl->block_size);
@@ -769,6 +782,12 @@ int ckv_paged_compress_plan(const ckv_paged_layout* pl, int32_t seq, const int32
   if (n_freed) *n_freed = freed_max;
   if (workspace_bytes) *workspace_bytes = need;
   return CKV_OK;
+}
+}  // namespace
+
+int ckv_paged_compress_plan(const ckv_paged_layout* pl, int32_t seq, const int32_t* seq_lens, const ckv_params* p,
+                            int32_t* out_seq, int32_t* n_freed, size_t* workspace_bytes) {
+  return paged_plan(pl, seq, seq_lens, p, Scratch::FASTEST, out_seq, n_freed, workspace_bytes);
 }
 
 int ckv_paged_compress(void* K_pool, void* V_pool, int32_t* deg_pool, int32_t* block_table, int32_t* lens,
@@ -784,7 +803,12 @@ int ckv_paged_compress(void* K_pool, void* V_pool, int32_t* deg_pool, int32_t* b
   if (!dims_supported(pl->dtype, pl->dim)) return CKV_EUNSUPPORTED;
   int32_t n_freed_max = 0;
   size_t need = 0;
-  st = ckv_paged_compress_plan(pl, seq, seq_lens, p, nullptr, &n_freed_max, &need);
+  Scratch scratch = Scratch::FASTEST;
+  st = paged_plan(pl, seq, seq_lens, p, scratch, nullptr, &n_freed_max, &need);
+  if (st == CKV_OK && workspace_bytes < need) {
+    scratch = Scratch::LEAST;
+    st = paged_plan(pl, seq, seq_lens, p, scratch, nullptr, nullptr, &need);
+  }
   if (st != CKV_OK) return st;
   if (workspace_bytes < need) return CKV_EWORKSPACE;
   if (freed && freed_stride < n_freed_max) return CKV_ESHAPE;
@@ -799,7 +823,7 @@ int ckv_paged_compress(void* K_pool, void* V_pool, int32_t* deg_pool, int32_t* b
     const PagedRun& run = runs[i];
     ckv_plan_t plan;
     PagedWs w;
-    st = paged_run_plan(pl, run, p, &plan, &w);
+    st = paged_run_plan(pl, run, p, scratch, &plan, &w);
     if (st != CKV_OK) return st;
     int32_t* table = block_table + (size_t)run.b0 * pl->max_blocks;
     int32_t* run_freed = freed ? freed + (size_t)run.b0 * freed_stride : nullptr;
@@ -815,7 +839,7 @@ int ckv_paged_compress(void* K_pool, void* V_pool, int32_t* deg_pool, int32_t* b
     pc.sV = ws + w.sV;
     pc.sdeg = reinterpret_cast<int32_t*>(ws + w.sdeg);
     if (plan.n_rounds > 0) {
-      st = run_rounds(K_pool, V_pool, deg_pool, &in, p, &plan, nullptr, nullptr, nullptr, &stg, nullptr, ws + w.inner, &pc, s);
+      st = run_rounds(K_pool, V_pool, deg_pool, &in, p, &plan, nullptr, nullptr, nullptr, &stg, nullptr, ws + w.inner, scratch, &pc, s);
       if (st != CKV_OK) return st;
     }
     // staged outputs into the sequences' first blocks, then the blocks behind the new length are released

@@ -894,6 +894,35 @@ def test_deferred_values_are_bit_identical_to_full_rounds(dtype, heads, seq, dim
         assert torch.equal(a, b), f"{n} differs between deferred and full rounds"
 
 
+@pytest.mark.parametrize("scope,dim,chunk,seq,rounds,n_sink,n_recent,least", [
+    ("chunk", 64, 64, 32768, [1.0, 1.0], 0, 0, "defer_always"),       # faster in one launch a round, smaller with values left
+    ("chunk", 128, 256, 131073, [1.0, 1.0, 0.5], 0, 0, "defer_always"),
+    ("head", 64, 16, 8192 + 80, [1.0, 1.0], 16, 64, "full_rounds"),   # without the member lists of a pair
+])
+def test_a_workspace_without_the_value_cache_is_enough(scope, dim, chunk, seq, rounds, n_sink, n_recent, least):
+    """Jobs of 1024 chunks and more run in the scratch they take where the size of the job alone decides whether values
+    are left to the next round: same bits, and not a byte less."""
+    _say(f"least workspace {scope} D={dim} c={chunk} S={seq}")
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    K, V = (torch.randn((1, 4, seq, dim), generator=gen, device=DEV).to(torch.bfloat16) for _ in range(2))
+    kw = dict(rounds=rounds, n_sink=n_sink, n_recent=n_recent, scope=scope)
+    need, enough = (ckv.plan(ckv.layout_of(K), ckv.make_params(chunk, route=r, **kw)).workspace_bytes for r in (None, least))
+    assert enough < need
+    want = ckv.compress(K, V, chunk, **kw)
+    ws = torch.empty(enough, dtype=torch.uint8, device=DEV)
+    ckv.timing_reset()
+    ckv.timing_enable(True)
+    got = ckv.compress(K, V, chunk, workspace=ws, **kw)
+    torch.cuda.synchronize()
+    ckv.timing_enable(False)
+    assert ("merge_keys_bf16" in ckv.timing_read()) == (least == "defer_always")
+    for n, a, e in zip(["K'", "V'", "deg'", "assign"], got, want):
+        assert torch.equal(a, e), n
+    with pytest.raises(ckv.CkvError) as e:
+        ckv.compress(K, V, chunk, workspace=ws[:enough - 256], **kw)
+    assert e.value.status == -4
+
+
 def test_deferred_values_with_strided_input_and_padded_output():
     _say("deferred values, [B,S,H,D] input")
     B, H, S, D, c = 2, 2, 3072, 128, 512

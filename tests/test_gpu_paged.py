@@ -340,3 +340,37 @@ def test_algorithm1_decode_loop_on_a_paged_cache():
     assert torch.equal(gK, rK) and torch.equal(gV, rV) and torch.equal(gdeg, rdeg)
     used = set(table[table >= 0].flatten().tolist())
     assert len(used) == B * ((s + bs - 1) // bs) and used.isdisjoint(free) and len(used) + len(free) == n_blocks
+
+
+def test_paged_compress_in_a_workspace_without_the_value_cache():
+    """The scratch that leaving values to the next round takes is enough where one launch a round is faster: the pages
+    hold the same bits, and not a byte less will do."""
+    H, S, D, bs, chunk = 4, 32768, 64, 16, 64
+    _say(f"paged compress, least workspace, S={S} c={chunk}")
+    gen = torch.Generator(device=DEV).manual_seed(9)
+    K, V = (torch.randn((1, H, S, D), generator=gen, device=DEV).to(torch.bfloat16) for _ in range(2))
+    blocks = torch.randperm(S // bs, generator=torch.Generator().manual_seed(1)).to(torch.int32).view(1, -1).to(DEV)
+
+    def pages():
+        K_pool = torch.zeros((S // bs, H, bs, D), dtype=K.dtype, device=DEV)
+        pools = (K_pool, torch.zeros_like(K_pool), torch.zeros((S // bs, H, bs), dtype=torch.int32, device=DEV))
+        table = blocks.clone()
+        ckv.paged_scatter(K, V, None, *pools, table, S)
+        return pools, table
+
+    pools, table = pages()
+    need, enough = (ckv.paged_compress_plan(ckv.paged_layout_of(pools[0], table), S, ckv.make_params(chunk, 0.25, route=r))[2]
+                    for r in (None, "defer_always"))
+    assert enough < need
+    out = []
+    for size in (need, enough):
+        pools, table = pages()
+        n, _ = ckv.paged_compress(*pools, table, S, chunk, retain_ratio=0.25, workspace=torch.empty(size, dtype=torch.uint8, device=DEV))
+        out.append(ckv.paged_gather(*pools, table, n))
+    torch.cuda.synchronize()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+    with pytest.raises(ckv.CkvError) as e:
+        ckv.paged_compress(*pools, blocks.clone(), S, chunk, retain_ratio=0.25,
+                           workspace=torch.empty(enough - 256, dtype=torch.uint8, device=DEV))
+    assert e.value.status == -4
