@@ -228,8 +228,9 @@ def compress(K: torch.Tensor, V: torch.Tensor, chunk: int, retain_ratio: float =
     `out` may pass preallocated (K_out, V_out, deg_out, assign) and `workspace` a uint8 tensor, so
     that a timed loop allocates nothing."""
     if workspace is not None and type(out) is tuple and len(out) == 4 and K.is_cuda:
+        # (lists and None are taken there; a generator must reach len() below whole, to be refused)
         st = (_native or _binding()).compress(
-            K, V, deg, chunk, retain_ratio, rounds if rounds is None or type(rounds) is list else list(rounds), n_sink,
+            K, V, deg, chunk, retain_ratio, list(rounds) if type(rounds) is tuple else rounds, n_sink,
             n_recent, SCOPES.get(scope), ROUTES.get(route), *out, workspace, _raw_stream())
         if st == 0:
             return out

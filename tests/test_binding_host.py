@@ -81,3 +81,21 @@ def test_a_call_the_binding_does_not_take_is_made_once(monkeypatch, library, nam
     monkeypatch.setattr(ckv, "_native", _Answer(None))
     _calls()[name]()
     assert library.made == 1
+
+
+@pytest.mark.parametrize("rounds,error", [((x for x in (1.0,)), TypeError), ({1.0: 1}, None), ({1.0}, None), ((1.0,), None), ([1.0], None)])
+def test_rounds_the_binding_does_not_know_go_to_ctypes_unread(monkeypatch, library, rounds, error):
+    """Whatever has a length and an order of its own is taken as before, and a generator is refused as before."""
+    class _Lists:
+        def compress(self, *args):
+            return 0 if args[5] is None or type(args[5]) is list else None
+    monkeypatch.setattr(ckv, "_native", _Lists())
+    K, ws = _t(B, H, S, D), _t(1 << 20, dtype=torch.uint8)
+    out = (_t(B, H, S, D), _t(B, H, S, D), _t(B, H, S, dtype=torch.int32), None)
+    call = lambda: ckv.compress(K, K, 64, rounds=rounds, out=out, workspace=ws)
+    if error:
+        with pytest.raises(error):
+            call()
+    else:
+        call()
+    assert library.made == (not error and not isinstance(rounds, (list, tuple)))
