@@ -273,6 +273,59 @@ def test_compress_config2_llama_layer_bf16():
 
 
 # ---- rounds of small chunks: one launch of 256 tokens per workgroup -----------------------------
+def _timed(call):
+    """call(), and the names of the kernels that made it."""
+    ckv.timing_reset()
+    ckv.timing_enable(True)
+    got = call()
+    torch.cuda.synchronize()
+    ckv.timing_enable(False)
+    return got, set(ckv.timing_read())
+
+
+def _by_separate_kernels(K, V, deg, chunk, r, n_sink=0, n_recent=0):
+    """One round with the top-r inside every chunk, by the match kernel and merge_kernel: every chunk as a sequence of its
+    own, the only and short chunk of 2048 tokens in it, which no kernel takes for a small one."""
+    B, H, S, D = K.shape
+    lo, hi = (n_sink, S - n_recent) if S > n_sink + n_recent else (0, 0)
+    deg = torch.ones((B, H, S), dtype=torch.int32, device=K.device) if deg is None else deg
+    parts = []                                   # K', V', deg', the tokens' places, by part of the sequence
+
+    def copied(a, b):
+        if b > a:
+            parts.append((K[:, :, a:b], V[:, :, a:b], deg[:, :, a:b],
+                          torch.arange(b - a, dtype=torch.int32, device=K.device).expand(B, H, b - a)))
+
+    def clustered(a, b, size):
+        n = (b - a) // size
+        if n == 0:
+            return
+        shape = (B, H * n, size)
+        k, v, d = (x[:, :, a:b].reshape(shape + x.shape[3:]).contiguous() for x in (K, V, deg))
+        (k, v, d, to), names = _timed(lambda: ckv.compress(k, v, 2048, rounds=[r], deg=d))
+        assert not any(x.startswith("round") for x in names) and any(x.startswith("merge") for x in names), names
+        left = k.shape[2]
+        to = to.view(B, H, n, size) + left * torch.arange(n, dtype=torch.int32, device=K.device).view(1, 1, n, 1)
+        parts.append((k.reshape(B, H, n * left, D), v.reshape(B, H, n * left, D), d.reshape(B, H, n * left), to.reshape(B, H, n * size)))
+
+    copied(0, lo if hi > lo else S)
+    if hi > lo:
+        whole = lo + (hi - lo) // chunk * chunk
+        clustered(lo, whole, chunk)
+        clustered(whole, hi, hi - whole or 1)
+        copied(hi, S)
+    at, places = 0, []
+    for k, _, _, to in parts:
+        places.append(to + at)
+        at += k.shape[2]
+    return [torch.cat([p[i] for p in parts], dim=2) for i in range(3)] + [torch.cat(places, dim=2)]
+
+
+def _same(got, want, what):
+    for n, a, e in zip(["K'", "V'", "deg'", "assign"], got, want):
+        assert torch.equal(a, e), f"{n} differs from {what}"
+
+
 @pytest.mark.parametrize("chunk", [64, 128, 256])
 @pytest.mark.parametrize("seq,dim,r,big_degrees,n_sink,n_recent", [
     (256, 128, 0.8, False, 0, 0),
@@ -284,8 +337,7 @@ def test_compress_config2_llama_layer_bf16():
     (300, 64, 0.0, False, 0, 9),             # nothing merged
 ])
 def test_rounds_of_small_chunks_in_one_launch(seq, dim, r, big_degrees, n_sink, n_recent, chunk):
-    """Against the oracle, and at r = 1 (where ranking per chunk and over the whole sequence merge the same
-    edges) bit for bit against the separate match, selection and merge kernels."""
+    """Against the oracle, and bit for bit against the separate match and merge kernels."""
     _say(f"round in one launch S={seq} D={dim} c={chunk} r={r} n1={n_sink} n2={n_recent}")
     K, V, _ = kv_host(41, 4, seq, dim, "bf16", alpha=0.9, n_outlier=4 if dim == 128 else 0)
     K, V = K.reshape(2, 2, seq, dim).to(DEV), V.reshape(2, 2, seq, dim).to(DEV)
@@ -293,23 +345,14 @@ def test_rounds_of_small_chunks_in_one_launch(seq, dim, r, big_degrees, n_sink, 
     if big_degrees:
         deg[1, 0, seq // 2:] *= 999
     deg = torch.from_numpy(deg.astype(np.int32)).to(DEV)
-    kw = dict(rounds=[r], deg=deg, n_sink=n_sink, n_recent=n_recent)
-    ckv.timing_reset()
-    ckv.timing_enable(True)
-    got = ckv.compress(K, V, chunk, **kw)
-    torch.cuda.synchronize()
-    ckv.timing_enable(False)
-    assert list(ckv.timing_read()) == ["round_bf16"]
+    got, names = _timed(lambda: ckv.compress(K, V, chunk, rounds=[r], deg=deg, n_sink=n_sink, n_recent=n_recent))
+    assert names == {"round_bf16"}
     for b in range(2):
         for h in range(2):
             check_round_with_edges(f64(K[b, h]), f64(V[b, h]), i64(deg[b, h]), chunk, r, "bf16", n_sink, n_recent,
                                    f64(got[0][b, h]), f64(got[1][b, h]), i64(got[2][b, h]), i64(got[3][b, h]),
                                    what=f"b{b} h{h}")
-    if r == 1.0:
-        ref = ckv.compress(K, V, chunk, scope="head", **kw)
-        torch.cuda.synchronize()
-        for n, a, e in zip(["K'", "V'", "deg'", "assign"], got, ref):
-            assert torch.equal(a, e), f"{n} differs from the separate kernels"
+    _same(got, _by_separate_kernels(K, V, deg, chunk, r, n_sink, n_recent), "the separate kernels")
 
 
 @pytest.mark.parametrize("chunk,dim", [(512, 128), (512, 64), (1024, 64)])
@@ -322,8 +365,7 @@ def test_rounds_of_small_chunks_in_one_launch(seq, dim, r, big_degrees, n_sink, 
     (2, 0, 1.0, 12),
 ])
 def test_rounds_of_one_chunk_per_workgroup(whole, tail, r, directions, chunk, dim):
-    """Chunks of 512 and 1024 tokens in one launch, against the oracle, and at r = 1 bit for bit against the separate
-    kernels."""
+    """Chunks of 512 and 1024 tokens in one launch, against the oracle, and bit for bit against the separate kernels."""
     from synth.kv import prototype_kv_host
     seq = whole * chunk + tail
     _say(f"round in one launch S={seq} D={dim} c={chunk} r={r} directions={directions}")
@@ -333,20 +375,12 @@ def test_rounds_of_one_chunk_per_workgroup(whole, tail, r, directions, chunk, di
         K, V, _ = kv_host(47, 2, seq, dim, "bf16", alpha=0.9, n_outlier=4 if dim == 128 else 0)
     K, V = K.to(DEV), V.to(DEV)
     deg = torch.from_numpy(np.random.default_rng(seq).integers(1, 9, (1, 2, seq)).astype(np.int32)).to(DEV)
-    ckv.timing_reset()
-    ckv.timing_enable(True)
-    got = ckv.compress(K, V, chunk, rounds=[r], deg=deg)
-    torch.cuda.synchronize()
-    ckv.timing_enable(False)
-    assert list(ckv.timing_read()) == ["round_bf16"]
+    got, names = _timed(lambda: ckv.compress(K, V, chunk, rounds=[r], deg=deg))
+    assert names == {"round_bf16"}
     for h in range(2):
         check_round(f64(K[0, h]), f64(V[0, h]), i64(deg[0, h]), chunk, r, "bf16", f64(got[0][0, h]), f64(got[1][0, h]),
                     i64(got[2][0, h]), i64(got[3][0, h]), what=f"h{h}")
-    if r == 1.0:
-        ref = ckv.compress(K, V, chunk, rounds=[r], deg=deg, scope="head")
-        torch.cuda.synchronize()
-        for n, a, e in zip(["K'", "V'", "deg'", "assign"], got, ref):
-            assert torch.equal(a, e), f"{n} differs from the separate kernels"
+    _same(got, _by_separate_kernels(K, V, deg, chunk, r), "the separate kernels")
 
 
 @pytest.mark.parametrize("route", [None, "full_rounds", "defer_always"])
@@ -386,15 +420,18 @@ def test_assignments_of_several_rounds_are_the_rounds_maps_chained(dtype, seq, d
     ("f32", 1000, 64, 64, [1.0], 0, 0),
 ])
 def test_ranking_over_the_whole_sequence_where_every_edge_is_merged(dtype, seq, dim, chunk, rounds, n_sink, n_recent):
-    """A round at r = 1 gives the same bits with either selection, alone and among others."""
+    """A round at r = 1 gives the bits of every chunk clustered by itself, alone and among others; rounds below 1 are
+    ranked over the whole sequence in either chain."""
     _say(f"whole-sequence ranking at r = 1 {dtype} S={seq} D={dim} c={chunk} rounds={rounds}")
     K, V, _ = kv_host(71, 2, seq, dim, dtype, alpha=0.9)
     K, V = K.to(DEV), V.to(DEV)
     got = ckv.compress(K, V, chunk, rounds=rounds, n_sink=n_sink, n_recent=n_recent, scope="head")
     k, v, deg, to = K, V, None, None
     for r in rounds:
-        k, v, deg, m = ckv.compress(k, v, chunk, rounds=[r], deg=deg, n_sink=n_sink, n_recent=n_recent,
-                                    scope="chunk" if r == 1.0 else "head")
+        if r == 1.0:
+            k, v, deg, m = _by_separate_kernels(k, v, deg, chunk, r, n_sink, n_recent)
+        else:
+            k, v, deg, m = ckv.compress(k, v, chunk, rounds=[r], deg=deg, n_sink=n_sink, n_recent=n_recent, scope="head")
         to = m if to is None else torch.gather(m, 2, to.long())
     torch.cuda.synchronize()
     for n, a, e in zip(["K'", "V'", "deg'", "assign"], got, (k, v, deg, to)):
@@ -455,21 +492,12 @@ def test_fp32_rounds_of_small_chunks_in_one_launch(seq, dim, r, n_sink, n_recent
     K, V, _ = kv_host(43, 3, seq, dim, "f32", alpha=0.9, n_outlier=4 if dim == 128 else 0)
     K, V = K.to(DEV), V.to(DEV)
     deg = torch.from_numpy(np.random.default_rng(seq).integers(1, 400, (1, 3, seq)).astype(np.int32)).to(DEV)
-    kw = dict(rounds=[r], deg=deg, n_sink=n_sink, n_recent=n_recent)
-    ckv.timing_reset()
-    ckv.timing_enable(True)
-    got = ckv.compress(K, V, chunk, **kw)
-    torch.cuda.synchronize()
-    ckv.timing_enable(False)
-    assert list(ckv.timing_read()) == ["round_f32"]
+    got, names = _timed(lambda: ckv.compress(K, V, chunk, rounds=[r], deg=deg, n_sink=n_sink, n_recent=n_recent))
+    assert names == {"round_f32"}
     for h in range(3):
         check_round_with_edges(f64(K[0, h]), f64(V[0, h]), i64(deg[0, h]), chunk, r, "f32", n_sink, n_recent, f64(got[0][0, h]),
                                f64(got[1][0, h]), i64(got[2][0, h]), i64(got[3][0, h]), what=f"h{h}")
-    if r == 1.0:
-        ref = ckv.compress(K, V, chunk, scope="head", **kw)
-        torch.cuda.synchronize()
-        for n, a, e in zip(["K'", "V'", "deg'", "assign"], got, ref):
-            assert torch.equal(a, e), f"{n} differs from the separate kernels"
+    _same(got, _by_separate_kernels(K, V, deg, chunk, r, n_sink, n_recent), "the separate kernels")
 
 
 @pytest.mark.parametrize("dtype,dim,chunk,r", [
