@@ -242,6 +242,20 @@ inline hipError_t kernel_setup(const void* kernel, size_t dynamic_lds, KernelSet
   return hipSuccess;
 }
 
+// CUs of the current device: 256 on the whole chip, less where it is partitioned.  (256 if there is no telling; the launch
+// that follows then reports why.)
+inline int cu_count() {
+  static std::atomic<int> known[kMaxDevices];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 256;
+  int n = known[dev].load(std::memory_order_relaxed);
+  if (n == 0) {
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) return 256;
+    known[dev].store(n, std::memory_order_relaxed);
+  }
+  return n;
+}
+
 bool timing_begin(const char* name, hipStream_t st);   // false: this launch is not being timed
 void timing_end(hipStream_t st);
 struct ScopedTimer {

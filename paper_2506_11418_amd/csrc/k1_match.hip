@@ -818,9 +818,7 @@ hipError_t launch_match_stream(const void* K, TensorView kv, int n_bh, int seq, 
   return hipGetLastError();
 }
 
-// Workgroups of 256 A rows a launch would have; up to kFillChip of them leave CUs idle (one workgroup each).
-constexpr int64_t kFillChip = 256;
-
+// Workgroups of 256 A rows a launch would have; up to one per CU leave CUs idle.
 int64_t row_blocks(int n_bh, int n_chunks, int longest) { return (int64_t)n_bh * n_chunks * div_up((longest + 1) / 2, 256); }
 
 // The general kernel for chunks first_chunk and after.  A wave takes two tiles of A rows (every B operand
@@ -841,10 +839,10 @@ hipError_t launch_match_general(const void* K, TensorView kv, int n_bh, int seq,
   return launch_match_bf16_nw<D, NW, RT, PAGED>(K, kv, n_bh, seq, chunk, dst_local, score, st, paged, first_chunk)
   if (longest <= 256) CKV_MATCH(4, 1);
   if (longest <= 512) {
-    if (D == 64 && blocks > 2 * kFillChip) CKV_MATCH(4, 2);
+    if (D == 64 && blocks > 2 * cu_count()) CKV_MATCH(4, 2);
     CKV_MATCH(8, 1);
   }
-  if (longest % 1024 == 0 && blocks > kFillChip) CKV_MATCH(8, 2);
+  if (longest % 1024 == 0 && blocks > cu_count()) CKV_MATCH(8, 2);
   CKV_MATCH(8, 1);
 #undef CKV_MATCH
 }
@@ -875,7 +873,7 @@ hipError_t launch_match(const void* K, int dtype, int dim, TensorView kv, int n_
     // (the persistent streaming kernel walks memory with fixed pitches: strided tensors only)
     const int whole = seq / chunk, tail = seq % chunk;
     if (!paged.table && dim == 128 && (chunk == 1024 || chunk == 2048) && whole > 0 && kv.stride_s <= (1 << 22) &&
-        row_blocks(n_bh, whole, chunk) > kFillChip && (tail == 0 || (chunk == 1024 && (int64_t)n_bh * whole >= kStreamRaggedChunks))) {
+        row_blocks(n_bh, whole, chunk) > cu_count() && (tail == 0 || (chunk == 1024 && (int64_t)n_bh * whole >= kStreamRaggedChunks))) {
       const hipError_t e = chunk == 1024 ? launch_match_stream<16>(K, kv, n_bh, seq, dst_local, score, st)
                                          : launch_match_stream<32>(K, kv, n_bh, seq, dst_local, score, st);
       if (e != hipSuccess || tail == 0) return e;

@@ -844,14 +844,14 @@ hipError_t launch_merge_t(const void* K, const void* V, const int32_t* deg_in, T
   const ValueOrigin o = org ? *org : ValueOrigin{};
   // Small launches: split every chunk's rows over several workgroups, five per CU in all, none without a batch of rows
   // and no more than 32 (every one repeats the bookkeeping).  Compression of 8 sequences of dim 128 to a quarter, us, with
-  // at most 8 a chunk in powers of two until there were 1024 / 1024 in all / 1280 / 1700: 2048 tokens, chunk 1024: 63.4 /
+  // at most 8 a chunk in powers of two until there were 1024 / 1024 in all / 1280 / 1700 (256 CUs): 2048 tokens, chunk 1024: 63.4 /
   // 50.6 / 50.4 / 50.6; 5000: 66.3 / 58.0 / 56.9 / 56.8; 12000: 75.1 / 71.4 / 74.4 / 79.6; 20001: 91.1 / 91.1 / 88.1 / 100.8;
   // 32768: 114.6 / 114.8 / 113.8 / 128.5; 5000, chunk 2048: 101.0 / 79.6 / 79.6 / 82.7; 20001, chunk 384: 89.1 / 79.3 / 76.5 /
   // 86.1; one round of 30000, chunk 1024, r = 0.8: 84.5 / 74.5 / 73.2 / 85.3.
-  constexpr int64_t kWorkgroups = 5 * 256;
+  const int64_t workgroups = 5 * (int64_t)cu_count();
   const int row_groups = kThreads / (D * (int)sizeof(T) / 16);
   const int batches = div_up(chunk_out(min(chunk, seq), r), row_groups * (org ? kRowsInFlightOrigin : kRowsInFlight));
-  const int parts = (int)max((int64_t)1, min((int64_t)min(32, batches), kWorkgroups / total));
+  const int parts = (int)max((int64_t)1, min((int64_t)min(32, batches), workgroups / total));
   // The copy of the set-aside tokens rides in the merge launch (a launch of its own costs 4 to 6 us a round),
   // unless the two together pass the 2^32 threads of a launch.
   const int64_t edge_blocks = edges ? (edges->total + kThreads - 1) / kThreads : 0;

@@ -592,6 +592,8 @@ hipError_t launch_mfma_g(int G, const AttnCall& c) {
 // eight (half to all of n tokens, two slices of four waves / one of eight: 256 pairs, n = 200 11.3 / 9.9,
 // 700 19.5 / 18.2, 2000 40.4 / 40.6, 4000 76.0 / 75.2; 192 pairs 11.1 / 9.8, 18.5 / 17.3, 37.7 / 37.6, 66.5 / 68.3; 160 pairs,
 // 700 15.4 / 17.1).
+//
+// The counts above are those of 256 CUs whatever the device: the cut also sizes the workspace, which is asked for without one.
 AttnCut attn_cut(int dtype, int n_b, int kv_heads, int q_heads, int dim, int seq, int span_limit) {
   const bool bf16 = dtype == CKV_BF16;
   const int group = q_heads / kv_heads;
