@@ -243,10 +243,11 @@ __device__ __forceinline__ void merge_slices(const float* __restrict__ o_part, c
 // precision, and after the first tiles the rescaling of the accumulators is rare.
 //
 // What bounds it: HBM reads (a kernel that does nothing but read reaches 6.2 TB/s on 134 MB, 6.7 on 403
-// MB), and for short caches the chain of a tile.  Four fp32 MFMAs of depth 4 per channel took 1024 MFMA cycles a tile, three
-// bf16 ones of depth 16 a third to half of that and fewer instructions to widen V.  Per layer, fp32 / bf16 parts (us, 4 heads
-// per KV head, dim 128): one sequence of 515 tokens 8.65 / 8.18, of 32768 (134 MB) 29.6 / 27.5; 16 sequences of 1000 17.8 /
-// 15.9, of 8000 92 / 88; 32 of 1000 28.5 / 24.0; 4 of 32768, 8 heads 96.3 / 92.9; dim 64, 8 of 5000, 2 heads 22.8 / 19.8.
+// MB), and for short caches the chain of a tile.  Against four fp32 MFMAs of depth 4 per channel, three bf16 ones of depth 16
+// keep the matrix units busy 0.41 of the cycles (counted over the 134 MB launch; vector instructions 2105 a wave against 2108,
+// what widened V now splits the weights).  Per layer, fp32 / bf16 parts, either in turn on one GPU (us, 4 heads per KV head, dim
+// 128): one sequence of 515 tokens 8.64 / 8.21, of 32768 (134 MB) 29.8 / 27.8; 16 sequences of 1000 17.6 / 15.9, of 8000 91.1 /
+// 87.6; 32 of 1000 28.4 / 23.8; 4 of 32768, 8 heads 95.0 / 90.8; dim 64, 8 of 5000, 2 heads 22.7 / 20.0.
 // Time line of the 134 MB launch with fp32 MFMAs, from clock readings in the kernel: the streaming loops end between 17 and
 // 24 us (3 us between the waves of a workgroup), the reduction after its slowest wave takes 1.8 us, partials are
 // acknowledged and counted in 1.1 us, the merge by the last arriver takes 2.4 us.

@@ -9,8 +9,9 @@
 // the rows of both tensors from memory behind LDS lookups and passes the matching through memory.
 // Same operand order, norms, fold, member order and rounding as those two: same bits.
 //
-// What bounds it: large launches the HBM stream (64 sequences of 50003 tokens, chunk 256, eight rounds: 9.1 GB
-// in 1603 us = 5.7 TB/s, nine tenths of the chip's copy rate; two launches a round took 2283), small ones the
+// What bounds it: large launches the HBM stream (64 sequences of 50003 tokens, chunk 256, seven rounds: 9.3 GB, by the
+// counters as by the sizes, in 1603 us = 5.8 TB/s, nine tenths of the chip's copy rate, the vector ALU busy 59 % of the
+// first; two launches a round took 2283), small ones the
 // chain of one workgroup: request 1.0 us, keys 1.8, similarity 2.2, ranking and lists 2.8, keys out 2.9, values
 // in and out 2.8 (8 x 8448 tokens, 21.6 us a call; two launches 35.4).  Two workgroups per CU: 64 KiB of rows
 // each, and 128 registers, 32 of them the waiting values.  Whole chunks (us a call, two launches a round / one): dim 128,
