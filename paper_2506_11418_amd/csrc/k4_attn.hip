@@ -32,6 +32,24 @@ __device__ __forceinline__ F2 load_shared(const float* p) {
                                                   __HIP_MEMORY_SCOPE_AGENT));
 }
 
+// op over the lanes of a wave whose numbers differ in the bits of MASK (0x30: the four 16-lane rows; 0x3f: all), the result in
+// every lane.  Inside the vector unit: the same through LDS (shuffles) took 0.1 us a step where a workgroup waits for it.
+template <int MASK, class Op>
+__device__ __forceinline__ float across_lanes(float x, Op&& op) {
+  auto dpp = [&](auto ctrl) { return op(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xF, 0xF, true))); };
+  if constexpr (MASK & 15) {
+    x = dpp(std::integral_constant<int, 0xB1>{});    // lane ^ 1
+    x = dpp(std::integral_constant<int, 0x4E>{});    // lane ^ 2
+    x = dpp(std::integral_constant<int, 0x141>{});   // mirrored within 8, then within 16
+    x = dpp(std::integral_constant<int, 0x140>{});
+  }
+  // (the rows of the first result are 0 0 2 2 and those of the second 1 1 3 3; then 0 1 0 1 and 2 3 2 3)
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return op(__uint_as_float(h[0]), __uint_as_float(h[1]));
+}
+
 // two neighbouring outputs: sums over the tokens divided by the sum of the weights (0 for an empty cache)
 __device__ __forceinline__ void put_out(void* __restrict__ o, int o_dtype, int64_t at, float x, float y, float den) {
   const float rx = den > 0.f ? x / den : 0.f, ry = den > 0.f ? y / den : 0.f;
@@ -167,23 +185,23 @@ __device__ __forceinline__ void merge_slices(const float* __restrict__ o_part, c
           for (int k = 0; k < NC; ++k) x[k][i] = load_shared(col[k] + min(s0 + i * SG, n_slices - 1) * pitch);
       }
   };
+  // the (max, sum) pairs first: they are waited for first
+  auto pair = [&](int g, int sp) { return load_shared(&ml_part[((sbase + sp) * G + g) * 2]); };
+  F2 mine = (wave < G && lane < n_slices) ? pair(wave, lane) : F2{-INFINITY, 0.f};   // read once: up to 64 slices need no more
   request(sg);
   for (int g = wave; g < G; g += W) {
-    auto pair = [&](int sp) { return load_shared(&ml_part[((sbase + sp) * G + g) * 2]); };
-    const F2 mine = (lane < n_slices) ? pair(lane) : F2{-INFINITY, 0.f};   // read once: up to 64 slices need no more
+    if (g != wave) mine = (lane < n_slices) ? pair(g, lane) : F2{-INFINITY, 0.f};
     float mloc = mine.x;
-    for (int sp = lane + 64; sp < n_slices; sp += 64) mloc = fmaxf(mloc, pair(sp).x);
-#pragma unroll
-    for (int sh = 32; sh > 0; sh >>= 1) mloc = fmaxf(mloc, __shfl_xor(mloc, sh));
+    for (int sp = lane + 64; sp < n_slices; sp += 64) mloc = fmaxf(mloc, pair(g, sp).x);
+    mloc = across_lanes<0x3f>(mloc, [](float a, float b) { return fmaxf(a, b); });
     float dloc = 0.f;
     for (int sp = lane; sp < n_slices; sp += 64) {
-      const F2 ml = (sp < 64) ? mine : pair(sp);
-      const float f = (ml.x == -INFINITY) ? 0.f : exp2f(ml.x - mloc);
+      const F2 ml = (sp < 64) ? mine : pair(g, sp);
+      const float f = (ml.x == -INFINITY) ? 0.f : exp2_raw(ml.x - mloc);
       s_w[g * kAttnMaxSplits + sp] = f;
       dloc += f * ml.y;
     }
-#pragma unroll
-    for (int sh = 32; sh > 0; sh >>= 1) dloc += __shfl_xor(dloc, sh);
+    dloc = across_lanes<0x3f>(dloc, [](float a, float b) { return a + b; });
     if (lane == 0) s_den[g] = dloc;
   }
   __syncthreads();
@@ -267,9 +285,8 @@ __global__ __launch_bounds__(W * 64, 2) void attn_mfma_kernel(
   typedef RowOf<D> R;
   constexpr int kThreads = W * 64;
   constexpr int kStageBytes = W * R::LDS;                 // the waves' K tiles (and V tiles at dim 64)
-  constexpr int kOutBytes = W * G * D * 4, kWeightBytes = G * kAttnMaxSplits * 4;
-  constexpr int kRawBytes = kStageBytes > kOutBytes ? (kStageBytes > kWeightBytes ? kStageBytes : kWeightBytes)
-                                                    : (kOutBytes > kWeightBytes ? kOutBytes : kWeightBytes);
+  constexpr int kWeightBytes = G * kAttnMaxSplits * 4;
+  constexpr int kRawBytes = kStageBytes > kWeightBytes ? kStageBytes : kWeightBytes;
   __shared__ __attribute__((aligned(16))) unsigned char s_raw[kRawBytes];   // one after the other
   __shared__ float s_m[W][G], s_l[W][G];
   __shared__ float s_red[2 * kThreads];
@@ -461,55 +478,48 @@ __global__ __launch_bounds__(W * 64, 2) void attn_mfma_kernel(
   }
 
   // ---- merge the waves of this workgroup -------------------------------------------------------
-  l += __shfl_xor(l, 16);
-  l += __shfl_xor(l, 32);
+  // Every wave leaves its sums as they are, in its own part of the staging area, and whoever adds them up works out the
+  // waves' weights for itself: one barrier.  (Weighed by the waves, behind a barrier of their own, and the sum of the weights
+  // worked out by G threads at the end: 1.2 us more from the slowest wave's last tile to the partial's store.)
+  l = across_lanes<0x30>(l, [](float a, float b) { return a + b; });
   if (lane < G) { s_m[wave][lane] = ref; s_l[wave][lane] = l; }   // (lane = column = head)
-  __syncthreads();                      // also: every wave is past its K tile, s_raw changes hands
-  float (*s_o)[G][D] = reinterpret_cast<float (*)[G][D]>(s_raw);
+  static_assert(G * D * 4 <= R::LDS, "a wave's sums in its own part");
+  float* s_o = reinterpret_cast<float*>(s_raw);
+  constexpr int kPart = R::LDS / 4;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int g = 4 * qd + i;
     if (g < G) {
-      float M = s_m[0][g];
+      float* at = s_o + wave * kPart + g * D + R::EV * n;
 #pragma unroll
-      for (int w = 1; w < W; ++w) M = fmaxf(M, s_m[w][g]);
-      const float mw = s_m[wave][g];
-      const float f = (mw == -INFINITY) ? 0.f : exp2f(mw - M);
-#pragma unroll
-      for (int j = 0; j < R::EV; ++j) s_o[wave][g][R::EV * n + j] = acc[j][i] * f;
+      for (int j = 0; j < R::EV; j += 4) *reinterpret_cast<f32x4*>(at + j) = f32x4{acc[j][i], acc[j + 1][i], acc[j + 2][i], acc[j + 3][i]};
     }
   }
   __syncthreads();
   const int64_t sbase = ((int64_t)b * kv_heads + kvh) * n_splits;
   const int64_t pbase = (sbase + split) * G, o_base = ((int64_t)b * kv_heads + kvh) * G * D;
-  auto sum_of = [&](int g) -> float {     // sum of exponentials of head g, relative to the workgroup's maximum
-    float M = s_m[0][g], L = 0.f;
-#pragma unroll
-    for (int w = 1; w < W; ++w) M = fmaxf(M, s_m[w][g]);
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-      const float mw = s_m[w][g];
-      L += (mw == -INFINITY) ? 0.f : s_l[w][g] * exp2f(mw - M);
-    }
-    return L;
-  };
   for (int c = 2 * tid; c < G * D; c += 2 * kThreads) {
-    float x = 0.f, y = 0.f;
+    const int g = c / D;
+    float f[W], M = s_m[0][g], L = 0.f, x = 0.f, y = 0.f;
+#pragma unroll
+    for (int w = 0; w < W; ++w) f[w] = s_m[w][g];
+#pragma unroll
+    for (int w = 1; w < W; ++w) M = fmaxf(M, f[w]);
 #pragma unroll
     for (int w = 0; w < W; ++w) {
-      x += s_o[w][c / D][c % D];
-      y += s_o[w][c / D][c % D + 1];
+      f[w] = (f[w] == -INFINITY) ? 0.f : exp2_raw(f[w] - M);
+      const float2 v = *reinterpret_cast<const float2*>(s_o + w * kPart + c);
+      x = fmaf(v.x, f[w], x);
+      y = fmaf(v.y, f[w], y);
+      L = fmaf(s_l[w][g], f[w], L);
     }
-    if (n_slices == 1) put_out(o, o_dtype, o_base + c, x, y, sum_of(c / D));   // the only slice: nothing to merge
-    else store_shared(&o_part[pbase * D + c], x, y);
+    if (n_slices == 1) put_out(o, o_dtype, o_base + c, x, y, L);   // the only slice: nothing to merge
+    else {
+      store_shared(&o_part[pbase * D + c], x, y);
+      if (c % D == 0) store_shared(&ml_part[(pbase + g) * 2], M, L);
+    }
   }
   if (n_slices == 1) return;
-  if (tid < G) {
-    float M = s_m[0][tid];
-#pragma unroll
-    for (int w = 1; w < W; ++w) M = fmaxf(M, s_m[w][tid]);
-    store_shared(&ml_part[(pbase + tid) * 2], M, sum_of(tid));
-  }
 
   // ---- the last slice of this (batch, KV head) to arrive merges them all ----------------------
   // Every thread waits until its own partial stores have been acknowledged, the workgroup meets,
