@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "ckv_internal.h"
 
 namespace ckv {
@@ -45,6 +47,226 @@ __device__ inline uint16_t f32_to_bf16_rne(float f) {
 // routine wraps it in a range fix-up for denormal results, five more instructions per call, which buys
 // nothing for a softmax weight.
 __device__ __forceinline__ float exp2_raw(float x) { return __builtin_amdgcn_exp2f(x); }
+
+namespace {
+
+// Partial results travel between workgroups that may sit on different XCDs (each with its own L2)
+// inside one launch.  They are written and read with device-scope relaxed atomic accesses (8 bytes
+// each), which go through to the level all XCDs share, instead of plain accesses bracketed by
+// device-scope fences: such a fence writes back / invalidates a whole L2, and one per workgroup cost
+// this kernel a factor of three.
+struct __attribute__((aligned(8))) F2 { float x, y; };
+__device__ __forceinline__ void store_shared(float* p, float x, float y) {
+  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), __builtin_bit_cast(uint64_t, F2{x, y}), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ F2 load_shared(const float* p) {
+  return __builtin_bit_cast(F2, __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT));
+}
+
+// op over the lanes of a wave whose numbers differ in the bits of MASK, the result in every one of them.  Inside the vector
+// unit: the same through LDS (shuffles) took 0.1 us a step where a workgroup waits for it.
+template <int MASK, class Op>
+__device__ __forceinline__ float across_lanes(float x, Op&& op) {
+  static_assert((MASK & 7) == 0 || (MASK & 7) == 7, "eight neighbouring lanes together or none");
+  auto dpp = [&](auto ctrl) {
+    return op(x, __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), decltype(ctrl)::value, 0xF, 0xF, true)));
+  };
+  if constexpr (MASK & 7) {
+    x = dpp(std::integral_constant<int, 0xB1>{});    // lane ^ 1
+    x = dpp(std::integral_constant<int, 0x4E>{});    // lane ^ 2
+    x = dpp(std::integral_constant<int, 0x141>{});   // mirrored within 8
+  }
+  if constexpr (MASK & 8) x = dpp(std::integral_constant<int, 0x128>{});   // lane ^ 8: turned by 8 within 16
+  if constexpr (MASK & 16) {             // (the rows of the first result are 0 0 2 2, those of the second 1 1 3 3)
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  }
+  if constexpr (MASK & 32) {             // (0 1 0 1 and 2 3 2 3)
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  }
+  return x;
+}
+
+// two neighbouring outputs: sums over the tokens divided by the sum of the weights (0 for an empty cache)
+__device__ __forceinline__ void put_out(void* __restrict__ o, int o_dtype, int64_t at, float x, float y, float den) {
+  const float rx = den > 0.f ? x / den : 0.f, ry = den > 0.f ? y / den : 0.f;
+  if (o_dtype == CKV_BF16) {
+    uint16_t* op = reinterpret_cast<uint16_t*>(o) + at;
+    op[0] = f32_to_bf16_rne(rx);
+    op[1] = f32_to_bf16_rne(ry);
+  } else {
+    float* op = reinterpret_cast<float*>(o) + at;
+    op[0] = rx;
+    op[1] = ry;
+  }
+}
+
+// The waves' sums of one slice, added up: as the slice's partial result, or as the output where it is the only one.
+// s_o: wave w's [G][D] sums at w * part floats; s_m, s_l: [W][G] its softmax references and sums of weights.  The waves leave
+// their sums unweighed and whoever adds them up works out the weights for itself: one barrier.  (Weighed by the waves, behind a
+// barrier of their own, and the sum of the weights worked out by G threads at the end: 1.1 us more from the slowest wave's last
+// tile to the partial's store.)
+template <int D, int G, int W>
+__device__ __forceinline__ void put_waves(const float* s_o, int part, const float* s_m, const float* s_l, bool only,
+                                          float* __restrict__ o_part, float* __restrict__ ml_part, int64_t pbase,
+                                          void* __restrict__ o, int o_dtype, int64_t o_base) {
+  for (int c = 2 * threadIdx.x; c < G * D; c += 2 * W * 64) {
+    const int g = c / D;
+    float f[W], M = -INFINITY, L = 0.f, x = 0.f, y = 0.f;
+#pragma unroll
+    for (int w = 0; w < W; ++w) f[w] = s_m[w * G + g];
+#pragma unroll
+    for (int w = 0; w < W; ++w) M = fmaxf(M, f[w]);
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      f[w] = (f[w] == -INFINITY) ? 0.f : exp2_raw(f[w] - M);
+      const float2 v = *reinterpret_cast<const float2*>(s_o + w * part + c);
+      x = fmaf(v.x, f[w], x);
+      y = fmaf(v.y, f[w], y);
+      L = fmaf(s_l[w * G + g], f[w], L);
+    }
+    if (only) put_out(o, o_dtype, o_base + c, x, y, L);
+    else {
+      store_shared(&o_part[pbase * D + c], x, y);
+      if (c % D == 0) store_shared(&ml_part[(pbase + g) * 2], M, L);
+    }
+  }
+}
+
+// The slices of one (batch, KV head), merged by the workgroup that arrived last: weights of the slices
+// per query head (a wave takes a head), and the slices' sums: every thread owns NC pairs of neighbouring
+// channels and adds them up over the slices; with fewer pairs than threads, groups of threads take every
+// SG-th slice and their sums are added in group order.  The first N slices of a thread (all of them for
+// up to N * SG slices) are requested before the weights are worked out, so that one memory latency covers both.
+// s_w: [G][kAttnMaxSplits] floats, s_red: two per thread.
+template <int D, int G, int W>
+__device__ __forceinline__ void merge_slices(const float* __restrict__ o_part, const float* __restrict__ ml_part,
+                                             int64_t sbase, int n_slices, float* s_w, float* s_den, float* s_red,
+                                             void* __restrict__ o, int o_dtype, int64_t o_base) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int kThreads = W * 64, PAIRS = G * D / 2;
+  constexpr int SG = (PAIRS < kThreads) ? kThreads / PAIRS : 1, NC = (PAIRS + kThreads - 1) / kThreads;
+  static_assert(PAIRS * SG == kThreads * NC, "whole pairs per thread");
+  constexpr int N = (SG * NC >= 4) ? 8 : 32 / (SG * NC);
+  const int sg = tid / (kThreads / SG);
+  float nx[NC], ny[NC];
+  const float* col[NC];
+  const float* wcol[NC];
+#pragma unroll
+  for (int k = 0; k < NC; ++k) {
+    const int c = 2 * ((tid % (kThreads / SG)) + k * kThreads);
+    nx[k] = ny[k] = 0.f;
+    col[k] = o_part + (sbase * G + c / D) * D + c % D;
+    wcol[k] = s_w + (c / D) * kAttnMaxSplits;
+  }
+  constexpr int64_t pitch = (int64_t)G * D;
+  F2 xa[NC][N], xb[NC][N];
+  // A whole block of N slices a thread without a question asked: where it is clamped and masked, a slice costs a dozen vector
+  // instructions, and one block at a time waits for memory as often (one pair of 20000 tokens, 2 heads of 4, bf16, 79 slices 13.4 ->
+  // 12.5 us; fp32, 8 pairs of 32769 tokens, 64 slices, 4 heads 59.5 -> 58.2).  In
+  // the last one four slices per branch, those past the last loaded as the last one and counted as zero: with a branch
+  // around each of them every weight read from LDS is waited for by itself (one pair of dim 128, 4 heads: 313
+  // slices 37.3 -> 32.1 us, 256 slices 35.7 -> 23.9; 8 heads, 313 slices 59.3 -> 46.5).
+  auto whole = [&](int s0) { return s0 - sg + SG * N <= n_slices; };
+  auto request = [&](F2 (&x)[NC][N], int s0) __attribute__((always_inline)) {
+    if (whole(s0)) {
+#pragma unroll
+      for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int k = 0; k < NC; ++k) x[k][i] = load_shared(col[k] + s0 * pitch + i * (SG * pitch));
+    } else {
+#pragma unroll
+      for (int i0 = 0; i0 < N; i0 += 4)
+        if (s0 + i0 * SG < n_slices) {
+#pragma unroll
+          for (int i = i0; i < i0 + 4; ++i)
+#pragma unroll
+            for (int k = 0; k < NC; ++k) x[k][i] = load_shared(col[k] + min(s0 + i * SG, n_slices - 1) * pitch);
+        }
+    }
+  };
+  // the (max, sum) pairs first: they are waited for first
+  auto pair = [&](int g, int sp) { return load_shared(&ml_part[((sbase + sp) * G + g) * 2]); };
+  F2 mine = (wave < G && lane < n_slices) ? pair(wave, lane) : F2{-INFINITY, 0.f};   // read once: up to 64 slices need no more
+  request(xa, sg);
+  for (int g = wave; g < G; g += W) {
+    if (g != wave) mine = (lane < n_slices) ? pair(g, lane) : F2{-INFINITY, 0.f};
+    float mloc = mine.x;
+    for (int sp = lane + 64; sp < n_slices; sp += 64) mloc = fmaxf(mloc, pair(g, sp).x);
+    mloc = across_lanes<0x3f>(mloc, [](float a, float b) { return fmaxf(a, b); });
+    float dloc = 0.f;
+    for (int sp = lane; sp < n_slices; sp += 64) {
+      const F2 ml = (sp < 64) ? mine : pair(g, sp);
+      const float f = (ml.x == -INFINITY) ? 0.f : exp2_raw(ml.x - mloc);
+      s_w[g * kAttnMaxSplits + sp] = f;
+      dloc += f * ml.y;
+    }
+    dloc = across_lanes<0x3f>(dloc, [](float a, float b) { return a + b; });
+    if (lane == 0) s_den[g] = dloc;
+  }
+  __syncthreads();
+  auto add = [&](const F2 (&x)[NC][N], int s0) __attribute__((always_inline)) {
+    if (whole(s0)) {
+#pragma unroll
+      for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int k = 0; k < NC; ++k) {
+          const float w = wcol[k][s0 + i * SG];
+          nx[k] = fmaf(x[k][i].x, w, nx[k]);
+          ny[k] = fmaf(x[k][i].y, w, ny[k]);
+        }
+    } else {
+#pragma unroll
+      for (int i0 = 0; i0 < N; i0 += 4)
+        if (s0 + i0 * SG < n_slices) {
+          float w[NC][4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int k = 0; k < NC; ++k) w[k][i] = wcol[k][min(s0 + (i0 + i) * SG, n_slices - 1)];
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int k = 0; k < NC; ++k) {
+              const bool in = s0 + (i0 + i) * SG < n_slices;
+              nx[k] = fmaf(in ? x[k][i0 + i].x : 0.f, in ? w[k][i] : 0.f, nx[k]);
+              ny[k] = fmaf(in ? x[k][i0 + i].y : 0.f, in ? w[k][i] : 0.f, ny[k]);
+            }
+        }
+    }
+  };
+  for (int s0 = sg;;) {                  // (the next block on its way while one is added up)
+    const int s1 = s0 + SG * N, s2 = s1 + SG * N;
+    if (s1 < n_slices) request(xb, s1);
+    add(xa, s0);
+    if (s1 >= n_slices) break;
+    if (s2 < n_slices) request(xa, s2);
+    add(xb, s1);
+    if (s2 >= n_slices) break;
+    s0 = s2;
+  }
+  if constexpr (SG > 1) {
+    s_red[2 * tid] = nx[0];
+    s_red[2 * tid + 1] = ny[0];
+    __syncthreads();
+    if (sg > 0) return;
+#pragma unroll
+    for (int i = 1; i < SG; ++i) {
+      nx[0] += s_red[2 * (tid + i * PAIRS)];
+      ny[0] += s_red[2 * (tid + i * PAIRS) + 1];
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < NC; ++k) {
+    const int c = 2 * ((tid % (kThreads / SG)) + k * kThreads);
+    put_out(o, o_dtype, o_base + c, nx[k], ny[k], s_den[c / D]);
+  }
+}
+
+}  // namespace
 
 hipError_t launch_attn_f32(int G, int dim, const AttnCall& c);
 

@@ -17,53 +17,6 @@ namespace {
 
 constexpr int kTableSlots = kAttnMaxTable + 64;   // block table of a slice in LDS: slices start and end on whole tiles
 
-// Partial results travel between workgroups that may sit on different XCDs (each with its own L2)
-// inside one launch.  They are written and read with device-scope relaxed atomic accesses (8 bytes
-// each), which go through to the level all XCDs share, instead of plain accesses bracketed by
-// device-scope fences: such a fence writes back / invalidates a whole L2, and one per workgroup cost
-// this kernel a factor of three.
-struct __attribute__((aligned(8))) F2 { float x, y; };
-__device__ __forceinline__ void store_shared(float* p, float x, float y) {
-  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), __builtin_bit_cast(uint64_t, F2{x, y}), __ATOMIC_RELAXED,
-                     __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ F2 load_shared(const float* p) {
-  return __builtin_bit_cast(F2, __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED,
-                                                  __HIP_MEMORY_SCOPE_AGENT));
-}
-
-// op over the lanes of a wave whose numbers differ in the bits of MASK (0x30: the four 16-lane rows; 0x3f: all), the result in
-// every lane.  Inside the vector unit: the same through LDS (shuffles) took 0.1 us a step where a workgroup waits for it.
-template <int MASK, class Op>
-__device__ __forceinline__ float across_lanes(float x, Op&& op) {
-  auto dpp = [&](auto ctrl) { return op(x, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), decltype(ctrl)::value, 0xF, 0xF, true))); };
-  if constexpr (MASK & 15) {
-    x = dpp(std::integral_constant<int, 0xB1>{});    // lane ^ 1
-    x = dpp(std::integral_constant<int, 0x4E>{});    // lane ^ 2
-    x = dpp(std::integral_constant<int, 0x141>{});   // mirrored within 8, then within 16
-    x = dpp(std::integral_constant<int, 0x140>{});
-  }
-  // (the rows of the first result are 0 0 2 2 and those of the second 1 1 3 3; then 0 1 0 1 and 2 3 2 3)
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  x = op(__uint_as_float(r[0]), __uint_as_float(r[1]));
-  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return op(__uint_as_float(h[0]), __uint_as_float(h[1]));
-}
-
-// two neighbouring outputs: sums over the tokens divided by the sum of the weights (0 for an empty cache)
-__device__ __forceinline__ void put_out(void* __restrict__ o, int o_dtype, int64_t at, float x, float y, float den) {
-  const float rx = den > 0.f ? x / den : 0.f, ry = den > 0.f ? y / den : 0.f;
-  if (o_dtype == CKV_BF16) {
-    uint16_t* op = reinterpret_cast<uint16_t*>(o) + at;
-    op[0] = f32_to_bf16_rne(rx);
-    op[1] = f32_to_bf16_rne(ry);
-  } else {
-    float* op = reinterpret_cast<float*>(o) + at;
-    op[0] = rx;
-    op[1] = ry;
-  }
-}
-
 // How a lane sees a cache row of D bf16 channels.  K rows arrive whole (16-byte pieces, consecutive lanes
 // consecutive pieces) and turn into MFMA operands through LDS.  Of a V row lane n of a 16-lane group
 // takes the EV = D/16 channels EV*n .. EV*n + EV - 1: at dim 128 a 16-byte piece straight from memory, at
@@ -141,107 +94,6 @@ __device__ __forceinline__ f32x4 qk_step(const uint4& k, const uint4& qv) {
            __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a.h[1], b.h[1], zero, 0, 0, 0);
   } else {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, k), __builtin_bit_cast(bf16x8, qv), zero, 0, 0, 0);
-  }
-}
-
-// The slices of one (batch, KV head), merged by the workgroup that arrived last: weights of the slices
-// per query head (a wave takes a head), and the slices' sums: every thread owns NC pairs of neighbouring
-// channels and adds them up over the slices; with fewer pairs than threads, groups of threads take every
-// SG-th slice and their sums are added in group order.  The first N slices of a thread (all of them for
-// up to N * SG slices) are requested before the weights are worked out, so that one memory latency covers both.
-// s_w: [G][kAttnMaxSplits] floats, s_red: two per thread.
-template <int D, int G, int W>
-__device__ __forceinline__ void merge_slices(const float* __restrict__ o_part, const float* __restrict__ ml_part,
-                                             int64_t sbase, int n_slices, float* s_w, float* s_den, float* s_red,
-                                             void* __restrict__ o, int o_dtype, int64_t o_base) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  constexpr int kThreads = W * 64, PAIRS = G * D / 2;
-  constexpr int SG = (PAIRS < kThreads) ? kThreads / PAIRS : 1, NC = (PAIRS + kThreads - 1) / kThreads;
-  static_assert(PAIRS * SG == kThreads * NC, "whole pairs per thread");
-  constexpr int N = (SG * NC >= 4) ? 8 : 32 / (SG * NC);
-  const int sg = tid / (kThreads / SG);
-  float nx[NC], ny[NC];
-  const float* col[NC];
-  const float* wcol[NC];
-#pragma unroll
-  for (int k = 0; k < NC; ++k) {
-    const int c = 2 * ((tid % (kThreads / SG)) + k * kThreads);
-    nx[k] = ny[k] = 0.f;
-    col[k] = o_part + (sbase * G + c / D) * D + c % D;
-    wcol[k] = s_w + (c / D) * kAttnMaxSplits;
-  }
-  constexpr int64_t pitch = (int64_t)G * D;
-  F2 x[NC][N];
-  // Four slices per branch, those past the last loaded as the last one and counted as zero: with a branch
-  // around each of them every weight read from LDS is waited for by itself (one pair of dim 128, 4 heads: 313
-  // slices 37.3 -> 32.1 us, 256 slices 35.7 -> 23.9; 8 heads, 313 slices 59.3 -> 46.5).
-  auto request = [&](int s0) {
-#pragma unroll
-    for (int i0 = 0; i0 < N; i0 += 4)
-      if (s0 + i0 * SG < n_slices) {
-#pragma unroll
-        for (int i = i0; i < i0 + 4; ++i)
-#pragma unroll
-          for (int k = 0; k < NC; ++k) x[k][i] = load_shared(col[k] + min(s0 + i * SG, n_slices - 1) * pitch);
-      }
-  };
-  // the (max, sum) pairs first: they are waited for first
-  auto pair = [&](int g, int sp) { return load_shared(&ml_part[((sbase + sp) * G + g) * 2]); };
-  F2 mine = (wave < G && lane < n_slices) ? pair(wave, lane) : F2{-INFINITY, 0.f};   // read once: up to 64 slices need no more
-  request(sg);
-  for (int g = wave; g < G; g += W) {
-    if (g != wave) mine = (lane < n_slices) ? pair(g, lane) : F2{-INFINITY, 0.f};
-    float mloc = mine.x;
-    for (int sp = lane + 64; sp < n_slices; sp += 64) mloc = fmaxf(mloc, pair(g, sp).x);
-    mloc = across_lanes<0x3f>(mloc, [](float a, float b) { return fmaxf(a, b); });
-    float dloc = 0.f;
-    for (int sp = lane; sp < n_slices; sp += 64) {
-      const F2 ml = (sp < 64) ? mine : pair(g, sp);
-      const float f = (ml.x == -INFINITY) ? 0.f : exp2_raw(ml.x - mloc);
-      s_w[g * kAttnMaxSplits + sp] = f;
-      dloc += f * ml.y;
-    }
-    dloc = across_lanes<0x3f>(dloc, [](float a, float b) { return a + b; });
-    if (lane == 0) s_den[g] = dloc;
-  }
-  __syncthreads();
-  for (int s0 = sg;;) {
-#pragma unroll
-    for (int i0 = 0; i0 < N; i0 += 4)
-      if (s0 + i0 * SG < n_slices) {
-        float w[NC][4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int k = 0; k < NC; ++k) w[k][i] = wcol[k][min(s0 + (i0 + i) * SG, n_slices - 1)];
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-          for (int k = 0; k < NC; ++k) {
-            const bool in = s0 + (i0 + i) * SG < n_slices;
-            nx[k] = fmaf(in ? x[k][i0 + i].x : 0.f, in ? w[k][i] : 0.f, nx[k]);
-            ny[k] = fmaf(in ? x[k][i0 + i].y : 0.f, in ? w[k][i] : 0.f, ny[k]);
-          }
-      }
-    s0 += SG * N;
-    if (s0 >= n_slices) break;
-    request(s0);
-  }
-  if constexpr (SG > 1) {
-    s_red[2 * tid] = nx[0];
-    s_red[2 * tid + 1] = ny[0];
-    __syncthreads();
-    if (sg > 0) return;
-#pragma unroll
-    for (int i = 1; i < SG; ++i) {
-      nx[0] += s_red[2 * (tid + i * PAIRS)];
-      ny[0] += s_red[2 * (tid + i * PAIRS) + 1];
-    }
-  }
-#pragma unroll
-  for (int k = 0; k < NC; ++k) {
-    const int c = 2 * ((tid % (kThreads / SG)) + k * kThreads);
-    put_out(o, o_dtype, o_base + c, nx[k], ny[k], s_den[c / D]);
   }
 }
 
@@ -477,10 +329,7 @@ __global__ __launch_bounds__(W * 64, 2) void attn_mfma_kernel(
     }
   }
 
-  // ---- merge the waves of this workgroup -------------------------------------------------------
-  // Every wave leaves its sums as they are, in its own part of the staging area, and whoever adds them up works out the
-  // waves' weights for itself: one barrier.  (Weighed by the waves, behind a barrier of their own, and the sum of the weights
-  // worked out by G threads at the end: 1.2 us more from the slowest wave's last tile to the partial's store.)
+  // ---- merge the waves of this workgroup: every wave leaves its sums as they are, in its own part of the staging area ------
   l = across_lanes<0x30>(l, [](float a, float b) { return a + b; });
   if (lane < G) { s_m[wave][lane] = ref; s_l[wave][lane] = l; }   // (lane = column = head)
   static_assert(G * D * 4 <= R::LDS, "a wave's sums in its own part");
@@ -498,27 +347,7 @@ __global__ __launch_bounds__(W * 64, 2) void attn_mfma_kernel(
   __syncthreads();
   const int64_t sbase = ((int64_t)b * kv_heads + kvh) * n_splits;
   const int64_t pbase = (sbase + split) * G, o_base = ((int64_t)b * kv_heads + kvh) * G * D;
-  for (int c = 2 * tid; c < G * D; c += 2 * kThreads) {
-    const int g = c / D;
-    float f[W], M = s_m[0][g], L = 0.f, x = 0.f, y = 0.f;
-#pragma unroll
-    for (int w = 0; w < W; ++w) f[w] = s_m[w][g];
-#pragma unroll
-    for (int w = 1; w < W; ++w) M = fmaxf(M, f[w]);
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-      f[w] = (f[w] == -INFINITY) ? 0.f : exp2_raw(f[w] - M);
-      const float2 v = *reinterpret_cast<const float2*>(s_o + w * kPart + c);
-      x = fmaf(v.x, f[w], x);
-      y = fmaf(v.y, f[w], y);
-      L = fmaf(s_l[w][g], f[w], L);
-    }
-    if (n_slices == 1) put_out(o, o_dtype, o_base + c, x, y, L);   // the only slice: nothing to merge
-    else {
-      store_shared(&o_part[pbase * D + c], x, y);
-      if (c % D == 0) store_shared(&ml_part[(pbase + g) * 2], M, L);
-    }
-  }
+  put_waves<D, G, W>(s_o, kPart, &s_m[0][0], &s_l[0][0], n_slices == 1, o_part, ml_part, pbase, o, o_dtype, o_base);
   if (n_slices == 1) return;
 
   // ---- the last slice of this (batch, KV head) to arrive merges them all ----------------------

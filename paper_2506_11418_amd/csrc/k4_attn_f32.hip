@@ -35,15 +35,6 @@ __device__ __forceinline__ float row_sum(float x) {
   return x;
 }
 
-// Partial results travel between workgroups with device-scope relaxed atomic accesses (see the bf16
-// kernel's file).
-__device__ __forceinline__ void store_shared_f32(float* p, float v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float load_shared_f32(const float* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // partial layout: o_part[((b*Hkv + kvh)*S + split)*G + g][D], ml_part[...][2] = (max, sum)
 //
 // Thread mapping: LPR = row_bytes/16 lanes share one cache row ("row group"); a wave holds 64/LPR
@@ -67,13 +58,12 @@ __global__ __launch_bounds__(kThreads, G <= 4 ? 3 : 2) void attn_f32_kernel(
   constexpr int LPR = D / E;
   constexpr int NRG = kThreads / LPR;
   constexpr int U = kUnroll;
-  __shared__ float s_m[NRG][G];
-  __shared__ float s_l[NRG][G];
-  constexpr int GG = (G < 4) ? G : 4;   // query heads merged per pass of the final reduction
-  // staging rows of the workgroup's reduction; later the slice weights [G][kAttnMaxSplits] of the merge
-  constexpr int kStageFloats = GG * NRG * D, kWeightFloats = G * kAttnMaxSplits;
-  __shared__ float s_raw[kStageFloats > kWeightFloats ? kStageFloats : kWeightFloats];
-  float (*s_o)[NRG][D] = reinterpret_cast<float (*)[NRG][D]>(s_raw);
+  constexpr int W = kThreads / 64;
+  __shared__ float s_m[W][G], s_l[W][G];
+  __shared__ float s_red[2 * kThreads];
+  // the waves' sums; later the slice weights [G][kAttnMaxSplits] of the merge
+  constexpr int kStageFloats = W * G * D, kWeightFloats = G * kAttnMaxSplits;
+  __shared__ __attribute__((aligned(16))) float s_raw[kStageFloats > kWeightFloats ? kStageFloats : kWeightFloats];
 
   const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
   const int tid = threadIdx.x, rg = tid / LPR, piece = tid % LPR;
@@ -191,46 +181,24 @@ __global__ __launch_bounds__(kThreads, G <= 4 ? 3 : 2) void attn_f32_kernel(
     }
   }
 
-  // ---- merge the NRG row groups of this workgroup ---------------------------------------------
-  if (piece == 0) {
+  // ---- merge the row groups of every wave, then the waves of this workgroup --------------------
+  const int lane = tid & 63, wave = tid >> 6;
 #pragma unroll
-    for (int g = 0; g < G; ++g) { s_m[rg][g] = m[g]; s_l[rg][g] = l[g]; }
+  for (int g = 0; g < G; ++g) {
+    constexpr int ROWS = 64 - LPR;        // the bits of a lane's number that say which row group it belongs to
+    const float mw = across_lanes<ROWS>(m[g], [](float a, float b2) { return fmaxf(a, b2); });
+    const float f = (m[g] == -INFINITY) ? 0.f : exp2_raw(m[g] - mw);
+    auto sum = [&](float x) { return across_lanes<ROWS>(x * f, [](float a, float b2) { return a + b2; }); };
+    float4 x;
+    x.x = sum(acc[g][0]); x.y = sum(acc[g][1]); x.z = sum(acc[g][2]); x.w = sum(acc[g][3]);
+    const float lw = sum(l[g]);
+    if (lane < LPR) *reinterpret_cast<float4*>(s_raw + (wave * G + g) * D + lane * E) = x;
+    if (lane == 0) { s_m[wave][g] = mw; s_l[wave][g] = lw; }
   }
   __syncthreads();
-  const int64_t pbase = (((int64_t)b * kv_heads + kvh) * n_splits + split) * G;
-  // GG heads at a time: every row group rescales its accumulators to the workgroup's maximum and
-  // parks them in LDS, then each thread sums a few (head, channel) columns over the row groups
-#pragma unroll
-  for (int g0 = 0; g0 < G; g0 += GG) {
-    if (g0 > 0) __syncthreads();
-#pragma unroll
-    for (int gg = 0; gg < GG; ++gg) {
-      const int g = g0 + gg;
-      float M = -INFINITY;
-      for (int r2 = 0; r2 < NRG; ++r2) M = fmaxf(M, s_m[r2][g]);
-      const float f = (m[g] == -INFINITY) ? 0.f : exp2f(m[g] - M);
-#pragma unroll
-      for (int e = 0; e < E; ++e) s_o[gg][rg][piece * E + e] = acc[g][e] * f;
-    }
-    __syncthreads();
-    for (int idx = tid; idx < GG * D; idx += kThreads) {
-      const int gg = idx / D, d = idx % D;
-      float sum = 0.f;
-      for (int r2 = 0; r2 < NRG; ++r2) sum += s_o[gg][r2][d];
-      store_shared_f32(&o_part[(pbase + g0 + gg) * D + d], sum);
-    }
-    if (tid < GG) {
-      const int g = g0 + tid;
-      float M = -INFINITY, L = 0.f;
-      for (int r2 = 0; r2 < NRG; ++r2) M = fmaxf(M, s_m[r2][g]);
-      for (int r2 = 0; r2 < NRG; ++r2) {
-        const float mr = s_m[r2][g];
-        L += (mr == -INFINITY) ? 0.f : s_l[r2][g] * exp2f(mr - M);
-      }
-      store_shared_f32(&ml_part[(pbase + g) * 2], M);
-      store_shared_f32(&ml_part[(pbase + g) * 2 + 1], L);
-    }
-  }
+  const int64_t sbase = ((int64_t)b * kv_heads + kvh) * n_splits, o_base = ((int64_t)b * kv_heads + kvh) * G * D;
+  put_waves<D, G, W>(s_raw, G * D, &s_m[0][0], &s_l[0][0], n_splits == 1, o_part, ml_part, (sbase + split) * G, o, o_dtype, o_base);
+  if (n_splits == 1) return;
 
   // ---- the last slice of this (batch, KV head) to arrive merges them all ----------------------
   // Every thread waits until its own partial stores have been acknowledged, the workgroup meets,
@@ -243,73 +211,8 @@ __global__ __launch_bounds__(kThreads, G <= 4 ? 3 : 2) void attn_f32_kernel(
   if (tid == 0) s_is_last = (atomicAdd(my_count, 1) == n_splits - 1);
   __syncthreads();
   if (!s_is_last) return;
-  // weights of the slices, per query head: a wave takes a head (two for G = 8)
-  float* s_w = s_raw;                     // [G][kAttnMaxSplits] (the staging rows are no longer needed)
-  float* s_den = &s_l[0][0];              // [G]
-  const int lane = tid & 63, wave = tid >> 6;
-  const int64_t sbase = ((int64_t)b * kv_heads + kvh) * n_splits;
-  for (int g = wave; g < G; g += kThreads / 64) {
-    float mloc = -INFINITY;
-    for (int sp = lane; sp < n_splits; sp += 64) mloc = fmaxf(mloc, load_shared_f32(&ml_part[((sbase + sp) * G + g) * 2]));
-#pragma unroll
-    for (int sh = 32; sh > 0; sh >>= 1) mloc = fmaxf(mloc, __shfl_xor(mloc, sh));
-    float dloc = 0.f;
-    for (int sp = lane; sp < n_splits; sp += 64) {
-      const float ms = load_shared_f32(&ml_part[((sbase + sp) * G + g) * 2]);       // max of slice sp
-      const float ls = load_shared_f32(&ml_part[((sbase + sp) * G + g) * 2 + 1]);   // its sum of exponentials
-      const float f = (ms == -INFINITY) ? 0.f : exp2f(ms - mloc);
-      s_w[g * kAttnMaxSplits + sp] = f;
-      dloc += f * ls;
-    }
-#pragma unroll
-    for (int sh = 32; sh > 0; sh >>= 1) dloc += __shfl_xor(dloc, sh);
-    if (lane == 0) s_den[g] = dloc;
-  }
-  __syncthreads();
-  // Every thread owns NC (head, channel) columns, consecutive threads consecutive channels (a wave's
-  // load is 256 contiguous bytes), and sums them over the slices in slice order: blocks of 32
-  // slices with all NC * 32 loads in flight, then blocks of 8, then single slices.  Which
-  // workgroup runs this never changes the order, so the bits are the same from run to run.
-  constexpr int NC = (G * D + kThreads - 1) / kThreads;
-  float num[NC];
-  const float* col[NC];
-  const float* wcol[NC];
-#pragma unroll
-  for (int k = 0; k < NC; ++k) {
-    const int c = min(tid + k * kThreads, G * D - 1);        // clamped: threads past the last column repeat it
-    num[k] = 0.f;
-    col[k] = o_part + (sbase * G + c / D) * D + c % D;
-    wcol[k] = s_w + (c / D) * kAttnMaxSplits;
-  }
-  const int64_t pitch = (int64_t)G * D;
-  auto block = [&](int s0, auto n_c) {
-    constexpr int N = decltype(n_c)::value;
-    float x[NC][N];
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-#pragma unroll
-      for (int k = 0; k < NC; ++k) x[k][i] = load_shared_f32(col[k] + (int64_t)(s0 + i) * pitch);
-#pragma unroll
-    for (int i = 0; i < N; ++i)
-#pragma unroll
-      for (int k = 0; k < NC; ++k) num[k] = fmaf(x[k][i], wcol[k][s0 + i], num[k]);
-  };
-  int s0 = 0;
-  for (; s0 + 32 <= n_splits; s0 += 32) block(s0, std::integral_constant<int, 32>{});
-  for (; s0 + 8 <= n_splits; s0 += 8) block(s0, std::integral_constant<int, 8>{});
-  for (; s0 < n_splits; ++s0) block(s0, std::integral_constant<int, 1>{});
-#pragma unroll
-  for (int k = 0; k < NC; ++k) {
-    const int c = tid + k * kThreads;
-    if (c < G * D) {
-      const float den = s_den[c / D];
-      const float res = den > 0.f ? num[k] / den : 0.f;
-      const int64_t oi = ((int64_t)b * kv_heads + kvh) * G * D + c;
-      if (o_dtype == CKV_BF16) reinterpret_cast<uint16_t*>(o)[oi] = f32_to_bf16_rne(res);
-      else reinterpret_cast<float*>(o)[oi] = res;
-    }
-  }
-  if (tid == 0) atomicExch(my_count, 0);  // the workspace is ready for the next call
+  if (tid == 0) atomicExch(my_count, 0);  // all have arrived: the workspace is ready for the next call
+  merge_slices<D, G, W>(o_part, ml_part, sbase, n_splits, s_raw, &s_l[0][0], s_red, o, o_dtype, o_base);
 }
 
 template <int D, int G>
