@@ -88,19 +88,55 @@ __device__ inline RowBases stage_row_bases(int32_t* s_rb, const PagedSide& pg, i
 }
 
 // RoundMap with fold > 0: the entries of the original tokens of input tokens [u0, u0 + n), n a whole number of chunks,
-// THREADS threads of which this is number `tid`; place(u): output index of input token u0 + u.  Four loads in flight.
-template <class F>
-__device__ __forceinline__ void fold_map(const RoundMap& map, int64_t bh, int u0, int n, int threads, int tid, F&& place) {
-  int32_t* a = map.p + bh * map.stride;
-  const int hi = (int)min((int64_t)map.len, ((int64_t)u0 + n) << map.fold);
-  for (int t = (u0 << map.fold) + tid; t < hi; t += 4 * threads) {
-    int u[4];
+// `threads` threads of which this is number `tid`; place(u): output index of input token u0 + u.  Four loads in flight,
+// the first of them as early as the caller likes.
+typedef int FoldAhead __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ int fold_end(const RoundMap& map, int u0, int n) {
+  return (int)min((int64_t)map.len, ((int64_t)u0 + n) << map.fold);
+}
+__device__ __forceinline__ FoldAhead fold_request(const RoundMap& map, int64_t bh, int hi, int threads, int t) {
+  const int32_t* a = map.p + bh * map.stride;
+  FoldAhead x;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) u[i] = a[min((int64_t)t + (int64_t)i * threads, (int64_t)hi - 1)];
+  for (int i = 0; i < 4; ++i) x[i] = a[min((int64_t)t + (int64_t)i * threads, (int64_t)hi - 1)];
+  return x;
+}
+template <class F>
+__device__ __forceinline__ void fold_map(const RoundMap& map, int64_t bh, int u0, int hi, int threads, int t, FoldAhead x, F&& place) {
+  int32_t* a = map.p + bh * map.stride;
+  while (t < hi) {
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      if ((int64_t)t + (int64_t)i * threads < hi) a[t + i * threads] = place(u[i] - u0);
+      if ((int64_t)t + (int64_t)i * threads < hi) a[t + i * threads] = place(x[i] - u0);
+    t += 4 * threads;
+    if (t < hi) x = fold_request(map, bh, hi, threads, t);
   }
+}
+template <class F>
+__device__ __forceinline__ void fold_map(const RoundMap& map, int64_t bh, int u0, int n, int threads, int tid, F&& place) {
+  const int hi = fold_end(map, u0, n), t = (u0 << map.fold) + tid;
+  if (t < hi) fold_map(map, bh, u0, hi, threads, t, fold_request(map, bh, hi, threads, t), place);
+}
+
+// Sum over this lane and the lanes before it in the wave, all 64 of them active: six additions on DPP, which a ds_bpermute
+// and its wait for each would take ten times as long for.
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t x) {
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);   // a row of 16: one, two, four, eight lanes up
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);   // the last lane of rows 0 and 2 into rows 1 and 3
+  x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);   // lane 31 into rows 2 and 3
+  return x;
+}
+// Sum over groups of N neighbouring lanes, all of them active, in each of them.
+template <int N>
+__device__ __forceinline__ int group_sum(int x) {
+  static_assert(N == 1 || N == 2 || N == 4 || N == 8, "lanes of a group");
+  if (N >= 2) x += __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, true);
+  if (N >= 4) x += __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, true);
+  if (N >= 8) x += __builtin_amdgcn_update_dpp(0, x, 0x141, 0xF, 0xF, true);
+  return x;
 }
 
 // fp32 -> uint32 whose unsigned order is the float order (-0 and +0 compare equal)

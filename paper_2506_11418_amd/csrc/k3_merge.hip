@@ -20,21 +20,16 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kMaxHalf = 1024;  // max |A| = |B| (chunk <= 2048); chunks up to 1024 tokens take half the LDS
 
-__device__ inline int block_exclusive_scan(int v, int* s_wave_tot, int* total) {
+__device__ inline uint32_t block_exclusive_scan(uint32_t v, uint32_t* s_wave_tot, uint32_t* total) {
   // 256 threads = 4 waves
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int inc = v;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int o = __shfl_up(inc, d);
-    if (lane >= d) inc += o;
-  }
+  const uint32_t inc = wave_inclusive_scan(v);
   if (lane == 63) s_wave_tot[wave] = inc;
   __syncthreads();
-  int base = 0, tot = 0;
+  uint32_t base = 0, tot = 0;
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
-    const int t = s_wave_tot[w];
+    const uint32_t t = s_wave_tot[w];
     if (w < wave) base += t;
     tot += t;
   }
@@ -101,7 +96,7 @@ enum { kMergeFull = 0, kMergeKeys = 1, kMergeOrigin = 2 };
 // EDGES: the first edge_blocks workgroups copy the tokens that bypass the clustering (none of the others
 // touches those rows).
 template <typename T, int D, int MODE, int MH, bool PAGED, bool EDGES>   // MH: capacity of the per-chunk LDS arrays (|A| = |B| <= MH)
-__global__ __launch_bounds__(kThreads) void merge_kernel(
+__global__ __launch_bounds__(kThreads, sizeof(T) == 2 && MODE == kMergeFull ? 5 : 1) void merge_kernel(
     const T* __restrict__ K, const T* __restrict__ V, const int32_t* __restrict__ deg_in, TensorView in,
     int seq, int chunk, int n_chunks, float r, const int32_t* __restrict__ dst_local,
     const float* __restrict__ score, T* __restrict__ K_out, T* __restrict__ V_out,
@@ -129,14 +124,15 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
   __shared__ __attribute__((aligned(16))) int32_t s_fill[MH];
   __shared__ int16_t s_start[MH];
   __shared__ int16_t s_members[MH];
-  __shared__ int16_t s_local_out[2 * MH];
-  __shared__ int16_t s_src_of_out[2 * MH];
-  __shared__ int s_wave_tot[4];
+  __shared__ __attribute__((aligned(16))) int16_t s_local_out[2 * MH];
+  __shared__ int16_t s_src_of_place[2 * MH];
+  __shared__ uint32_t s_wave_tot[4];
   // kMergeOrigin, chunks up to 1024 tokens: per output row, everything the emit loop would look up
   // through the lists, resolved once (three 8-byte words: the row's own sources, then where the
   // value rows of its own token and of its first merged source come from)
   constexpr bool DESC = (MODE == kMergeOrigin) && (MH <= 512);
   __shared__ uint2 s_desc[DESC ? 3 * 2 * MH : 1];
+  __shared__ int16_t s_out_of_place[MODE == kMergeOrigin && !DESC ? 2 * MH : 1];
   __shared__ int32_t s_rb_in[PAGED ? 2 * MH / 8 + 2 : 1];
   __shared__ int32_t s_rb_org[(PAGED && MODE == kMergeOrigin) ? 4 * MH / 8 + 2 : 1];
   __shared__ int32_t s_rb_out[PAGED ? 2 * MH / 8 + 2 : 1];
@@ -190,6 +186,22 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
     const int i = tid + it * kThreads;
     d_of[it] = (i < nA && m > 0) ? dst_local[src_base + i] : -1;
   }
+  // (so are the map's entries and the lists of the round before: each was a memory latency of its own further down)
+  const int map_threads = parts * kThreads, map_hi = fold_end(map, g0, chunk), map_t = (g0 << map.fold) + part * kThreads + tid;
+  FoldAhead map_ahead{};
+  if (map.p != nullptr && map.fold > 0) map_ahead = fold_request(map, bh, map_hi, map_threads, map_t);
+  constexpr int LP = (6 * MH / 8 + kThreads - 1) / kThreads;
+  static_assert(LP == 2 || LP == 3, "pieces of the lists per thread");
+  u32x4 piece0{}, piece1{}, piece2{};                // (an array of them ends up in scratch)
+  const int n_list = MODE == kMergeOrigin ? min(2, org.n_chunks0 - 2 * g) * 3 * half : 0;   // of one or two chunks, side by side
+  const int16_t* lists_in = MODE == kMergeOrigin ? org.lists + ((int64_t)bh * org.n_chunks0 + 2 * g) * 3 * half : nullptr;
+  const bool by_piece = half % 8 == 0 && (reinterpret_cast<uintptr_t>(lists_in) & 15) == 0;
+  if (MODE == kMergeOrigin && by_piece) {
+    auto request = [&](int i) { return *reinterpret_cast<const u32x4*>(lists_in + 8 * min(tid + i * kThreads, n_list / 8 - 1)); };
+    piece0 = request(0);
+    piece1 = request(1);
+    if (LP > 2) piece2 = request(2);
+  }
   const bool ranked = m > 0 && m < nA;
   uint32_t key[PER];
   static_assert(MH >= 512 && kThreads == 256, "two histograms of a digit in either array");
@@ -238,21 +250,16 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
       c[0] = (int)h.w; c[1] = (int)h.z; c[2] = (int)h.y; c[3] = (int)h.x;
 #pragma unroll
       for (int e = 0; e < 4; ++e) sum += c[e];
-      int inc = sum;
-#pragma unroll
-      for (int x = 1; x < 64; x <<= 1) {
-        const int o = __shfl_up(inc, x);
-        if (lane >= x) inc += o;
-      }
+      const int inc = (int)wave_inclusive_scan((uint32_t)sum);
       const int owner = __ffsll((unsigned long long)__ballot(inc >= left)) - 1;   // (the last lane's sum reaches it)
       int above = inc - sum, e = 0;
 #pragma unroll
       for (int k = 0; k < 3; ++k)
         if (e == k && above + c[k] < left) { above += c[k]; ++e; }
       const int n = e == 0 ? c[0] : e == 1 ? c[1] : e == 2 ? c[2] : c[3];
-      cut |= (uint32_t)__shfl(255 - 4 * lane - e, owner) << shift;
-      left -= __shfl(above, owner);
-      equal = __shfl(n, owner);
+      cut |= (uint32_t)__builtin_amdgcn_readlane(255 - 4 * lane - e, owner) << shift;
+      left -= __builtin_amdgcn_readlane(above, owner);
+      equal = __builtin_amdgcn_readlane(n, owner);
     }
     if (left < equal) {                            // (the same for every thread) only the earliest of the equal ones
       int16_t* at_cut = s_local_out;               // (not in use yet)
@@ -300,8 +307,8 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
       sum += c[e];
       longest = max(longest, c[e]);
     }
-    int tot;
-    int base = block_exclusive_scan(sum, s_wave_tot, &tot);
+    uint32_t tot;
+    uint32_t base = block_exclusive_scan((uint32_t)sum, s_wave_tot, &tot);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int j = tid * 4 + e;
@@ -342,24 +349,34 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
   }
 
   // ---- retained tokens: prefix sum over the chunk --------------------------------------------
+  // Their output rows, and the places at which they are emitted: rows of two or more sources first, then rows of
+  // one, the copies last, so that the row groups of a wave do the same work side by side.  One scan of three sums
+  // (10, 11 and 11 bits; 2048 copies, a whole chunk, pass theirs only in the total).
   {
-    int flags = 0, cnt = 0;
+    auto sums = [](int n) -> uint32_t { return n > 1 ? 1u : n == 1 ? 1u << 10 : 1u << 21; };
+    int n[8];                                       // sources of a retained token, -1: merged away
+    uint32_t mine = 0;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const int u = tid * 8 + e;
-      const bool ret = (u < L) && ((u & 1) || s_dstk[u >> 1] < 0);
-      flags |= (int)ret << e;
-      cnt += ret;
+      n[e] = u >= L ? -1 : (u & 1) ? s_cnt[u >> 1] : s_dstk[u >> 1] < 0 ? 0 : -1;
+      if (n[e] >= 0) mine += sums(n[e]);
     }
-    int tot;
-    int base = block_exclusive_scan(cnt, s_wave_tot, &tot);
+    uint32_t tot;
+    uint32_t before = block_exclusive_scan(mine, s_wave_tot, &tot);
+    const int n_long = (int)(tot & 1023u);
+    const int n_merged = n_long + (int)(tot >> 10 & 2047u);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       const int u = tid * 8 + e;
-      if ((flags >> e) & 1) {
-        s_local_out[u] = (int16_t)base;
-        s_src_of_out[base] = (int16_t)u;
-        ++base;
+      if (n[e] >= 0) {
+        const int b2 = (int)(before & 1023u), b1 = (int)(before >> 10 & 2047u), b0 = (int)(before >> 21);
+        const int o = b2 + b1 + b0, place = n[e] > 1 ? b2 : n[e] == 1 ? n_long + b1 : n_merged + b0;
+        s_local_out[u] = (int16_t)o;
+        s_src_of_place[place] = (int16_t)u;
+        if constexpr (DESC) s_desc[3 * place].y = (uint32_t)o;      // (s_local_out is overwritten below)
+        else if constexpr (MODE == kMergeOrigin) s_out_of_place[place] = (int16_t)o;
+        before += sums(n[e]);
       }
     }
   }
@@ -381,7 +398,7 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
       return map.offset + out_base + ((d < 0) ? s_local_out[u] : s_local_out[2 * d + 1]);
     };
     if (map.fold > 0) {
-      fold_map(map, bh, g0, chunk, parts * kThreads, part * kThreads + tid, place);
+      fold_map(map, bh, g0, map_hi, map_threads, map_t, map_ahead, place);
     } else if (part == 0) {
       int32_t* mp = map.p + (int64_t)bh * map.stride + g0;
       for (int u = tid; u < L; u += kThreads) mp[u] = place(u);
@@ -395,17 +412,20 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
   int16_t (*s0_mem)[MH] = reinterpret_cast<int16_t (*)[MH]>(s_local_out);
   if (MODE == kMergeOrigin) {
     __syncthreads();
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int c0 = 2 * g + h;
-      if (c0 < org.n_chunks0) {
-        const int16_t* lst = org.lists + ((int64_t)bh * org.n_chunks0 + c0) * 3 * half;
-        for (int i = tid; i < half; i += kThreads) {
-          s0_cnt[h][i] = lst[i];
-          s0_start[h][i] = lst[half + i];
-          s0_mem[h][i] = lst[2 * half + i];
-        }
-      }
+    auto list_at = [&](int e) -> int16_t* {          // where element e of the lists goes
+      const int h = e >= 3 * half, i = e - h * 3 * half;
+      return i < half ? &s0_cnt[h][i] : i < 2 * half ? &s0_start[h][i - half] : &s0_mem[h][i - 2 * half];
+    };
+    if (by_piece) {                                  // (no piece straddles two of them)
+      auto park = [&](int i, u32x4 x) {
+        const int e = 8 * (tid + i * kThreads);
+        if (e < n_list) *reinterpret_cast<u32x4*>(list_at(e)) = x;
+      };
+      park(0, piece0);
+      park(1, piece1);
+      if (LP > 2) park(2, piece2);
+    } else {
+      for (int e = tid; e < n_list; e += kThreads) *list_at(e) = lists_in[e];
     }
     __syncthreads();
     if constexpr (DESC) {
@@ -420,12 +440,13 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
         return make_uint2((uint32_t)tb | ((uint32_t)ta << 16), (uint32_t)n | ((uint32_t)off << 16));
       };
       for (int o = tid; o < n_out; o += kThreads) {
-        const int tok = s_src_of_out[o];
+        const int tok = s_src_of_place[o];
         const bool isB = tok & 1;
         const int nmem = isB ? s_cnt[tok >> 1] : 0;
         const int first = isB ? (int)s_start[tok >> 1] : 0;
         const int mem0 = (nmem > 0) ? 2 * (int)s_members[first] : tok;
-        s_desc[3 * o] = make_uint2((uint32_t)tok | ((uint32_t)mem0 << 16), (uint32_t)nmem | ((uint32_t)first << 16));
+        s_desc[3 * o] = make_uint2((uint32_t)tok | ((uint32_t)mem0 << 16),
+                                   (uint32_t)nmem | ((uint32_t)first << 10) | (s_desc[3 * o].y << 20));
         s_desc[3 * o + 1] = value_words(tok);
         s_desc[3 * o + 2] = value_words(mem0);
       }
@@ -547,36 +568,35 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
   // One batch = U output rows per row group: where they come from (LDS lookups) and the loads of
   // their own rows and first merged sources, all issued before anything is consumed.
   struct Batch {
-    int ob;
-    int tok[U], nmem[U], first[U], du[U], dm[U];
+    int o[U], tok[U], nmem[U], first[U], du[U], dm[U];
     bool valid[U];
     Raw kb[U], km[U];
     typename std::conditional<MODE == kMergeKeys, NoVLoad, VLoad>::type vb[U], vm[U];
   };
   struct Where {
-    int ob;
-    int tok[U], mem0[U], nmem[U], first[U];
+    int o[U], tok[U], mem0[U], nmem[U], first[U];
     bool valid[U];
     uint2 wb[U], wm[U];
   };
   auto lookup = [&](int ob) -> Where {
     Where w;
-    w.ob = ob;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int o = ob + u * NRG + rg;
-      w.valid[u] = o < n_out;
-      const int oo = w.valid[u] ? o : n_out - 1;
+      const int at = ob + u * NRG + rg;
+      w.valid[u] = at < n_out;
+      const int place = w.valid[u] ? at : n_out - 1;
       if constexpr (DESC) {
-        const uint2 k = s_desc[3 * oo];
-        w.wb[u] = s_desc[3 * oo + 1];
-        w.wm[u] = s_desc[3 * oo + 2];
+        const uint2 k = s_desc[3 * place];
+        w.wb[u] = s_desc[3 * place + 1];
+        w.wm[u] = s_desc[3 * place + 2];
         w.tok[u] = (int)(k.x & 0xffffu);
         w.mem0[u] = (int)(k.x >> 16);
-        w.nmem[u] = (int)(k.y & 0xffffu);
-        w.first[u] = (int)(k.y >> 16);
+        w.nmem[u] = (int)(k.y & 1023u);
+        w.first[u] = (int)(k.y >> 10 & 1023u);
+        w.o[u] = (int)(k.y >> 20);
       } else {
-        w.tok[u] = s_src_of_out[oo];
+        w.tok[u] = s_src_of_place[place];
+        w.o[u] = MODE == kMergeOrigin ? s_out_of_place[place] : s_local_out[w.tok[u]];
         const bool isB = w.tok[u] & 1;
         w.nmem[u] = isB ? s_cnt[w.tok[u] >> 1] : 0;
         w.first[u] = isB ? (int)s_start[w.tok[u] >> 1] : 0;
@@ -587,24 +607,23 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
   };
   auto issue = [&](const Where& w) -> Batch {
     Batch x;
-    x.ob = w.ob;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       x.valid[u] = w.valid[u];
       x.tok[u] = w.tok[u];
+      x.o[u] = w.o[u];
       x.nmem[u] = w.nmem[u];
       x.first[u] = w.first[u];
       x.kb[u] = Row<T>::load_raw(Kin + in_off(w.tok[u]));
-      x.km[u] = Row<T>::load_raw(Kin + in_off(w.mem0[u]));
-      if constexpr (DESC) {
-        x.vb[u] = v_issue_resolved(w.wb[u]);
-        x.vm[u] = v_issue_resolved(w.wm[u]);
-      } else if constexpr (MODE != kMergeKeys) {
-        x.vb[u] = v_issue(w.tok[u]);
-        x.vm[u] = v_issue(w.mem0[u]);
-      }
+      if constexpr (DESC) x.vb[u] = v_issue_resolved(w.wb[u]);
+      else if constexpr (MODE != kMergeKeys) x.vb[u] = v_issue(w.tok[u]);
       x.du[u] = dseq ? in_deg(w.tok[u]) : 1;
-      x.dm[u] = dseq ? in_deg(w.mem0[u]) : 1;
+      if (MODE != kMergeOrigin || w.nmem[u] > 0) {
+        x.km[u] = Row<T>::load_raw(Kin + in_off(w.mem0[u]));
+        if constexpr (DESC) x.vm[u] = v_issue_resolved(w.wm[u]);
+        else if constexpr (MODE != kMergeKeys) x.vm[u] = v_issue(w.mem0[u]);
+        x.dm[u] = dseq ? in_deg(w.mem0[u]) : 1;
+      }
     }
     return x;
   };
@@ -614,7 +633,7 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (!x.valid[u]) continue;
-      const int o = x.ob + u * NRG + rg;
+      const int o = x.o[u];
       if (PAGED && !out_ok(o)) continue;
       if (x.nmem[u] == 0) {  // untouched token: bit copy
         Row<T>::store_raw(Ko + ok_off(o), x.kb[u]);
@@ -705,7 +724,7 @@ __global__ __launch_bounds__(kThreads) void merge_kernel(
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         if (!x.valid[u]) continue;
-        const int o = x.ob + u * NRG + rg;
+        const int o = x.o[u];
         if (PAGED && !out_ok(o)) continue;
         if (x.nmem[u] == 0) {  // untouched token: bit copy of the key; its value row is one cluster
           Row<T>::store_raw(Ko + ok_off(o), x.kb[u]);

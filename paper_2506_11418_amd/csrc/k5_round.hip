@@ -91,8 +91,7 @@ __device__ __forceinline__ void round_lists(RoundLds<HALF>& s, int n_tok, int ch
         rank += (so.x >= (o < a ? key : above)) + (so.y >= (o + 1 < a ? key : above)) +
                 (so.z >= (o + 2 < a ? key : above)) + (so.w >= (o + 3 < a ? key : above));
       }
-#pragma unroll
-      for (int x = 1; x < LPA; x <<= 1) rank += __shfl_xor(rank, x);
+      rank = group_sum<LPA>(rank);
       if (rank >= m) d = -1;
     }
   }
@@ -114,12 +113,7 @@ __device__ __forceinline__ void round_lists(RoundLds<HALF>& s, int n_tok, int ch
           int c[4], sum = 0;
 #pragma unroll
           for (int e = 0; e < 4; ++e) sum += c[e] = (int)histogram[255 - 4 * lane - e];
-          int inc = sum;
-#pragma unroll
-          for (int x = 1; x < 64; x <<= 1) {
-            const int o = __shfl_up(inc, x);
-            if (lane >= x) inc += o;
-          }
+          const int inc = (int)wave_inclusive_scan((uint32_t)sum);
           int above = inc - sum;
           if (above < left && inc >= left) {       // the bin of the left-th largest is one of this lane's
             int e = 0;
@@ -159,13 +153,8 @@ __device__ __forceinline__ void round_lists(RoundLds<HALF>& s, int n_tok, int ch
       c[e] = lane * PER + e < HALF ? s.cnt[lane * PER + e] : 0;
       mine += sums(c[e]);
     }
-    uint32_t inc = mine;
-#pragma unroll
-    for (int x = 1; x < 64; x <<= 1) {
-      const uint32_t o = __shfl_up(inc, x);
-      if (lane >= x) inc += o;
-    }
-    const uint32_t all = __shfl(inc, 63);
+    const uint32_t inc = wave_inclusive_scan(mine);
+    const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
     const int n_long = (int)(all >> 10 & 1023u);
     uint32_t before = inc - mine;
 #pragma unroll
@@ -187,13 +176,7 @@ __device__ __forceinline__ void round_lists(RoundLds<HALF>& s, int n_tok, int ch
       keep[e] = u < n_tok && ((u & 1) || s.kept[u >> 1] < 0);
       mine += keep[e];
     }
-    int inc = mine;
-#pragma unroll
-    for (int x = 1; x < 64; x <<= 1) {
-      const int o = __shfl_up(inc, x);
-      if (lane >= x) inc += o;
-    }
-    int at = inc - mine;
+    int at = (int)wave_inclusive_scan((uint32_t)mine) - mine;
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
       s.slot[lane * PER + e] = (int16_t)at;
@@ -214,8 +197,7 @@ __device__ __forceinline__ void round_lists(RoundLds<HALF>& s, int n_tok, int ch
 #pragma unroll
       for (int i = 0; i < 8; ++i) pos += (x.v[i] == d) && (o + i < a);
     }
-#pragma unroll
-    for (int x = 1; x < LPA; x <<= 1) pos += __shfl_xor(pos, x);
+    pos = group_sum<LPA>(pos);
   }
   __syncthreads();
   // Rows with two or more members come first, then those with one, then the copies: the row groups of a wave
@@ -229,7 +211,7 @@ __device__ __forceinline__ void round_lists(RoundLds<HALF>& s, int n_tok, int ch
     const uint64_t mask = __ballot(copied);
     int at = 0;
     if (lane == 0) at = atomicAdd(&s.n_copied, __popcll(mask));
-    at = s.n_merged + __shfl(at, 0) + __popcll(mask & ((1ull << lane) - 1));
+    at = s.n_merged + __builtin_amdgcn_readfirstlane(at) + __popcll(mask & ((1ull << lane) - 1));
     const uint32_t o = (uint32_t)s.slot[u];
     if (copied) s.desc[at] = make_uint2(s.word[row], o);
     else if (u < n_tok && into < 0) s.desc[s.place[j]] = make_uint2(s.word[row], o | (uint32_t)n << 10 | (uint32_t)s.start[j] << 20);

@@ -971,6 +971,37 @@ def test_deferred_values_with_strided_input_and_padded_output():
     assert torch.equal(odeg[:, :, :out_len], ref[2]) and not bool(oV[:, :, out_len:].any())
 
 
+@pytest.mark.parametrize("r", [1.0, 0.7])
+@pytest.mark.parametrize("each", [1, 2, 3])
+@pytest.mark.parametrize("dim,chunk", [(128, 384), (128, 1024), (128, 2048), (64, 2048)])
+def test_rows_of_one_two_and_more_sources_are_emitted_where_they_belong(dim, chunk, each, r):
+    """Whole chunks whose destinations have exactly `each` sources or none (one each: as many rows of one source as a
+    chunk can have), and a tail in which nobody is alike, on every route of the merge."""
+    _say(f"rows by sources D={dim} c={chunk} each={each} r={r}")
+    rng = np.random.default_rng(17 * chunk + each)
+    seq, half = 4 * chunk + 77, chunk // 2
+    K = rng.standard_normal((2, seq, dim))
+    for h in range(2):
+        for lo in range(0, 4 * chunk, chunk):
+            sources = lo + 2 * rng.permutation(half)
+            K[h, sources] = K[h, lo + 1 + 2 * (rng.permutation(half)[np.arange(half) // each])]
+    K = torch.from_numpy(K).to(torch.bfloat16)[None].to(DEV)
+    V = torch.from_numpy(rng.standard_normal((1, 2, seq, dim))).to(torch.bfloat16).to(DEV)
+    kw = dict(rounds=[1.0, r])
+    got, ref = _compress("defer_always", K, V, chunk, **kw), _compress("full_rounds", K, V, chunk, **kw)
+    one = _compress("full_rounds", K, V, chunk, rounds=[r])
+    torch.cuda.synchronize()
+    for n, a, b in zip(["K'", "V'", "deg'", "assign"], got, ref):
+        assert torch.equal(a, b), f"{n} differs between deferred and full rounds"
+    ones = np.ones(seq, dtype=np.int64)
+    for h in range(2):
+        check_round(f64(K[0, h]), f64(V[0, h]), ones, chunk, r, "bf16", f64(one[0][0, h]), f64(one[1][0, h]),
+                    i64(one[2][0, h]), i64(one[3][0, h]), what=f"h{h}")
+        if r == 1.0:                                 # the chunks really were as described
+            sizes = i64(one[2][0, h])[:4 * half]
+            assert set(sizes.tolist()) <= {1, 1 + each, 1 + half % each}
+
+
 @pytest.mark.parametrize("dtype,seq,dim,chunk,n_proto,rounds", [
     ("bf16", 4096, 128, 1024, 6, [1.0, 1.0]),
     ("bf16", 4096 + 300, 128, 1024, 40, [1.0, 0.8]),
