@@ -361,30 +361,38 @@ __global__ __launch_bounds__(kThreads, sizeof(T) == 2 && MODE == kMergeFull ? 5 
   // (10, 11 and 11 bits; 2048 copies, a whole chunk, pass theirs only in the total).
   {
     auto sums = [](int n) -> uint32_t { return n > 1 ? 1u : n == 1 ? 1u << 10 : 1u << 21; };
-    int n[8];                                       // sources of a retained token, -1: merged away
+    const bool sources_left = m < nA;               // (else no source is looked at: every workgroup of a chunk does this)
+    int n[4];                                       // sources of the destinations, -1: past the end
+    bool left[4];
     uint32_t mine = 0;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int u = tid * 8 + e;
-      n[e] = u >= L ? -1 : (u & 1) ? s_cnt[u >> 1] : s_dstk[u >> 1] < 0 ? 0 : -1;
-      if (n[e] >= 0) mine += sums(n[e]);
+    for (int e = 0; e < 4; ++e) {
+      const int u = tid * 8 + 2 * e;
+      left[e] = sources_left && u < L && s_dstk[u >> 1] < 0;
+      n[e] = u + 1 < L ? s_cnt[u >> 1] : -1;
+      mine += ((uint32_t)left[e] << 21) + (n[e] >= 0 ? sums(n[e]) : 0u);
     }
     uint32_t tot;
-    uint32_t before = block_exclusive_scan(mine, s_wave_tot, &tot);
-    const int n_long = (int)(tot & 1023u);
-    const int n_merged = n_long + (int)(tot >> 10 & 2047u);
+    const uint32_t before = block_exclusive_scan(mine, s_wave_tot, &tot);
+    const int n_long = (int)(tot & 1023u), n_merged = n_long + (int)(tot >> 10 & 2047u);
+    int at2 = (int)(before & 1023u), at1 = (int)(before >> 10 & 2047u), at0 = (int)(before >> 21), o = at2 + at1 + at0;
+    at1 += n_long;
+    at0 += n_merged;
+    auto put = [&](int u, int place) {
+      s_local_out[u] = (int16_t)o;
+      s_src_of_place[place] = (int16_t)u;
+      if constexpr (DESC) s_desc[3 * place].y = (uint32_t)o;        // (s_local_out is overwritten below)
+      else if constexpr (MODE == kMergeOrigin) s_out_of_place[place] = (int16_t)o;
+      ++o;
+    };
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int u = tid * 8 + e;
-      if (n[e] >= 0) {
-        const int b2 = (int)(before & 1023u), b1 = (int)(before >> 10 & 2047u), b0 = (int)(before >> 21);
-        const int o = b2 + b1 + b0, place = n[e] > 1 ? b2 : n[e] == 1 ? n_long + b1 : n_merged + b0;
-        s_local_out[u] = (int16_t)o;
-        s_src_of_place[place] = (int16_t)u;
-        if constexpr (DESC) s_desc[3 * place].y = (uint32_t)o;      // (s_local_out is overwritten below)
-        else if constexpr (MODE == kMergeOrigin) s_out_of_place[place] = (int16_t)o;
-        before += sums(n[e]);
-      }
+    for (int e = 0; e < 4; ++e) {
+      const int u = tid * 8 + 2 * e;
+      if (left[e]) put(u, at0++);
+      if (n[e] >= 0) put(u + 1, n[e] > 1 ? at2 : n[e] == 1 ? at1 : at0);
+      at2 += n[e] > 1;
+      at1 += n[e] == 1;
+      at0 += n[e] == 0;
     }
   }
   __syncthreads();
