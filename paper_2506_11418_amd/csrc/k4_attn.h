@@ -45,7 +45,8 @@ __device__ inline uint16_t f32_to_bf16_rne(float f) {
 
 // 2^x as the bare hardware instruction (1 ulp; results below 2^-126 come out as zero).  The library
 // routine wraps it in a range fix-up for denormal results, five more instructions per call, which buys
-// nothing for a softmax weight.
+// nothing for a token's softmax weight.  The weights of row groups, waves and slices, worked out once each, take exp2f:
+// a factor that came out as zero there would make a NaN of an infinite sum.
 __device__ __forceinline__ float exp2_raw(float x) { return __builtin_amdgcn_exp2f(x); }
 
 namespace {
@@ -122,7 +123,7 @@ __device__ __forceinline__ void put_waves(const float* s_o, int part, const floa
     for (int w = 0; w < W; ++w) M = fmaxf(M, f[w]);
 #pragma unroll
     for (int w = 0; w < W; ++w) {
-      f[w] = (f[w] == -INFINITY) ? 0.f : exp2_raw(f[w] - M);
+      f[w] = (f[w] == -INFINITY) ? 0.f : exp2f(f[w] - M);
       const float2 v = *reinterpret_cast<const float2*>(s_o + w * part + c);
       x = fmaf(v.x, f[w], x);
       y = fmaf(v.y, f[w], y);
@@ -200,7 +201,7 @@ __device__ __forceinline__ void merge_slices(const float* __restrict__ o_part, c
     float dloc = 0.f;
     for (int sp = lane; sp < n_slices; sp += 64) {
       const F2 ml = (sp < 64) ? mine : pair(g, sp);
-      const float f = (ml.x == -INFINITY) ? 0.f : exp2_raw(ml.x - mloc);
+      const float f = (ml.x == -INFINITY) ? 0.f : exp2f(ml.x - mloc);
       s_w[g * kAttnMaxSplits + sp] = f;
       dloc += f * ml.y;
     }

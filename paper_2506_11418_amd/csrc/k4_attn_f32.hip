@@ -187,7 +187,7 @@ __global__ __launch_bounds__(kThreads, G <= 4 ? 3 : 2) void attn_f32_kernel(
   for (int g = 0; g < G; ++g) {
     constexpr int ROWS = 64 - LPR;        // the bits of a lane's number that say which row group it belongs to
     const float mw = across_lanes<ROWS>(m[g], [](float a, float b2) { return fmaxf(a, b2); });
-    const float f = (m[g] == -INFINITY) ? 0.f : exp2_raw(m[g] - mw);
+    const float f = (m[g] == -INFINITY) ? 0.f : exp2f(m[g] - mw);
     auto sum = [&](float x) { return across_lanes<ROWS>(x * f, [](float a, float b2) { return a + b2; }); };
     float4 x;
     x.x = sum(acc[g][0]); x.y = sum(acc[g][1]); x.z = sum(acc[g][2]); x.w = sum(acc[g][3]);

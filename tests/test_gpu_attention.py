@@ -167,6 +167,39 @@ def test_infinite_values_reach_their_own_channels_only(B, Hkv, G, L, D, scale):
     assert torch.equal(o[:, :, rest], plain[:, :, rest])
 
 
+@pytest.mark.parametrize("dtype,Hkv,G,L,D,low", [
+    ("bf16", 2, 4, 64, 128, lambda t, L, D: t % 64 < 16),                        # one wave of four
+    ("bf16", 2, 8, 128, 64, lambda t, L, D: t % 128 < 32),
+    ("bf16", 1, 1, 40000, 128, lambda t, L, D: t < L // 2),                      # slices, of eight waves each ...
+    ("bf16", 2, 2, 4096, 64, lambda t, L, D: t < L // 2),                        # ... and of four
+    ("f32", 2, 4, 64, 128, lambda t, L, D: t % (1024 // D) == 0),                # one row group
+    ("f32", 2, 2, 64, 32, lambda t, L, D: t % (1024 // D) == 0),
+    ("f32", 2, 8, 64, 128, lambda t, L, D: t % (1024 // D) < 256 // D),          # one wave's row groups
+    ("f32", 2, 1, 128, 64, lambda t, L, D: t % (1024 // D) < 256 // D),
+    ("f32", 1, 8, 3000, 128, lambda t, L, D: t < L // 2),                        # slices
+])
+def test_weights_down_to_the_smallest_denormal_count(dtype, Hkv, G, L, D, low):
+    """Parts of a cache whose logits lie 2^-140 below the rest's: their weight is not zero, and an infinite value
+    among them gives infinity in its channel, not 0 x infinity.  Every other channel as without it."""
+    _say(f"attn small weights {dtype} Hkv={Hkv} G={G} L={L} D={D}")
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    t = torch.arange(L)
+    K = torch.zeros((1, Hkv, L, D))
+    K[:, :, :, 0] = torch.where(low(t, L, D), 0.0, 97.0)           # 97 log2(e) = 139.9
+    V = torch.from_numpy(np.random.default_rng(L).standard_normal((1, Hkv, L, D)).astype(np.float32))
+    q = torch.zeros((1, Hkv * G, D))
+    q[:, :, 0] = 1.0
+    K, V, q = K.to(td).to(DEV), V.to(td).to(DEV), q.to(td).to(DEV)
+    P = V.clone()
+    P[:, :, 0, 5], P[:, :, 0, D - 1] = np.inf, -np.inf
+    o, plain = (ckv.decode_attn(q, K, x, scale=1.0, out_dtype=torch.float32) for x in (P, V))
+    torch.cuda.synchronize()
+    assert bool((o[:, :, 5] == np.inf).all()) and bool((o[:, :, D - 1] == -np.inf).all())
+    rest = [c for c in range(D) if c not in (5, D - 1)]
+    assert torch.equal(o[:, :, rest], plain[:, :, rest])
+    _check(q * np.sqrt(D), K, V, None, None, plain, 1e-4 if dtype == "f32" else ATTN_TOL, "without it")
+
+
 def test_outlier_keys_large_logits_bf16():
     """Keys with x10 outlier channels give logits of several tens: the softmax must stay stable."""
     _say("attn outliers")
