@@ -128,8 +128,13 @@ __device__ __forceinline__ f32x4 qk_step(const uint4& k, const uint4& qv) {
 // [n_blocks, heads, block_size].  A table entry outside the pool masks its tokens.
 //
 // partial layout: o_part[((b*Hkv + kvh)*S + split)*G + g][D], ml_part[...][2] = (max, sum)
+//
+// Registers: three waves per SIMD (168) wherever the compiler gets there without scratch, for which the wave's number, and with
+// it the loop over the tiles, is scalar; the other paged variants, with a row's address to work out for every load, stay at two.
+// With 172 and two waves (us, two waves / three): 40 sequences of 8 heads, 4000 tokens, one query head each 123.1 / 106.1, eight on
+// pages of 16 125.2 / 115.9; 80 of 6000, one 338.6 / 304.1; 256 of 300, one 51.2 / 48.0.
 template <int D, int G, int W, bool PAGED>   // W: waves per workgroup
-__global__ __launch_bounds__(W * 64, 2) void attn_mfma_kernel(
+__global__ __launch_bounds__(W * 64, !PAGED || (D == 128 && G == 8) ? 3 : 2) void attn_mfma_kernel(
     const __bf16* __restrict__ q, const __bf16* __restrict__ K, const __bf16* __restrict__ V, TensorView kv, int kv_heads,
     int seq, const int32_t* __restrict__ lens, const int32_t* __restrict__ deg, float scale_log2e,
     int n_splits, float* __restrict__ o_part, float* __restrict__ ml_part,
@@ -146,7 +151,7 @@ __global__ __launch_bounds__(W * 64, 2) void attn_mfma_kernel(
   __shared__ int32_t s_tbl[PAGED ? kTableSlots : 1];
 
   const int split = blockIdx.x, kvh = blockIdx.y, b = blockIdx.z;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int qd = lane >> 4, n = lane & 15;
   const int len = lens ? max(min(lens[b], seq), 0) : seq;
   // whole tiles, split evenly over as many slices as give every wave one (a sequence far below the
