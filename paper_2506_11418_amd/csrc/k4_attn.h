@@ -142,8 +142,14 @@ __device__ __forceinline__ void put_waves(const float* s_o, int part, const floa
 // channels and adds them up over the slices; with fewer pairs than threads, groups of threads take every
 // SG-th slice and their sums are added in group order.  The first N slices of a thread (all of them for
 // up to N * SG slices) are requested before the weights are worked out, so that one memory latency covers both.
+//
+// TWO: the next block is asked for before one is added up (bf16).  Without (fp32), a whole block is requested and added up as it
+// arrives, in one piece of code: the long merges of fp32 are bound by what one CU takes in, and a wait that is decided behind a
+// branch is one for the whole block.  fp32, us a layer, with TWO / without: 1 pair of 100000 tokens, 391 slices, 8 heads
+// 65.4 / 59.1, 4 heads 38.9 / 36.5; dim 64, 8 heads 39.1 / 36.3; 4 pairs of 60000, 8 heads 67.4 / 63.7; 8 of 32769 65.5 / 65.1;
+// bf16, 4 heads, 1 pair of 100000 21.5 / 22.3, 8 of 32769 24.5 / 24.7.
 // s_w: [G][kAttnMaxSplits] floats, s_red: two per thread.
-template <int D, int G, int W>
+template <int D, int G, int W, bool TWO>
 __device__ __forceinline__ void merge_slices(const float* __restrict__ o_part, const float* __restrict__ ml_part,
                                              int64_t sbase, int n_slices, float* s_w, float* s_den, float* s_red,
                                              void* __restrict__ o, int o_dtype, int64_t o_base) {
@@ -164,20 +170,23 @@ __device__ __forceinline__ void merge_slices(const float* __restrict__ o_part, c
     wcol[k] = s_w + (c / D) * kAttnMaxSplits;
   }
   constexpr int64_t pitch = (int64_t)G * D;
-  F2 xa[NC][N], xb[NC][N];
+  F2 xa[NC][N], xb[TWO ? NC : 1][TWO ? N : 1];
   // A whole block of N slices a thread without a question asked: where it is clamped and masked, a slice costs a dozen vector
-  // instructions, and one block at a time waits for memory as often (one pair of 20000 tokens, 2 heads of 4, bf16, 79 slices 13.4 ->
-  // 12.5 us; fp32, 8 pairs of 32769 tokens, 64 slices, 4 heads 59.5 -> 58.2).  In
+  // instructions (one pair of 20000 tokens, 2 heads of 4, bf16, 79 slices 13.4 -> 12.5 us; fp32, 8 pairs of 32769 tokens, 64
+  // slices, 4 heads 59.5 -> 58.2).  In
   // the last one four slices per branch, those past the last loaded as the last one and counted as zero: with a branch
   // around each of them every weight read from LDS is waited for by itself (one pair of dim 128, 4 heads: 313
   // slices 37.3 -> 32.1 us, 256 slices 35.7 -> 23.9; 8 heads, 313 slices 59.3 -> 46.5).
   auto whole = [&](int s0) { return s0 - sg + SG * N <= n_slices; };
+  auto request_whole = [&](F2 (&x)[NC][N], int s0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int k = 0; k < NC; ++k) x[k][i] = load_shared(col[k] + s0 * pitch + i * (SG * pitch));
+  };
   auto request = [&](F2 (&x)[NC][N], int s0) __attribute__((always_inline)) {
     if (whole(s0)) {
-#pragma unroll
-      for (int i = 0; i < N; ++i)
-#pragma unroll
-        for (int k = 0; k < NC; ++k) x[k][i] = load_shared(col[k] + s0 * pitch + i * (SG * pitch));
+      request_whole(x, s0);
     } else {
 #pragma unroll
       for (int i0 = 0; i0 < N; i0 += 4)
@@ -189,36 +198,54 @@ __device__ __forceinline__ void merge_slices(const float* __restrict__ o_part, c
         }
     }
   };
-  // the (max, sum) pairs first: they are waited for first
+  // the (max, sum) pairs of all of a wave's heads first: they are waited for first, and loads come back in order
   auto pair = [&](int g, int sp) { return load_shared(&ml_part[((sbase + sp) * G + g) * 2]); };
-  F2 mine = (wave < G && lane < n_slices) ? pair(wave, lane) : F2{-INFINITY, 0.f};   // read once: up to 64 slices need no more
+  constexpr int H = (G + W - 1) / W, M = TWO ? 1 : 2;      // heads of a wave; slices of a lane that are read once
+  F2 mine[H][M];
+#pragma unroll
+  for (int h = 0; h < H; ++h)
+#pragma unroll
+    for (int i = 0; i < M; ++i) {
+      const int g = wave + h * W, sp = lane + 64 * i;
+      mine[h][i] = (g < G && sp < n_slices) ? pair(g, sp) : F2{-INFINITY, 0.f};
+    }
   request(xa, sg);
-  for (int g = wave; g < G; g += W) {
-    if (g != wave) mine = (lane < n_slices) ? pair(g, lane) : F2{-INFINITY, 0.f};
-    float mloc = mine.x;
-    for (int sp = lane + 64; sp < n_slices; sp += 64) mloc = fmaxf(mloc, pair(g, sp).x);
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    const int g = wave + h * W;
+    if (g >= G) break;
+    float mloc = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < M; ++i) mloc = fmaxf(mloc, mine[h][i].x);
+    for (int sp = lane + 64 * M; sp < n_slices; sp += 64) mloc = fmaxf(mloc, pair(g, sp).x);
     mloc = across_lanes<0x3f>(mloc, [](float a, float b) { return fmaxf(a, b); });
     float dloc = 0.f;
-    for (int sp = lane; sp < n_slices; sp += 64) {
-      const F2 ml = (sp < 64) ? mine : pair(g, sp);
+    auto weigh = [&](const F2& ml, int sp) {
       const float f = (ml.x == -INFINITY) ? 0.f : exp2f(ml.x - mloc);
       s_w[g * kAttnMaxSplits + sp] = f;
       dloc += f * ml.y;
-    }
+    };
+#pragma unroll
+    for (int i = 0; i < M; ++i)
+      if (lane + 64 * i < n_slices) weigh(mine[h][i], lane + 64 * i);
+    for (int sp = lane + 64 * M; sp < n_slices; sp += 64) weigh(pair(g, sp), sp);
     dloc = across_lanes<0x3f>(dloc, [](float a, float b) { return a + b; });
     if (lane == 0) s_den[g] = dloc;
   }
   __syncthreads();
+  auto add_whole = [&](const F2 (&x)[NC][N], int s0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+      for (int k = 0; k < NC; ++k) {
+        const float w = wcol[k][s0 + i * SG];
+        nx[k] = fmaf(x[k][i].x, w, nx[k]);
+        ny[k] = fmaf(x[k][i].y, w, ny[k]);
+      }
+  };
   auto add = [&](const F2 (&x)[NC][N], int s0) __attribute__((always_inline)) {
     if (whole(s0)) {
-#pragma unroll
-      for (int i = 0; i < N; ++i)
-#pragma unroll
-        for (int k = 0; k < NC; ++k) {
-          const float w = wcol[k][s0 + i * SG];
-          nx[k] = fmaf(x[k][i].x, w, nx[k]);
-          ny[k] = fmaf(x[k][i].y, w, ny[k]);
-        }
+      add_whole(x, s0);
     } else {
 #pragma unroll
       for (int i0 = 0; i0 < N; i0 += 4)
@@ -239,15 +266,28 @@ __device__ __forceinline__ void merge_slices(const float* __restrict__ o_part, c
         }
     }
   };
-  for (int s0 = sg;;) {                  // (the next block on its way while one is added up)
-    const int s1 = s0 + SG * N, s2 = s1 + SG * N;
-    if (s1 < n_slices) request(xb, s1);
+  if constexpr (TWO) {
+    for (int s0 = sg;;) {                // (the next block asked for before one is added up)
+      const int s1 = s0 + SG * N, s2 = s1 + SG * N;
+      if (s1 < n_slices) request(xb, s1);
+      add(xa, s0);
+      if (s1 >= n_slices) break;
+      if (s2 < n_slices) request(xa, s2);
+      add(xb, s1);
+      if (s2 >= n_slices) break;
+      s0 = s2;
+    }
+  } else {
+    int s0 = sg;
     add(xa, s0);
-    if (s1 >= n_slices) break;
-    if (s2 < n_slices) request(xa, s2);
-    add(xb, s1);
-    if (s2 >= n_slices) break;
-    s0 = s2;
+    for (s0 += SG * N; whole(s0); s0 += SG * N) {
+      request_whole(xa, s0);
+      add_whole(xa, s0);
+    }
+    if (s0 < n_slices) {
+      request(xa, s0);
+      add(xa, s0);
+    }
   }
   if constexpr (SG > 1) {
     s_red[2 * tid] = nx[0];

@@ -366,7 +366,7 @@ __global__ __launch_bounds__(W * 64, !PAGED || (D == 128 && G == 8) ? 3 : 2) voi
   __syncthreads();
   if (!s_is_last) return;
   if (tid == 0) atomicExch(my_count, 0);  // all have arrived: the workspace is ready for the next call
-  merge_slices<D, G, W>(o_part, ml_part, sbase, n_slices, reinterpret_cast<float*>(s_raw), &s_l[0][0], s_red, o, o_dtype,
+  merge_slices<D, G, W, true>(o_part, ml_part, sbase, n_slices, reinterpret_cast<float*>(s_raw), &s_l[0][0], s_red, o, o_dtype,
                         o_base);
 }
 

@@ -212,7 +212,7 @@ __global__ __launch_bounds__(kThreads, G <= 4 ? 3 : 2) void attn_f32_kernel(
   __syncthreads();
   if (!s_is_last) return;
   if (tid == 0) atomicExch(my_count, 0);  // all have arrived: the workspace is ready for the next call
-  merge_slices<D, G, W>(o_part, ml_part, sbase, n_splits, s_raw, &s_l[0][0], s_red, o, o_dtype, o_base);
+  merge_slices<D, G, W, false>(o_part, ml_part, sbase, n_splits, s_raw, &s_l[0][0], s_red, o, o_dtype, o_base);
 }
 
 template <int D, int G>

@@ -84,6 +84,15 @@ def test_decode_attn_shapes(B, Hkv, G, L, D, dtype):
     (2, 2, 4, 9000, 64, "f32"),
     (17, 1, 4, 2100, 128, "bf16"),     # more pairs than eight waves are taken for
     (520, 1, 1, 300, 64, "bf16"),      # one slice per pair: written without a merge
+    (2, 1, 1, 100000, 32, "f32"),      # slices merged in whole blocks and a rest, threads in 16, 8, 4 and 2 groups ...
+    (1, 1, 2, 40000, 32, "f32"),
+    (2, 1, 4, 2100, 32, "f32"),
+    (1, 2, 8, 40000, 32, "f32"),
+    (1, 1, 8, 40000, 64, "f32"),       # ... in one, a thread's one pair of channels ...
+    (2, 1, 8, 40000, 128, "f32"),      # ... and its two
+    (1, 2, 8, 2100, 128, "f32"),
+    (1, 1, 8, 24000, 64, "bf16"),      # bf16: two blocks of 32 slices and a rest ...
+    (1, 1, 8, 32000, 128, "bf16"),     # ... and, with two pairs of channels a thread, seven of 16
 ])
 def test_attn_tile_and_slice_edges(B, Hkv, G, L, D, dtype):
     """Lengths around the tiles and slices of the kernel, most of them far below the cache's capacity, with
