@@ -894,7 +894,11 @@ hipError_t launch_merge_t(const void* K, const void* V, const int32_t* deg_in, T
   // 50.6 / 50.4 / 50.6; 5000: 66.3 / 58.0 / 56.9 / 56.8; 12000: 75.1 / 71.4 / 74.4 / 79.6; 20001: 91.1 / 91.1 / 88.1 / 100.8;
   // 32768: 114.6 / 114.8 / 113.8 / 128.5; 5000, chunk 2048: 101.0 / 79.6 / 79.6 / 82.7; 20001, chunk 384: 89.1 / 79.3 / 76.5 /
   // 86.1; one round of 30000, chunk 1024, r = 0.8: 84.5 / 74.5 / 73.2 / 85.3.
-  const int64_t workgroups = 5 * (int64_t)cu_count();
+  // fp32 over pages in full mode holds 99 registers and so four per CU: with five, 8 sequences of 16384 tokens of dim 128, chunk 1024,
+  // r = 0.5, one workgroup in five ran by itself at the end, 68.7 us a launch, 56.9 now (held to 96 registers, 12 bytes of scratch:
+  // 58.1, and 32 such sequences at chunk 512, one workgroup a chunk, 120.5 -> 126.5).
+  const bool full_f32_paged = sizeof(T) == 4 && !org && !lists_out && (pin.table || pok.table || pov.table);
+  const int64_t workgroups = (full_f32_paged ? 4 : 5) * (int64_t)cu_count();
   const int row_groups = kThreads / (D * (int)sizeof(T) / 16);
   const int batches = div_up(chunk_out(min(chunk, seq), r), row_groups * (org ? kRowsInFlightOrigin : kRowsInFlight));
   const int parts = (int)max((int64_t)1, min((int64_t)min(32, batches), workgroups / total));

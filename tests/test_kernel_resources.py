@@ -55,3 +55,14 @@ def test_bf16_attention_keeps_its_waves(kernels):
     for (dim, heads, waves, paged), (registers, scratch) in found.items():
         three = paged == "0" or (dim, heads) == ("128", "8")
         assert scratch == 0 and registers <= (168 if three else 256), (dim, heads, waves, paged, registers, scratch)
+
+
+def test_full_merges_hold_the_workgroups_per_cu_that_small_launches_are_cut_into(kernels):
+    """Workgroups of four waves: one per CU for every wave a SIMD holds.  Registers come in eights, 512 a SIMD."""
+    found = _instances(kernels, "merge_kernel")
+    full = {k: v for k, v in found.items() if k[2] == "0"}
+    assert len(full) == 2 * 2 * 2 * 2 + 4 * 2 * 2  # bf16: dims, capacities, pages, sinks; fp32: one kernel with and without sinks
+    for (dtype, dim, _, capacity, paged, _), (registers, scratch) in full.items():
+        waves = 512 // (-(-registers // 8) * 8)
+        assert scratch == 0 and waves >= (4 if (dtype, paged) == ("f", "1") else 5), (dtype, dim, capacity, paged, registers, scratch)
+    assert all(scratch == 0 for _, scratch in found.values())
