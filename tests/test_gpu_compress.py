@@ -5,7 +5,7 @@ import torch
 
 import oracle
 import paper_2506_11418_amd as ckv
-from parity_util import DT, TOL, assert_rows_close, check_match, check_round, check_round_with_edges, f64, i64
+from parity_util import DT, TOL, assert_rows_close, check_match, check_round, check_round_head, check_round_with_edges, f64, i64
 from synth import kv_host
 
 pytestmark = pytest.mark.gpu
@@ -976,7 +976,8 @@ def test_deferred_values_with_strided_input_and_padded_output():
 @pytest.mark.parametrize("dim,chunk", [(128, 384), (128, 1024), (128, 2048), (64, 2048)])
 def test_rows_of_one_two_and_more_sources_are_emitted_where_they_belong(dim, chunk, each, r):
     """Whole chunks whose destinations have exactly `each` sources or none (one each: as many rows of one source as a
-    chunk can have), and a tail in which nobody is alike, on every route of the merge."""
+    chunk can have), and a tail in which nobody is alike: bf16, strided, a deferred pair and full rounds (the other forms of
+    the merge: the test below)."""
     _say(f"rows by sources D={dim} c={chunk} each={each} r={r}")
     rng = np.random.default_rng(17 * chunk + each)
     seq, half = 4 * chunk + 77, chunk // 2
@@ -1000,6 +1001,71 @@ def test_rows_of_one_two_and_more_sources_are_emitted_where_they_belong(dim, chu
         if r == 1.0:                                 # the chunks really were as described
             sizes = i64(one[2][0, h])[:4 * half]
             assert set(sizes.tolist()) <= {1, 1 + each, 1 + half % each}
+
+
+@pytest.mark.parametrize("dtype,heads,seq,dim,chunk,r,scope", [
+    ("bf16", 2, 2048 + 77, 128, 1024, 1.0, "chunk"),      # 32 workgroups of 16 row groups for 512 rows: output order ...
+    ("bf16", 2, 2048 + 77, 128, 1024, 0.998, "chunk"),    # ... for 514: by sources
+    ("bf16", 2, 4096 + 5, 64, 2048, 1.0, "chunk"),        # 32 of 32 for 1024
+    ("bf16", 28, 4 * 384 + 1, 128, 384, 1.0, "chunk"),    # 9 of 16 for 192: by sources; a tail of one token
+    ("bf16", 2, 4000, 128, 1000, 1.0, "chunk"),           # lists of 500, not read in pieces
+    ("bf16", 2, 4 * 1024, 128, 1024, 0.5, "head"),        # a number of rows for every chunk
+    ("f32", 2, 1024 + 90, 128, 512, 1.0, "chunk"),        # 32 of 8 for 256: output order ...
+    ("f32", 2, 1040 + 90, 128, 520, 1.0, "chunk"),        # ... for 260: by sources
+    ("f32", 1, 4096 + 3, 32, 2048, 0.7, "head"),
+])
+def test_rows_in_output_order_and_by_sources_on_strided_caches_and_pages(dtype, heads, seq, dim, chunk, r, scope):
+    """Launches on either side of the line up to which every output row has a row group: one round against the oracle, and
+    two rounds in full, deferred, and both again over pages, bit for bit."""
+    _say(f"rows in output order {dtype} H={heads} S={seq} D={dim} c={chunk} r={r} {scope}")
+    K, V, _ = kv_host(61, heads, seq, dim, dtype, alpha=0.9, n_outlier=0)
+    K, V = K.to(DEV), V.to(DEV)
+    one = _compress("full_rounds", K, V, chunk, rounds=[r], scope=scope)
+    kw = dict(rounds=[1.0, r], scope=scope)
+    ref = _compress("full_rounds", K, V, chunk, **kw)
+    got = _compress("defer_always", K, V, chunk, **kw)
+    torch.cuda.synchronize()
+    for n, a, b in zip(["K'", "V'", "deg'", "assign"], got, ref):
+        assert torch.equal(a, b), f"{n} differs between deferred and full rounds"
+    check = check_round if scope == "chunk" else check_round_head
+    for h in {0, heads - 1}:
+        check(f64(K[0, h]), f64(V[0, h]), np.ones(seq, dtype=np.int64), chunk, r, dtype, f64(one[0][0, h]), f64(one[1][0, h]),
+              i64(one[2][0, h]), i64(one[3][0, h]), what=f"h{h}")
+    n_blocks = -(-seq // 16)
+    for route in ("full_rounds", "defer_always"):
+        table = torch.randperm(n_blocks, generator=torch.Generator().manual_seed(3)).to(torch.int32).view(1, -1).to(DEV)
+        K_pool = torch.zeros((n_blocks, heads, 16, dim), dtype=K.dtype, device=DEV)
+        pools = (K_pool, torch.zeros_like(K_pool), torch.zeros(K_pool.shape[:3], dtype=torch.int32, device=DEV))
+        ckv.paged_scatter(K, V, None, *pools, table, seq)
+        n, _ = ckv.paged_compress(*pools, table, seq, chunk, route=route, **kw)
+        pages = ckv.paged_gather(*pools, table, n)
+        torch.cuda.synchronize()
+        for name, a, b in zip(["K'", "V'", "deg'"], pages, ref):
+            assert torch.equal(a, b), f"{name} differs on pages ({route})"
+
+
+@pytest.mark.parametrize("dtype,dim", [("bf16", 128), ("f32", 64)])
+def test_a_whole_chunk_of_2048_copies(dtype, dim):
+    """Chunks in which no edge is merged copy all 2048 tokens: in every chunk (r = 0), in front of a round, and in one
+    chunk whose edges are all worse than the next chunk's."""
+    _say(f"whole chunks of copies {dtype}")
+    seq, chunk = 2 * 2048 + 1, 2048
+    K, V, _ = kv_host(62, 1, seq, dim, dtype, alpha=0.9, n_outlier=0)
+    K[:, :, 2048:4096:2] = K[:, :, 2049:4096:2]
+    K, V = K.to(DEV), V.to(DEV)
+    same = ckv.compress(K, V, chunk, rounds=[0.0])
+    want, got = ckv.compress(K, V, chunk, rounds=[0.5]), ckv.compress(K, V, chunk, rounds=[0.0, 0.5])
+    half = ckv.compress(K, V, chunk, rounds=[0.499], scope="head")      # 1021 of the second chunk's 1024 edges
+    torch.cuda.synchronize()
+    assert torch.equal(same[0], K) and torch.equal(same[1], V) and bool((same[2] == 1).all())
+    assert torch.equal(same[3][0, 0].cpu().long(), torch.arange(seq))
+    for n, a, b in zip(["K'", "V'", "deg'", "assign"], got, want):
+        assert torch.equal(a, b), n
+    assert half[0].shape[2] == seq - 1021
+    assert torch.equal(half[0][:, :, :2048], K[:, :, :2048]) and torch.equal(half[1][:, :, :2048], V[:, :, :2048])
+    assert torch.equal(half[3][0, 0, :2048].cpu().long(), torch.arange(2048)) and bool((half[2][:, :, :2048] == 1).all())
+    check_round_head(f64(K[0, 0]), f64(V[0, 0]), np.ones(seq, dtype=np.int64), chunk, 0.499, dtype, f64(half[0][0, 0]),
+                     f64(half[1][0, 0]), i64(half[2][0, 0]), i64(half[3][0, 0]), what="one chunk without an edge")
 
 
 @pytest.mark.parametrize("dtype,seq,dim,chunk,n_proto,rounds", [
