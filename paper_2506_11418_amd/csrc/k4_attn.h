@@ -137,6 +137,55 @@ __device__ __forceinline__ void put_waves(const float* s_o, int part, const floa
   }
 }
 
+// The weights of a (batch, KV head)'s slices in the merge, per query head (a wave takes a head): s_w [G][kAttnMaxSplits], and in
+// s_den the sums that they divide by.  A lane's first M slices are read by request(), for all of its wave's heads, so that they
+// come back before what the caller requests next.
+template <int G, int W, int M>
+struct SliceWeights {
+  static constexpr int H = (G + W - 1) / W;                // heads of a wave
+  const float* ml_part;
+  int64_t sbase;
+  int n_slices;
+  F2 mine[H][M];
+  __device__ __forceinline__ F2 pair(int g, int sp) const { return load_shared(&ml_part[((sbase + sp) * G + g) * 2]); }
+  __device__ __forceinline__ void request(const float* ml_part_, int64_t sbase_, int n_slices_) {
+    ml_part = ml_part_, sbase = sbase_, n_slices = n_slices_;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+#pragma unroll
+      for (int i = 0; i < M; ++i) {
+        const int g = wave + h * W, sp = lane + 64 * i;
+        mine[h][i] = (g < G && sp < n_slices) ? pair(g, sp) : F2{-INFINITY, 0.f};
+      }
+  }
+  __device__ __forceinline__ void work_out(float* s_w, float* s_den) const {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      const int g = wave + h * W;
+      if (g >= G) break;
+      float mloc = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < M; ++i) mloc = fmaxf(mloc, mine[h][i].x);
+      for (int sp = lane + 64 * M; sp < n_slices; sp += 64) mloc = fmaxf(mloc, pair(g, sp).x);
+      mloc = across_lanes<0x3f>(mloc, [](float a, float b) { return fmaxf(a, b); });
+      float dloc = 0.f;
+      auto weigh = [&](const F2& ml, int sp) {
+        const float f = (ml.x == -INFINITY) ? 0.f : exp2f(ml.x - mloc);
+        s_w[g * kAttnMaxSplits + sp] = f;
+        dloc += f * ml.y;
+      };
+#pragma unroll
+      for (int i = 0; i < M; ++i)
+        if (lane + 64 * i < n_slices) weigh(mine[h][i], lane + 64 * i);
+      for (int sp = lane + 64 * M; sp < n_slices; sp += 64) weigh(pair(g, sp), sp);
+      dloc = across_lanes<0x3f>(dloc, [](float a, float b) { return a + b; });
+      if (lane == 0) s_den[g] = dloc;
+    }
+  }
+};
+
 // The slices of one (batch, KV head), merged by the workgroup that arrived last: weights of the slices
 // per query head (a wave takes a head), and the slices' sums: every thread owns NC pairs of neighbouring
 // channels and adds them up over the slices; with fewer pairs than threads, groups of threads take every
@@ -144,16 +193,15 @@ __device__ __forceinline__ void put_waves(const float* s_o, int part, const floa
 // up to N * SG slices) are requested before the weights are worked out, so that one memory latency covers both.
 //
 // TWO: the next block is asked for before one is added up (bf16).  Without (fp32), a whole block is requested and added up as it
-// arrives, in one piece of code: the long merges of fp32 are bound by what one CU takes in, and a wait that is decided behind a
-// branch is one for the whole block.  fp32, us a layer, with TWO / without: 1 pair of 100000 tokens, 391 slices, 8 heads
-// 65.4 / 59.1, 4 heads 38.9 / 36.5; dim 64, 8 heads 39.1 / 36.3; 4 pairs of 60000, 8 heads 67.4 / 63.7; 8 of 32769 65.5 / 65.1;
-// bf16, 4 heads, 1 pair of 100000 21.5 / 22.3, 8 of 32769 24.5 / 24.7.
+// arrives, in one piece of code: the longer merges of fp32 are bound by what one CU takes in, and a wait that is decided behind a
+// branch is one for the whole block.  us a layer, with TWO / without: fp32, 2 pairs of 60000 tokens, 2 heads 32.0 / 30.8, 1 head
+// 29.5 / 28.4; bf16, 4 heads, 1 pair of 100000 21.5 / 22.3, 8 of 32769 24.5 / 24.7.
 // s_w: [G][kAttnMaxSplits] floats, s_red: two per thread.
 template <int D, int G, int W, bool TWO>
 __device__ __forceinline__ void merge_slices(const float* __restrict__ o_part, const float* __restrict__ ml_part,
                                              int64_t sbase, int n_slices, float* s_w, float* s_den, float* s_red,
                                              void* __restrict__ o, int o_dtype, int64_t o_base) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x;
   constexpr int kThreads = W * 64, PAIRS = G * D / 2;
   constexpr int SG = (PAIRS < kThreads) ? kThreads / PAIRS : 1, NC = (PAIRS + kThreads - 1) / kThreads;
   static_assert(PAIRS * SG == kThreads * NC, "whole pairs per thread");
@@ -198,40 +246,10 @@ __device__ __forceinline__ void merge_slices(const float* __restrict__ o_part, c
         }
     }
   };
-  // the (max, sum) pairs of all of a wave's heads first: they are waited for first, and loads come back in order
-  auto pair = [&](int g, int sp) { return load_shared(&ml_part[((sbase + sp) * G + g) * 2]); };
-  constexpr int H = (G + W - 1) / W, M = TWO ? 1 : 2;      // heads of a wave; slices of a lane that are read once
-  F2 mine[H][M];
-#pragma unroll
-  for (int h = 0; h < H; ++h)
-#pragma unroll
-    for (int i = 0; i < M; ++i) {
-      const int g = wave + h * W, sp = lane + 64 * i;
-      mine[h][i] = (g < G && sp < n_slices) ? pair(g, sp) : F2{-INFINITY, 0.f};
-    }
+  SliceWeights<G, W, TWO ? 1 : 2> weights;
+  weights.request(ml_part, sbase, n_slices);
   request(xa, sg);
-#pragma unroll
-  for (int h = 0; h < H; ++h) {
-    const int g = wave + h * W;
-    if (g >= G) break;
-    float mloc = -INFINITY;
-#pragma unroll
-    for (int i = 0; i < M; ++i) mloc = fmaxf(mloc, mine[h][i].x);
-    for (int sp = lane + 64 * M; sp < n_slices; sp += 64) mloc = fmaxf(mloc, pair(g, sp).x);
-    mloc = across_lanes<0x3f>(mloc, [](float a, float b) { return fmaxf(a, b); });
-    float dloc = 0.f;
-    auto weigh = [&](const F2& ml, int sp) {
-      const float f = (ml.x == -INFINITY) ? 0.f : exp2f(ml.x - mloc);
-      s_w[g * kAttnMaxSplits + sp] = f;
-      dloc += f * ml.y;
-    };
-#pragma unroll
-    for (int i = 0; i < M; ++i)
-      if (lane + 64 * i < n_slices) weigh(mine[h][i], lane + 64 * i);
-    for (int sp = lane + 64 * M; sp < n_slices; sp += 64) weigh(pair(g, sp), sp);
-    dloc = across_lanes<0x3f>(dloc, [](float a, float b) { return a + b; });
-    if (lane == 0) s_den[g] = dloc;
-  }
+  weights.work_out(s_w, s_den);
   __syncthreads();
   auto add_whole = [&](const F2 (&x)[NC][N], int s0) __attribute__((always_inline)) {
 #pragma unroll
@@ -304,6 +322,55 @@ __device__ __forceinline__ void merge_slices(const float* __restrict__ o_part, c
   for (int k = 0; k < NC; ++k) {
     const int c = 2 * ((tid % (kThreads / SG)) + k * kThreads);
     put_out(o, o_dtype, o_base + c, nx[k], ny[k], s_den[c / D]);
+  }
+}
+
+// The same where fp32 caches leave many slices and two channels a thread or more: every thread owns NC channels, consecutive
+// threads consecutive ones, and adds them up in slice order (the same bits), in blocks of 32 slices.  By pairs of channels two
+// merges at a time take in a tenth less.  us a layer, before fp32 shared merge_slices / with it / this: 8 heads of dim 128, 2 pairs
+// of 60000 tokens, 235 slices 56.4 / 58.4 / 51.4, over pages 57.6 / 63.0 / 56.4, 4 pairs 71.4 / 72.7 / 69.6, 1 pair of 120000 67.7 /
+// 67.7 / 61.6; dim 64, 2 pairs of 60000 36.1 / 37.3 / 32.2; 4 heads of dim 128 35.8 / 36.8 / 33.3.
+template <int D, int G, int W>
+__device__ __forceinline__ void merge_many_slices(const float* __restrict__ o_part, const float* __restrict__ ml_part,
+                                                  int64_t sbase, int n_slices, float* s_w, float* s_den,
+                                                  void* __restrict__ o, int o_dtype, int64_t o_base) {
+  constexpr int kThreads = W * 64, NC = G * D / kThreads, N = 32;
+  static_assert(NC >= 2 && G * D % kThreads == 0, "whole channels per thread");
+  const int tid = threadIdx.x;
+  SliceWeights<G, W, 4> weights;
+  weights.request(ml_part, sbase, n_slices);
+  const float* col = o_part + sbase * G * D + tid;
+  constexpr int64_t pitch = (int64_t)G * D;
+  float num[NC] = {}, x[NC][N];
+  auto load = [&](int k, int sp) { return __hip_atomic_load(col + sp * pitch + k * kThreads, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  auto weight = [&](int k, int sp) { return s_w[(tid + k * kThreads) / D * kAttnMaxSplits + sp]; };
+  auto request = [&](int s0, auto n_c) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < decltype(n_c)::value; ++i)
+#pragma unroll
+      for (int k = 0; k < NC; ++k) x[k][i] = load(k, s0 + i);
+  };
+  auto add = [&](int s0, auto n_c) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < decltype(n_c)::value; ++i)
+#pragma unroll
+      for (int k = 0; k < NC; ++k) num[k] = fmaf(x[k][i], weight(k, s0 + i), num[k]);
+  };
+  constexpr std::integral_constant<int, N> whole{};
+  constexpr std::integral_constant<int, 8> eight{};
+  constexpr std::integral_constant<int, 1> one{};
+  weights.work_out(s_w, s_den);
+  __syncthreads();
+  int s0 = 0;
+  for (; s0 + N <= n_slices; s0 += N) { request(s0, whole); add(s0, whole); }
+  for (; s0 + 8 <= n_slices; s0 += 8) { request(s0, eight); add(s0, eight); }
+  for (; s0 < n_slices; ++s0) { request(s0, one); add(s0, one); }
+#pragma unroll
+  for (int k = 0; k < NC; ++k) {
+    const int c = tid + k * kThreads;
+    const float den = s_den[c / D], res = den > 0.f ? num[k] / den : 0.f;
+    if (o_dtype == CKV_BF16) reinterpret_cast<uint16_t*>(o)[o_base + c] = f32_to_bf16_rne(res);
+    else reinterpret_cast<float*>(o)[o_base + c] = res;
   }
 }
 

@@ -91,6 +91,11 @@ def test_decode_attn_shapes(B, Hkv, G, L, D, dtype):
     (1, 1, 8, 40000, 64, "f32"),       # ... in one, a thread's one pair of channels ...
     (2, 1, 8, 40000, 128, "f32"),      # ... and its two
     (1, 2, 8, 2100, 128, "f32"),
+    (1, 1, 8, 8192, 128, "f32"),       # 32 slices by pairs of channels ...
+    (1, 1, 8, 8193, 128, "f32"),       # ... and 33 by single ones: a block of 32 and one more ...
+    (1, 2, 4, 16384, 128, "f32"),
+    (1, 2, 4, 27400, 128, "f32"),      # ... 108: three, one of eight and four
+    (2, 1, 8, 18000, 64, "f32"),
     (1, 1, 8, 24000, 64, "bf16"),      # bf16: two blocks of 32 slices and a rest ...
     (1, 1, 8, 32000, 128, "bf16"),     # ... and, with two pairs of channels a thread, seven of 16
 ])
@@ -186,6 +191,7 @@ def test_infinite_values_reach_their_own_channels_only(B, Hkv, G, L, D, scale):
     ("f32", 2, 8, 64, 128, lambda t, L, D: t % (1024 // D) < 256 // D),          # one wave's row groups
     ("f32", 2, 1, 128, 64, lambda t, L, D: t % (1024 // D) < 256 // D),
     ("f32", 1, 8, 3000, 128, lambda t, L, D: t < L // 2),                        # slices
+    ("f32", 1, 8, 20000, 128, lambda t, L, D: t < L // 2),                       # ... merged by single channels
 ])
 def test_weights_down_to_the_smallest_denormal_count(dtype, Hkv, G, L, D, low):
     """Parts of a cache whose logits lie 2^-140 below the rest's: their weight is not zero, and an infinite value
@@ -207,6 +213,19 @@ def test_weights_down_to_the_smallest_denormal_count(dtype, Hkv, G, L, D, low):
     rest = [c for c in range(D) if c not in (5, D - 1)]
     assert torch.equal(o[:, :, rest], plain[:, :, rest])
     _check(q * np.sqrt(D), K, V, None, None, plain, 1e-4 if dtype == "f32" else ATTN_TOL, "without it")
+
+
+@pytest.mark.parametrize("L", [200, 9000, 17000])      # one slice, 36, 67
+def test_fp32_caches_with_bf16_outputs(L):
+    """The fp32 result, rounded once."""
+    _say(f"attn fp32 cache, bf16 output L={L}")
+    gen = torch.Generator(device=DEV).manual_seed(L)
+    K, V = (torch.randn((1, 2, L, 128), generator=gen, device=DEV) for _ in range(2))
+    q = torch.randn((1, 16, 128), generator=gen, device=DEV)
+    o, full = (ckv.decode_attn(q, K, V, out_dtype=t) for t in (torch.bfloat16, torch.float32))
+    torch.cuda.synchronize()
+    assert torch.equal(o, full.to(torch.bfloat16))
+    _check(q, K, V, None, None, full, 1e-4, "fp32")
 
 
 def test_outlier_keys_large_logits_bf16():
