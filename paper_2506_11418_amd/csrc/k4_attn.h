@@ -138,53 +138,55 @@ __device__ __forceinline__ void put_waves(const float* s_o, int part, const floa
 }
 
 // The weights of a (batch, KV head)'s slices in the merge, per query head (a wave takes a head): s_w [G][kAttnMaxSplits], and in
-// s_den the sums that they divide by.  A lane's first M slices are read by request(), for all of its wave's heads, so that they
-// come back before what the caller requests next.
-template <int G, int W, int M>
-struct SliceWeights {
-  static constexpr int H = (G + W - 1) / W;                // heads of a wave
-  const float* ml_part;
-  int64_t sbase;
-  int n_slices;
-  F2 mine[H][M];
-  __device__ __forceinline__ F2 pair(int g, int sp) const { return load_shared(&ml_part[((sbase + sp) * G + g) * 2]); }
-  __device__ __forceinline__ void request(const float* ml_part_, int64_t sbase_, int n_slices_) {
-    ml_part = ml_part_, sbase = sbase_, n_slices = n_slices_;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// s_den the sums that they divide by.  A lane's first M slices are read once, before request() asks for what comes next: loads
+// come back in order.  M = 1 (bf16): of a wave's first head; M > 1 (fp32): of all its heads.
+template <int G, int W, int M, class F>
+__device__ __forceinline__ void weigh_slices(const float* __restrict__ ml_part, int64_t sbase, int n_slices, float* s_w,
+                                             float* s_den, F&& request) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  auto pair = [&](int g, int sp) { return load_shared(&ml_part[((sbase + sp) * G + g) * 2]); };
+  auto weigh = [&](int g, const F2 (&mine)[M]) __attribute__((always_inline)) {
+    float mloc = mine[0].x;
+#pragma unroll
+    for (int i = 1; i < M; ++i) mloc = fmaxf(mloc, mine[i].x);
+    for (int sp = lane + 64 * M; sp < n_slices; sp += 64) mloc = fmaxf(mloc, pair(g, sp).x);
+    mloc = across_lanes<0x3f>(mloc, [](float a, float b) { return fmaxf(a, b); });
+    float dloc = 0.f;
+    auto count = [&](const F2& ml, int sp) {
+      const float f = (ml.x == -INFINITY) ? 0.f : exp2f(ml.x - mloc);
+      s_w[g * kAttnMaxSplits + sp] = f;
+      dloc += f * ml.y;
+    };
+#pragma unroll
+    for (int i = 0; i < M; ++i)
+      if (lane + 64 * i < n_slices) count(mine[i], lane + 64 * i);
+    for (int sp = lane + 64 * M; sp < n_slices; sp += 64) count(pair(g, sp), sp);
+    dloc = across_lanes<0x3f>(dloc, [](float a, float b) { return a + b; });
+    if (lane == 0) s_den[g] = dloc;
+  };
+  auto first = [&](int g, F2 (&mine)[M]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < M; ++i) mine[i] = (g < G && lane + 64 * i < n_slices) ? pair(g, lane + 64 * i) : F2{-INFINITY, 0.f};
+  };
+  if constexpr (M == 1) {
+    F2 mine[1];
+    first(wave, mine);
+    request();
+    for (int g = wave; g < G; g += W) {
+      if (g != wave) first(g, mine);
+      weigh(g, mine);
+    }
+  } else {
+    constexpr int H = (G + W - 1) / W;
+    F2 mine[H][M];
+#pragma unroll
+    for (int h = 0; h < H; ++h) first(wave + h * W, mine[h]);
+    request();
 #pragma unroll
     for (int h = 0; h < H; ++h)
-#pragma unroll
-      for (int i = 0; i < M; ++i) {
-        const int g = wave + h * W, sp = lane + 64 * i;
-        mine[h][i] = (g < G && sp < n_slices) ? pair(g, sp) : F2{-INFINITY, 0.f};
-      }
+      if (wave + h * W < G) weigh(wave + h * W, mine[h]);
   }
-  __device__ __forceinline__ void work_out(float* s_w, float* s_den) const {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int h = 0; h < H; ++h) {
-      const int g = wave + h * W;
-      if (g >= G) break;
-      float mloc = -INFINITY;
-#pragma unroll
-      for (int i = 0; i < M; ++i) mloc = fmaxf(mloc, mine[h][i].x);
-      for (int sp = lane + 64 * M; sp < n_slices; sp += 64) mloc = fmaxf(mloc, pair(g, sp).x);
-      mloc = across_lanes<0x3f>(mloc, [](float a, float b) { return fmaxf(a, b); });
-      float dloc = 0.f;
-      auto weigh = [&](const F2& ml, int sp) {
-        const float f = (ml.x == -INFINITY) ? 0.f : exp2f(ml.x - mloc);
-        s_w[g * kAttnMaxSplits + sp] = f;
-        dloc += f * ml.y;
-      };
-#pragma unroll
-      for (int i = 0; i < M; ++i)
-        if (lane + 64 * i < n_slices) weigh(mine[h][i], lane + 64 * i);
-      for (int sp = lane + 64 * M; sp < n_slices; sp += 64) weigh(pair(g, sp), sp);
-      dloc = across_lanes<0x3f>(dloc, [](float a, float b) { return a + b; });
-      if (lane == 0) s_den[g] = dloc;
-    }
-  }
-};
+}
 
 // The slices of one (batch, KV head), merged by the workgroup that arrived last: weights of the slices
 // per query head (a wave takes a head), and the slices' sums: every thread owns NC pairs of neighbouring
@@ -246,10 +248,7 @@ __device__ __forceinline__ void merge_slices(const float* __restrict__ o_part, c
         }
     }
   };
-  SliceWeights<G, W, TWO ? 1 : 2> weights;
-  weights.request(ml_part, sbase, n_slices);
-  request(xa, sg);
-  weights.work_out(s_w, s_den);
+  weigh_slices<G, W, TWO ? 1 : 2>(ml_part, sbase, n_slices, s_w, s_den, [&] { request(xa, sg); });
   __syncthreads();
   auto add_whole = [&](const F2 (&x)[NC][N], int s0) __attribute__((always_inline)) {
 #pragma unroll
@@ -337,8 +336,6 @@ __device__ __forceinline__ void merge_many_slices(const float* __restrict__ o_pa
   constexpr int kThreads = W * 64, NC = G * D / kThreads, N = 32;
   static_assert(NC >= 2 && G * D % kThreads == 0, "whole channels per thread");
   const int tid = threadIdx.x;
-  SliceWeights<G, W, 4> weights;
-  weights.request(ml_part, sbase, n_slices);
   const float* col = o_part + sbase * G * D + tid;
   constexpr int64_t pitch = (int64_t)G * D;
   float num[NC] = {}, x[NC][N];
@@ -359,7 +356,7 @@ __device__ __forceinline__ void merge_many_slices(const float* __restrict__ o_pa
   constexpr std::integral_constant<int, N> whole{};
   constexpr std::integral_constant<int, 8> eight{};
   constexpr std::integral_constant<int, 1> one{};
-  weights.work_out(s_w, s_den);
+  weigh_slices<G, W, 4>(ml_part, sbase, n_slices, s_w, s_den, [] {});
   __syncthreads();
   int s0 = 0;
   for (; s0 + N <= n_slices; s0 += N) { request(s0, whole); add(s0, whole); }
