@@ -10,12 +10,13 @@
 // Rows are then produced gather-style: 16-byte pieces, one row per group of row_bytes/16 lanes,
 // fp32 accumulation for bf16 (fp64 for fp32 storage), one rounding to the storage type.
 //
-// What bounds it: large launches the HBM stream at 0.80 to 0.85 of the copy rate and, beside it, the vector
-// ALU; small ones the chain from the matches to the last row of one workgroup.  So the rows are emitted by the
+// What bounds it: large launches the HBM stream, at 0.82 to 0.86 of the copy rate; beside it origin mode has the vector ALU
+// busy 58 % of the time at four waves per SIMD, keys-only mode 41 %.  Small ones the chain from the matches to the last row of
+// one workgroup.  So the rows are emitted by the
 // number of their sources, the row groups of a wave side by side, and nothing that a later step looks up waits
 // for it: the matches, the map's entries and the lists of the round before are requested at the start.  us a
 // launch, in output order with each requested where it is used / now: origin mode, 256 x 65536 tokens, chunk 1024
-// 3570 / 3395; 8 x 524288, chunk 2048 929 / 875; over pages, 32 x 16384 81 / 73.
+// 3559 / 3388; 8 x 524288, chunk 2048 925 / 865; over pages, 32 x 16384 80 / 76.
 #include <type_traits>
 
 #include "ckv_internal.h"
@@ -102,6 +103,10 @@ enum { kMergeFull = 0, kMergeKeys = 1, kMergeOrigin = 2 };
 //
 // EDGES: the first edge_blocks workgroups copy the tokens that bypass the clustering (none of the others
 // touches those rows).
+//
+// Launch bounds: bf16 in full mode is to hold five waves per SIMD, the workgroups per CU that small launches are cut into
+// (launch_merge_t).  It takes 92 to 96 registers, with or without being told; 97 would be four waves, and a fifth of the
+// workgroups by themselves at the end.
 template <typename T, int D, int MODE, int MH, bool PAGED, bool EDGES>   // MH: capacity of the per-chunk LDS arrays (|A| = |B| <= MH)
 __global__ __launch_bounds__(kThreads, sizeof(T) == 2 && MODE == kMergeFull ? 5 : 1) void merge_kernel(
     const T* __restrict__ K, const T* __restrict__ V, const int32_t* __restrict__ deg_in, TensorView in,

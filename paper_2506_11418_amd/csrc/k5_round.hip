@@ -505,7 +505,8 @@ __global__ __launch_bounds__(TOK * D / 64, 4) void round_small_kernel(
 // start four banks apart), every dot product and norm one chain of fused multiply-adds over the channels as in
 // match_f32_kernel, centroids in 64 bits as in merge_kernel: same bits.  These caches are small, so what counts is
 // the chain of one workgroup: every load is requested at the start, and the products are taken NI x NJ rows per
-// thread from registers.  1024 tokens of dim 64, chunk 64: 10.0 us, the two launches, with loads element by element and
+// thread from registers.  (With more than one row a thread the compiler holds the waiting values in scratch, 48 to 144 bytes a
+// lane: they are waited for before the similarity starts, stored there, and read back once the keys are out.)  1024 tokens of dim 64, chunk 64: 10.0 us, the two launches, with loads element by element and
 // two LDS reads to a product, 11.6 + 7.3; 4 x 8192 tokens of dim 128, chunk 256, two rounds 75 us a call (157); 64 x 16384
 // of dim 64, chunk 64 198 us (526).
 template <int D, int CHUNK>
